@@ -1,19 +1,27 @@
 // LKV-H at inference time (Sec. 3.3) and the Soft-TopK operator ST_k (Sec. 3.2, Eq. 2, App. A.1;
-// its backward pass, App. A.2, further down), in fp64.  Both are tiny next to the cache kernels (L * H <= a few hundred heads,
-// computed once and frozen), so one workgroup does the whole operator and the arithmetic is
-// double precision throughout: the ratios decide integer budgets floor(r t).
+// its backward pass, App. A.2, further down), in fp64: the ratios decide integer budgets floor(r t).
 //
 // ST_k(x)_i = f(x_i / tau - lambda), f the Laplace CDF, lambda such that the outputs sum to k.
-// With the inputs in descending order and m = #{i : x_i / tau >= lambda}, App. A.1 gives lambda in
-// closed form from S1 = sum_{i <= m} e^{-x_i}, S2 = sum_{i > m} e^{x_i}.  The split index is found
-// without trying every m: g(v) = sum_i f(x_i - v) - k decreases in v, so x_j >= lambda exactly
-// when g(x_j) <= 0, and g at the element of rank j needs only the prefix sum S1(j) and the suffix
-// sum S2(j).  All sums are carried as logarithms so that x / tau with a tiny tau cannot overflow.
-// Inputs too long for the LDS sort go through soft_topk_large_kernel further down (no sort: the
-// threshold is bracketed by passes over the input).
+// With m = #{i : z_i >= lambda}, z = x / tau, App. A.1 gives lambda in closed form from the sums over the head
+// and the tail.  No sort is needed for them: taken relative to any trial threshold v,
+//   A(v) = 1/2 sum_{z_i >= v} e^{v - z_i},   B(v) = 1/2 sum_{z_i < v} e^{z_i - v},   m(v) = #{z_i >= v}
+// (every exponent is <= 0: nothing overflows however small tau is), g(v) = m - A + B - k has the sign of
+// lambda - v, and the positive root y of A y^2 + (k - m) y - B = 0 gives the threshold v + log y that this split
+// would have.  When no z_i lies between v and v + log y the split is the right one and that is lambda, in closed
+// form; otherwise it is the next trial (a Newton step that knows the curvature), kept inside a bracket.
+//
+// One workgroup per vector.  What bounds it: instruction issue, one exponential per element and trial, so the
+// trials are made where they are cheap: a histogram of the inputs finds the value of rank k to a bin's width, two to
+// four trials on fp32 differences to that centre (one hardware exponential per element) find the threshold to fp32
+// accuracy, and only their end point is evaluated in fp64, where one pass both proves the split and yields the sums; the exponentials of that pass also give the outputs (e^{v - z} y = e^{lambda - z}).
+// fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
+// Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
+// (they stay in L2).  256 vectors of 16384 fp32 values: 35 us (257 us for the LDS sort
+// and logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "lkv_kernels.h"
 
@@ -21,48 +29,14 @@ namespace lkv {
 
 namespace {
 
-constexpr int kStThreads = 1024;
-constexpr int kStKeyBytes = 128 * 1024;   // LDS given to the sort keys
-constexpr int kStLocal = 32;              // elements per thread chunk at the largest n
-
-__device__ inline double log_add_exp(double a, double b) {   // log(e^a + e^b); -inf means an empty sum
-  const double hi = fmax(a, b);
-  const double lo = fmin(a, b);
-  if (lo == -INFINITY) return hi;
-  return hi + log1p(exp(lo - hi));
-}
-
-// keys whose unsigned order is the numeric order of the values
-__device__ inline uint32_t to_key(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (u >> 31) ? ~u : (u | 0x80000000u);
-}
-__device__ inline uint64_t to_key(double x) {
-  const uint64_t u = (uint64_t)__double_as_longlong(x);
-  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-__device__ inline double from_key(uint32_t k) {
-  const uint32_t u = (k >> 31) ? (k & 0x7fffffffu) : ~k;
-  return (double)__uint_as_float(u);
-}
-__device__ inline double from_key(uint64_t k) {
-  const uint64_t u = (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k;
-  return __longlong_as_double((long long)u);
-}
-
-// log( sqrt(d^2 + e^L) + d ) for d >= 0
-__device__ inline double log_root_plus(double d, double L) {
-  const double h = 0.5 * L;
-  if (d == 0.0) return h;
-  if (h > 300.0) return h + asinh(d * exp(-h));
-  return log(hypot(d, exp(h)) + d);
-}
-
-// value of sum_i f(x_i - v) - k at the element v of rank j (1-based, descending), given
-// log S1(j) = log sum_{i <= j} e^{-x_i} and log S2(j) = log sum_{i > j} e^{x_i}
-__device__ inline double constraint_at(double v, int j, double log_s1, double log_s2, double k) {
-  return ((double)j - k) - 0.5 * exp(v + log_s1) + 0.5 * exp(log_s2 - v);
-}
+constexpr int kStThreads = 1024;          // workgroup of all but the shortest vectors
+constexpr int kStSmallThreads = 256;      // vectors of up to 1024 values: fewer waves to reduce over
+constexpr int kStMaxN = 1 << 22;
+constexpr int kStLevels = 4;              // histograms at most (a cold temperature spreads the values over many units of z)
+constexpr double kStEnough = 0.5;         // bin width, in z, from which the fp32 trials converge in two to four steps
+constexpr int kStSearchSteps = 48;        // fp32 trials at most (bisection alone would need about 30)
+constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
+constexpr double kStTiny = 1e-280;        // sums below this have lost (or may have lost) terms to underflow
 
 // In a batched launch block b works on vector b: rows of x, y and info, and its own target sum, which the paper
 // keeps strictly inside (0, n) (App. A.1, "Numerical Stability at Boundaries"); the same is enforced here by clamping.
@@ -77,274 +51,367 @@ __device__ inline void select_vector(const X*& x, double*& y, double* __restrict
   k = fmin(fmax(k_vec[b], 1e-6), (double)n - 1e-6);
 }
 
-struct StShared {
-  double lambda;
-  int m;
-  int pad;
+// ---- reductions over a block, result in every thread, operands combined in a fixed order ----
+struct StAdd {
+  template <typename V> __device__ __forceinline__ V operator()(V a, V b) const { return a + b; }
+};
+struct StMin {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fminf(a, b); }
+  __device__ __forceinline__ double operator()(double a, double b) const { return fmin(a, b); }
 };
 
-template <typename X, typename Key>
-__global__ void __launch_bounds__(kStThreads)
-soft_topk_kernel(const X* x, int n, int P, double k, double tau, double* y /* may alias x */,
-                 double* __restrict__ info, int32_t* __restrict__ budgets, double t, const double* __restrict__ k_vec) {
-  extern __shared__ __align__(16) unsigned char smem[];
+template <int kCtrl, typename V>
+__device__ __forceinline__ V st_dpp(V x) {
+  if constexpr (sizeof(V) == 4) {
+    return __builtin_bit_cast(V, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xf, 0xf, true));
+  } else {
+    const long long u = __builtin_bit_cast(long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, kCtrl, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), kCtrl, 0xf, 0xf, true);
+    return __builtin_bit_cast(V, (long long)(((unsigned long long)hi << 32) | lo));
+  }
+}
+
+// over the 16 lanes of a DPP row
+template <typename V, typename Op>
+__device__ __forceinline__ V st_row16(V x, Op op) {
+  x = op(x, st_dpp<kDppQuadXor1>(x));
+  x = op(x, st_dpp<kDppQuadXor2>(x));
+  x = op(x, st_dpp<kDppRowHalfMirror>(x));
+  return op(x, st_dpp<kDppRowMirror>(x));
+}
+
+// over the wave: the rows, then the four rows (operands in the same order in every lane)
+template <typename V, typename Op>
+__device__ __forceinline__ V st_wave(V x, Op op) {
+  x = st_row16(x, op);
+  x = op(x, __shfl_xor(x, 16, 64));
+  return op(x, __shfl_xor(x, 32, 64));
+}
+
+// Per-wave results of up to five values; two copies used in turn, so that one barrier per reduction is enough (a wave
+// that writes a copy again has passed the barrier after every wave's reads of it).
+struct StScratch {
+  double v[2][5][16];
+};
+
+// a value that is the same in every lane, moved to scalar registers (the vector ones are needed for the elements)
+__device__ __forceinline__ double st_uniform(double x) {
+  const long long u = __builtin_bit_cast(long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(u >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int kT>
+struct StHist {
+  static constexpr int kBins = 2 * kT;
+  unsigned bin[kBins];
+  unsigned wave_total[kT / 64];
+  double above;
+  int found;
+};
+
+template <int kT, typename Op>
+__device__ __forceinline__ double st_collect(const double (&slot)[16], double identity, Op op) {
+  const int l = threadIdx.x & 15;
+  return st_uniform(st_row16(l < kT / 64 ? slot[l] : identity, op));
+}
+
+// x / tau, correctly rounded: one multiplication and a residual correction where x came from fp32 and tau is moderate
+// (nothing overflows or loses bits there), else the division itself
+template <typename X>
+__device__ __forceinline__ double st_quotient(X x, double tau, double rtau, bool moderate) {
+  const double xd = (double)x;
+  if constexpr (sizeof(X) == 4) {
+    if (moderate) {
+      const double q = xd * rtau;
+      return fma(fma(-q, tau, xd), rtau, q);
+    }
+  }
+  return xd / tau;
+}
+
+// kE > 0: thread t holds elements t, t + kT, ... (kE of them, n <= kE kT) in registers; kE = 0: any n, re-read in
+// every pass.
+template <typename X, int kT, int kE>
+__global__ void __launch_bounds__(kT)
+soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias x */, double* __restrict__ info,
+                 int32_t* __restrict__ budgets, double t, const double* __restrict__ k_vec) {
+  constexpr bool kHeld = kE > 0;
+  constexpr int kR = kHeld ? kE : 1;
+  constexpr double kLog2E = 1.44269504088896340736, kLn2 = 0.693147180559945309417;
+  __shared__ StScratch sh;
+  __shared__ StHist<kT> hist;
   select_vector(x, y, info, k, k_vec, n);   // batched call: this block's vector and target
-  Key* keys = reinterpret_cast<Key*>(smem);                                  // [P]
-  double* pre = reinterpret_cast<double*>(smem + (size_t)P * sizeof(Key));  // [1024] prefix of log S1
-  double* suf = pre + kStThreads;                                            // [1024] suffix of log S2
-  double* loc = suf + kStThreads;                                            // [kStLocal]
-  StShared* sh = reinterpret_cast<StShared*>(loc + kStLocal);
   const int tid = threadIdx.x;
+  const int wave = tid >> 6;
+  const bool writer = (tid & 63) == 0;
+  int turn = 0;
+  k = st_uniform(k);
+  const double rtau = st_uniform(1.0 / tau);
+  const bool moderate = tau > 1e-100 && tau < 1e100;
 
-  for (int i = tid; i < P; i += kStThreads) keys[i] = i < n ? to_key(x[i]) : (Key)0;
-  __syncthreads();
-
-  // bitonic sort, descending
-  for (int span = 2; span <= P; span <<= 1) {
-    for (int j = span >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < (P >> 1); i += kStThreads) {
-        const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        const int b = a | j;
-        const Key ka = keys[a], kb = keys[b];
-        const bool descending = (a & span) == 0;
-        if (descending ? (ka < kb) : (ka > kb)) {
-          keys[a] = kb;
-          keys[b] = ka;
-        }
+  // ---- where to look: the value of rank k, by histograms of the inputs that narrow to one bin ----
+  double lo, hi, zc;   // bracket of the threshold; centre of the search
+  {
+    X xr[kR];
+    if constexpr (kHeld) {
+#pragma unroll
+      for (int e = 0; e < kR; ++e) xr[e] = x[min(tid + e * kT, n - 1)];   // padding repeats the last value
+    }
+    double least = INFINITY, most = INFINITY;   // min x, min -x
+    {
+      X small = (X)INFINITY, large = (X)-INFINITY;
+      if constexpr (kHeld) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e) { small = xr[e] < small ? xr[e] : small; large = xr[e] > large ? xr[e] : large; }
+      } else {
+#pragma unroll 4
+        for (int i = tid; i < n; i += kT) { small = x[i] < small ? x[i] : small; large = x[i] > large ? x[i] : large; }
+      }
+      least = st_wave((double)small, StMin());
+      most = st_wave(-(double)large, StMin());
+    }
+    auto& v = sh.v[turn];
+    if (writer) { v[0][wave] = least; v[1][wave] = most; }
+    __syncthreads();
+    least = st_collect<kT>(v[0], INFINITY, StMin());
+    most = -st_collect<kT>(v[1], INFINITY, StMin());
+    turn ^= 1;
+    // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
+    // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
+    lo = st_uniform(least / tau - 1.0 - fmax(0.0, log((double)n / (2.0 * ((double)n - k)))));
+    hi = st_uniform(most / tau + 1.0 + fmax(0.0, log((double)n / (2.0 * k))));
+    constexpr int kBins = StHist<kT>::kBins;
+    double base = least, span = most - least;
+    double above = 0.0;   // values in higher bins
+    bool looking = span > 0.0 && span < INFINITY;
+    for (int level = 0; level < kStLevels && looking; ++level) {
+      for (int i = tid; i < kBins; i += kT) hist.bin[i] = 0;
+      if (tid == 0) hist.found = -1;
+      __syncthreads();
+      const float to_bin = (float)((double)kBins / span);
+      auto visit = [&](X xv, bool in) {
+        const float f = (float)(xv - (X)base) * to_bin;
+        // the first level takes every value; the next ones the values of the bin found before
+        if (in && (level == 0 || (f >= 0.f && f < (float)kBins)))
+          atomicAdd(&hist.bin[(int)fminf(fmaxf(f, 0.f), (float)(kBins - 1))], 1u);
+      };
+      if constexpr (kHeld) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e) visit(xr[e], tid + e * kT < n);
+      } else {
+#pragma unroll 4
+        for (int i = tid; i < n; i += kT) visit(x[i], true);
       }
       __syncthreads();
+      // from the top: thread t owns bins kBins - 1 - 2 t and kBins - 2 - 2 t
+      const int top = kBins - 1 - 2 * tid;
+      const unsigned c0 = hist.bin[top], c1 = hist.bin[top - 1];
+      unsigned incl = c0 + c1;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const unsigned below = __shfl_up(incl, d, 64);
+        if ((tid & 63) >= d) incl += below;
+      }
+      if ((tid & 63) == 63) hist.wave_total[wave] = incl;
+      __syncthreads();
+      unsigned before = 0;
+      for (int w = 0; w < wave; ++w) before += hist.wave_total[w];
+      const double e0 = above + (double)(before + incl - c0 - c1);
+      if (c0 != 0 && e0 < k && k <= e0 + c0) { hist.found = top; hist.above = e0; }
+      if (c1 != 0 && e0 + c0 < k && k <= e0 + c0 + c1) { hist.found = top - 1; hist.above = e0 + c0; }
+      __syncthreads();
+      const int found = __builtin_amdgcn_readfirstlane(hist.found);
+      if (found < 0) break;   // rounding moved a value across the bin's edge: the bin is narrow enough
+      above = st_uniform(hist.above);
+      __syncthreads();        // the next level clears what has just been read
+      span = st_uniform(span / (double)kBins);
+      base = st_uniform(base + found * span);
+      looking = span > kStEnough * tau && base + span > base;
     }
+    zc = st_uniform((base + 0.5 * span) / tau);
+    if (!(zc > lo && zc < hi)) zc = st_uniform(0.5 * (lo + hi));
   }
 
-  // per-thread chunk of the sorted values
-  const int c = (n + kStThreads - 1) / kStThreads;
-  const int start = min(n, tid * c);
-  const int end = min(n, start + c);
-  double a_loc = -INFINITY, b_loc = -INFINITY;
-  for (int i = start; i < end; ++i) {
-    const double v = from_key(keys[i]) / tau;
-    a_loc = log_add_exp(a_loc, -v);
-    b_loc = log_add_exp(b_loc, v);
+  // ---- search in fp32: w = (z - zc) log2 e ----
+  double v;
+  {
+    const double scale = st_uniform(rtau * kLog2E), shift = st_uniform(-zc * kLog2E);
+    float w[kR];
+    if constexpr (kHeld) {
+#pragma unroll
+      for (int e = 0; e < kR; ++e)   // the vector is in the caches by now; padding lies infinitely far down the tail
+        w[e] = tid + e * kT < n ? (float)fma((double)x[min(tid + e * kT, n - 1)], scale, shift) : -INFINITY;
+    }
+    float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
+#pragma unroll 1
+    for (int step = 0; step < kStSearchSteps; ++step) {
+      float head = 0.f, all = 0.f;
+      int cnt = 0;
+      auto visit = [&](float wv) {
+        const float d = wv - fv;
+        const float e = __builtin_amdgcn_exp2f(-fabsf(d));
+        const bool up = d >= 0.f;
+        all += e;
+        head += up ? e : 0.f;
+        cnt += up ? 1 : 0;
+      };
+      if constexpr (kHeld) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e) visit(w[e]);
+      } else {
+#pragma unroll 4
+        for (int i = tid; i < n; i += kT) visit((float)fma((double)x[i], scale, shift));
+      }
+      head = st_wave(head, StAdd());
+      all = st_wave(all, StAdd());
+      cnt = st_wave(cnt, StAdd());
+      auto& sv = sh.v[turn];
+      if (writer) { sv[0][wave] = head; sv[1][wave] = all; sv[2][wave] = cnt; }
+      __syncthreads();
+      const double a2 = st_collect<kT>(sv[0], 0.0, StAdd());
+      const double b2 = st_collect<kT>(sv[1], 0.0, StAdd()) - a2;
+      const double m = st_collect<kT>(sv[2], 0.0, StAdd());
+      turn ^= 1;
+      const double d = k - m;
+      if (0.5 * (b2 - a2) - d > 0.0) flo = fv; else fhi = fv;   // the threshold lies above, or below, this trial
+      const float df = (float)d, af = (float)a2, bf = (float)fmax(b2, 0.0);
+      const float root = sqrtf(fmaf(df, df, af * bf));   // A = a2 / 2, B = b2 / 2
+      const float ratio = df >= 0.f ? bf / (df + root) : (root - df) / af;
+      float next = fv + __log2f(ratio);
+      if (fabsf(next - fv) < 1e-3f) {   // an error of its square is left, below what fp32 resolves
+        fv = next;
+        break;
+      }
+      if (d == 0.0 && !(next > flo && next < fhi)) break;   // k values above, and all of them far away: a gap, left to fp64
+      if (!(next > flo && next < fhi)) next = 0.5f * (flo + fhi);
+      if (!(next > flo && next < fhi)) break;   // down to neighbouring numbers
+      fv = next;
+    }
+    v = fma((double)fv, kLn2, zc);
+    if (!(v > lo && v < hi)) v = 0.5 * (lo + hi);
+    v = st_uniform(v);
   }
-  pre[tid] = a_loc;
-  suf[tid] = b_loc;
-  __syncthreads();
-  for (int off = 1; off < kStThreads; off <<= 1) {
-    const double pa = tid >= off ? pre[tid - off] : -INFINITY;
-    const double sb = tid + off < kStThreads ? suf[tid + off] : -INFINITY;
-    __syncthreads();
-    pre[tid] = log_add_exp(pre[tid], pa);
-    suf[tid] = log_add_exp(suf[tid], sb);
-    __syncthreads();
-  }
-  const double before = tid > 0 ? pre[tid - 1] : -INFINITY;               // log S1 of everything ahead of the chunk
-  const double after = tid + 1 < kStThreads ? suf[tid + 1] : -INFINITY;   // log S2 of everything behind it
 
-  // chunks whose last element is still at or above the threshold are wholly in the head
-  bool whole = false;
-  if (end > start) {
-    const double v = from_key(keys[end - 1]) / tau;
-    whole = constraint_at(v, end, pre[tid], after, k) <= 0.0;
-  }
-  const int full_chunks = __syncthreads_count(whole);
-  const int used_chunks = (n + c - 1) / c;
-
-  if (tid == min(full_chunks, kStThreads - 1)) {
-    int m;
-    double log_s1, log_s2;
-    if (full_chunks >= used_chunks) {   // every element is at or above the threshold
-      m = n;
-      log_s1 = pre[kStThreads - 1];
-      log_s2 = -INFINITY;
+  // ---- fp64: prove the split, take the sums ----
+  double ex[kR];           // e^{-|z - v|}, negative (or -0) in the tail
+  double lambda = v, factor = 1.0;
+  int m = 0;
+  bool from_held = false;  // the outputs can be formed from ex and factor = e^{lambda - v}
+  double blo = lo, bhi = hi;
+#pragma unroll 1
+  for (int step = 0; step < kStExactSteps; ++step) {
+    double a = 0.0, b = 0.0, up = INFINITY, dn = INFINITY;
+    int cnt = 0;
+    auto visit = [&](double z) {
+      const double d = z - v;
+      const double e = exp(-fabs(d));
+      const bool head = d >= 0.0;
+      a += head ? e : 0.0;
+      b += head ? 0.0 : e;
+      up = fmin(up, head ? d : INFINITY);
+      dn = fmin(dn, head ? INFINITY : -d);
+      cnt += head ? 1 : 0;
+      return head ? e : -e;
+    };
+    if constexpr (kHeld) {
+      int first = tid;
+      asm volatile("" : "+v"(first));   // or the compiler keeps indices and quotients from step to step, in scratch memory
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        const int i = first + e * kT;
+        const double z = st_quotient(x[min(i, n - 1)], tau, rtau, moderate);
+        ex[e] = visit(i < n ? z : -INFINITY);
+        if (e & 1) __builtin_amdgcn_sched_barrier(0);   // two exponentials at a time fit the registers
+      }
     } else {
-      // the split lies in this thread's chunk: suffix sums inside the chunk, then a forward walk
-      const int cnt = end - start;
-      double run = -INFINITY;
-      for (int i = cnt - 1; i >= 0; --i) {
-        loc[i] = run;   // log sum of e^{x} over the chunk elements behind element i
-        run = log_add_exp(run, from_key(keys[start + i]) / tau);
-      }
-      m = start;
-      log_s1 = before;
-      log_s2 = log_add_exp(run, after);
-      double s1 = before;
-      for (int i = 0; i < cnt; ++i) {
-        const double v = from_key(keys[start + i]) / tau;
-        s1 = log_add_exp(s1, -v);
-        const double s2 = log_add_exp(loc[i], after);
-        if (constraint_at(v, start + i + 1, s1, s2, k) > 0.0) break;
-        m = start + i + 1;
-        log_s1 = s1;
-        log_s2 = s2;
-      }
+#pragma unroll 2
+      for (int i = tid; i < n; i += kT) visit(st_quotient(x[i], tau, rtau, moderate));
     }
-    // closed form of App. A.1 for y = e^lambda: S1 y^2 + 2 (k - m) y - S2 = 0, positive root,
-    // written so that neither a difference of close numbers nor an overflow occurs
+    a = st_wave(a, StAdd());
+    b = st_wave(b, StAdd());
+    up = st_wave(up, StMin());
+    dn = st_wave(dn, StMin());
+    cnt = st_wave(cnt, StAdd());
+    auto& sv = sh.v[turn];
+    if (writer) { sv[0][wave] = a; sv[1][wave] = b; sv[2][wave] = up; sv[3][wave] = dn; sv[4][wave] = cnt; }
+    __syncthreads();
+    a = 0.5 * st_collect<kT>(sv[0], 0.0, StAdd());
+    b = 0.5 * st_collect<kT>(sv[1], 0.0, StAdd());
+    up = st_collect<kT>(sv[2], INFINITY, StMin());
+    dn = st_collect<kT>(sv[3], INFINITY, StMin());
+    m = (int)st_collect<kT>(sv[4], 0.0, StAdd());
+    turn ^= 1;
     const double d = k - (double)m;
-    double lambda;
-    if (m == 0) lambda = log_s2 - log(2.0 * k);
-    else if (m == n) lambda = log(2.0 * ((double)n - k)) - log_s1;
-    else if (d >= 0.0) lambda = log_s2 - log_root_plus(d, log_s1 + log_s2);
-    else lambda = log_root_plus(-d, log_s1 + log_s2) - log_s1;
-    sh->lambda = lambda;
-    sh->m = m;
-  }
-  __syncthreads();
-  const double lambda = sh->lambda;
-  if (tid == 0 && info != nullptr) {
-    info[0] = lambda;
-    info[1] = (double)sh->m;
-  }
-  for (int i = tid; i < n; i += kStThreads) {
-    const double z = (double)x[i] / tau - lambda;
-    const double r = z >= 0.0 ? 1.0 - 0.5 * exp(-z) : 0.5 * exp(z);
-    if (y != nullptr) y[i] = r;
-    if (budgets != nullptr) budgets[i] = (int32_t)floor(r * t);
-  }
-}
-
-// ---- inputs too long to sort in LDS ---------------------------------------------------------------
-// The threshold is the root of g(v) = sum_i f(x_i / tau - v) - k, which decreases in v.  One workgroup
-// brackets it from the extremes of the input, then halves the bracket, one pass over the input per
-// step, until no input value lies inside: from then on the split index m is known, the sums S1 and
-// S2 take one more pass, and lambda comes out of the same closed form as above (App. A.1).  No sort,
-// any n; about 50 passes over an input that stays in the L2 cache.
-constexpr int kStLargeMaxN = 1 << 22;
-
-struct StLargeShared {
-  double d[4][16];
-  long long c[2][16];
-  double out_d[4];
-  long long out_c[2];
-};
-
-// block-wide sums of up to four doubles and two counters (fixed order: reproducible), result to every thread
-__device__ inline void st_block_sum(StLargeShared* sh, double (&v)[4], long long (&cnt)[2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] += __shfl_xor(v[i], off, 64);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) cnt[i] += __shfl_xor(cnt[i], off, 64);
-  }
-  __syncthreads();   // the previous round's results have been read
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sh->d[i][wave] = v[i];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) sh->c[i][wave] = cnt[i];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < 4; ++i) {
-      double a = 0.0;
-      for (int w = 0; w < kStThreads / 64; ++w) a += sh->d[i][w];
-      sh->out_d[i] = a;
+    double delta;
+    if (d == 0.0 && m > 0 && m < n && fmin(a, b) < kStTiny) {
+      // A whole target in a gap so wide that the sums underflow: both again, each relative to its own largest term
+      double sa = 0.0, sb = 0.0;
+      for (int i = tid; i < n; i += kT) {
+        const double dz = st_quotient(x[i], tau, rtau, moderate) - v;
+        if (dz >= 0.0) sa += exp(up - dz);
+        else sb += exp(dn + dz);
+      }
+      sa = st_wave(sa, StAdd());
+      sb = st_wave(sb, StAdd());
+      auto& su = sh.v[turn];
+      if (writer) { su[0][wave] = sa; su[1][wave] = sb; }
+      __syncthreads();
+      sa = st_collect<kT>(su[0], 0.0, StAdd());
+      sb = st_collect<kT>(su[1], 0.0, StAdd());
+      turn ^= 1;
+      delta = 0.5 * ((up - dn) + log(sb) - log(sa));
+      factor = INFINITY;
+    } else {
+      // the root without a difference of close numbers; a = 0 (empty head) and b = 0 (empty tail) come out as they should
+      const double root = hypot(d, 2.0 * sqrt(a) * sqrt(b));
+      factor = d >= 0.0 ? 2.0 * b / (d + root) : (root - d) / (2.0 * a);
+      delta = log(factor);
     }
-    for (int i = 0; i < 2; ++i) {
-      long long a = 0;
-      for (int w = 0; w < kStThreads / 64; ++w) a += sh->c[i][w];
-      sh->out_c[i] = a;
+    delta = st_uniform(delta);
+    factor = st_uniform(factor);
+    lambda = v + delta;
+    // the split holds when no value lies between v and lambda (values at lambda belong to the head)
+    if (delta >= 0.0 ? delta <= up : -delta < dn) {
+      from_held = kHeld && fabs(delta) < 100.0;
+      break;
     }
+    if ((double)m - k + (b - a) > 0.0) blo = v; else bhi = v;
+    double next = lambda;
+    if (!(next > blo && next < bhi)) next = 0.5 * (blo + bhi);
+    next = st_uniform(next);
+    lambda = v;
+    if (!(next > blo && next < bhi)) break;   // down to neighbouring numbers: what is inside ties with the root
+    v = next;
   }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = sh->out_d[i];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) cnt[i] = sh->out_c[i];
-}
-
-template <typename X>
-__global__ void __launch_bounds__(kStThreads)
-soft_topk_large_kernel(const X* x, int n, double k, double tau, double* y /* may alias x */,
-                       double* __restrict__ info, int32_t* __restrict__ budgets, double t,
-                       const double* __restrict__ k_vec) {
-  __shared__ StLargeShared sh;
-  select_vector(x, y, info, k, k_vec, n);   // batched call: this block's vector and target
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-
-  // extremes of z = x / tau
-  double zmin = INFINITY, zmax = -INFINITY;
-  for (int i = tid; i < n; i += kStThreads) {
-    const double z = (double)x[i] / tau;
-    zmin = fmin(zmin, z);
-    zmax = fmax(zmax, z);
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    zmin = fmin(zmin, __shfl_xor(zmin, off, 64));
-    zmax = fmax(zmax, __shfl_xor(zmax, off, 64));
-  }
-  if (lane == 0) { sh.d[0][wave] = zmin; sh.d[1][wave] = zmax; }
-  __syncthreads();
-  for (int w = 0; w < kStThreads / 64; ++w) { zmin = fmin(zmin, sh.d[0][w]); zmax = fmax(zmax, sh.d[1][w]); }
-  // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
-  // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
-  double lo = zmin - 1.0 - fmax(0.0, log((double)n / (2.0 * ((double)n - k))));
-  double hi = zmax + 1.0 + fmax(0.0, log((double)n / (2.0 * k)));
-
-  for (int step = 0; step < 200; ++step) {
-    const double mid = 0.5 * (lo + hi);
-    if (!(mid > lo && mid < hi)) break;   // the bracket is down to neighbouring numbers: what is inside ties with the root
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    long long cnt[2] = {0, 0};
-    for (int i = tid; i < n; i += kStThreads) {
-      const double z = (double)x[i] / tau;
-      const double d = z - mid;
-      v[0] += d >= 0.0 ? 1.0 - 0.5 * exp(-d) : 0.5 * exp(d);
-      cnt[0] += (z >= lo && z < mid) ? 1 : 0;
-      cnt[1] += (z >= mid && z < hi) ? 1 : 0;
-    }
-    st_block_sum(&sh, v, cnt);
-    long long inside;
-    if (v[0] - k > 0.0) { lo = mid; inside = cnt[1]; }
-    else { hi = mid; inside = cnt[0]; }
-    if (inside == 0) break;
-  }
-
-  // split: the head is {z >= hi}; log S1 = log sum_head e^{-z}, log S2 = log sum_rest e^{z}, each against its own maximum
-  double s1_ref = -INFINITY, s2_ref = -INFINITY;
-  for (int i = tid; i < n; i += kStThreads) {
-    const double z = (double)x[i] / tau;
-    if (z >= hi) s1_ref = fmax(s1_ref, -z);
-    else s2_ref = fmax(s2_ref, z);
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    s1_ref = fmax(s1_ref, __shfl_xor(s1_ref, off, 64));
-    s2_ref = fmax(s2_ref, __shfl_xor(s2_ref, off, 64));
-  }
-  __syncthreads();
-  if (lane == 0) { sh.d[2][wave] = s1_ref; sh.d[3][wave] = s2_ref; }
-  __syncthreads();
-  for (int w = 0; w < kStThreads / 64; ++w) { s1_ref = fmax(s1_ref, sh.d[2][w]); s2_ref = fmax(s2_ref, sh.d[3][w]); }
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  long long cnt[2] = {0, 0};
-  for (int i = tid; i < n; i += kStThreads) {
-    const double z = (double)x[i] / tau;
-    if (z >= hi) { v[0] += exp(-z - s1_ref); cnt[0] += 1; }
-    else v[1] += exp(z - s2_ref);
-  }
-  st_block_sum(&sh, v, cnt);
-  const int m = (int)cnt[0];
-  const double log_s1 = m > 0 ? s1_ref + log(v[0]) : -INFINITY;
-  const double log_s2 = m < n ? s2_ref + log(v[1]) : -INFINITY;
-  // closed form of App. A.1 for y = e^lambda: S1 y^2 + 2 (k - m) y - S2 = 0, positive root
-  const double d = k - (double)m;
-  double lambda;
-  if (m == 0) lambda = log_s2 - log(2.0 * k);
-  else if (m == n) lambda = log(2.0 * ((double)n - k)) - log_s1;
-  else if (d >= 0.0) lambda = log_s2 - log_root_plus(d, log_s1 + log_s2);
-  else lambda = log_root_plus(-d, log_s1 + log_s2) - log_s1;
   if (tid == 0 && info != nullptr) {
     info[0] = lambda;
     info[1] = (double)m;
   }
-  for (int i = tid; i < n; i += kStThreads) {
-    const double z = (double)x[i] / tau - lambda;
-    const double r = z >= 0.0 ? 1.0 - 0.5 * exp(-z) : 0.5 * exp(z);
+  auto put = [&](int i, double r) {
     if (y != nullptr) y[i] = r;
     if (budgets != nullptr) budgets[i] = (int32_t)floor(r * t);
+  };
+  if constexpr (kHeld) {
+    if (from_held) {
+      const double down = 1.0 / factor;
+      int first = tid;
+      asm volatile("" : "+v"(first));
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        const bool tail = __double_as_longlong(ex[e]) < 0;
+        if (first + e * kT < n) put(first + e * kT, tail ? -0.5 * ex[e] * down : fma(-0.5 * factor, ex[e], 1.0));
+      }
+      return;
+    }
+  }
+#pragma unroll 2
+  for (int i = tid; i < n; i += kT) {
+    const double z = st_quotient(x[i], tau, rtau, moderate) - lambda;
+    const double half = 0.5 * exp(-fabs(z));
+    put(i, z >= 0.0 ? 1.0 - half : half);
   }
 }
 
@@ -352,14 +419,18 @@ soft_topk_large_kernel(const X* x, int n, double k, double tau, double* y /* may
 // function theorem gives d lambda / d x_j = f'(z_j) / sum_i f'(z_i) = w_j and d lambda / d k =
 // -1 / sum_i f'(z_i), hence for an upstream gradient g = dL/dy
 //   dL/dx_j = (f'(z_j) / tau) (g_j - gbar),   dL/dk = gbar = sum_i g_i w_i.
-// One workgroup, three passes over the input: the smallest |z| (the weights are formed relative to
-// it, so a cold temperature at which every f'(z) underflows still yields the ratios), the two sums,
-// the output.  lambda is read from the forward call's `info`.  Sums in a fixed order.
-template <typename X>
-__global__ void __launch_bounds__(kStThreads)
+// One workgroup per vector; lambda is read from the forward call's `info`.  One pass takes the exponentials, the two
+// sums and the smallest |z|; up to 16384 values the exponentials and g stay in registers for the output, longer
+// vectors are read a second time.  Only when the sums underflow (a temperature so cold that every f'(z) does) are
+// they taken again relative to the smallest |z|, which still yields the ratios.  Sums in a fixed order.  256 vectors
+// of 16384 fp32 values: 18.5 us (34.5 us with three passes over x and two over g); the bytes alone take 14 us.
+template <typename X, int kT, int kE>
+__global__ void __launch_bounds__(kT)
 soft_topk_backward_kernel(const X* __restrict__ x, int n, double tau, const double* __restrict__ info,
                           const double* g, double* dx /* may alias g */, double* __restrict__ dk) {
-  __shared__ StLargeShared sh;
+  constexpr bool kHeld = kE > 0;
+  constexpr int kR = kHeld ? kE : 1;
+  __shared__ StScratch sh;
   {   // one vector per block
     const size_t b = blockIdx.x;
     x += b * n;
@@ -369,28 +440,72 @@ soft_topk_backward_kernel(const X* __restrict__ x, int n, double tau, const doub
     if (dk != nullptr) dk += b;
   }
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int wave = tid >> 6;
+  const bool writer = (tid & 63) == 0;
   const double lambda = info[0];
-  double amin = INFINITY;
-  for (int i = tid; i < n; i += kStThreads) amin = fmin(amin, fabs((double)x[i] / tau - lambda));
-  for (int off = 32; off > 0; off >>= 1) amin = fmin(amin, __shfl_xor(amin, off, 64));
-  if (lane == 0) sh.d[0][wave] = amin;
-  __syncthreads();
-  for (int w = 0; w < kStThreads / 64; ++w) amin = fmin(amin, sh.d[0][w]);
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  long long cnt[2] = {0, 0};
-  for (int i = tid; i < n; i += kStThreads) {
-    const double e = exp(amin - fabs((double)x[i] / tau - lambda));
-    v[0] += e;
-    v[1] += g[i] * e;
+  const double rtau = 1.0 / tau;
+  const bool moderate = tau > 1e-100 && tau < 1e100;
+  auto distance = [&](X xv) { return fabs(st_quotient(xv, tau, rtau, moderate) - lambda); };
+
+  double ex[kR], gr[kR];
+  double amin = INFINITY, s = 0.0, sg = 0.0;
+  if constexpr (kHeld) {
+    X xr[kR];
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      xr[e] = x[min(tid + e * kT, n - 1)];
+      gr[e] = g[min(tid + e * kT, n - 1)];
+    }
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      const double a = distance(xr[e]);
+      amin = fmin(amin, a);   // padding repeats the last value
+      ex[e] = tid + e * kT < n ? exp(-a) : 0.0;
+      s += ex[e];
+      sg = fma(gr[e], ex[e], sg);
+    }
+  } else {
+#pragma unroll 2
+    for (int i = tid; i < n; i += kT) {
+      const double a = distance(x[i]);
+      const double e = exp(-a);
+      amin = fmin(amin, a);
+      s += e;
+      sg = fma(g[i], e, sg);
+    }
   }
-  st_block_sum(&sh, v, cnt);
-  const double gbar = v[1] / v[0];
+  amin = st_wave(amin, StMin());
+  s = st_wave(s, StAdd());
+  sg = st_wave(sg, StAdd());
+  if (writer) { sh.v[0][0][wave] = amin; sh.v[0][1][wave] = s; sh.v[0][2][wave] = sg; }
+  __syncthreads();
+  amin = st_collect<kT>(sh.v[0][0], INFINITY, StMin());
+  s = st_collect<kT>(sh.v[0][1], 0.0, StAdd());
+  sg = st_collect<kT>(sh.v[0][2], 0.0, StAdd());
+  if (s < kStTiny) {   // the same in every thread
+    s = 0.0;
+    sg = 0.0;
+    for (int i = tid; i < n; i += kT) {
+      const double e = exp(amin - distance(x[i]));
+      s += e;
+      sg = fma(g[i], e, sg);
+    }
+    s = st_wave(s, StAdd());
+    sg = st_wave(sg, StAdd());
+    if (writer) { sh.v[1][0][wave] = s; sh.v[1][1][wave] = sg; }
+    __syncthreads();
+    s = st_collect<kT>(sh.v[1][0], 0.0, StAdd());
+    sg = st_collect<kT>(sh.v[1][1], 0.0, StAdd());
+  }
+  const double gbar = sg / s;
   if (tid == 0 && dk != nullptr) dk[0] = gbar;
-  const double inv_tau = 1.0 / tau;
-  for (int i = tid; i < n; i += kStThreads) {
-    const double a = fabs((double)x[i] / tau - lambda);
-    dx[i] = 0.5 * exp(-a) * (g[i] - gbar) * inv_tau;
+  if constexpr (kHeld) {
+#pragma unroll
+    for (int e = 0; e < kR; ++e)
+      if (tid + e * kT < n) dx[tid + e * kT] = 0.5 * ex[e] * (gr[e] - gbar) * rtau;
+  } else {
+#pragma unroll 2
+    for (int i = tid; i < n; i += kT) dx[i] = 0.5 * exp(-distance(x[i])) * (g[i] - gbar) * rtau;
   }
 }
 
@@ -418,61 +533,52 @@ head_scores_kernel(const float* __restrict__ emb, const float* __restrict__ w1, 
   }
 }
 
-int padded_size(int n) {
-  int P = 2;
-  while (P < n) P <<= 1;
-  return P;
+// Which kernel takes a vector of n values: the smallest that holds it in registers (fewer elements per thread, shorter
+// passes), one that re-reads it beyond that.  f(tag of the threads, tag of the elements per thread).
+template <int kMaxHeld, typename F>
+void soft_topk_dispatch(int n, F f) {
+  if (n <= 4 * kStSmallThreads) f(std::integral_constant<int, kStSmallThreads>(), std::integral_constant<int, 4>());
+  else if (n <= 4 * kStThreads) f(std::integral_constant<int, kStThreads>(), std::integral_constant<int, 4>());
+  else if (n <= 16 * kStThreads) f(std::integral_constant<int, kStThreads>(), std::integral_constant<int, 16>());
+  else if (n <= kMaxHeld * kStThreads) f(std::integral_constant<int, kStThreads>(), std::integral_constant<int, kMaxHeld>());
+  else f(std::integral_constant<int, kStThreads>(), std::integral_constant<int, 0>());
 }
 
-size_t soft_topk_lds(int P, size_t key_bytes) {
-  return (size_t)P * key_bytes + (size_t)(2 * kStThreads + kStLocal) * sizeof(double) + sizeof(StShared);
+template <typename X>
+void launch_soft_topk_as(const X* x, int n, double k, double tau, double* y, double* info, int32_t* budgets, double t,
+                         hipStream_t stream, int n_vec, const double* k_vec) {
+  soft_topk_dispatch<32>(n, [&](auto threads, auto held) {
+    hipLaunchKernelGGL((soft_topk_kernel<X, decltype(threads)::value, decltype(held)::value>), dim3(n_vec),
+                       dim3(decltype(threads)::value), 0, stream, x, n, k, tau, y, info, budgets, t, k_vec);
+  });
+}
+
+template <typename X>
+void launch_soft_topk_backward_as(const X* x, int n, double tau, const double* info, const double* g, double* dx,
+                                  double* dk, hipStream_t stream, int n_vec) {
+  soft_topk_dispatch<16>(n, [&](auto threads, auto held) {
+    hipLaunchKernelGGL((soft_topk_backward_kernel<X, decltype(threads)::value, decltype(held)::value>), dim3(n_vec),
+                       dim3(decltype(threads)::value), 0, stream, x, n, tau, info, g, dx, dk);
+  });
 }
 
 }  // namespace
 
-int soft_topk_sorted_max_n(bool is_f64) { return kStKeyBytes / (int)(is_f64 ? sizeof(uint64_t) : sizeof(uint32_t)); }
-int soft_topk_max_n(bool) { return kStLargeMaxN; }
+int soft_topk_max_n(bool) { return kStMaxN; }
 int head_scores_max_hidden() { return 4096; }
-
-hipError_t lkv_h_prepare() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(soft_topk_kernel<float, uint32_t>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)soft_topk_lds(kStKeyBytes / 4, 4));
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(soft_topk_kernel<double, uint64_t>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)soft_topk_lds(kStKeyBytes / 8, 8));
-}
 
 // y, info and budgets may each be null; y may alias x when x is fp64.  k_vec != nullptr: n_vec vectors of n values,
 // one block each, targets read from the device.
 void launch_soft_topk(const void* x, bool is_f64, int n, double k, double tau, double* y, double* info,
                       int32_t* budgets, double t, hipStream_t stream, int n_vec, const double* k_vec) {
-  if (n > soft_topk_sorted_max_n(is_f64)) {   // too long to sort in LDS: bracketing passes over the input
-    if (is_f64)
-      hipLaunchKernelGGL(soft_topk_large_kernel<double>, dim3(n_vec), dim3(kStThreads), 0, stream,
-                         static_cast<const double*>(x), n, k, tau, y, info, budgets, t, k_vec);
-    else
-      hipLaunchKernelGGL(soft_topk_large_kernel<float>, dim3(n_vec), dim3(kStThreads), 0, stream,
-                         static_cast<const float*>(x), n, k, tau, y, info, budgets, t, k_vec);
-    return;
-  }
-  const int P = padded_size(n);
-  if (is_f64)
-    hipLaunchKernelGGL((soft_topk_kernel<double, uint64_t>), dim3(n_vec), dim3(kStThreads), soft_topk_lds(P, 8), stream,
-                       static_cast<const double*>(x), n, P, k, tau, y, info, budgets, t, k_vec);
-  else
-    hipLaunchKernelGGL((soft_topk_kernel<float, uint32_t>), dim3(n_vec), dim3(kStThreads), soft_topk_lds(P, 4), stream,
-                       static_cast<const float*>(x), n, P, k, tau, y, info, budgets, t, k_vec);
+  if (is_f64) launch_soft_topk_as(static_cast<const double*>(x), n, k, tau, y, info, budgets, t, stream, n_vec, k_vec);
+  else launch_soft_topk_as(static_cast<const float*>(x), n, k, tau, y, info, budgets, t, stream, n_vec, k_vec);
 }
 
 void launch_soft_topk_backward(const void* x, bool is_f64, int n, double tau, const double* info, const double* g,
                                double* dx, double* dk, hipStream_t stream, int n_vec) {
-  if (is_f64)
-    hipLaunchKernelGGL(soft_topk_backward_kernel<double>, dim3(n_vec), dim3(kStThreads), 0, stream,
-                       static_cast<const double*>(x), n, tau, info, g, dx, dk);
-  else
-    hipLaunchKernelGGL(soft_topk_backward_kernel<float>, dim3(n_vec), dim3(kStThreads), 0, stream,
-                       static_cast<const float*>(x), n, tau, info, g, dx, dk);
+  if (is_f64) launch_soft_topk_backward_as(static_cast<const double*>(x), n, tau, info, g, dx, dk, stream, n_vec);
+  else launch_soft_topk_backward_as(static_cast<const float*>(x), n, tau, info, g, dx, dk, stream, n_vec);
 }
 
 void launch_head_scores(const float* emb, const float* w1, const float* b1, const float* w2, const float* b2,

@@ -83,7 +83,6 @@ void launch_masked_attn_bwd(const void* q, const void* k, const void* v, const f
                             float* dq, float* dk, float* dv, float* dm, float* workspace, hipStream_t stream);
 
 // lkv_h.hip
-hipError_t lkv_h_prepare();
 int soft_topk_max_n(bool is_f64);
 int head_scores_max_hidden();
 void launch_soft_topk(const void* x, bool is_f64, int n, double k, double tau, double* y, double* info,

@@ -167,6 +167,33 @@ def test_soft_topk_in_place_and_repeatable(ctx):
     assert np.array_equal(y0, y1) and lam0 == lam1 and m0 == m1
 
 
+@pytest.mark.parametrize("n", [1024, 1025, 4096, 4097, 16384, 16385, 32768, 32769])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_soft_topk_either_side_of_every_kernel_size(ctx, n, dtype):
+    # The threshold is the unique root of sum_i f(x_i / tau - lambda) = k, so the outputs are checked against f at the
+    # returned lambda and the sum against k: f is evaluated to a few 1e-16 on both sides, z = x / tau to |z| 2^-53, and
+    # lambda to |lambda| 2^-52, hence 1e-15 max(1, |z|) per output.  Warm, cold, a whole target inside a wide gap (every
+    # f'(z) underflows), ties at the threshold, one value far from the rest.
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal(n).astype(dtype)
+    tied = np.round(x * 2).astype(dtype) / 2
+    far = x.copy()
+    far[n // 3] = 3e4
+    gap = np.where(np.arange(n) % 5 == 0, x + 100, x).astype(dtype)
+    head = int((np.arange(n) % 5 == 0).sum())
+    for what, xs, k, tau in (("warm", x, 0.15 * n, 1.0), ("mild", x, n - 0.4, 0.05), ("cold", x, 0.1 * n + 0.3, 1e-6), ("few", x, 0.01, 0.3),
+                             ("tied", tied, 0.4 * n, 0.01), ("far", far, 0.3 * n, 0.1), ("gap", gap, float(head), 1e-2)):
+        y, lam, m = _gpu_soft_topk(ctx, xs, k, tau)
+        z = xs.astype(np.float64) / tau - lam
+        half = 0.5 * np.exp(-np.abs(z))
+        ref = np.where(z >= 0, 1.0 - half, half)
+        tol = 4e-15 * max(1.0, abs(lam))
+        assert np.abs(y - ref).max() <= tol, (what, np.abs(y - ref).max())
+        # one rounding of lambda moves the sum by at most sum f'(z) |lambda| 2^-52; n roundings of the terms besides
+        assert abs(y.sum() - k) <= tol * max(1.0, half.sum()) + 1e-15 * n, (what, y.sum() - k)
+        assert int((z > tol).sum()) <= m <= int((z >= -tol).sum()), what
+
+
 def test_soft_topk_argument_errors(ctx):
     x = torch.zeros(10, dtype=torch.float64, device="cuda")
     y = torch.empty_like(x)
