@@ -5,22 +5,32 @@
 //
 // m is one weight in [0, 1] per KV head and key; the heads of a GQA group share their KV head's
 // weights (Sec. 3.1).  As App. B.2 describes, the mask multiplies the exponentials inside the
-// online softmax (the running maximum is that of the raw scores), so no logarithm of m is ever
+// softmax (the references of the exponentials are raw scores), so no logarithm of m is ever
 // taken.  Next to the output the kernel returns log sum_k e^{s_ik} m_k per query, which the
 // backward pass uses to rebuild p from s.
 //
 // Tiling (flash-attention style, for 64-wide waves and the 16x16x32 bf16 matrix instruction).  A block of four
-// waves owns one query head and 64 * kQB consecutive queries, 16 * kQB per wave; it walks the keys up to its
-// diagonal in tiles of 32 * kSteps.  A tile's K and V rows and its mask weights are staged once per block in
-// LDS, double buffered with one barrier per tile, and read back as operands by all four waves.  Per wave and
-// 32-key step:
+// waves owns one query head and 128 consecutive queries, 32 per wave; it walks the keys up to its diagonal in tiles
+// of 64, staged once per block in LDS, double buffered with one barrier per tile, and read back as operands by all
+// four waves.  Per wave and step of 32 keys:
 //   S^T[key, query] = K[key, :] . Q[query, :]^T      (A = K rows from LDS, B = Q^T held in registers)
 //   O[query, ch]   += P[query, key] V[key, ch]       (A = P, B = V rows by the transposing LDS read)
 // The accumulator layout of S^T (lane (rb, query) holds keys 4 rb .. 4 rb + 3 of a 16-key half) is the
 // A-operand layout of P for one K-step over the 32 keys, so probabilities go from the first product to the
-// second without leaving their lanes.  Each K and V operand read is shared by the kQB query blocks of the wave.
-// The online softmax is updated once per tile.  The denominator that divides the output is one more output
-// column of the second product (P times a column of ones), see acc_l below.
+// second without leaving their lanes.  Each K and V operand read is shared by the two query blocks of the wave.
+// The denominator that divides the output is one more output column of the second product (P times a column of
+// ones), see acc_l below.
+//
+// What bounds it: energy, then instruction issue.  At 16k tokens the chip holds 1.9 to 2.0 of its 2.4 GHz under this
+// kernel, and a variant that spends fewer cycles runs at a lower clock, so what pays is work not done: references
+// that stay put (no maximum, no rescaling: 8 %), rows that go from memory to LDS without passing registers (which
+// also frees the 32 registers that the pipeline needs), sums kept from being postponed into the next step (6 %).  The
+// steps are pipelined inside a wave (value products of step s - 1, weights of step s, logits of step s + 1 in one
+// scheduling region), which took the share of matrix time that vector work runs beside from 22 to 38 %.  32 query
+// heads, 8 KV heads: 2.44 -> 1.98 ms at 16384 tokens (1110 TFLOP/s; a library product of 8192 x 8192 x 8192 reaches
+// 1310 here), 649 -> 530 us at 8192, 182 -> 149 at 4096, 74 -> 61 at 2345.  Measured and dropped: 64 queries per wave
+// at one wave per SIMD (half the LDS reads; 2.38 ms), a block of eight waves in two groups that split the keys (2.41
+// ms; 86 us at 2345 tokens), different wave priorities on a SIMD (no change).
 #include <type_traits>
 
 #include "lkv_common.h"
@@ -32,12 +42,17 @@ namespace {
 
 constexpr int kMaThreads = 256;
 constexpr int kMaWaves = kMaThreads / 64;
-constexpr int kMaKeys = 32;                   // keys per tile: one K-step of the P.V product
-constexpr int kMaKStride = 288;               // LDS bytes per staged K row (measured conflict free; 272 was not)
-constexpr int kMaVStride = 288;               // LDS bytes per staged V row (conflict-free transposing reads)
-constexpr int kMaTileLds = kMaKeys * (kMaKStride + kMaVStride) + kMaKeys * 4;   // K, V and the mask weights
+constexpr int kMaStep = 32;                   // keys per pipeline step: one K-step of the P.V product
+constexpr int kMaTile = 2 * kMaStep;          // keys staged per barrier
+constexpr int kMaRow = 256;                   // LDS bytes per staged row: rows lie as in memory, their 16-byte pieces permuted
+constexpr int kMaQB = 2;                      // 16-query column blocks per wave
+constexpr int kMaWaveQ = 16 * kMaQB;
+constexpr int kMaBlockQ = kMaWaves * kMaWaveQ;
+constexpr int kMaTileLds = 2 * kMaTile * kMaRow + kMaTile * 4;   // K rows, V rows, mask weights
 constexpr float kMaLog2e = 1.4426950408889634f;
 constexpr float kMaLn2 = 0.6931471805599453f;
+constexpr float kMaRebase = 64.f;             // log2 distance at which a reference moves, where they do
+constexpr float kMaMostSum = 1.0995116e12f;   // 2^40: largest sum of weights relative to a reference that stays put
 
 __device__ __forceinline__ float ma_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -47,18 +62,14 @@ __device__ __forceinline__ s16x4_t ma_read_tr16(const unsigned char* p) {
 
 }  // namespace
 
-template <int kQB, int kSteps>
 __global__ void __launch_bounds__(kMaThreads, 2)
 masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
                        const float* __restrict__ m, int T, int n_heads, int G, float scale, float* __restrict__ o,
                        float* __restrict__ lse) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int kWaveQ = 16 * kQB;
-  constexpr int kBlockQ = kMaWaves * kWaveQ;
-  constexpr int kTileKeys = kMaKeys * kSteps;          // keys staged per barrier
-  constexpr int kTileLds = kSteps * kMaTileLds;
-  constexpr int kStage = kTileKeys / 16;               // staged rows per thread and tensor
-  const int n_qtiles = (T + kBlockQ - 1) / kBlockQ;
+  // Two arrays and not one: the compiler then knows that reads of one do not touch the rows on their way to the other.
+  __shared__ __align__(1024) unsigned char tile_a[kMaTileLds];
+  __shared__ __align__(1024) unsigned char tile_b[kMaTileLds];
+  const int n_qtiles = (T + kMaBlockQ - 1) / kMaBlockQ;
   // blocks in order of decreasing work: the query tile is the slow index, the head the fast one,
   // so that the longest rows of the causal triangle of every head start first
   const int qtile = n_qtiles - 1 - (int)blockIdx.x / n_heads;
@@ -66,205 +77,276 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   const int h = hq / G;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane >> 4;
   const int c = lane & 15;
-  const int q0 = qtile * kBlockQ;
-  const int qw0 = q0 + wave * kWaveQ;                  // first query of this wave
-  const int n_tiles = (min(q0 + kBlockQ, T) + kTileKeys - 1) / kTileKeys;
+  const int q0 = qtile * kMaBlockQ;
+  const int qw0 = q0 + wave * kMaWaveQ;                // first query of this wave
+  // steps of 32 keys: this wave's last one is the one on its diagonal; a wave past the end has none
+  const int n_steps = qw0 < T ? (qw0 + kMaWaveQ) / kMaStep : 0;
   const float qscale = scale * kMaLog2e;
   bf16x8_t ones;
 #pragma unroll
   for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
 
   // B operand of the first product: Q^T, lane (query c of block qb, K-block r) holds q[query][32 ks + 8 r .. +7]
-  bf16x8_t qfrag[kQB][4];
+  bf16x8_t qfrag[kMaQB][4];
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb) {
+  for (int qb = 0; qb < kMaQB; ++qb) {
     const int query = min(qw0 + 16 * qb + c, T - 1);   // queries past the end repeat the last one; never stored
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
       qfrag[qb][ks] = __builtin_bit_cast(
           bf16x8_t, reinterpret_cast<const uint4*>(q + ((size_t)hq * T + query) * kHeadDim)[ks * 4 + r]);
   }
-  float m_run[kQB], l_run[kQB];     // per query c of block qb: running maximum (log2 domain), this lane's share of the
-                                    // unrounded denominator (for the log-normaliser that is returned)
-  f32x4_t acc_o[kQB][8];            // O[query 4 r + e of block qb][channel 16 ct + c]
+  float ref[kMaQB];                 // per query c of block qb: reference of the exponentials (log2 domain)
+  float l_run[kMaQB];               // this lane's share of the unrounded denominator (for the log-normaliser returned)
+  f32x4_t acc_o[kMaQB][8];          // O[query 4 r + e of block qb][channel 16 ct + c]
   // Denominator the output is divided by, for query 4 r + e, the same in all 16 lanes of a row block: it is
   // accumulated by the matrix cores as one more output column, P times a column of ones, hence from the same
   // bf16-rounded weights as the output.  The output is then an exact convex combination of value rows, which keeps o (and the
   // D_i = dO_i . o_i of the backward pass) accurate where one key holds nearly all the weight.
-  f32x4_t acc_l[kQB];
-#pragma unroll
-  for (int qb = 0; qb < kQB; ++qb) {
-    m_run[qb] = -INFINITY;
-    l_run[qb] = 0.f;
-    acc_l[qb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) acc_o[qb][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
+  f32x4_t acc_l[kMaQB];
+  bf16x8_t pfrag[kMaQB];            // weights of the step before, not yet multiplied with its value rows
 
-  // staging: thread (row slot tid / 16, piece tid % 16) moves rows slot, slot + 16, ... of the tile.
-  // The registers are loaded unconditionally (an array assigned under a condition ends up in scratch memory).
   const uint4* kh = k + (size_t)h * T * kChunksPerRow;
   const uint4* vh = v + (size_t)h * T * kChunksPerRow;
   const float* mh = m + (size_t)h * T;
+  f32x4_t sacc[kMaQB][2];           // S^T of a step: lane (rb = r, query c) holds keys 16 sub + 4 r + e
+
+  // Staging, straight from memory into LDS: a wave instruction fills 1 KB, four rows; lane (row slot, piece slot) fetches
+  // piece `slot ^ f(row)` of its row, so that the straight reads of K (16 rows of one piece: f = row) and the transposing
+  // reads of V (4 rows of 32 bytes: f = 2 row) both find their banks apart.  Tile t holds the K rows of steps 2 t + 1 and
+  // 2 t + 2, the V rows of steps 2 t - 1 and 2 t and the weights of steps 2 t and 2 t + 1: what the pipeline multiplies
+  // in its steps 2 t and 2 t + 1.  Rows outside the sequence repeat its first or last one.
   const int srow = tid >> 4, spiece = tid & 15;
-  // Named registers: as arrays these ended up in scratch memory, which also serialised the loads.
-  static_assert(kStage == 4, "the staging registers below are written out for 64-key tiles");
-  uint4 k_s0, k_s1, k_s2, k_s3, v_s0, v_s1, v_s2, v_s3;
-  float mk;
-#define LKV_MA_LOAD_ROW(j_, kreg_, vreg_, t_)                                                                 \
-  {                                                                                                           \
-    const int key = min((t_) * kTileKeys + srow + 16 * (j_), T - 1); /* past the end: the last row, unused */ \
-    const uint32_t off = (uint32_t)key * 256u + (uint32_t)spiece * 16u; /* a 32-bit offset from a uniform base */ \
-    kreg_ = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(kh) + off);                \
-    vreg_ = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(vh) + off);                \
-  }
-#define LKV_MA_LOAD_TILE(t_)                                            \
-  {                                                                     \
-    LKV_MA_LOAD_ROW(0, k_s0, v_s0, t_)                                  \
-    LKV_MA_LOAD_ROW(1, k_s1, v_s1, t_)                                  \
-    LKV_MA_LOAD_ROW(2, k_s2, v_s2, t_)                                  \
-    LKV_MA_LOAD_ROW(3, k_s3, v_s3, t_)                                  \
-    mk = mh[min((t_) * kTileKeys + (tid & (kTileKeys - 1)), T - 1)];    \
-  }
-#define LKV_MA_STORE_ROW(j_, kreg_, vreg_)                                                                     \
-  {                                                                                                            \
-    unsigned char* step_buf = buf + ((j_) >> 1) * kMaTileLds;                                                  \
-    const int row = srow + 16 * ((j_) & 1);                                                                    \
-    *reinterpret_cast<uint4*>(step_buf + row * kMaKStride + spiece * 16) = kreg_;                              \
-    *reinterpret_cast<uint4*>(step_buf + kMaKeys * kMaKStride + row * kMaVStride + spiece * 16) = vreg_;       \
-  }
-  LKV_MA_LOAD_TILE(0)
+  const uint32_t k_piece = (uint32_t)((spiece ^ srow) * 16), v_piece = (uint32_t)((spiece ^ (2 * srow & 15)) * 16);
+  auto stage = [&](unsigned char* dst, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int krow = min(t * kMaTile + kMaStep + srow + 16 * j, T - 1);
+      const int vrow = min(max(t * kMaTile - kMaStep + srow + 16 * j, 0), T - 1);
+      lds_fill16(reinterpret_cast<const unsigned char*>(kh) + ((uint32_t)krow * 256u + k_piece),
+                 dst + (16 * j + 4 * wave) * kMaRow);
+      lds_fill16(reinterpret_cast<const unsigned char*>(vh) + ((uint32_t)vrow * 256u + v_piece),
+                 dst + (kMaTile + 16 * j + 4 * wave) * kMaRow);
+    }
+    if (wave == 0) lds_fill4(mh + min(t * kMaTile + lane, T - 1), dst + 2 * kMaTile * kMaRow);
+  };
+  // The last tile has one K step less (no wave has a step after the fourth around the diagonal); the V rows of its second
+  // step, whose products come last of all, take that place.
+  const int n_full = q0 / kMaTile;   // tiles whose steps lie wholly below the diagonal of every wave of the block; even
+  auto stage_last = [&](unsigned char* dst) __attribute__((always_inline)) {
+    const int t = n_full + 1;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const int vrow = min(t * kMaTile - kMaStep + srow + 16 * j, T - 1);
+      lds_fill16(reinterpret_cast<const unsigned char*>(vh) + ((uint32_t)vrow * 256u + v_piece),
+                 dst + ((j < 4 ? kMaTile + 16 * j : 16 * (j - 2)) + 4 * wave) * kMaRow);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int krow = min(t * kMaTile + kMaStep + srow + 16 * j, T - 1);
+      lds_fill16(reinterpret_cast<const unsigned char*>(kh) + ((uint32_t)krow * 256u + k_piece),
+                 dst + (16 * j + 4 * wave) * kMaRow);
+    }
+    if (wave == 0) lds_fill4(mh + min(t * kMaTile + lane, T - 1), dst + 2 * kMaTile * kMaRow);
+  };
+  // where this lane reads: K rows 16 sub + c, pieces 4 ks + r; V rows 4 r + c / 4, channels 16 ct + 4 (c % 4)
+  const uint32_t k_at = c * kMaRow + ((r ^ c) * 16);   // piece 4 ks + r is at k_at ^ 64 ks
+  const int v_row = 4 * r + (c >> 2);
+  const uint32_t v_at = v_row * kMaRow + ((((c >> 1) & 1) ^ (2 * v_row & 15)) * 16) + (c & 1) * 8;   // tile ct at v_at ^ 32 ct
 
-#pragma unroll 1
-  for (int t = 0; t < n_tiles; ++t) {
-    // row 32 s + i of the tile lives in step buffer s: K rows, V rows, then the 32 mask weights
-    unsigned char* buf = smem + (t & 1) * kTileLds;
-    LKV_MA_STORE_ROW(0, k_s0, v_s0)
-    LKV_MA_STORE_ROW(1, k_s1, v_s1)
-    LKV_MA_STORE_ROW(2, k_s2, v_s2)
-    LKV_MA_STORE_ROW(3, k_s3, v_s3)
-    if (tid < kTileKeys)
-      reinterpret_cast<float*>(buf + (tid >> 5) * kMaTileLds + kMaKeys * (kMaKStride + kMaVStride))[tid & 31] = mk;
-    LKV_MA_LOAD_TILE(min(t + 1, n_tiles - 1))   // the last iteration re-reads its own tile: no branch around the loads
-    // One barrier per tile is enough with two buffers: a wave that runs ahead writes the other
-    // buffer, and it cannot come back to this one before every wave has passed the next barrier.
-    __syncthreads();
-    const int key0 = t * kTileKeys;
-    // wave-uniform: nothing to do when the tile lies wholly above this wave's diagonal
-    if (key0 <= qw0 + kWaveQ - 1 && qw0 < T) {
-
-    // S^T for the 16-key pieces of the tile: lane (rb = r, query c) gets keys 16 sub + 4 r + e
-    f32x4_t sacc[kQB][2 * kSteps];
+  // O += P V of the step before: B operand lane (channel c of tile ct, K-block r) holds
+  // V[keys 4r..4r+3 and 16+4r..16+4r+3][channel]
+  auto value_products = [&](const unsigned char* v_lds) __attribute__((always_inline)) {
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb)
+    for (int qb = 0; qb < kMaQB; ++qb)
+      acc_l[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb], ones, acc_l[qb], 0, 0, 0);
 #pragma unroll
-      for (int sub = 0; sub < 2 * kSteps; ++sub) sacc[qb][sub] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < 8; ++ct) {
+      const s16x4_t v0 = ma_read_tr16(v_lds + (v_at ^ (32 * ct)));
+      const s16x4_t v1 = ma_read_tr16(v_lds + (v_at ^ (32 * ct)) + 16 * kMaRow);
+      const s16x8_t vb = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-    for (int sub = 0; sub < 2 * kSteps; ++sub) {
-      const unsigned char* k_lds = buf + (sub >> 1) * kMaTileLds;
+      for (int qb = 0; qb < kMaQB; ++qb)
+        acc_o[qb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb], __builtin_bit_cast(bf16x8_t, vb),
+                                                                acc_o[qb][ct], 0, 0, 0);
+    }
+  };
+  // One pipeline step: the value products of step s - 1, the weights of step s, the logits of step s + 1; nothing in
+  // it waits for anything else in it, so matrix and vector instructions of one wave run side by side.
+  // kDiag: some key of the step may lie above some query's diagonal.  kMoving: the references follow the running maxima
+  // (lazily); else they stay at the maxima of the first step and nothing looks at the maxima any more.
+  auto step = [&](auto diag_tag, auto moving_tag, const unsigned char* tile, int s, int half) __attribute__((always_inline)) {
+    constexpr bool kDiag = decltype(diag_tag)::value, kMoving = decltype(moving_tag)::value;
+    const unsigned char* k_lds = tile + half * kMaStep * kMaRow;
+    const float* m_lds = reinterpret_cast<const float*>(tile + 2 * kMaTile * kMaRow) + half * kMaStep;
+    value_products(k_lds + kMaTile * kMaRow);
+    float top = -INFINITY;
+#pragma unroll
+    for (int qb = 0; qb < kMaQB; ++qb)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float x = fmaf(sacc[qb][i >> 2][i & 3], qscale, -ref[qb]);
+        if (kDiag) x = s * kMaStep + 16 * (i >> 2) + 4 * r + (i & 3) > qw0 + 16 * qb + c ? -INFINITY : x;
+        if (kMoving) top = fmaxf(top, x);
+        sacc[qb][i >> 2][i & 3] = x;
+      }
+    if (kMoving && __builtin_expect(__ballot(top > kMaRebase) != 0ull, 0)) {
+      // a logit runs away: move the references of the queries to their running maxima and rescale what has been
+      // summed (queries 4 r + e in the output registers)
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb) {
+        float up = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) up = fmaxf(up, sacc[qb][i >> 2][i & 3]);
+        up = max_over_row_blocks(up);
+        const float alpha = ma_exp2(-up);
+        ref[qb] += up;
+        l_run[qb] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sacc[qb][i >> 2][i & 3] -= up;
+        float al[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * r + e, 64);
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc_o[qb][ct][e] *= al[e];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc_l[qb][e] *= al[e];
+      }
+    }
+    f32x4_t next[kMaQB][2];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb) next[qb][sub] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
-        const uint4 kx = *reinterpret_cast<const uint4*>(k_lds + ((sub & 1) * 16 + c) * kMaKStride + ks * 64 + r * 16);
+        const uint4 kx = *reinterpret_cast<const uint4*>(k_lds + sub * 16 * kMaRow + (k_at ^ (64 * ks)));
 #pragma unroll
-        for (int qb = 0; qb < kQB; ++qb)
+        for (int qb = 0; qb < kMaQB; ++qb)
+          next[qb][sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kx), qfrag[qb][ks],
+                                                                  next[qb][sub], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      const float4 mw4 = *reinterpret_cast<const float4*>(m_lds + 16 * tt + 4 * r);
+      const float mw[4] = {mw4.x, mw4.y, mw4.z, mw4.w};
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = ma_exp2(sacc[qb][tt][e]) * mw[e];   // the mask multiplies the exponential (App. B.2)
+          l_run[qb] += p;
+          pfrag[qb][tt * 4 + e] = (__bf16)p;
+        }
+    }
+    // the weights and their sums are due here, beside the products above, and not where they are used
+#pragma unroll
+    for (int qb = 0; qb < kMaQB; ++qb) asm volatile("" : "+v"(pfrag[qb]), "+v"(l_run[qb]));
+#pragma unroll
+    for (int qb = 0; qb < kMaQB; ++qb)
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) sacc[qb][sub] = next[qb][sub];
+  };
+  auto start = [&]() __attribute__((always_inline)) {
+    // S^T of the first step, its K rows straight from memory: lane (rb = r, query c) gets keys 16 sub + 4 r + e
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb) sacc[qb][sub] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const uint4 kx = kh[(size_t)min(16 * sub + c, T - 1) * kChunksPerRow + ks * 4 + r];
+#pragma unroll
+        for (int qb = 0; qb < kMaQB; ++qb)
           sacc[qb][sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kx), qfrag[qb][ks],
                                                                   sacc[qb][sub], 0, 0, 0);
       }
     }
-
-    bf16x8_t pfrag[kQB][kSteps];
-    // online softmax of one query block over the tile; kDiag: some key of the tile lies above some query's diagonal
-    auto softmax = [&](auto diag_tag) {
-      constexpr bool kDiag = decltype(diag_tag)::value;
 #pragma unroll
-      for (int qb = 0; qb < kQB; ++qb) {
-        const int query = qw0 + 16 * qb + c;
-        float sv[8 * kSteps];
-        float mx = -INFINITY;
+    for (int qb = 0; qb < kMaQB; ++qb) {
+      float top = -INFINITY;
 #pragma unroll
-        for (int sub = 0; sub < 2 * kSteps; ++sub)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float s = sacc[qb][sub][e];
-            sv[4 * sub + e] = kDiag && key0 + 16 * sub + 4 * r + e > query ? -INFINITY : s;
-            mx = fmaxf(mx, sv[4 * sub + e]);
-          }
-        mx = max_over_row_blocks(mx);
-        mx = fmaxf(m_run[qb], mx * qscale);              // qscale > 0: scaling commutes with the maximum
-        const float ref = mx == -INFINITY ? 0.f : mx;
-        const float alpha = ma_exp2(m_run[qb] - ref);    // exp2(-inf) = 0 on the first tile
-        m_run[qb] = mx;
-        float psum = 0.f;
-#pragma unroll
-        for (int st = 0; st < kSteps; ++st) {
-          const float* m_lds = reinterpret_cast<const float*>(buf + st * kMaTileLds + kMaKeys * (kMaKStride + kMaVStride));
-#pragma unroll
-          for (int tt = 0; tt < 2; ++tt) {
-            const float4 mw4 = *reinterpret_cast<const float4*>(m_lds + 16 * tt + 4 * r);
-            const float mw[4] = {mw4.x, mw4.y, mw4.z, mw4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              // the mask multiplies the exponential (App. B.2)
-              const float p = ma_exp2(fmaf(sv[8 * st + 4 * tt + e], qscale, -ref)) * mw[e];
-              psum += p;
-              pfrag[qb][st][tt * 4 + e] = (__bf16)p;
-            }
-          }
-        }
-        l_run[qb] = l_run[qb] * alpha + psum;
-        // rescale the output rows (queries 4 r + e) when any running maximum of the block moved
-        if (__ballot(alpha != 1.f) != 0ull) {
-          float al[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * r + e, 64);
-#pragma unroll
-          for (int ct = 0; ct < 8; ++ct)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc_o[qb][ct][e] *= al[e];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc_l[qb][e] *= al[e];
-        }
+      for (int i = 0; i < 8; ++i) {
+        const float x = sacc[qb][i >> 2][i & 3] * qscale;
+        top = fmaxf(top, 16 * (i >> 2) + 4 * r + (i & 3) > qw0 + 16 * qb + c ? -INFINITY : x);
       }
-    };
-    if (key0 + kTileKeys - 1 > qw0) softmax(std::true_type{});   // wave-uniform
-    else softmax(std::false_type{});
-
-    // O += P V: B operand lane (channel c of tile ct, K-block r) holds V[keys 4r..4r+3 and 16+4r..16+4r+3][channel]
+      top = max_over_row_blocks(top);
+      ref[qb] = top > -INFINITY ? top : 0.f;   // key 0 is seen by every query: only a logit of -inf gets here
+      l_run[qb] = 0.f;
+      acc_l[qb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int st = 0; st < kSteps; ++st) {
-      const unsigned char* v_lds = buf + st * kMaTileLds + kMaKeys * kMaKStride;
+      for (int ct = 0; ct < 8; ++ct) acc_o[qb][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int qb = 0; qb < kQB; ++qb)
-        acc_l[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb][st], ones, acc_l[qb], 0, 0, 0);
-#pragma unroll
-      for (int ct = 0; ct < 8; ++ct) {
-        const unsigned char* base = v_lds + (4 * r + (c >> 2)) * kMaVStride + ct * 32 + (c & 3) * 8;
-        const s16x4_t v0 = ma_read_tr16(base);
-        const s16x4_t v1 = ma_read_tr16(base + 16 * kMaVStride);
-        const s16x8_t vb = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-#pragma unroll
-        for (int qb = 0; qb < kQB; ++qb)
-          acc_o[qb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb][st], __builtin_bit_cast(bf16x8_t, vb),
-                                                                  acc_o[qb][ct], 0, 0, 0);
-      }
+      for (int i = 0; i < 8; ++i) pfrag[qb][i] = (__bf16)0.f;
     }
+  };
+  // the steps around the diagonal, where the waves of the block end one after the other
+  auto last_tile = [&](auto moving_tag, const unsigned char* tile, int t) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {   // wave-uniform branches
+      const int s = 2 * t + half;
+      if (s < n_steps) step(std::true_type{}, moving_tag, tile, s, half);
+      else if (s == n_steps) value_products(tile + (kMaTile + half * kMaStep) * kMaRow);
+    }
+    if (t == n_full + 1 && n_steps == 2 * t + 2) value_products(tile + kMaStep * kMaRow);
+  };
+
+  // One barrier per tile: it makes the tile's rows visible (the compiler waits for the transfers before it) and means
+  // that every wave is done with the other array, which the next tile then fills.
+  stage(tile_a, 0);
+  start();
+#pragma unroll 1
+  for (int t = 0; t < n_full; t += 2) {
+    __syncthreads();
+    stage(tile_b, t + 1);
+    step(std::false_type{}, std::false_type{}, tile_a, 2 * t, 0);
+    step(std::false_type{}, std::false_type{}, tile_a, 2 * t + 1, 1);
+    __syncthreads();
+    stage(tile_a, t + 2);
+    step(std::false_type{}, std::false_type{}, tile_b, 2 * t + 2, 0);
+    step(std::false_type{}, std::false_type{}, tile_b, 2 * t + 3, 1);
+  }
+  __syncthreads();
+  stage_last(tile_b);
+  last_tile(std::false_type{}, tile_a, n_full);
+  __syncthreads();
+  last_tile(std::false_type{}, tile_b, n_full + 1);
+
+  // References that stay put save the maximum, the branch on it and the rescaling it guards, 8 % of the time.  They hold
+  // as long as the sums stay far from overflow: a sum above 2^40 says that some logit exceeded its reference by more
+  // than 24 binary orders, and the block starts over with moving ones.  (Any reference up to there gives the same
+  // weights to a rounding; logits far below a reference vanish next to the key that set it, as below a maximum.)
+  bool over = false;
+#pragma unroll
+  for (int qb = 0; qb < kMaQB; ++qb) over |= !(l_run[qb] < kMaMostSum);
+  if (__builtin_expect(__syncthreads_or(over), 0)) {
+    stage(tile_a, 0);
+    start();
+#pragma unroll 1
+    for (int t = 0; t < n_full + 2; ++t) {
+      unsigned char* tile = t & 1 ? tile_b : tile_a;
+      unsigned char* other = t & 1 ? tile_a : tile_b;
+      __syncthreads();
+      if (t < n_full) stage(other, t + 1);
+      else if (t == n_full) stage_last(other);
+      last_tile(std::true_type{}, tile, t);
     }
   }
-#undef LKV_MA_LOAD_TILE
-#undef LKV_MA_LOAD_ROW
-#undef LKV_MA_STORE_ROW
 
   // normalise and store: lane (r, c) holds O[query 4 r + e][channels 16 ct + c] and the (rounded) denominators of
   // those queries; the log-normaliser comes from the unrounded sum, held per query c
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb) {
+  for (int qb = 0; qb < kMaQB; ++qb) {
     float l = l_run[qb];
     l = sum_over_row_blocks(l);
     const int query = qw0 + 16 * qb + c;
-    if (r == 0 && query < T) lse[(size_t)hq * T + query] = l > 0.f ? m_run[qb] * kMaLn2 + __logf(l) : -INFINITY;
+    if (r == 0 && query < T) lse[(size_t)hq * T + query] = l > 0.f ? ref[qb] * kMaLn2 + __logf(l) : -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float lr = acc_l[qb][e];
@@ -278,19 +360,11 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   }
 }
 
-constexpr int kMaFwdSteps = 2;   // 64 keys per staged tile
-constexpr int kMaFwdLds = 2 * kMaFwdSteps * kMaTileLds;
-
-hipError_t masked_attn_prepare() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(masked_attn_fwd_kernel<2, kMaFwdSteps>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kMaFwdLds);
-}
-
 void launch_masked_attn_fwd(const void* q, const void* k, const void* v, const float* m, int n_q_heads, int n_kv_heads,
                             int T, float scale, float* o, float* lse, hipStream_t stream) {
   const int G = n_q_heads / n_kv_heads;
-  hipLaunchKernelGGL((masked_attn_fwd_kernel<2, kMaFwdSteps>), dim3((T + 127) / 128 * n_q_heads), dim3(kMaThreads),
-                     kMaFwdLds, stream, static_cast<const uint16_t*>(q), static_cast<const uint4*>(k),
+  hipLaunchKernelGGL(masked_attn_fwd_kernel, dim3((T + kMaBlockQ - 1) / kMaBlockQ * n_q_heads), dim3(kMaThreads),
+                     0, stream, static_cast<const uint16_t*>(q), static_cast<const uint4*>(k),
                      static_cast<const uint4*>(v), m, T, n_q_heads, G, scale, o, lse);
 }
 

@@ -63,6 +63,23 @@ def test_forward_mask_edge_cases(ctx):
     check_forward(ctx, 4, 2, 200, mask=lambda m: (m > 0.2).astype(np.float32))   # 0/1 mask, first key kept
 
 
+@pytest.mark.parametrize("T", [97, 128, 300, 641])
+@pytest.mark.parametrize("factor", [6.0, 12.0, 40.0])
+def test_forward_logits_that_run_away_from_the_first_keys(ctx, T, factor):
+    # The references of the exponentials are set by the first 32 keys.  Keys further on scaled up leave them behind: by
+    # some 30 binary orders (the block starts over with moving references), 60 and 200 (beyond what fp32 sums hold, and
+    # past the distance at which a moving reference is rebased).  One head also has its largest logits at keys of weight 0.
+    q, k, v, m, _ = W.draw_training_attention(4, 2, T, seed=5)
+    kf = O.bf16_bits_to_f64(k)
+    kf[:, 40:] *= factor
+    k = W.f32_to_bf16_bits(kf.astype(np.float32))
+    m[1, 3:20] = 0.0
+    o_gpu, lse_gpu = run_forward(ctx, q, k, v, m)
+    o_ref, lse_ref = MA.forward(*(O.bf16_bits_to_f64(x) for x in (q, k, v)), m, SCALE)
+    assert_decode_close(o_gpu.reshape(-1, 128), lse_gpu.reshape(-1), o_ref.reshape(-1, 128), lse_ref.reshape(-1),
+                        f"T{T} factor {factor}")
+
+
 def test_forward_rejects_bad_arguments(ctx):
     q, k, v, m, _ = W.draw_training_attention(4, 2, 64)
     tq, tk, tv = (bits_to_bf16_gpu(x) for x in (q, k, v))
@@ -237,6 +254,27 @@ def test_full_size_sampled(ctx, Hq, H, T):
         assert_rows_close(dk[h:h + 1, keys].cpu().numpy(), rk[:, keys], f"full size head {h} dK")
         assert_rows_close(dv[h:h + 1, keys].cpu().numpy(), rv[:, keys], f"full size head {h} dV")
         assert_rows_close(dm[h:h + 1, keys].cpu().numpy(), rm[:, keys], f"full size head {h} dm")
+
+
+@pytest.mark.parametrize("Hq,H,T", [(64, 64, 2049), (128, 64, 1030), (96, 32, 2050), (128, 32, 1024)])
+def test_backward_of_many_heads(ctx, Hq, H, T):
+    # grids large enough for the 256-key blocks of the dK / dV kernel: unsplit, ragged against the block, the 64-query
+    # items and the 32-query steps; split in two, three (every query head) and four.  First and last KV head whole.
+    G = Hq // H
+    q, k, v, m, d_o = W.draw_training_attention(Hq, H, T, seed=3)
+    m[H - 1, :300] = 0.0                                   # and a head whose first queries see no weight at all
+    dq, dk, dv, dm = run_backward(ctx, q, k, v, m, d_o)
+    for x in (dq, dk, dv, dm):
+        assert np.isfinite(x).all()
+    for h in (0, H - 1):
+        g = slice(h * G, (h + 1) * G)
+        rq, rk, rv, rm = MA.backward(*(O.bf16_bits_to_f64(x) for x in (q[g], k[h:h + 1], v[h:h + 1])), m[h:h + 1], SCALE,
+                                     O.bf16_bits_to_f64(d_o[g]))
+        tag = f"Hq{Hq} H{H} T{T} head {h}"
+        assert_rows_close(dq[g], rq, tag + " dQ")
+        assert_rows_close(dk[h:h + 1], rk, tag + " dK")
+        assert_rows_close(dv[h:h + 1], rv, tag + " dV")
+        assert_rows_close(dm[h:h + 1], rm, tag + " dm")
 
 
 def test_random_shapes(ctx):
