@@ -35,6 +35,7 @@
 
 #include "lkv_common.h"
 #include "lkv_kernels.h"
+#include "lkv_lds.h"
 
 namespace lkv {
 

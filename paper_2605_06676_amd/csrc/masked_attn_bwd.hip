@@ -32,6 +32,7 @@
 
 #include "lkv_common.h"
 #include "lkv_kernels.h"
+#include "lkv_lds.h"
 
 namespace lkv {
 
