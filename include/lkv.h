@@ -189,7 +189,7 @@ lkv_status lkv_select(lkv_ctx *ctx, const lkv_cache *cache, const float *const *
  * the way, counts those 11-bit digits per segment (inside the scoring kernel for the MLP scorers;
  * by one extra pass over the scores, 4 bytes per token, for the linear scorer).
  * lkv_select_counted then starts from the counts instead of from a pass over the scores: heads too
- * long for the top-k's on-chip key cache (more than 34304 tokens) are read twice instead of three
+ * long for the top-k to hold on chip (more than 34816 tokens) are read twice instead of three
  * times, shorter ones skip the counting.  Same result as lkv_select, bit for bit.
  * counts : DEVICE uint32 [n_seq * L * H, 2048], 16-byte aligned, lkv_counts_bytes(n_segments) bytes.
  *          Must be all zero when lkv_score_counted is called; lkv_select_counted reads every

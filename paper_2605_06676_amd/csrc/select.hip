@@ -2,39 +2,31 @@
 // paper, inference), with the budget b an input (LKV-H, Sec. 3.3).
 //
 // One workgroup of 1024 threads per segment (sequence, layer, head).
-//   1. Scores are mapped to order-preserving uint32 keys (NaN -> -inf first).
-//   2. The key of the b-th largest score is found by a radix descent over the
-//      key bits in three levels of 11, 11 and 10 bits: an LDS histogram of the
-//      keys that still match the prefix, then a block-wide scan from the top
-//      bin down.  This yields the threshold key `thr` and `need`, the number of
-//      tokens equal to `thr` that are kept.
-//   3. Emission in ascending token order: a token is kept if key > thr, or if
-//      key == thr and fewer than `need` tokens with that key precede it.  Each
-//      wave owns a contiguous range of tokens; per-wave counts are scanned once
-//      across the block, then every wave writes its range using prefix counts.
-//      The lower-index tie rule and the ascending output order both fall out of
-//      this ordered scan; no atomic decides a position, so the result is unique
-//      and reproducible bit for bit.
-// Where the keys live depends on the head length T:
-//   * T <= 34304: the keys are cached in LDS by one batched read of the scores (the first
-//     level's histogram is counted on the way in); the later passes and the classification
-//     read LDS, eight keys at a time.
-//   * longer heads do not fit.  The first level reads the scores from memory (they sit in L2 /
-//     the memory-side cache right after scoring).  A second read settles every token outside
-//     the one undecided bin and lists the tokens inside it (up to 16384 indices, in the LDS the
-//     emission stages through later); the last two levels and the final comparison touch the
-//     listed tokens only.  If more tokens than that share the bin, all three levels and the
+//   1. Scores are compared as order-preserving uint32 keys (NaN -> -inf first).
+//   2. A histogram over 2048 bins that do not decrease with the key, scanned from the top, gives the bin of the b-th
+//      largest key: linear bins over the bulk of the scores, or the first 11 bits of the keys when the scoring launch has
+//      counted those or the linear bins do not spread a sample of the scores (heavy tails, ties).  Tokens above the bin are kept, tokens below it are not, tokens inside it are listed.
+//   3. The listed tokens are narrowed by a radix descent over their keys (11 + 11 + 10 bits) until no more than 256 are
+//      left in question, and those are ranked against one another by (key, token): the lower-index tie rule.  Where more
+//      than that share one key (ties), the descent ends at that threshold key and the first `need` of its copies are kept.
+//   4. Emission in ascending token order from bitmaps of the kept tokens (1024 tokens per wave step): every lane expands
+//      its 16 bits into the wave's LDS staging buffer at the position given by a prefix count, then the wave copies
+//      the staged indices out with fully coalesced stores.  No atomic decides a position, so the result is unique and
+//      reproducible bit for bit.
+// Where the scores live depends on the head length T:
+//   * T <= 34816: in the registers of the workgroup (select_held_kernel), read once.
+//   * longer heads (select_kernel) read them from memory for the first histogram and once more to settle every token outside
+//     the undecided bin and to list those inside it (up to 16384 indices, in the LDS the emission stages through later); the rest
+//     happens on the listed tokens, in registers.  If more tokens than that share the bin, all three levels and the
 //     classification re-read the scores instead.
-//   In every case each token is classified against `thr` into two LDS bitmaps (greater / equal)
-//   and the ordered emission runs on the bitmaps, 1024 tokens per wave step: every lane expands
-//   its 16 bits into the wave's LDS staging buffer at the position given by a prefix count, then
-//   the wave copies the staged indices out with fully coalesced stores.
 //   * T <= 327680 is the limit for the bitmaps; longer heads re-read the scores in order during
 //     emission, 64 tokens a step.
-// All global reads are issued eight at a time per thread before any is used: the kernel is
+// All global reads are issued many at a time per thread before any is used: the kernels are
 // latency-bound, not bandwidth-bound, so what counts is how few dependent round trips each pass
 // makes.  A launch can also rank ragged pieces of one flat score array (the re-eviction of a
 // packed cache) instead of the heads of a [L, H, T] tensor.
+#include <type_traits>
+
 #include "lkv_common.h"
 
 namespace lkv {
@@ -42,13 +34,20 @@ namespace lkv {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelBins = 2048;
-constexpr int kSelRegionBytes = 144 * 1024;                 // LDS after the histogram: key cache and/or bitmaps
-constexpr int kSelMaxCachedKeys = 34304;                    // 134 KB of keys + 8.4 KB of bitmaps fit the region
+constexpr int kSelRegionBytes = 144 * 1024;                 // LDS after the histogram: bitmaps, then the staging buffer
+constexpr int kSelMaxHeld = 34;                             // scores per thread held in registers
+constexpr int kSelMaxHeldT = kSelMaxHeld * kSelThreads;     // 34816: longer heads re-read their scores
+constexpr int kSelRankMax = 256;                            // tokens left undecided from which ranking them one by one pays
+constexpr int kSelCopies = 8;                               // copies of a histogram while it is counted
+constexpr float kSelBinSpan = 5.f;                          // linear bins cover the mean of the scores +- this many deviations
 constexpr int kSelStageWords = 1024;                        // staged indices per wave and step (one per token of the step)
 constexpr int kSelStageBytes = kSelWaves * kSelStageWords * 4;   // 64 KB
 constexpr int kSelCandCap = kSelStageBytes / 4;             // candidate tokens of a long head (they overlay the staging buffer)
 constexpr int kSelMaxBitmapT = (kSelRegionBytes - kSelStageBytes) / 8 * 32;   // 327680 tokens: two bitmaps + staging
-static_assert(kSelMaxCachedKeys * 4 + 2 * ((kSelMaxCachedKeys + 31) / 32) * 4 <= kSelRegionBytes, "key cache + bitmaps");
+static_assert(kSelMaxHeld * kSelWaves <= kSelThreads, "one mask of a round per thread");
+static_assert(kSelBins * kSelCopies * 4 <= kSelStageBytes, "the copies lie where the emission stages later");
+static_assert(4 * kSelRankMax <= kSelThreads, "four threads rank a token");
+static_assert(2 * kSelRankMax <= kSelBins, "the tokens to rank are listed where the histogram was");
 constexpr int kSelBatch = 8;                                // loads in flight per thread
 constexpr int kSelInlineOffsets = 640;                      // offsets that fit the kernel arguments next to the launch table
 constexpr int kSelSplitMaxHeads = 64;                       // launches with at most this many (long) heads split each head's pass
@@ -60,32 +59,37 @@ struct InlineOffsets {
 };
 
 struct SelShared {
-  uint32_t hist[kSelBins];
+  alignas(16) uint32_t hist[kSelBins];
   uint32_t wave_tot[kSelWaves];
   uint32_t wave_gt[kSelWaves];
   uint32_t wave_eq[kSelWaves];
+  float stat[3][kSelWaves];
   uint32_t found_bin;
   uint32_t found_above;
   uint32_t found_count;
   uint32_t cand_count;
 };
 
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  return x;
+// Inclusive prefix sum over the 64 lanes of a wave: four shifts within the rows of 16 lanes, then the last lane of a row
+// joins the rows after it.  On the vector ALU; the same through the LDS crossbar waits for six round trips.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xf, true);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+  x = dpp_add<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8 (zeros move in)
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  x = dpp_add<0x118, 0xf>(x);
+  x = dpp_add<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
 }
 
+// The value of the last lane (a scalar).
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+
 // Sum of x over the 64 lanes of a wave, in every lane.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-  return x;
-}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) { return last_lane(wave_inclusive_scan(x)); }
 
 // Sum of the per-wave totals of the waves ahead of `wave`: one LDS read per lane and a wave
 // reduction instead of a chain of dependent reads.
@@ -93,11 +97,11 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t* totals, int wav
   return wave_sum(lane < wave ? totals[lane] : 0u);
 }
 
-// Calls f(key, token) for every token of the head, in no particular order, reading the fp32
+// Calls f(score, token) for every token of the head, in no particular order, reading the fp32
 // scores from global memory with kSelBatch loads in flight per thread (16-byte loads when the
 // head is 16-byte aligned and its length a multiple of four).
 template <typename F>
-__device__ __forceinline__ void for_each_global_key(const float* __restrict__ u, int T, F f) {
+__device__ __forceinline__ void for_each_global_score(const float* __restrict__ u, int T, F f) {
   const int tid = threadIdx.x;
   if ((T & 3) == 0 && (reinterpret_cast<uintptr_t>(u) & 15u) == 0) {
     const float4* u4 = reinterpret_cast<const float4*>(u);
@@ -113,10 +117,10 @@ __device__ __forceinline__ void for_each_global_key(const float* __restrict__ u,
       for (int k = 0; k < kSelBatch; ++k) {
         const int i = base + k * kSelThreads;
         if (i < n4) {
-          f(order_key(v[k].x), 4 * i);
-          f(order_key(v[k].y), 4 * i + 1);
-          f(order_key(v[k].z), 4 * i + 2);
-          f(order_key(v[k].w), 4 * i + 3);
+          f(v[k].x, 4 * i);
+          f(v[k].y, 4 * i + 1);
+          f(v[k].z, 4 * i + 2);
+          f(v[k].w, 4 * i + 3);
         }
       }
     }
@@ -131,40 +135,56 @@ __device__ __forceinline__ void for_each_global_key(const float* __restrict__ u,
 #pragma unroll
       for (int k = 0; k < kSelBatch; ++k) {
         const int i = base + k * kSelThreads;
-        if (i < T) f(order_key(v[k]), i);
+        if (i < T) f(v[k], i);
       }
     }
   }
 }
 
-// One level of the radix descent.  `count(fn)` must call fn(key) for every key of the head.
-// On return prefix / prefix_mask / need are advanced by this level's digit.  Returns the number of
-// keys in the bin the descent entered (the same value in every thread: it is published by the one
-// thread that found the bin and read between two block barriers, so a branch on it is uniform).
-// `counted`: the histogram of this level has already been filled (and a barrier passed).
-template <typename Count>
-__device__ __forceinline__ uint32_t descend_level(SelShared& sh, int level, uint32_t& prefix, uint32_t& prefix_mask,
-                                              uint32_t& need, Count count, bool counted = false) {
+template <typename F>
+__device__ __forceinline__ void for_each_global_key(const float* __restrict__ u, int T, F f) {
+  for_each_global_score(u, T, [&](float s, int i) { f(order_key(s), i); });
+}
+
+// Digits of the keys are counted in kSelCopies copies of a histogram, side by side, lane l in copy l mod kSelCopies:
+// atomics on one address run one after the other (about two cycles a lane), and ties or the leading digits of scores
+// of one magnitude put most of a wave into one bin.  (8 heads of 32768 equal scores: 124 us with one copy, 29 us with
+// eight.  Linear bins that spread the scores need one: clearing and adding up the copies costs 1 us.)
+__device__ __forceinline__ void count_bin(uint32_t* copies, uint32_t bin) {
+  atomicAdd(&copies[bin * kSelCopies + (threadIdx.x & (kSelCopies - 1))], 1u);
+}
+__device__ __forceinline__ void clear_copies(uint32_t* copies) {
+  for (int i = threadIdx.x; i < kSelBins * kSelCopies / 4; i += kSelThreads)
+    reinterpret_cast<uint4*>(copies)[i] = make_uint4(0, 0, 0, 0);
+}
+__device__ __forceinline__ uint32_t sum_copies(const uint32_t* copies, int bin) {
+  const uint4* c = reinterpret_cast<const uint4*>(copies + (size_t)bin * kSelCopies);
+  uint32_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < kSelCopies / 4; ++j) sum += c[j].x + c[j].y + c[j].z + c[j].w;
+  return sum;
+}
+
+// Whether a wave's lanes crowd into few bins: 8 of them share one (the same answer in every lane).
+__device__ __forceinline__ bool lanes_crowd(int bin) {
+  return __popcll(__ballot(bin == __builtin_amdgcn_readfirstlane(bin))) >= 8 ||
+         __popcll(__ballot(bin == __builtin_amdgcn_readlane(bin, 37))) >= 8;
+}
+
+// The bin that holds the key of rank `need` from the top: sh.found_bin, found_above (keys in higher bins) and
+// found_count, to be read before the next barrier.  count_of(bin) reads the histogram, which must be complete (a barrier
+// passed).
+template <typename CountOf>
+__device__ __forceinline__ void find_bin(SelShared& sh, int nbins, uint32_t need, CountOf count_of) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int shift = level == 0 ? 21 : (level == 1 ? 10 : 0);
-  const int nbins = level == 2 ? 1024 : 2048;
-  if (!counted) {
-    for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = 0;
-    __syncthreads();   // also orders an LDS key cache fill before its first use
-    const uint32_t pfx = prefix, msk = prefix_mask;
-    count([&](uint32_t key) {
-      if ((key & msk) == pfx) atomicAdd(&sh.hist[(key >> shift) & (nbins - 1)], 1u);
-    });
-    __syncthreads();
-  }
   // scan the bins from the top: thread t owns bins nbins-1-2t and nbins-2-2t
   uint32_t c0 = 0, c1 = 0;
   const int top = nbins - 1 - 2 * tid;
-  if (top >= 0) c0 = sh.hist[top];
-  if (top - 1 >= 0) c1 = sh.hist[top - 1];
-  const uint32_t incl = wave_inclusive_scan(c0 + c1, lane);
+  if (top >= 0) c0 = count_of(top);
+  if (top - 1 >= 0) c1 = count_of(top - 1);
+  const uint32_t incl = wave_inclusive_scan(c0 + c1);
   if (lane == 63) sh.wave_tot[wave] = incl;
   __syncthreads();
   const uint32_t before = waves_before(sh.wave_tot, wave, lane);
@@ -177,12 +197,41 @@ __device__ __forceinline__ uint32_t descend_level(SelShared& sh, int level, uint
     sh.found_count = c1;
   }
   __syncthreads();
+}
+
+// One level of the radix descent.  `count(fn)` must call fn(key) for every key of the head.
+// On return prefix / prefix_mask / need are advanced by this level's digit.  Returns the number of
+// keys in the bin the descent entered (the same value in every thread: it is published by the one
+// thread that found the bin and read between two block barriers, so a branch on it is uniform).
+__device__ __forceinline__ uint32_t enter_found_bin(SelShared& sh, int level, uint32_t& prefix, uint32_t& prefix_mask,
+                                                    uint32_t& need) {
+  const int shift = level == 0 ? 21 : (level == 1 ? 10 : 0);
   prefix |= sh.found_bin << shift;
-  prefix_mask |= (uint32_t)(nbins - 1) << shift;
+  prefix_mask |= (uint32_t)((level == 2 ? 1024 : 2048) - 1) << shift;
   need -= sh.found_above;
   const uint32_t in_bin = sh.found_count;
-  __syncthreads();   // found_* and hist are rewritten at the next level
+  __syncthreads();   // found_* and the histogram are rewritten at the next level
   return in_bin;
+}
+template <typename Count>
+__device__ __forceinline__ uint32_t descend_level(SelShared& sh, uint32_t* copies, int level, uint32_t& prefix,
+                                                  uint32_t& prefix_mask, uint32_t& need, Count count) {
+  const int shift = level == 0 ? 21 : (level == 1 ? 10 : 0);
+  const int nbins = level == 2 ? 1024 : 2048;
+  clear_copies(copies);
+  __syncthreads();
+  const uint32_t pfx = prefix, msk = prefix_mask;
+  count([&](uint32_t key) {
+    if ((key & msk) == pfx) count_bin(copies, (key >> shift) & (uint32_t)(nbins - 1));
+  });
+  __syncthreads();
+  find_bin(sh, nbins, need, [&](int bin) { return sum_copies(copies, bin); });
+  return enter_found_bin(sh, level, prefix, prefix_mask, need);
+}
+// The first level when sh.hist already holds its counts (and a barrier has passed).
+__device__ __forceinline__ uint32_t descend_counted_level(SelShared& sh, uint32_t& prefix, uint32_t& prefix_mask, uint32_t& need) {
+  find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist[bin]; });
+  return enter_found_bin(sh, 0, prefix, prefix_mask, need);
 }
 
 // Ordered emission from a per-token key source `key_of(i)` (LDS key cache, or global scores).
@@ -250,6 +299,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // one 16-bit half word per lane.  Loops whose trip count could differ between lanes are avoided
 // (the expansion loop runs a fixed 16 times), and every cross-lane exchange of a step comes
 // before the staging traffic.
+// kEq = false: there is no map of equal keys, every kept token is in gt_map.
+template <bool kEq>
 __device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t need, int32_t* __restrict__ out,
                                                   const uint32_t* gt_map, const uint32_t* eq_map, uint32_t* stage_all) {
   const int lane = threadIdx.x & 63;
@@ -260,13 +311,13 @@ __device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t
   const int lo = wave * per;
   const int hi = min(n_words, lo + per);
   uint32_t n_gt = 0, n_eq = 0;
-  for (int w = lo + lane; w < hi; w += 64) { n_gt += __popc(gt_map[w]); n_eq += __popc(eq_map[w]); }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) { n_gt += __shfl_xor(n_gt, d, 64); n_eq += __shfl_xor(n_eq, d, 64); }
+  for (int w = lo + lane; w < hi; w += 64) { n_gt += __popc(gt_map[w]); if (kEq) n_eq += __popc(eq_map[w]); }
+  n_gt = wave_sum(n_gt);
+  if (kEq) n_eq = wave_sum(n_eq);
   if (lane == 0) { sh.wave_gt[wave] = n_gt; sh.wave_eq[wave] = n_eq; }
   __syncthreads();
   const uint32_t gt_before = waves_before(sh.wave_gt, wave, lane);
-  const uint32_t eq_before = waves_before(sh.wave_eq, wave, lane);
+  const uint32_t eq_before = kEq ? waves_before(sh.wave_eq, wave, lane) : 0u;
   uint32_t eq_seen = eq_before;
   uint32_t pos = gt_before + min(eq_before, need);
   const int half = lane & 1;
@@ -274,17 +325,20 @@ __device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t
     const int w = base + (lane >> 1);
     const bool in = w < hi;
     const uint32_t gth = in ? (gt_map[w] >> (16 * half)) & 0xffffu : 0u;
-    const uint32_t eqh = in ? (eq_map[w] >> (16 * half)) & 0xffffu : 0u;
-    // copies of thr before this lane's half word, and how many of its own copies are still kept
-    const uint32_t eq_cnt = __popc(eqh);
-    const uint32_t eq_incl = wave_inclusive_scan(eq_cnt, lane);
-    const uint32_t eq_rank = eq_seen + eq_incl - eq_cnt;
-    const uint32_t take = eq_rank < need ? min(eq_cnt, need - eq_rank) : 0u;
-    uint32_t bits = gth | lowest_set_bits(eqh, take);
+    uint32_t bits = gth;
+    if (kEq) {
+      const uint32_t eqh = in ? (eq_map[w] >> (16 * half)) & 0xffffu : 0u;
+      // copies of thr before this lane's half word, and how many of its own copies are still kept
+      const uint32_t eq_cnt = __popc(eqh);
+      const uint32_t eq_incl = wave_inclusive_scan(eq_cnt);
+      const uint32_t eq_rank = eq_seen + eq_incl - eq_cnt;
+      const uint32_t take = eq_rank < need ? min(eq_cnt, need - eq_rank) : 0u;
+      bits |= lowest_set_bits(eqh, take);
+      eq_seen += last_lane(eq_incl);
+    }
     const uint32_t cnt = __popc(bits);
-    const uint32_t incl = wave_inclusive_scan(cnt, lane);
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)__shfl(incl, 63, 64));
-    eq_seen += __shfl(eq_incl, 63, 64);
+    const uint32_t incl = wave_inclusive_scan(cnt);
+    const uint32_t total = last_lane(incl);
     uint32_t p = incl - cnt;
     const uint32_t tok0 = ((uint32_t)w << 5) + 16u * half;
 #pragma unroll
@@ -315,6 +369,215 @@ struct SelRagged {
   const int32_t* len;
 };
 
+// Bins that spread the scores of a head evenly: equal steps over mean +- kSelBinSpan deviations, the rest in the end
+// bins.  The radix digits of the scores do not: one head's lie within a few powers of two, so most of its tokens
+// count into a few dozen of the 2048 digits, and atomics on one address run one after the other.  bin() does
+// not decrease with the score (nor with its key; NaN and -inf are in bin 0), which is all that the selection asks of it.
+struct LinearBins {
+  float lo, scale;
+  __device__ __forceinline__ int bin(float u) const {
+    return (int)fminf(fmaxf((u - lo) * scale, 0.f), (float)(kSelBins - 1));   // a NaN product goes to 0
+  }
+};
+
+// From every thread's sums over finite values (count, sum, sum of squares of value - shift); also clears the histogram.
+__device__ __forceinline__ LinearBins linear_bins(SelShared& sh, float shift, float n, float sum, float sq) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  n = sum_over_row_blocks(row16_allreduce_sum(n));
+  sum = sum_over_row_blocks(row16_allreduce_sum(sum));
+  sq = sum_over_row_blocks(row16_allreduce_sum(sq));
+  if (lane == 0) { sh.stat[0][wave] = n; sh.stat[1][wave] = sum; sh.stat[2][wave] = sq; }
+  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = 0;
+  __syncthreads();
+  n = fmaxf(row16_allreduce_sum(sh.stat[0][lane & 15]), 1.f);
+  const float mean = row16_allreduce_sum(sh.stat[1][lane & 15]) / n;
+  const float dev = sqrtf(fmaxf(row16_allreduce_sum(sh.stat[2][lane & 15]) / n - mean * mean, 0.f));
+  return {shift + mean - kSelBinSpan * dev, (float)kSelBins / (2.f * kSelBinSpan * dev)};
+}
+
+__device__ __forceinline__ bool is_finite_score(float u) { return (__float_as_uint(u) & 0x7f800000u) != 0x7f800000u; }
+
+// A listed token as one number, larger for what is kept first: the key, then the lower index.
+__device__ __forceinline__ uint64_t* ranking_list(SelShared& sh) { return reinterpret_cast<uint64_t*>(sh.hist); }
+__device__ __forceinline__ void list_for_ranking(SelShared& sh, uint32_t key, uint32_t token) {
+  const uint32_t slot = atomicAdd(&sh.cand_count, 1u);
+  if (slot < (uint32_t)kSelRankMax) ranking_list(sh)[slot] = ((uint64_t)key << 32) | (uint32_t)~token;
+}
+
+// The `need` best of the n <= kSelRankMax listed tokens join gt_map: those with fewer than `need` listed before them.
+__device__ __forceinline__ void keep_best_listed(SelShared& sh, uint32_t n, uint32_t need, uint32_t* gt_map) {
+  const uint64_t* list = ranking_list(sh);
+  const uint32_t j = threadIdx.x >> 2, part = threadIdx.x & 3;   // a quad per token, a quarter of the list per thread
+  if (j < n) {
+    const uint64_t mine = list[j];
+    uint32_t rank = 0;
+#pragma unroll 4
+    for (uint32_t i = part; i < n; i += 4) rank += list[i] > mine ? 1u : 0u;
+    rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0xb1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
+    rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0x4e, 0xf, 0xf, true);   // quad_perm [2, 3, 0, 1]
+    const uint32_t token = ~(uint32_t)mine;
+    if (part == 0 && rank < need) atomicOr(&gt_map[token >> 5], 1u << (token & 31));
+  }
+}
+
+// Heads of at most kE * 1024 tokens: every thread holds kE scores in registers and nothing is read twice.  What bounds
+// it is a chain of short steps in one workgroup per head (load, histogram, scan, classification, emission), so the
+// steps are few: a histogram over linear bins, the tokens above the bin of the threshold kept, the few dozen inside it
+// ranked one by one.  Where a sample says that linear bins would not spread the scores (8 of a wave's 64 in one bin) or
+// more than kSelRankMax tokens share the bin, the radix descent over the held keys narrows them instead.  8 heads of
+// 32768 normal scores: 16.5 us, 256 heads 20 us, 8 heads of 4000: 7 us; of exp(3 x): 20 us; all equal: 29 us.  (With the
+// keys cached in LDS, three radix levels over them and prefix sums through the LDS crossbar: 24, 30, 11, 24 and 99 us.)
+// Emitting a run of 64 tokens at a time from a prefix count over runs instead of from the masks: 1.5 us more.
+template <bool kInline, int kE>
+__global__ void __launch_bounds__(kSelThreads)
+select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __restrict__ offsets, int32_t* __restrict__ idx,
+                   uint32_t* __restrict__ counts, int seg_base, int seg_stride, int map_words /* of the launch's longest head */) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  SelShared& sh = *reinterpret_cast<SelShared*>(smem);
+  uint32_t* gt_map = reinterpret_cast<uint32_t*>(smem + sizeof(SelShared));
+  uint32_t* eq_map = gt_map + map_words;
+  uint32_t* stage = eq_map + map_words;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int local_seg = blockIdx.x;
+  const int seq = seq_of_unit(tab, local_seg);
+  const int lh = local_seg - tab.first[seq];
+  const int seg = seg_base + seq * seg_stride + lh;
+  // a ragged segment can be no longer than the launch table says (registers and LDS are sized by it)
+  const int T = ragged.flat != nullptr ? min(ragged.len[seg], tab.T[seq]) : tab.T[seq];
+  if (tab.T[seq] > kE * kSelThreads) return;   // left to select_kernel
+  const float* u = ragged.flat != nullptr ? ragged.flat + ragged.start[seg] : tab.scores[seq] + (size_t)lh * (size_t)T;
+  const int off = kInline ? inl.v[seg] : offsets[seg];
+  const int budget = (kInline ? inl.v[seg + 1] : offsets[seg + 1]) - off;
+  if (kInline && tid == 0) {
+    offsets[seg] = off;
+    if (local_seg == (int)gridDim.x - 1) offsets[seg + 1] = off + budget;   // the total, by the launch's last block
+  }
+  int32_t* out = idx + off;
+  if (counts != nullptr)   // not needed here, but left zero for the next scoring launch
+    for (int i = tid; i < kLevel0Bins; i += kSelThreads) counts[(size_t)seg * kLevel0Bins + i] = 0;
+  if (budget <= 0 || budget >= T) {   // nothing or everything is kept
+    if (budget > 0)
+      for (int i = tid; i < T; i += kSelThreads) out[i] = i;
+    return;
+  }
+
+  // round k, token k * 1024 + tid: a wave's 64 tokens of a round are two words of the bitmaps
+  float v[kE];
+#pragma unroll
+  for (int k = 0; k < kE; ++k) v[k] = u[min(k * kSelThreads + tid, T - 1)];
+  const int rounds = (T + kSelThreads - 1) / kSelThreads;
+  auto for_each = [&](auto f) {
+#pragma unroll
+    for (int k = 0; k < kE; ++k)
+      if (k * kSelThreads + tid < T) f(v[k], k * kSelThreads + tid);
+  };
+  if (tid == 0) sh.cand_count = 0;
+  uint32_t need = (uint32_t)budget;   // rank of the threshold among the keys not yet decided (1-based)
+  uint32_t prefix = 0, prefix_mask = 0;
+  auto count = [&](auto fn) { for_each([&](float x, int) { fn(order_key(x)); }); };
+  int at_bin[kE];
+  // the bins come from some rounds' scores: any bins give the same selection, these a short list
+  constexpr int kSampleStep = kE < 16 ? 1 : 4;
+  const float first = u[0];
+  const float shift = is_finite_score(first) ? first : 0.f;
+  float n = 0.f, sum = 0.f, sq = 0.f;
+#pragma unroll
+  for (int k = 0; k < kE; k += kSampleStep) {
+    const bool fin = k * kSelThreads + tid < T && is_finite_score(v[k]);
+    const float d = fin ? v[k] - shift : 0.f;
+    n += fin ? 1.f : 0.f;
+    sum += d;
+    sq = fmaf(d, d, sq);
+  }
+  const LinearBins bins = linear_bins(sh, shift, n, sum, sq);
+  bool crowded = false;
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    at_bin[k] = bins.bin(v[k]);
+    if (k % 8 == 0 && (k == 0 || (k + 1) * kSelThreads <= T)) crowded |= lanes_crowd(at_bin[k]);
+  }
+  uint32_t n_left = kSelRankMax + 1;
+  int bin = 0;
+  if (!__syncthreads_or(crowded && wave * 64 + 64 <= T)) {
+#pragma unroll
+    for (int k = 0; k < kE; ++k)
+      if (k * kSelThreads + tid < T) atomicAdd(&sh.hist[at_bin[k]], 1u);
+    __syncthreads();
+    find_bin(sh, kSelBins, need, [&](int b) { return sh.hist[b]; });
+    n_left = sh.found_count;
+    bin = (int)sh.found_bin;
+    if (n_left <= (uint32_t)kSelRankMax) need -= sh.found_above;
+    __syncthreads();   // the histogram and found_* are rewritten
+  }
+  if (n_left > (uint32_t)kSelRankMax) {
+#pragma unroll 1
+    for (int level = 0; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
+      n_left = descend_level(sh, stage, level, prefix, prefix_mask, need, count);
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      const uint32_t decided = order_key(v[k]) & prefix_mask;
+      at_bin[k] = decided > prefix ? 2 : decided == prefix ? 1 : 0;
+    }
+    bin = 1;
+  }
+  if (n_left <= (uint32_t)kSelRankMax) {
+    // tokens above the undecided bin to the bitmap, those inside it to the list
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      if (k < rounds) {   // uniform
+        const int i = k * kSelThreads + tid;
+        const bool above = i < T && at_bin[k] > bin;
+        const bool inside = i < T && at_bin[k] == bin;
+        const unsigned long long m = __ballot(above);
+        if (lane == 0) reinterpret_cast<unsigned long long*>(gt_map)[k * kSelWaves + wave] = m;
+        if (inside) list_for_ranking(sh, order_key(v[k]), (uint32_t)i);
+      }
+    }
+    __syncthreads();
+    keep_best_listed(sh, n_left, need, gt_map);
+    __syncthreads();
+    // kept tokens ahead of every wave and round, then every round's tokens straight to their places
+    const unsigned long long* masks = reinterpret_cast<const unsigned long long*>(gt_map);
+    const int n_masks = rounds * kSelWaves;   // at most 544: one per thread
+    const uint32_t cnt = tid < n_masks ? (uint32_t)__popcll(masks[tid]) : 0u;
+    const uint32_t incl = wave_inclusive_scan(cnt);
+    if (lane == 63) sh.wave_tot[wave] = incl;
+    __syncthreads();
+    const uint32_t before_wave = waves_before(sh.wave_tot, wave, lane);   // by all lanes
+    if (tid < n_masks) eq_map[tid] = before_wave + incl - cnt;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      if (k < rounds) {
+        const unsigned long long m = masks[k * kSelWaves + wave];
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if ((m >> lane) & 1ull) out[eq_map[k * kSelWaves + wave] + before] = k * kSelThreads + tid;
+      }
+    }
+    return;
+  }
+  // more than kSelRankMax copies of the threshold key
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    if (k < rounds) {   // uniform
+      const bool in = k * kSelThreads + tid < T;
+      const unsigned long long m_gt = __ballot(in && at_bin[k] > bin);
+      const unsigned long long m_eq = __ballot(in && at_bin[k] == bin);
+      if (lane == 0) {
+        reinterpret_cast<unsigned long long*>(gt_map)[k * kSelWaves + wave] = m_gt;
+        reinterpret_cast<unsigned long long*>(eq_map)[k * kSelWaves + wave] = m_eq;
+      }
+    }
+  }
+  __syncthreads();
+  emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, stage);
+}
+
 // kCounted: the first-level digits of every segment's scores have already been counted by the scoring launch
 // (`counts`: uint32 [segments][kLevel0Bins]); the block takes its histogram from there instead of from a pass over
 // the scores, and leaves the counters zero for the next scoring launch.
@@ -325,9 +588,9 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
               const uint32_t* __restrict__ pre_maps /* per segment [2][pre_words]: written by select_classify_kernel, or null */,
               int pre_words,
               int seg_base, int seg_stride /* global segment = seg_base + sequence * seg_stride + head */,
-              int cached_limit /* heads of at most this many tokens use the LDS key cache */,
-              int bitmap_limit /* longer heads up to this many tokens use the LDS bitmaps */,
-              int cached_stage_off, int bitmap_stage_off /* word offsets of the staging buffer in the region */) {
+              int held_limit /* heads of at most this many tokens are left to select_held_kernel */,
+              int bitmap_limit /* heads of up to this many tokens use the LDS bitmaps */,
+              int bitmap_stage_off /* word offset of the staging buffer in the region */) {
   extern __shared__ __align__(16) unsigned char smem[];
   SelShared& sh = *reinterpret_cast<SelShared*>(smem);
   uint32_t* region = reinterpret_cast<uint32_t*>(smem + sizeof(SelShared));
@@ -339,6 +602,7 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
   const int seg = seg_base + seq * seg_stride + lh;
   // a ragged segment can be no longer than the launch table says (the LDS region is sized by it)
   const int T = ragged.flat != nullptr ? min(ragged.len[seg], tab.T[seq]) : tab.T[seq];
+  if (tab.T[seq] <= held_limit) return;
   const float* u = ragged.flat != nullptr ? ragged.flat + ragged.start[seg] : tab.scores[seq] + (size_t)lh * (size_t)T;
   const int off = kInline ? inl.v[seg] : offsets[seg];
   const int budget = (kInline ? inl.v[seg + 1] : offsets[seg + 1]) - off;
@@ -363,88 +627,55 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
     __syncthreads();
   }
 
+  uint32_t* copies = region + bitmap_stage_off;   // of a histogram; then the listed tokens, then the staging buffer
   uint32_t prefix = 0;        // bits of the threshold key decided so far
   uint32_t prefix_mask = 0;   // which bits those are
   uint32_t need = (uint32_t)budget;   // rank of the threshold among keys that match the prefix (1-based)
 
-  if (T <= cached_limit) {
-    uint32_t* keys = region;
-    const int n_words = (T + 31) >> 5;
-    uint32_t* gt_map = region + cached_limit;   // after the key cache of the launch's longest cached head
-    uint32_t* eq_map = gt_map + n_words;
-    // the first level's histogram is counted while the keys pass through registers on their way to LDS
-    // (unless the scoring launch has counted it already)
-    if (kCounted) {
-      for_each_global_key(u, T, [&](uint32_t key, int i) { keys[i] = key; });
-    } else {
-      for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = 0;
-      __syncthreads();
-      for_each_global_key(u, T, [&](uint32_t key, int i) {
-        keys[i] = key;
-        atomicAdd(&sh.hist[key >> 21], 1u);
-      });
-    }
-    __syncthreads();
-    // later levels read the cached keys eight at a time so that the LDS latency is paid once per batch
-    auto count = [&](auto fn) {
-      for (int base = tid; base < T; base += kSelThreads * kSelBatch) {
-        uint32_t kb[kSelBatch];
-#pragma unroll
-        for (int k = 0; k < kSelBatch; ++k) {
-          const int i = base + k * kSelThreads;
-          kb[k] = keys[i < T ? i : base];
-        }
-#pragma unroll
-        for (int k = 0; k < kSelBatch; ++k)
-          if (base + k * kSelThreads < T) fn(kb[k]);
-      }
-    };
-    descend_level(sh, 0, prefix, prefix_mask, need, count, true);
-#pragma unroll 1
-    for (int level = 1; level < 3; ++level) descend_level(sh, level, prefix, prefix_mask, need, count);
-    const uint32_t thr = prefix;
-    // classification: a wave covers 64 consecutive tokens, so a ballot is two finished bitmap
-    // words.  The words of 32 rounds are collected in registers (lane 2k + j keeps half j of round
-    // k) and written with one LDS store per lane and map.
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    constexpr int kClsBatch = 4;
-    for (int chunk0 = 0; chunk0 < T; chunk0 += 32 * kSelThreads) {   // one pass for every length the cache holds up to 32768
-      uint32_t my_gt = 0, my_eq = 0;
-      const int rounds = min(32, (T - chunk0 + kSelThreads - 1) / kSelThreads);   // short heads need fewer
-#pragma unroll 1
-      for (int kk = 0; kk < rounds; kk += kClsBatch) {
-        uint32_t kb[kClsBatch];
-#pragma unroll
-        for (int k = 0; k < kClsBatch; ++k) {
-          const int i = chunk0 + (kk + k) * kSelThreads + wave * 64 + lane;
-          kb[k] = i < T ? keys[i] : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kClsBatch; ++k) {
-          const int i = chunk0 + (kk + k) * kSelThreads + wave * 64 + lane;
-          const unsigned long long m_gt = __ballot(i < T && kb[k] > thr);
-          const unsigned long long m_eq = __ballot(i < T && kb[k] == thr);
-          const int slot = 2 * (kk + k);
-          if (lane == slot) { my_gt = (uint32_t)m_gt; my_eq = (uint32_t)m_eq; }
-          if (lane == slot + 1) { my_gt = (uint32_t)(m_gt >> 32); my_eq = (uint32_t)(m_eq >> 32); }
-        }
-      }
-      const int w = ((chunk0 + (lane >> 1) * kSelThreads + wave * 64) >> 5) + (lane & 1);
-      if (w < n_words) { gt_map[w] = my_gt; eq_map[w] = my_eq; }
-    }
-    __syncthreads();
-    emit_from_bitmaps(sh, T, need, out, gt_map, eq_map, region + cached_stage_off);   // the key cache is dead by now
-    return;
-  }
-
   auto count = [&](auto fn) { for_each_global_key(u, T, [&](uint32_t key, int) { fn(key); }); };
-  const uint32_t n_cand = descend_level(sh, 0, prefix, prefix_mask, need, count, kCounted);   // keys left in the undecided bin
-  // Heads too long for the key cache: the first level leaves one bin of 2048 undecided.  When its
-  // keys are few enough to list (their token indices, in the space the emission stages through
-  // later), one more pass over the scores settles everything above that bin and collects the
-  // list; the remaining two levels and the final comparison then touch the listed tokens only.
-  const uint32_t bin0 = prefix >> 21;
+  // The first level leaves one bin undecided: of the radix digits when the scoring launch has counted them, else of
+  // linear bins over what four runs of 1024 scores say about the distribution.  When the tokens of that bin are few
+  // enough to list (their indices, in the space the emission stages through later), one more pass over the scores settles
+  // everything above the bin and collects the list; the rest touches the listed tokens only, their scores in registers.
+  uint32_t n_cand;
+  LinearBins bins = {0.f, 0.f};
+  bool keyed = kCounted;
+  uint32_t bin0;
+  if (!kCounted) {
+    const float first = u[0];
+    const float shift = is_finite_score(first) ? first : 0.f;
+    float x[4], n = 0.f, sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = u[(int)(((int64_t)T * k) >> 2) + min(tid, max((T >> 2) - 1, 0))];   // a ragged segment may be short
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool fin = is_finite_score(x[k]);
+      const float d = fin ? x[k] - shift : 0.f;
+      n += fin ? 1.f : 0.f;
+      sum += d;
+      sq = fmaf(d, d, sq);
+    }
+    bins = linear_bins(sh, shift, n, sum, sq);
+    bool crowded = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) crowded |= lanes_crowd(bins.bin(x[k]));
+    keyed = __syncthreads_or(crowded && (tid | 63) < (T >> 2));
+  }
+  if (kCounted) {
+    n_cand = descend_counted_level(sh, prefix, prefix_mask, need);
+    bin0 = prefix >> 21;
+  } else if (keyed) {
+    n_cand = descend_level(sh, copies, 0, prefix, prefix_mask, need, count);
+    bin0 = prefix >> 21;
+  } else {
+    for_each_global_score(u, T, [&](float s, int) { atomicAdd(&sh.hist[bins.bin(s)], 1u); });
+    __syncthreads();
+    find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist[bin]; });
+    n_cand = sh.found_count;
+    bin0 = sh.found_bin;
+    if (n_cand <= (uint32_t)kSelCandCap && T <= bitmap_limit) need -= sh.found_above;
+    __syncthreads();   // found_* and the histogram are rewritten below
+  }
   if (T <= bitmap_limit && n_cand <= (uint32_t)kSelCandCap) {
     const int n_words = (T + 31) >> 5;
     uint32_t* gt_map = region;
@@ -455,27 +686,33 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       // (above the undecided bin / inside it) and list the tokens inside
       const uint32_t* pre_gt = pre_maps + (size_t)seg * 2 * pre_words;
       const uint32_t* pre_in = pre_gt + pre_words;
-      for (int i = tid; i < n_words; i += kSelThreads) { gt_map[i] = pre_gt[i]; eq_map[i] = 0; }
+      for (int i = tid; i < n_words; i += kSelThreads) gt_map[i] = pre_gt[i];
       if (tid == 0) sh.cand_count = 0;
       __syncthreads();
-      for (int w0 = 0; w0 < n_words; w0 += kSelThreads) {   // uniform trip counts, here and in the inner loop
+      for (int w0 = 0; w0 < n_words; w0 += kSelThreads) {   // uniform trip counts
         const int w = w0 + tid;
         uint32_t bits = w < n_words ? pre_in[w] : 0u;
+        // one place in the list per wave and round, shared out by a prefix count
+        const uint32_t n_bits = __popc(bits);
+        const uint32_t incl = wave_inclusive_scan(n_bits);
+        uint32_t base = 0;
+        if ((tid & 63) == 63) base = atomicAdd(&sh.cand_count, incl);
+        uint32_t slot = __shfl(base, 63, 64) + incl - n_bits;
         while (__ballot(bits != 0u) != 0ull) {
           if (bits) {
-            const uint32_t slot = atomicAdd(&sh.cand_count, 1u);
             if (slot < (uint32_t)kSelCandCap) cand[slot] = ((uint32_t)w << 5) + (uint32_t)__builtin_ctz(bits);
+            ++slot;
             bits &= bits - 1;
           }
         }
       }
       __syncthreads();
     } else {
-      for (int i = tid; i < 2 * n_words; i += kSelThreads) region[i] = 0;
+      for (int i = tid; i < n_words; i += kSelThreads) gt_map[i] = 0;
       if (tid == 0) sh.cand_count = 0;
       __syncthreads();
-      for_each_global_key(u, T, [&](uint32_t key, int i) {
-        const uint32_t top = key >> 21;
+      for_each_global_score(u, T, [&](float s, int i) {
+        const uint32_t top = keyed ? order_key(s) >> 21 : (uint32_t)bins.bin(s);
         if (top > bin0) {
           atomicOr(&gt_map[i >> 5], 1u << (i & 31));
         } else if (top == bin0) {
@@ -486,24 +723,50 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       });
       __syncthreads();
     }
-    auto count_listed = [&](auto fn) {
-      for (uint32_t j = tid; j < n_cand; j += kSelThreads) fn(order_key(u[cand[j]]));
+    // the listed tokens and their keys, in registers: one round of gathers, all in flight
+    constexpr int kHeldCand = kSelCandCap / kSelThreads;
+    uint32_t token[kHeldCand], key[kHeldCand];
+#pragma unroll
+    for (int k = 0; k < kHeldCand; ++k)
+      token[k] = min(cand[min((uint32_t)(k * kSelThreads + tid), max(n_cand, 1u) - 1)], (uint32_t)T - 1);   // in range whatever the counts said
+#pragma unroll
+    for (int k = 0; k < kHeldCand; ++k) key[k] = order_key(u[token[k]]);
+    auto for_each_listed = [&](auto fn) {
+#pragma unroll
+      for (int k = 0; k < kHeldCand; ++k)
+        if ((uint32_t)(k * kSelThreads + tid) < n_cand) fn(key[k], token[k]);
     };
+    if (tid == 0) sh.cand_count = 0;
+    __syncthreads();   // the list is dead: its space becomes the staging buffer; the list for the ranking starts empty
+    uint32_t n_left = n_cand;
 #pragma unroll 1
-    for (int level = 1; level < 3; ++level) descend_level(sh, level, prefix, prefix_mask, need, count_listed);
-    const uint32_t thr_listed = prefix;
-    for (uint32_t j = tid; j < n_cand; j += kSelThreads) {
-      const uint32_t i = cand[j];
-      const uint32_t key = order_key(u[i]);
-      if (key > thr_listed) atomicOr(&gt_map[i >> 5], 1u << (i & 31));
-      else if (key == thr_listed) atomicOr(&eq_map[i >> 5], 1u << (i & 31));
+    for (int level = keyed ? 1 : 0; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
+      n_left = descend_level(sh, copies, level, prefix, prefix_mask, need, [&](auto fn) { for_each_listed([&](uint32_t k, uint32_t) { fn(k); }); });
+    if (n_left <= (uint32_t)kSelRankMax) {
+      for_each_listed([&](uint32_t k, uint32_t t) {
+        const uint32_t decided = k & prefix_mask;
+        if (decided > prefix) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
+        else if (decided == prefix) list_for_ranking(sh, k, t);
+      });
+      __syncthreads();
+      keep_best_listed(sh, n_left, need, gt_map);
+      __syncthreads();
+      emit_from_bitmaps<false>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+      return;
     }
-    __syncthreads();   // the list is dead: its space becomes the staging buffer
-    emit_from_bitmaps(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+    for (int i = tid; i < n_words; i += kSelThreads) eq_map[i] = 0;
+    __syncthreads();
+    const uint32_t thr_listed = prefix;
+    for_each_listed([&](uint32_t k, uint32_t t) {
+      if (k > thr_listed) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
+      else if (k == thr_listed) atomicOr(&eq_map[t >> 5], 1u << (t & 31));
+    });
+    __syncthreads();
+    emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
     return;
   }
 #pragma unroll 1
-  for (int level = 1; level < 3; ++level) descend_level(sh, level, prefix, prefix_mask, need, count);
+  for (int level = keyed ? 1 : 0; level < 3; ++level) descend_level(sh, copies, level, prefix, prefix_mask, need, count);
   const uint32_t thr = prefix;   // full 32-bit key of the budget-th largest score; keep `need` of its copies
 
   if (T <= bitmap_limit) {
@@ -517,7 +780,7 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       else if (key == thr) atomicOr(&eq_map[i >> 5], 1u << (i & 31));
     });
     __syncthreads();
-    emit_from_bitmaps(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+    emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
   } else {
     emit_from_keys(sh, T, thr, need, out, [&](int i) { return order_key(u[i]); });
   }
@@ -550,7 +813,7 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
   for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = my_counts[i];
   __syncthreads();
   uint32_t prefix = 0, prefix_mask = 0, need = (uint32_t)budget;
-  const uint32_t n_cand = descend_level(sh, 0, prefix, prefix_mask, need, [](auto) {}, true);
+  const uint32_t n_cand = descend_counted_level(sh, prefix, prefix_mask, need);
   if (n_cand > (uint32_t)kSelCandCap) return;
   const uint32_t bin0 = prefix >> 21;
   uint32_t* out_gt = pre_maps + (size_t)seg * 2 * pre_words;
@@ -588,10 +851,13 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
 
 hipError_t select_prepare() {
   const int lds = (int)(sizeof(SelShared) + (size_t)kSelRegionBytes);
-  const void* kernels[] = {reinterpret_cast<const void*>(select_kernel<false, false>),
-                           reinterpret_cast<const void*>(select_kernel<true, false>),
-                           reinterpret_cast<const void*>(select_kernel<false, true>),
-                           reinterpret_cast<const void*>(select_kernel<true, true>)};
+  const void* kernels[] = {
+      reinterpret_cast<const void*>(select_kernel<false, false>), reinterpret_cast<const void*>(select_kernel<true, false>),
+      reinterpret_cast<const void*>(select_kernel<false, true>),  reinterpret_cast<const void*>(select_kernel<true, true>),
+#define LKV_HELD_KERNELS(kE)                                                                                             \
+  reinterpret_cast<const void*>(select_held_kernel<false, kE>), reinterpret_cast<const void*>(select_held_kernel<true, kE>)
+      LKV_HELD_KERNELS(8), LKV_HELD_KERNELS(16), LKV_HELD_KERNELS(kSelMaxHeld)};
+#undef LKV_HELD_KERNELS
   for (const void* k : kernels)
     if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
   return hipSuccess;
@@ -609,32 +875,28 @@ void launch_select(const SeqTable& tab, const int32_t* host_offsets, int n_total
                    int pre_words) {
   const int segs = tab.first[tab.n];
   if (segs <= 0) return;
-  // the LDS region is sized for the longest sequence of this launch that can use it
-  int cached_limit = 0, bitmap_limit = 0;
+  // heads whose scores fit a workgroup's registers, and longer ones; the LDS of either kernel is sized for the longest
+  // sequence of this launch that it takes
+  int held_limit = 0, longer = 0, bitmap_limit = 0;
   for (int i = 0; i < tab.n; ++i) {
     const int T = tab.T[i];
-    if (T <= kSelMaxCachedKeys) { if (T > cached_limit) cached_limit = T; }
-    else if (T <= kSelMaxBitmapT) { if (T > bitmap_limit) bitmap_limit = T; }
+    if (T <= kSelMaxHeldT) held_limit = T > held_limit ? T : held_limit;
+    else ++longer;
+    if (T > kSelMaxHeldT && T <= kSelMaxBitmapT && T > bitmap_limit) bitmap_limit = T;
   }
-  // Region layout.  Cached heads: key cache of the longest one, then two bitmaps; the staging
-  // buffer of the emission overlays the (by then dead) key cache when that is large enough,
-  // else it follows the bitmaps.  Longer heads: two bitmaps, then the staging buffer.
-  const size_t cached_words = cached_limit > 0 ? (size_t)cached_limit + 2 * (size_t)((cached_limit + 31) / 32) : 0;
-  const bool overlay = (size_t)cached_limit * 4 >= (size_t)kSelStageBytes;
-  const size_t cached_stage_off = overlay ? 0 : cached_words;
-  size_t region = cached_limit > 0 ? (overlay ? cached_words * 4 : cached_words * 4 + kSelStageBytes) : 0;
-  const size_t bitmap_stage_off = 2 * (size_t)((bitmap_limit + 31) / 32);
-  if (bitmap_limit > 0 && bitmap_stage_off * 4 + kSelStageBytes > region) region = bitmap_stage_off * 4 + kSelStageBytes;
+  const int map_words = (held_limit + kSelThreads - 1) / kSelThreads * 32;
+  const size_t held_lds = sizeof(SelShared) + 2 * (size_t)map_words * 4 + kSelStageBytes;
+  const size_t bitmap_stage_off = (2 * (size_t)((bitmap_limit + 31) / 32) + 3) & ~(size_t)3;   // two bitmaps, then the staging buffer
+  const size_t lds = sizeof(SelShared) + bitmap_stage_off * 4 + kSelStageBytes;
   const SelRagged ragged = {ragged_scores, ragged_start, ragged_len};
   InlineOffsets inl = {};
   if (host_offsets != nullptr)
     for (int i = 0; i <= n_total_segments; ++i) inl.v[i] = host_offsets[i];
   const dim3 grid(segs), block(kSelThreads);
-  const size_t lds = sizeof(SelShared) + region;
   // Few long heads (a layer at a time): split the pass over the scores of every head over several workgroups first.
   // Needs the first-level counts, room for the two bitmaps, heads too long for the key cache and offsets on the device.
   bool split_heads = counts != nullptr && pre_maps != nullptr && host_offsets == nullptr && ragged_scores == nullptr &&
-                     cached_limit == 0 && bitmap_limit > 0 && segs <= kSelSplitMaxHeads;
+                     held_limit == 0 && bitmap_limit > 0 && segs <= kSelSplitMaxHeads;
   for (int i = 0; i < tab.n && split_heads; ++i)
     if (tab.T[i] > kSelMaxBitmapT || (tab.T[i] + 31) / 32 > pre_words) split_heads = false;
   if (split_heads) {
@@ -645,16 +907,24 @@ void launch_select(const SeqTable& tab, const int32_t* host_offsets, int n_total
   } else {
     pre_maps = nullptr;
   }
-#define LKV_SELECT_LAUNCH(kInline, kCounted)                                                                          \
-  hipLaunchKernelGGL((select_kernel<kInline, kCounted>), grid, block, lds, stream, tab, inl, ragged, offsets, idx,     \
-                     counts, pre_maps, pre_words, seg_base, seg_stride, cached_limit, bitmap_limit,                    \
-                     (int)cached_stage_off, (int)bitmap_stage_off)
+  auto launch = [&](auto inline_tag, auto counted_tag) {
+    constexpr bool kInline = decltype(inline_tag)::value, kCounted = decltype(counted_tag)::value;
+    auto held = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, held_lds, stream, tab, inl, ragged, offsets, idx, counts, seg_base, seg_stride,
+                         map_words);
+    };
+    if (held_limit > 16 * kSelThreads) held(select_held_kernel<kInline, kSelMaxHeld>);
+    else if (held_limit > 8 * kSelThreads) held(select_held_kernel<kInline, 16>);
+    else if (held_limit > 0) held(select_held_kernel<kInline, 8>);
+    if (longer > 0)
+      hipLaunchKernelGGL((select_kernel<kInline, kCounted>), grid, block, lds, stream, tab, inl, ragged, offsets, idx, counts,
+                         pre_maps, pre_words, seg_base, seg_stride, held_limit, bitmap_limit, (int)bitmap_stage_off);
+  };
   if (host_offsets != nullptr) {
-    if (counts != nullptr) LKV_SELECT_LAUNCH(true, true); else LKV_SELECT_LAUNCH(true, false);
+    if (counts != nullptr) launch(std::true_type{}, std::true_type{}); else launch(std::true_type{}, std::false_type{});
   } else {
-    if (counts != nullptr) LKV_SELECT_LAUNCH(false, true); else LKV_SELECT_LAUNCH(false, false);
+    if (counts != nullptr) launch(std::false_type{}, std::true_type{}); else launch(std::false_type{}, std::false_type{});
   }
-#undef LKV_SELECT_LAUNCH
 }
 
 }  // namespace lkv

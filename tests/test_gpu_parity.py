@@ -196,6 +196,55 @@ def test_select_on_crafted_scores(ctx, T):
         assert np.array_equal(got[off_ref[h]:off_ref[h + 1]], idx_ref[off_ref[h]:off_ref[h + 1]]), f"head {h}"
 
 
+@pytest.mark.parametrize("lengths", [(8192, 8193), (16384, 16385), (34816, 34817), (1023, 40001, 513, 34816)])
+@pytest.mark.parametrize("budget_share", [0.003, 0.15, 0.9])
+def test_select_on_distributions_the_bins_do_not_spread(ctx, lengths, budget_share):
+    # Either side of every kernel size, and short and long sequences in one call.  Distributions: plain; one value far from
+    # the rest (all others share a bin); +inf on a stretch, as a window scorer leaves it; a narrow cluster at the threshold
+    # (more than can be ranked one by one, and more than the list of a long head holds); ties at the threshold; values
+    # whose squares overflow.  Exact, so against the oracle's sort.
+    H = 6
+    rng = np.random.default_rng(sum(lengths))
+    us = []
+    for T in lengths:
+        u = rng.standard_normal((1, H, T)).astype(np.float32)
+        u[0, 1, T // 3] = 1e30
+        u[0, 2, T - min(T // 4, 100):] = np.inf
+        n_top = max(1, int(T * budget_share) - 700)
+        u[0, 3] = 1.0 + rng.integers(0, 64, T).astype(np.float32) * np.float32(2 ** -23)
+        u[0, 3, rng.permutation(T)[:n_top]] = 2.0
+        u[0, 4] = np.round(u[0, 4] * 8) / 8
+        u[0, 5] *= np.float32(1e30)
+        u[0, 5, ::11] = np.nan
+        us.append(u)
+    kv = [torch.empty((1, H, T, 128), dtype=torch.bfloat16, device="cuda") for T in lengths]   # contents unused by lkv_select
+    cache = lkv.Cache(kv, kv, H)
+    budgets = np.concatenate([np.full(H, max(1, int(T * budget_share)), dtype=np.int32) + np.arange(H, dtype=np.int32) for T in lengths])
+    scores = [torch.from_numpy(u).cuda() for u in us]
+    total = int(budgets.sum())
+    idx = torch.full((total + 64,), -1, dtype=torch.int32, device="cuda")
+    offsets = torch.empty(budgets.size + 1, dtype=torch.int32, device="cuda")
+    counts = torch.empty(lkv.lkv_counts_bytes(budgets.size), dtype=torch.uint8, device="cuda")
+    ref = [O.select(us[s // H][0, s % H], int(b)) for s, b in enumerate(budgets)]
+    for counted in (False, True):
+        idx.fill_(-1)
+        if counted:   # the first-level digits as a scoring launch leaves them
+            keys = [np.where(np.isnan(u), -np.inf, u).astype(np.float32).view(np.uint32) for u in us]
+            keys = [np.where(k >> 31, ~k, k | np.uint32(0x80000000)) >> 21 for k in keys]
+            hist = np.stack([np.bincount(k[0, h], minlength=2048) for k in keys for h in range(H)]).astype(np.int32)
+            counts[:] = torch.from_numpy(hist.reshape(-1).view(np.uint8)).cuda()
+            lkv.lkv_select_counted(ctx, cache, scores, budgets, counts, idx, offsets)
+        else:
+            lkv.lkv_select(ctx, cache, scores, budgets, idx, offsets)
+        torch.cuda.synchronize()
+        got, off = idx.cpu().numpy(), offsets.cpu().numpy()
+        assert (got[total:] == -1).all(), "writes past the end of idx"
+        for s, r in enumerate(ref):
+            assert np.array_equal(got[off[s]:off[s + 1]], r), (counted, "sequence", s // H, "head", s % H)
+        if counted:
+            assert not bool(counts.any()), "counters left behind"
+
+
 @pytest.mark.parametrize("n_top", [16383, 16384, 16385, 30000])
 def test_select_long_head_candidate_list_limit(ctx, n_top):
     # a head too long for the key cache: after the first radix level the undecided bin holds n_top keys;
