@@ -16,10 +16,20 @@
 // not worth four waves and three block barriers: such pieces are dealt round robin to single
 // waves, which run them on their own from load to store, so that a run of short segments inside
 // a chunk (skewed budgets leave dozens of heads at the floor) costs a quarter of the serial
-// latency chains it would otherwise.  (Merging inside
-// the first kernel, by the block that delivers a segment's last piece, needs
-// device-scope fences; with one L2 per XCD those write back and invalidate L2
-// and were measured to cost more than the second launch.)
+// latency chains it would otherwise.
+//
+// A step over few segments (up to kDecAlignedSegments: one layer of a small batch) is a chain of memory latencies, and
+// a chunk that crosses a segment boundary goes through it once per piece.  There the chunks start at the segments
+// instead: every wave loads the bounds of all segments at once, one per lane, and a prefix sum over the chunks of each
+// tells its block which segment and which rows are its own.  The grid is the most chunks that any split of the rows
+// over the segments can give.  (8 heads, 5 thousand rows, in a captured graph: 11.4 us with flat chunks, 8.6 us with
+// these; 40 thousand rows 18.1 and 13.6 us, 160 thousand 29.6 and 25.7 us; one head with nearly all of 5 thousand rows
+// 17.8 and 10.5 us.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
+// one round of resident blocks however the rows are spread; with 256 segments of 5 thousand rows each the ends of the
+// segments would need a second round.
+//
+// (Merging inside the first kernel, by the block that delivers a segment's last piece, needs device-scope fences; with
+// one L2 per XCD those write back and invalidate L2 and were measured to cost more than the second launch.)
 //
 // Arithmetic.  With up to 16 query heads per KV head the two products are
 // skinny GEMMs, and doing them on the vector ALUs costs more issue slots per
@@ -36,6 +46,8 @@
 // gfx950 (row stride 288 B); both strides make the reads bank-conflict free.
 // The next 32 rows are prefetched into registers while the current 32 are
 // multiplied.  Softmax runs in fp32 in the log2 domain.
+#include <type_traits>
+
 #include "lkv_common.h"
 
 namespace lkv {
@@ -53,6 +65,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 constexpr int kDecTargetBlocks = 512;        // chunks per launch: one round of resident blocks (2 per compute unit)
 constexpr int kDecMinChunk = 128;            // rows; shorter chunks only add partials to merge
+constexpr int kDecAlignedSegments = 64;      // chunks start at the segments in launches over at most this many: one per lane
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -69,10 +82,50 @@ __device__ __forceinline__ s16x4_t lds_read_tr16(const unsigned char* p) {
       (__attribute__((address_space(3))) s16x4_t*)(p));
 }
 
+// Chunks that start at the segments: which rows of which segment chunk `chunk` is, and the segment's share of the chunks.
+struct AlignedChunk {
+  int segment;      // -1: there are fewer chunks
+  int lo, hi;       // the segment's rows in use
+  int first, n;     // its chunks
+};
+
+// Bounds, chunk count and chunks ahead of the segment of this lane (zero chunks past the last segment).
+__device__ __forceinline__ void aligned_chunks(const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths,
+                                               int n_segments, int chunk_rows, int lane, int& lo, int& hi, int& n, int& upto) {
+  const int s = min(lane, n_segments - 1);
+  lo = offsets[s];
+  hi = lengths != nullptr ? lo + lengths[s] : offsets[s + 1];
+  n = lane < n_segments ? (int)(((uint32_t)max(hi - lo, 0) + (uint32_t)chunk_rows - 1u) / (uint32_t)chunk_rows) : 0;
+  upto = n;   // inclusive prefix sum over the lanes
+#define LKV_SCAN_STEP(ctrl, rows) upto += __builtin_amdgcn_update_dpp(0, upto, ctrl, rows, 0xf, true)
+  LKV_SCAN_STEP(0x111, 0xf);   // row_shr:1, 2, 4, 8
+  LKV_SCAN_STEP(0x112, 0xf);
+  LKV_SCAN_STEP(0x114, 0xf);
+  LKV_SCAN_STEP(0x118, 0xf);
+  LKV_SCAN_STEP(0x142, 0xa);   // the last lane of a row into the rows after it
+  LKV_SCAN_STEP(0x143, 0xc);
+#undef LKV_SCAN_STEP
+}
+
+__device__ __forceinline__ AlignedChunk take_segment(int s, int lo, int hi, int n, int upto) {
+  const int count = __builtin_amdgcn_readlane(n, s);
+  return {s, __builtin_amdgcn_readlane(lo, s), __builtin_amdgcn_readlane(hi, s), __builtin_amdgcn_readlane(upto, s) - count, count};
+}
+
+// By all lanes of a wave.
+__device__ __forceinline__ AlignedChunk find_aligned_chunk(const int32_t* offsets, const int32_t* lengths, int n_segments,
+                                                           int chunk_rows, int chunk, int lane) {
+  int lo, hi, n, upto;
+  aligned_chunks(offsets, lengths, n_segments, chunk_rows, lane, lo, hi, n, upto);
+  const unsigned long long later = __ballot(upto > chunk);
+  if (later == 0) return {-1, 0, 0, 0, 0};
+  return take_segment(__builtin_ctzll(later), lo, hi, n, upto);
+}
+
 // kMasked: every row carries a retention weight m in [0, 1] and the probabilities are
 // p_i = e^{s_i} m_i / sum_j e^{s_j} m_j (the multiplicative mask of App. B.2, which is softmax(s + log m));
-// the rows are then those of the uncompacted cache.
-template <bool kMasked>
+// the rows are then those of the uncompacted cache.  kAligned: chunks start at the segments.
+template <bool kMasked, bool kAligned>
 __global__ void __launch_bounds__(kDecThreads, 2)
 decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ kp,
                       const uint4* __restrict__ vp, const int32_t* __restrict__ offsets,
@@ -83,10 +136,15 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int chunk = blockIdx.x;
-  const int64_t p0 = (int64_t)chunk * chunk_rows;
-  const int64_t p1 = min(p0 + (int64_t)chunk_rows, total_kept);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
+  AlignedChunk mine = {};
+  if (kAligned) {
+    mine = find_aligned_chunk(offsets, lengths, n_segments, chunk_rows, chunk, lane);
+    if (mine.segment < 0) return;   // the whole block
+  }
+  const int64_t p0 = kAligned ? (int64_t)mine.lo + (int64_t)(chunk - mine.first) * chunk_rows : (int64_t)chunk * chunk_rows;
+  const int64_t p1 = min(p0 + (int64_t)chunk_rows, total_kept);
   const int wave = tid >> 6;
   const int r = lane >> 4;     // load view: row slot.   operand view: K-block kb / accumulator row block rb
   const int c = lane & 15;     // load view: 16-byte piece. operand view: token / head / channel index
@@ -95,17 +153,20 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
   DecMerge& mg = *reinterpret_cast<DecMerge*>(smem);
   const float qscale = scale * kLog2e;
   // first segment of this block: the one that contains row p0, i.e. the last with offsets[s] <= p0
-  const int s_first = wave_upper_segment(offsets, n_segments, p0, lane);
+  const int s_first = kAligned ? mine.segment : wave_upper_segment(offsets, n_segments, p0, lane);
   int small_seen = 0;   // short pieces met so far in this chunk (the same count in every wave)
 
 #pragma unroll 1
   for (int s = s_first; s < n_segments; ++s) {
-    const int64_t seg_lo = offsets[s];
+    const int64_t seg_lo = kAligned ? mine.lo : offsets[s];
     if (seg_lo >= p1) break;
     // rows behind the ones in use (spare rows for later tokens) are never read
-    const int64_t seg_hi = lengths != nullptr ? seg_lo + lengths[s] : (int64_t)offsets[s + 1];
+    const int64_t seg_hi = kAligned ? mine.hi : lengths != nullptr ? seg_lo + lengths[s] : (int64_t)offsets[s + 1];
     const int64_t a = max(p0, seg_lo), b = min(p1, seg_hi);
-    if (b <= a) continue;   // empty segment (the merge kernel zeroes its output)
+    if (b <= a) {   // empty segment (the merge kernel zeroes its output)
+      if (kAligned) return;
+      continue;
+    }
     const int n_rows = (int)(b - a);
     const int n_tiles = (n_rows + kDecTile - 1) / kDecTile;
 
@@ -115,7 +176,10 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
     if (small) {
       const int owner = small_seen & (kDecWaves - 1);
       ++small_seen;
-      if (wave != owner) continue;
+      if (wave != owner) {
+        if (kAligned) return;   // there is no next segment
+        continue;
+      }
       t_first = 0;
       t_step = 1;
     }
@@ -235,7 +299,7 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
 
     l_run = sum_over_row_blocks(l_run);
     const bool whole = seg_lo >= p0 && seg_hi <= p1;
-    const size_t slot = (size_t)s + (size_t)chunk;
+    const size_t slot = kAligned ? (size_t)chunk : (size_t)s + (size_t)chunk;
     if (small) {
       // ---- one wave had the whole piece: it writes the result (or the partial) straight from its registers;
       // head h's maximum and denominator sit in lane h ----
@@ -261,6 +325,7 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
           }
         }
       }
+      if (kAligned) return;
       continue;
     }
     // ---- combine the four waves through LDS (the staging tiles are free now) ----
@@ -297,6 +362,7 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
         if (ch == 0) { ws_m[slot * G + h] = mxw; ws_l[slot * G + h] = den; }
       }
     }
+    if (kAligned) return;
     __syncthreads();   // the merge scratch becomes staging tiles again
   }
 }
@@ -306,24 +372,34 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
 // ceil(G * 128 / 256) blocks.  The kernel is a short chain of dependent memory latencies, so
 // the partials of up to eight pieces are loaded together and folded in with a running maximum:
 // the chain is the offsets load plus one round per eight pieces.
+template <bool kAligned>
 __global__ void __launch_bounds__(kDecThreads)
-decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths, int G,
+decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths, int n_segments, int G,
                     int blocks_per_segment, int chunk_rows,
                     const float* __restrict__ ws_acc, const float* __restrict__ ws_m,
                     const float* __restrict__ ws_l, float* __restrict__ out, float* __restrict__ lse) {
   const int s = blockIdx.x / blocks_per_segment;
   const int o = (blockIdx.x - s * blocks_per_segment) * kDecThreads + threadIdx.x;
+  AlignedChunk seg = {};
+  if (kAligned) {
+    int lo, hi, n, upto;   // by all lanes, before any leaves
+    aligned_chunks(offsets, lengths, n_segments, chunk_rows, threadIdx.x & 63, lo, hi, n, upto);
+    seg = take_segment(s, lo, hi, n, upto);
+  }
   if (o >= G * kHeadDim) return;
   const int h = o / kHeadDim, ch = o - h * kHeadDim;
-  const int64_t a = offsets[s];
-  const int64_t b = lengths != nullptr ? a + lengths[s] : (int64_t)offsets[s + 1];
+  const int64_t a = kAligned ? seg.lo : offsets[s];
+  const int64_t b = kAligned ? seg.hi : lengths != nullptr ? a + lengths[s] : (int64_t)offsets[s + 1];
   const size_t row = (size_t)s * G + h;
   if (b <= a) {   // empty segment: zero output, lse = -inf
     out[row * kHeadDim + ch] = 0.f;
     if (ch == 0 && lse != nullptr) lse[row] = -INFINITY;
     return;
   }
-  const int c_first = (int)(a / chunk_rows), c_last = (int)((b - 1) / chunk_rows);
+  // the segment's chunks; their slots are counted by chunk, and with flat chunks by segment too
+  const int c_first = kAligned ? seg.first : (int)(a / chunk_rows);
+  const int c_last = kAligned ? seg.first + seg.n - 1 : (int)((b - 1) / chunk_rows);
+  const size_t slot0 = kAligned ? 0 : (size_t)s;
   if (c_first == c_last) return;   // a whole segment inside one chunk was finished by the first kernel
   constexpr int kU = 8;
   float mx = -INFINITY, num = 0.f, den = 0.f;
@@ -332,7 +408,7 @@ decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restri
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int cc = min(c0 + u, c_last);
-      const size_t sl = (size_t)s + cc;
+      const size_t sl = slot0 + cc;
       mv[u] = ws_m[sl * G + h];
       lv[u] = ws_l[sl * G + h];
       av[u] = ws_acc[(sl * G + h) * kHeadDim + ch];
@@ -362,6 +438,13 @@ int decode_chunk_rows(int64_t total_kept) {
   c = (c + kDecTile - 1) / kDecTile * kDecTile;
   if (c < kDecMinChunk) c = kDecMinChunk;
   return (int)c;
+}
+
+// Rows per chunk where chunks start at the segments: every segment may end in a short one, and the grid with all of those
+// is still about one round of resident blocks.  Never less than decode_chunk_rows, whose slots hold these chunks too.
+static int decode_aligned_chunk_rows(int n_segments, int64_t total_kept) {
+  const int64_t c = (total_kept + kDecTargetBlocks - n_segments - 1) / (kDecTargetBlocks - n_segments);
+  return (int)(c <= kDecMinChunk ? kDecMinChunk : (c + kDecTile - 1) / kDecTile * kDecTile);
 }
 
 static size_t decode_slots(int n_segments, int64_t total_kept) {
@@ -395,12 +478,15 @@ void* decode_static_scratch(int device) {
 // Once per device, with that device current (lkv_create calls it right after selecting the device).
 // The four staging tiles exceed the default 64 KB of LDS per workgroup.
 hipError_t decode_prepare(int device) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kDecWaves * kDecWaveLds);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_partial_kernel<true>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kDecWaves * kDecWaveLds);
-  if (e != hipSuccess) return e;
+  const void* kernels[] = {reinterpret_cast<const void*>(decode_partial_kernel<false, false>),
+                           reinterpret_cast<const void*>(decode_partial_kernel<false, true>),
+                           reinterpret_cast<const void*>(decode_partial_kernel<true, false>),
+                           reinterpret_cast<const void*>(decode_partial_kernel<true, true>)};
+  hipError_t e = hipSuccess;
+  for (const void* k : kernels) {
+    e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kDecWaves * kDecWaveLds);
+    if (e != hipSuccess) return e;
+  }
   if (device < 0 || device >= kDecMaxDevices) return hipErrorInvalidDevice;
   if (g_scratch_ptr[device] == nullptr) {
     void* ptr = nullptr;
@@ -431,22 +517,25 @@ hipError_t launch_decode(int G, const void* q, const void* kp, const void* vp, c
   float* ws_acc = ws;
   float* ws_m = ws + slots * G * kHeadDim;
   float* ws_l = ws_m + slots * G;
-  const int chunk_rows = decode_chunk_rows(total_kept);
-  const int chunks = (int)((total_kept + chunk_rows - 1) / chunk_rows);
-  if (chunks > 0 && mask == nullptr) {
-    hipLaunchKernelGGL(decode_partial_kernel<false>, dim3(chunks), dim3(kDecThreads), kDecWaves * kDecWaveLds, stream,
-                       reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint4*>(kp),
-                       reinterpret_cast<const uint4*>(vp), offsets, lengths, n_segments, total_kept, chunk_rows, G, scale,
-                       out, lse, ws_acc, ws_m, ws_l, mask);
-  } else if (chunks > 0) {
-    hipLaunchKernelGGL(decode_partial_kernel<true>, dim3(chunks), dim3(kDecThreads), kDecWaves * kDecWaveLds, stream,
-                       reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint4*>(kp),
-                       reinterpret_cast<const uint4*>(vp), offsets, lengths, n_segments, total_kept, chunk_rows, G, scale,
-                       out, lse, ws_acc, ws_m, ws_l, mask);
-  }
   const int blocks_per_segment = (G * kHeadDim + kDecThreads - 1) / kDecThreads;
-  hipLaunchKernelGGL(decode_merge_kernel, dim3(n_segments * blocks_per_segment), dim3(kDecThreads), 0, stream,
-                     offsets, lengths, G, blocks_per_segment, chunk_rows, ws_acc, ws_m, ws_l, out, lse);
+  auto launch = [&](auto masked_tag, auto aligned_tag) {
+    constexpr bool kMasked = decltype(masked_tag)::value, kAligned = decltype(aligned_tag)::value;
+    const int chunk_rows = kAligned ? decode_aligned_chunk_rows(n_segments, total_kept) : decode_chunk_rows(total_kept);
+    const int chunks = kAligned ? (int)(total_kept / chunk_rows) + n_segments   // each segment may end in a short one
+                                : (int)((total_kept + chunk_rows - 1) / chunk_rows);
+    if (total_kept > 0)
+      hipLaunchKernelGGL((decode_partial_kernel<kMasked, kAligned>), dim3(chunks), dim3(kDecThreads), kDecWaves * kDecWaveLds,
+                         stream, reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint4*>(kp),
+                         reinterpret_cast<const uint4*>(vp), offsets, lengths, n_segments, total_kept, chunk_rows, G, scale,
+                         out, lse, ws_acc, ws_m, ws_l, mask);
+    hipLaunchKernelGGL(decode_merge_kernel<kAligned>, dim3(n_segments * blocks_per_segment), dim3(kDecThreads), 0, stream,
+                       offsets, lengths, n_segments, G, blocks_per_segment, chunk_rows, ws_acc, ws_m, ws_l, out, lse);
+  };
+  if (n_segments <= kDecAlignedSegments) {
+    if (mask != nullptr) launch(std::true_type{}, std::true_type{}); else launch(std::false_type{}, std::true_type{});
+  } else {
+    if (mask != nullptr) launch(std::true_type{}, std::false_type{}); else launch(std::false_type{}, std::false_type{});
+  }
   return hipGetLastError();
 }
 

@@ -142,6 +142,17 @@ def test_random_shapes(ctx, seed):
     _run_and_check(ctx, w, Ts, seed=seed, budgets=budgets, what=f"random {seed}")
 
 
+@pytest.mark.parametrize("L,H,Hq,T", [(1, 1, 4, 300), (8, 8, 8, 300), (13, 5, 10, 300), (1, 8, 32, 40000)])
+def test_decode_chunks_that_start_at_the_segments_and_flat_ones(ctx, L, H, Hq, T):
+    """Up to 64 segments each start their own chunks, more are cut without regard to them.  Segment lengths on either
+    side of a tile of 32 rows, of a piece for one wave (64) and of a chunk (128 rows, or 192 for the long heads), and
+    empty ones in between."""
+    w = W.scaled(W.CONFIGS[0], L=L, H=H, Hq=Hq, T=T, b_min=0)
+    edges = [0, 1, 31, 32, 33, 64, 65, 127, 128, 129, 0, 256, 257, T] if T < 1000 else [T, 0, 191, 192, 193, 12345, 1, T - 1]
+    budgets = [np.resize(np.array(edges[::-1] if L == 1 and H == 1 else edges, dtype=np.int32), (L, H))]
+    _run_and_check(ctx, w, [T], seed=3, budgets=budgets, what=f"decode chunks {L}x{H}")
+
+
 def test_group_size_limit(ctx):
     w = W.scaled(W.CONFIGS[0], L=1, H=1, Hq=17, T=64, b_min=4)
     K, V, Q, sc, B = _inputs(w, [64])
