@@ -85,6 +85,14 @@ def test_mlp_scorer(ctx, hidden, act, per_head):
     print(f"mlp {hidden} {act}: worst score ratio {ws:.3g}")
 
 
+@pytest.mark.parametrize("L,H,hidden,T", [(16, 32, 64, 300), (16, 32, 128, 600), (16, 32, 64, 257), (19, 27, 32, 300), (1, 8, 64, 16385)])
+def test_mlp_tiles_that_fill_one_round_of_blocks(ctx, L, H, hidden, T):
+    """A launch over one sequence divides the heads evenly over the blocks the chip holds: tiles of 320 rows (the last
+    one short), one or more to a head, and a launch over one head too many for that."""
+    w = W.scaled(W.CONFIGS[2], L=L, H=H, Hq=H, T=T, b_min=4, hidden=hidden, act="gelu")
+    _run_and_check(ctx, w, [T], seed=9, what=f"one round {L}x{H} {hidden} {T}")
+
+
 def test_mlp_without_output_bias_and_heavy_tails(ctx):
     w = W.scaled(W.CONFIGS[4], L=2, H=2, Hq=14, T=2500, n_seq=2, b_min=8)
     K, V, Q, sc, B = _inputs(w, [2500, 2500])
