@@ -419,8 +419,8 @@ lkv_status lkv_masked_attn_forward(lkv_ctx *ctx, int32_t n_q_heads, int32_t n_kv
  * dq  : DEVICE fp32 [n_q_heads, seq_len, d];  dk, dv : DEVICE fp32 [n_kv_heads, seq_len, d]
  * dm  : DEVICE fp32 [n_kv_heads, seq_len]
  * workspace : DEVICE, at least lkv_masked_attn_backward_workspace_bytes(n_q_heads, n_kv_heads, seq_len)
- *             bytes, 16-byte aligned (holds D and, for short sequences with grouped heads, per-query-head
- *             partial sums of dk, dv and dm that a last pass adds up in a fixed order).
+ *             bytes, 16-byte aligned (holds D and, where the query heads of a group are dealt to several
+ *             blocks, their partial sums of dk, dv and dm, which a last pass adds up in a fixed order).
  * Every output element is written exactly once (no atomics: results are reproducible bit for bit).
  * Outputs and workspace must not overlap the inputs or each other.
  * Errors as for the forward call, plus LKV_ERR_WORKSPACE. */
