@@ -298,25 +298,25 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
     if (t == n_full + 1 && n_steps == 2 * t + 2) value_products(tile + kMaStep * kMaRow);
   };
 
-  // One barrier per tile: it makes the tile's rows visible (the compiler waits for the transfers before it) and means
-  // that every wave is done with the other array, which the next tile then fills.
+  // One barrier per tile: every wave waits for its transfers of the tile before it, so it makes the tile's rows visible,
+  // and it means that every wave is done with the other array, which the next tile then fills.
   stage(tile_a, 0);
   start();
 #pragma unroll 1
   for (int t = 0; t < n_full; t += 2) {
-    __syncthreads();
+    lds_fill_barrier();
     stage(tile_b, t + 1);
     step(std::false_type{}, std::false_type{}, tile_a, 2 * t, 0);
     step(std::false_type{}, std::false_type{}, tile_a, 2 * t + 1, 1);
-    __syncthreads();
+    lds_fill_barrier();
     stage(tile_a, t + 2);
     step(std::false_type{}, std::false_type{}, tile_b, 2 * t + 2, 0);
     step(std::false_type{}, std::false_type{}, tile_b, 2 * t + 3, 1);
   }
-  __syncthreads();
+  lds_fill_barrier();
   stage_last(tile_b);
   last_tile(std::false_type{}, tile_a, n_full);
-  __syncthreads();
+  lds_fill_barrier();
   last_tile(std::false_type{}, tile_b, n_full + 1);
 
   // References that stay put save the maximum, the branch on it and the rescaling it guards, 8 % of the time.  They hold
@@ -333,7 +333,7 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
     for (int t = 0; t < n_full + 2; ++t) {
       unsigned char* tile = t & 1 ? tile_b : tile_a;
       unsigned char* other = t & 1 ? tile_a : tile_b;
-      __syncthreads();
+      lds_fill_barrier();
       if (t < n_full) stage(other, t + 1);
       else if (t == n_full) stage_last(other);
       last_tile(std::true_type{}, tile, t);
