@@ -471,17 +471,17 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     }
     q0 = q0 + kMbTile < T ? q0 + kMbTile : k0;
   };
-  // One barrier per item: it makes the item's rows visible (the compiler waits for the transfers before it) and means
-  // that every wave is done with the other array, which the next item then fills.
+  // One barrier per item: every wave waits for its transfers of the item before it, so it makes the item's rows visible,
+  // and it means that every wave is done with the other array, which the next item then fills.
   put_aux(aux_a);
 #pragma unroll 1
   for (int it = 0; it < n_items; it += 2) {
-    __syncthreads();
+    lds_fill_barrier();
     fetch(tile_b);
     item(tile_a, aux_a);
     put_aux(aux_b);
     if (it + 1 >= n_items) break;
-    __syncthreads();
+    lds_fill_barrier();
     fetch(tile_a);
     item(tile_b, aux_b);
     put_aux(aux_a);
