@@ -363,7 +363,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       sb = st_collect<kT>(su[1], 0.0, StAdd());
       turn ^= 1;
       delta = 0.5 * ((up - dn) + log(sb) - log(sa));
-      factor = INFINITY;
+      factor = exp(delta);   // used for the outputs below only where the trial lies near the middle of the gap
     } else {
       // the root without a difference of close numbers; a = 0 (empty head) and b = 0 (empty tail) come out as they should
       const double root = hypot(d, 2.0 * sqrt(a) * sqrt(b));

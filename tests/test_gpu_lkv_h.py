@@ -194,6 +194,54 @@ def test_soft_topk_either_side_of_every_kernel_size(ctx, n, dtype):
         assert int((z > tol).sum()) <= m <= int((z >= -tol).sum()), what
 
 
+def _check_at_returned_threshold(xs, y, lam, m, k, tau, what):
+    """y against f at the returned lambda, their sum against k, the split index against lambda; the bounds are those of
+    the test above."""
+    with np.errstate(over="ignore"):
+        z = xs.astype(np.float64) / tau - lam
+    half = 0.5 * np.exp(-np.abs(z))
+    ref = np.where(z >= 0, 1.0 - half, half)
+    tol = 4e-15 * max(1.0, abs(lam))
+    assert np.isfinite(lam) and np.isfinite(y).all() and y.min() >= 0.0 and y.max() <= 1.0, (what, lam, y.min(), y.max())
+    assert np.abs(y - ref).max() <= tol, (what, np.abs(y - ref).max())
+    assert abs(y.sum() - k) <= tol * max(1.0, half.sum()) + 1e-15 * len(xs), (what, y.sum() - k)
+    assert int((z > tol).sum()) <= m <= int((z >= -tol).sum()), what
+
+
+def _gpu_soft_topk_rows(ctx, rows, k, tau):
+    x = torch.from_numpy(np.ascontiguousarray(rows)).cuda()
+    y = torch.empty(rows.shape, dtype=torch.float64, device="cuda")
+    info = torch.empty((len(rows), 2), dtype=torch.float64, device="cuda")
+    lkv.lkv_soft_topk_batched(ctx, x, torch.tensor(k, dtype=torch.float64, device="cuda"), tau, y, info)
+    torch.cuda.synchronize()
+    return y.cpu().numpy(), info.cpu().numpy()
+
+
+@pytest.mark.parametrize("n", [5, 1000, 1025, 16384, 32768, 32769])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_soft_topk_whole_target_in_a_gap_with_one_value_far_away(ctx, n, dtype):
+    # Two clusters 1100 units of z apart, the upper one exactly the target, and one value so far below (or above) that the
+    # first trial lies somewhere in the gap: about the middle where the distance is the number of histogram bins times
+    # the gap.  Every f'(z) of one side or of both underflows there.
+    rng = np.random.default_rng(n)
+    tau, gap, head = 0.01, 11.0, max(2, n // 5)
+    rows, ks = [], []
+    for times in np.concatenate([np.linspace(300, 700, 21), np.linspace(1800, 2300, 21), [1.0, 30.0, 1e4, 1e6]]):
+        for sign in (-1, 1):
+            x = rng.uniform(0, 0.3 * tau, n)
+            x[:head] += gap
+            x[-1 if sign < 0 else 0] = sign * times * gap
+            rows.append(x.astype(dtype))
+            ks.append(float(head))
+    rows[0] = np.concatenate([np.array([-4600, 0, 0, 11, 11]), np.full(n - 5, -4600)]).astype(dtype)
+    ks[0] = 2.0
+    y, info = _gpu_soft_topk_rows(ctx, np.stack(rows), ks, tau)
+    for i, x in enumerate(rows):
+        _check_at_returned_threshold(x, y[i], info[i, 0], int(info[i, 1]), ks[i], tau, i)
+    y0, lam, m = _gpu_soft_topk(ctx, rows[0], 2.0, tau)
+    assert np.array_equal(y0, y[0]) and lam == info[0, 0] and m == 2
+
+
 def test_soft_topk_argument_errors(ctx):
     x = torch.zeros(10, dtype=torch.float64, device="cuda")
     y = torch.empty_like(x)
