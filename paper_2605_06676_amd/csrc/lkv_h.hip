@@ -13,13 +13,19 @@
 // One workgroup per vector.  What bounds it: instruction issue, one exponential per element and trial, so the
 // trials are made where they are cheap: a histogram of the inputs finds the value of rank k to a bin's width, two to
 // four trials on fp32 differences to that centre (one hardware exponential per element) find the threshold to fp32
-// accuracy, and only their end point is evaluated in fp64, where one pass both proves the split and yields the sums; the exponentials of that pass also give the outputs (e^{v - z} y = e^{lambda - z}).
+// accuracy, and only their end point is evaluated in fp64, where one pass both proves the split and yields the sums;
+// the exponentials of that pass also give the outputs (e^{v - z} y = e^{lambda - z}).
+// The trials never pass the threshold (beyond a crossed value the closed form takes more than f does) but cross few
+// values each where z is sparse, so they have to begin near rank k: where far values keep the histograms from getting
+// there, the value of rank k is found exactly, from the bits.  (256 vectors of 16384, half of them masked with the
+// type's lowest: 88 us, 1.5 ms by halving the bracket that such values stretch.)
 // fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
 // Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
 // (they stay in L2).  256 vectors of 16384 fp32 values: 35 us (257 us for the LDS sort
 // and logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -33,9 +39,13 @@ constexpr int kStThreads = 1024;          // workgroup of all but the shortest v
 constexpr int kStSmallThreads = 256;      // vectors of up to 1024 values: fewer waves to reduce over
 constexpr int kStMaxN = 1 << 22;
 constexpr int kStLevels = 4;              // histograms at most (a cold temperature spreads the values over many units of z)
+constexpr double kStWiden = 1.0 + 1e-6;   // bins this much wider than the span over their number: its upper end falls inside the last one
 constexpr double kStEnough = 0.5;         // bin width, in z, from which the fp32 trials converge in two to four steps
+constexpr double kStFar = 32.0;           // bin width, in z, up to which the trials still do without an exact start
 constexpr int kStSearchSteps = 48;        // fp32 trials at most (bisection alone would need about 30)
 constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
+constexpr double kStCoarse = 1e15;         // |z| from which fp64 no longer resolves tenths of a unit
+constexpr double kStMost = 1e300;         // centre of the search at most: its multiples do not overflow
 constexpr double kStTiny = 1e-280;        // sums below this have lost (or may have lost) terms to underflow
 
 // In a batched launch block b works on vector b: rows of x, y and info, and its own target sum, which the paper
@@ -118,8 +128,22 @@ __device__ __forceinline__ double st_collect(const double (&slot)[16], double id
   return st_uniform(st_row16(l < kT / 64 ? slot[l] : identity, op));
 }
 
+// keys whose unsigned order is the numeric order of the values
+__device__ __forceinline__ uint32_t st_key(float x) {
+  const uint32_t u = __float_as_uint(x);
+  return (u >> 31) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ uint64_t st_key(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+__device__ __forceinline__ float st_value(uint32_t k) { return __uint_as_float((k >> 31) ? (k & 0x7fffffffu) : ~k); }
+__device__ __forceinline__ double st_value(uint64_t k) {
+  return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+
 // x / tau, correctly rounded: one multiplication and a residual correction where x came from fp32 and tau is moderate
-// (nothing overflows or loses bits there), else the division itself
+// (nothing overflows or loses bits there) and x finite, else the division itself
 template <typename X>
 __device__ __forceinline__ double st_quotient(X x, double tau, double rtau, bool moderate) {
   const double xd = (double)x;
@@ -150,7 +174,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
   int turn = 0;
   k = st_uniform(k);
   const double rtau = st_uniform(1.0 / tau);
-  const bool moderate = tau > 1e-100 && tau < 1e100;
+  bool moderate = tau > 1e-100 && tau < 1e100;
 
   // ---- where to look: the value of rank k, by histograms of the inputs that narrow to one bin ----
   double lo, hi, zc;   // bracket of the threshold; centre of the search
@@ -181,23 +205,12 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     turn ^= 1;
     // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
     // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
+    moderate = moderate && least > -INFINITY && most < INFINITY;
     lo = st_uniform(least / tau - 1.0 - fmax(0.0, log((double)n / (2.0 * ((double)n - k)))));
     hi = st_uniform(most / tau + 1.0 + fmax(0.0, log((double)n / (2.0 * k))));
     constexpr int kBins = StHist<kT>::kBins;
-    double base = least, span = most - least;
     double above = 0.0;   // values in higher bins
-    bool looking = span > 0.0 && span < INFINITY;
-    for (int level = 0; level < kStLevels && looking; ++level) {
-      for (int i = tid; i < kBins; i += kT) hist.bin[i] = 0;
-      if (tid == 0) hist.found = -1;
-      __syncthreads();
-      const float to_bin = (float)((double)kBins / span);
-      auto visit = [&](X xv, bool in) {
-        const float f = (float)(xv - (X)base) * to_bin;
-        // the first level takes every value; the next ones the values of the bin found before
-        if (in && (level == 0 || (f >= 0.f && f < (float)kBins)))
-          atomicAdd(&hist.bin[(int)fminf(fmaxf(f, 0.f), (float)(kBins - 1))], 1u);
-      };
+    auto for_each = [&](auto visit) {
       if constexpr (kHeld) {
 #pragma unroll
         for (int e = 0; e < kR; ++e) visit(xr[e], tid + e * kT < n);
@@ -205,6 +218,14 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
 #pragma unroll 4
         for (int i = tid; i < n; i += kT) visit(x[i], true);
       }
+    };
+    auto clear = [&]() {
+      for (int i = tid; i < kBins; i += kT) hist.bin[i] = 0;
+      if (tid == 0) hist.found = -1;
+      __syncthreads();
+    };
+    // the bin with the value of rank k from the top, or -1; advances `above`
+    auto find_bin = [&]() {
       __syncthreads();
       // from the top: thread t owns bins kBins - 1 - 2 t and kBins - 2 - 2 t
       const int top = kBins - 1 - 2 * tid;
@@ -224,15 +245,55 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       if (c1 != 0 && e0 + c0 < k && k <= e0 + c0 + c1) { hist.found = top - 1; hist.above = e0 + c0; }
       __syncthreads();
       const int found = __builtin_amdgcn_readfirstlane(hist.found);
-      if (found < 0) break;   // rounding moved a value across the bin's edge: the bin is narrow enough
-      above = st_uniform(hist.above);
+      if (found >= 0) above = st_uniform(hist.above);
       __syncthreads();        // the next level clears what has just been read
-      span = st_uniform(span / (double)kBins);
+      return found;
+    };
+    double base = least, span = most - least;
+    bool looking = span > 0.0 && span < INFINITY;
+    for (int level = 0; level < kStLevels && looking; ++level) {
+      clear();
+      const double width = st_uniform(span * (kStWiden / (double)kBins));
+      const float to_bin = (float)(1.0 / width);
+      for_each([&](X xv, bool in) {
+        const float f = (float)(xv - (X)base) * to_bin;
+        // the first level takes every value; the next ones the values of the bin found before
+        if (in && (level == 0 || (f >= 0.f && f < (float)kBins)))
+          atomicAdd(&hist.bin[(int)fminf(fmaxf(f, 0.f), (float)(kBins - 1))], 1u);
+      });
+      const int found = find_bin();
+      if (found < 0) break;   // rounding moved a value across the bin's edge
+      span = width;
       base = st_uniform(base + found * span);
       looking = span > kStEnough * tau && base + span > base;
     }
-    zc = st_uniform((base + 0.5 * span) / tau);
-    if (!(zc > lo && zc < hi)) zc = st_uniform(0.5 * (lo + hi));
+    if (__builtin_expect(span <= kStFar * tau, 1)) {
+      zc = st_uniform((base + 0.5 * span) / tau);
+    } else {
+      // Values so far apart (masked with the type's lowest, or infinite) that equal steps do not come down to the rest
+      // of them: the value of rank k itself, digit by digit of its ordered bits.
+      using Key = decltype(st_key(X()));
+      constexpr int kDigit = kT == 1024 ? 11 : 9;
+      static_assert(1 << kDigit == kBins, "a digit per bin");
+      Key key = 0;
+      above = 0.0;
+#pragma unroll 1
+      for (int left = 8 * (int)sizeof(Key); left > 0;) {   // bits of the key not yet known
+        const int shift = left > kDigit ? left - kDigit : 0;
+        clear();
+#pragma unroll 4
+        for (int i = tid; i < n; i += kT) {
+          const Key own = st_key(x[i]);
+          if (left == 8 * (int)sizeof(Key) || (own ^ key) >> left == 0)   // agrees in the bits known
+            atomicAdd(&hist.bin[(own >> shift) & (Key)((1 << (left - shift)) - 1)], 1u);
+        }
+        key |= (Key)max(find_bin(), 0) << shift;
+        left = shift;
+      }
+      zc = st_uniform((double)st_value(key) / tau);
+    }
+    zc = st_uniform(fmin(fmax(zc, -kStMost), kStMost));   // an infinite value of rank k: any threshold beyond the others
+    if (!(zc >= lo && zc <= hi)) zc = st_uniform(0.5 * (lo + hi));
   }
 
   // ---- search in fp32: w = (z - zc) log2 e ----
@@ -246,8 +307,10 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
         w[e] = tid + e * kT < n ? (float)fma((double)x[min(tid + e * kT, n - 1)], scale, shift) : -INFINITY;
     }
     float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
+    // nothing to search for at a centre that itself rounds to about a unit
+    const int n_search = fabs(zc) < kStCoarse ? kStSearchSteps : 0;
 #pragma unroll 1
-    for (int step = 0; step < kStSearchSteps; ++step) {
+    for (int step = 0; step < n_search; ++step) {
       float head = 0.f, all = 0.f;
       int cnt = 0;
       auto visit = [&](float wv) {
@@ -291,7 +354,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       fv = next;
     }
     v = fma((double)fv, kLn2, zc);
-    if (!(v > lo && v < hi)) v = 0.5 * (lo + hi);
+    if (!(v >= lo && v <= hi)) v = 0.5 * (lo + hi);
     v = st_uniform(v);
   }
 
@@ -362,7 +425,8 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       sa = st_collect<kT>(su[0], 0.0, StAdd());
       sb = st_collect<kT>(su[1], 0.0, StAdd());
       turn ^= 1;
-      delta = 0.5 * ((up - dn) + log(sb) - log(sa));
+      // (a head or a tail of infinite values only: far enough that the other side's f round to 1 or 0)
+      delta = dn == INFINITY ? -746.0 : up == INFINITY ? 746.0 : 0.5 * ((up - dn) + log(sb) - log(sa));
       factor = exp(delta);   // used for the outputs below only where the trial lies near the middle of the gap
     } else {
       // the root without a difference of close numbers; a = 0 (empty head) and b = 0 (empty tail) come out as they should
@@ -374,7 +438,9 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     factor = st_uniform(factor);
     lambda = v + delta;
     // the split holds when no value lies between v and lambda (values at lambda belong to the head)
-    if (delta >= 0.0 ? delta <= up : -delta < dn) {
+    // or the step is lost in rounding v (values beyond 2^53 units of z that tie with the threshold); NaN among the inputs
+    // makes every output NaN
+    if ((delta >= 0.0 ? delta <= up : -delta < dn) || lambda == v || lambda != lambda) {
       from_held = kHeld && fabs(delta) < 100.0;
       break;
     }
@@ -445,7 +511,11 @@ soft_topk_backward_kernel(const X* __restrict__ x, int n, double tau, const doub
   const double lambda = info[0];
   const double rtau = 1.0 / tau;
   const bool moderate = tau > 1e-100 && tau < 1e100;
-  auto distance = [&](X xv) { return fabs(st_quotient(xv, tau, rtau, moderate) - lambda); };
+  auto distance = [&](X xv) {
+    // an infinite (masked) value counts as the type's largest: the quotient's correction would make it NaN
+    if constexpr (sizeof(X) == 4) xv = __builtin_amdgcn_fmed3f(xv, -FLT_MAX, FLT_MAX);
+    return fabs(st_quotient(xv, tau, rtau, moderate) - lambda);
+  };
 
   double ex[kR], gr[kR];
   double amin = INFINITY, s = 0.0, sg = 0.0;

@@ -242,6 +242,40 @@ def test_soft_topk_whole_target_in_a_gap_with_one_value_far_away(ctx, n, dtype):
     assert np.array_equal(y0, y[0]) and lam == info[0, 0] and m == 2
 
 
+@pytest.mark.parametrize("n", [300, 1024, 1025, 16384, 32769])
+@pytest.mark.parametrize("dtype,far", [(np.float32, -1e20), (np.float32, 1e30), (np.float32, -np.finfo(np.float32).max),
+                                       (np.float32, -np.inf), (np.float32, np.inf), (np.float64, -1e30),
+                                       (np.float64, -np.finfo(np.float64).max), (np.float64, -np.inf)])
+def test_soft_topk_of_masked_values(ctx, n, dtype, far):
+    # Values masked with a number far beyond the rest, up to the type's lowest and infinity: half of them below, or three
+    # above.  The masked ones take 0 (or 1) and the threshold is that of the others with what is left of the target.
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal(n).astype(dtype)
+    masked = np.arange(n) % 2 == 1 if far < 0 else np.arange(n) < 3
+    x[masked] = far
+    taken = 3.0 if far > 0 else 0.0
+    for tau in (1.0, 0.1, 1e-3):
+        for k in (0.15 * n, taken + 0.3, n // 2 - 1.25):
+            y, info = _gpu_soft_topk_rows(ctx, x[None], [k], tau)
+            lam, m = info[0]
+            assert np.abs(y[0, masked] - (1.0 if far > 0 else 0.0)).max() <= 1e-300, (tau, k)
+            _check_at_returned_threshold(x[~masked], y[0, ~masked], lam, int(m - taken), k - taken, tau, (tau, k))
+            one, lam1, m1 = _gpu_soft_topk(ctx, x, k, tau)
+            assert np.array_equal(one, y[0]) and lam1 == lam and m1 == m
+            # backward: nothing reaches the masked values, the others as if alone
+            g = rng.standard_normal(n)
+            dx, alone = (torch.empty(c, dtype=torch.float64, device="cuda") for c in (n, n - int(masked.sum())))
+            li = torch.tensor([lam, m], device="cuda")
+            lkv.lkv_soft_topk_backward(ctx, torch.from_numpy(x).cuda(), tau, li, torch.from_numpy(g).cuda(), dx)
+            lkv.lkv_soft_topk_backward(ctx, torch.from_numpy(x[~masked]).cuda(), tau, li, torch.from_numpy(g[~masked]).cuda(), alone)
+            dx, alone = dx.cpu().numpy(), alone.cpu().numpy()
+            assert np.abs(dx[masked]).max() <= 1e-300 and np.isfinite(dx).all(), (tau, k)
+            assert np.abs(dx[~masked] - alone).max() <= 1e-9 * np.abs(alone).max() + 1e-300, (tau, k)
+        # a whole target: every value that is not masked from below, or only those masked from above
+        y, info = _gpu_soft_topk_rows(ctx, x[None], [float((~masked).sum() if far < 0 else 3)], tau)
+        assert np.abs(y[0] - (x > far if far < 0 else x >= far)).max() <= 1e-300 and np.isfinite(info[0, 0]), tau
+
+
 def test_soft_topk_argument_errors(ctx):
     x = torch.zeros(10, dtype=torch.float64, device="cuda")
     y = torch.empty_like(x)
