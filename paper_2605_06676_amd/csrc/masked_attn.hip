@@ -52,8 +52,7 @@ constexpr int kMaBlockQ = kMaWaves * kMaWaveQ;
 constexpr int kMaTileLds = 2 * kMaTile * kMaRow + kMaTile * 4;   // K rows, V rows, mask weights
 constexpr float kMaLog2e = 1.4426950408889634f;
 constexpr float kMaLn2 = 0.6931471805599453f;
-constexpr float kMaRebase = 64.f;             // log2 distance at which a reference moves, where they do
-constexpr float kMaMostSum = 1.0995116e12f;   // 2^40: largest sum of weights relative to a reference that stays put
+constexpr float kMaMoveSum = 1048576.f;       // 2^20: sum of weights at which a reference moves
 
 __device__ __forceinline__ float ma_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -175,10 +174,25 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
                                                                 acc_o[qb][ct], 0, 0, 0);
     }
   };
+  // The reference of this lane's query of block qb goes up by `up`, what has been summed against it goes down by
+  // alpha = 2^-up (queries 4 r + e in the output registers).
+  auto lower_by = [&](int qb, float up, float alpha) __attribute__((always_inline)) {
+    ref[qb] += up;
+    l_run[qb] *= alpha;
+    float al[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * r + e, 64);
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc_o[qb][ct][e] *= al[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc_l[qb][e] *= al[e];
+  };
   // One pipeline step: the value products of step s - 1, the weights of step s, the logits of step s + 1; nothing in
   // it waits for anything else in it, so matrix and vector instructions of one wave run side by side.
-  // kDiag: some key of the step may lie above some query's diagonal.  kMoving: the references follow the running maxima
-  // (lazily); else they stay at the maxima of the first step and nothing looks at the maxima any more.
+  // kDiag: some key of the step may lie above some query's diagonal.  kMoving: the references follow the running maxima;
+  // else they stay and nothing looks at the maxima.
   auto step = [&](auto diag_tag, auto moving_tag, const unsigned char* tile, int s, int half) __attribute__((always_inline)) {
     constexpr bool kDiag = decltype(diag_tag)::value, kMoving = decltype(moving_tag)::value;
     const unsigned char* k_lds = tile + half * kMaStep * kMaRow;
@@ -194,29 +208,16 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
         if (kMoving) top = fmaxf(top, x);
         sacc[qb][i >> 2][i & 3] = x;
       }
-    if (kMoving && __builtin_expect(__ballot(top > kMaRebase) != 0ull, 0)) {
-      // a logit runs away: move the references of the queries to their running maxima and rescale what has been
-      // summed (queries 4 r + e in the output registers)
+    if (kMoving && __ballot(top > 0.f) != 0ull) {
 #pragma unroll
       for (int qb = 0; qb < kMaQB; ++qb) {
         float up = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) up = fmaxf(up, sacc[qb][i >> 2][i & 3]);
         up = max_over_row_blocks(up);
-        const float alpha = ma_exp2(-up);
-        ref[qb] += up;
-        l_run[qb] *= alpha;
 #pragma unroll
         for (int i = 0; i < 8; ++i) sacc[qb][i >> 2][i & 3] -= up;
-        float al[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * r + e, 64);
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc_o[qb][ct][e] *= al[e];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc_l[qb][e] *= al[e];
+        lower_by(qb, up, ma_exp2(-up));
       }
     }
     f32x4_t next[kMaQB][2];
@@ -253,6 +254,24 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
     for (int qb = 0; qb < kMaQB; ++qb)
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) sacc[qb][sub] = next[qb][sub];
+  };
+  // References that stay put save the maximum, the branch on it and the rescaling it guards, 8 % of the time.  Any
+  // reference gives the same weights to a rounding as long as no sum overflows (logits far below a reference vanish next
+  // to the key that set it, as below a maximum), so a wave looks at its sums every 128 keys, and where one has passed
+  // 2^20 moves the references up by whole binary orders.  Where a logit ran away so far from one look to the next that
+  // something overflowed all the same, it stays infinite or NaN to the end, and the block starts over with references that
+  // follow the running maxima.  (Starting over wherever a sum passes 2^40, with no look in between, cost 1.3 to 1.9
+  // times the time on logits of a deviation of 8 and 16.)
+  auto move_references = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int qb = 0; qb < kMaQB; ++qb) {
+      const float sum = max_over_row_blocks(l_run[qb]);
+      const int up = min(max((__float_as_int(sum) >> 23) - 127, 0), 120);
+      const float alpha = __int_as_float((127 - up) << 23);
+      lower_by(qb, (float)up, alpha);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pfrag[qb][i] = (__bf16)((float)pfrag[qb][i] * alpha);   // not yet multiplied
+    }
   };
   auto start = [&]() __attribute__((always_inline)) {
     // S^T of the first step, its K rows straight from memory: lane (rb = r, query c) gets keys 16 sub + 4 r + e
@@ -306,6 +325,7 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   for (int t = 0; t < n_full; t += 2) {
     lds_fill_barrier();
     stage(tile_b, t + 1);
+    if (__builtin_expect(__ballot(!(fmaxf(l_run[0], l_run[1]) < kMaMoveSum)) != 0ull, 0)) move_references();
     step(std::false_type{}, std::false_type{}, tile_a, 2 * t, 0);
     step(std::false_type{}, std::false_type{}, tile_a, 2 * t + 1, 1);
     lds_fill_barrier();
@@ -319,14 +339,16 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   lds_fill_barrier();
   last_tile(std::false_type{}, tile_b, n_full + 1);
 
-  // References that stay put save the maximum, the branch on it and the rescaling it guards, 8 % of the time.  They hold
-  // as long as the sums stay far from overflow: a sum above 2^40 says that some logit exceeded its reference by more
-  // than 24 binary orders, and the block starts over with moving ones.  (Any reference up to there gives the same
-  // weights to a rounding; logits far below a reference vanish next to the key that set it, as below a maximum.)
-  bool over = false;
+  float finite = 0.f;   // NaN where anything is not
 #pragma unroll
-  for (int qb = 0; qb < kMaQB; ++qb) over |= !(l_run[qb] < kMaMostSum);
-  if (__builtin_expect(__syncthreads_or(over), 0)) {
+  for (int qb = 0; qb < kMaQB; ++qb) {
+    finite = fmaf(l_run[qb], 0.f, finite);
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) finite = fmaf(acc_o[qb][ct][e], 0.f, finite);
+  }
+  if (__builtin_expect(__syncthreads_or(finite != 0.f), 0)) {
     stage(tile_a, 0);
     start();
 #pragma unroll 1

@@ -66,9 +66,9 @@ def test_forward_mask_edge_cases(ctx):
 @pytest.mark.parametrize("T", [97, 128, 300, 641])
 @pytest.mark.parametrize("factor", [6.0, 12.0, 40.0])
 def test_forward_logits_that_run_away_from_the_first_keys(ctx, T, factor):
-    # The references of the exponentials are set by the first 32 keys.  Keys further on scaled up leave them behind: by
-    # some 30 binary orders (the block starts over with moving references), 60 and 200 (beyond what fp32 sums hold, and
-    # past the distance at which a moving reference is rebased).  One head also has its largest logits at keys of weight 0.
+    # The references of the exponentials are set by the first 32 keys.  Keys further on scaled up leave them behind: the
+    # sums against them reach up to 2^34 with factor 6, more than 2^56 with 12 and more than fp32 holds with 40.  One head
+    # also has its largest logits at keys of weight 0.
     q, k, v, m, _ = W.draw_training_attention(4, 2, T, seed=5)
     kf = O.bf16_bits_to_f64(k)
     kf[:, 40:] *= factor
@@ -78,6 +78,47 @@ def test_forward_logits_that_run_away_from_the_first_keys(ctx, T, factor):
     o_ref, lse_ref = MA.forward(*(O.bf16_bits_to_f64(x) for x in (q, k, v)), m, SCALE)
     assert_decode_close(o_gpu.reshape(-1, 128), lse_gpu.reshape(-1), o_ref.reshape(-1, 128), lse_ref.reshape(-1),
                         f"T{T} factor {factor}")
+
+
+def _log2_sum_against_first_keys(q, k, m):
+    """Largest log2 over all queries of sum_j 2^(x_ij - ref_i) m_j, ref_i the largest x_ij among the first 32 keys."""
+    G, most = q.shape[0] // k.shape[0], -np.inf
+    for hq in range(q.shape[0]):
+        x = q[hq] @ k[hq // G].T * SCALE * np.log2(np.e)
+        x[np.triu_indices_from(x, 1)] = -np.inf
+        y = x + np.log2(np.maximum(m[hq // G].astype(np.float64), 1e-300))[None, :] - x[:, :32].max(axis=1, keepdims=True)
+        top = y.max(axis=1)
+        most = max(most, (top + np.log2(np.exp2(y - top[:, None]).sum(axis=1))).max())
+    return most
+
+
+@pytest.mark.parametrize("T", [300, 641])
+@pytest.mark.parametrize("reach,v_scale", [(15, 1.0), (25, 1.0), (118, 1.0), (135, 1.0), (300, 1.0), (40, 2.0 ** 100)])
+def test_forward_either_side_of_the_limits_of_the_sums(ctx, T, reach, v_scale):
+    # A wave that finds a lane's sum (a quarter of a query's, 2^2 less at most) above 2^20 moves the references of its
+    # queries; where a sum, or its product with the value rows, leaves fp32's range (2^128), the block starts over with
+    # references that follow the maxima.  Keys from 40 on are scaled so that the largest sum comes out at 2^reach, within
+    # three binary orders of what bf16 keys can be set to.
+    q, k, v, m, _ = W.draw_training_attention(2, 1, T, seed=6)
+    qf, kf = O.bf16_bits_to_f64(q), O.bf16_bits_to_f64(k)
+
+    def scaled(factor):
+        x = kf.copy()
+        x[:, 40:] *= factor
+        return W.f32_to_bf16_bits(x.astype(np.float32))
+
+    lo, hi = 1.0, 200.0
+    for _ in range(20):
+        mid = np.sqrt(lo * hi)
+        if _log2_sum_against_first_keys(qf, O.bf16_bits_to_f64(scaled(mid)), m) < reach: lo = mid
+        else: hi = mid
+    k = scaled(lo)
+    assert abs(_log2_sum_against_first_keys(qf, O.bf16_bits_to_f64(k), m) - reach) < 3
+    v = W.f32_to_bf16_bits((O.bf16_bits_to_f64(v) * v_scale).astype(np.float32))
+    o_gpu, lse_gpu = run_forward(ctx, q, k, v, m)
+    o_ref, lse_ref = MA.forward(qf, O.bf16_bits_to_f64(k), O.bf16_bits_to_f64(v), m, SCALE)
+    assert_decode_close(o_gpu.reshape(-1, 128), lse_gpu.reshape(-1), o_ref.reshape(-1, 128), lse_ref.reshape(-1),
+                        f"T{T} reach {reach} v {v_scale:g}")
 
 
 def test_forward_rejects_bad_arguments(ctx):
