@@ -80,6 +80,20 @@ def test_forward_logits_that_run_away_from_the_first_keys(ctx, T, factor):
                         f"T{T} factor {factor}")
 
 
+@pytest.mark.parametrize("Hq,H,T", [(4, 2, 1), (4, 2, 31), (2, 1, 128), (4, 1, 129), (4, 2, 700)])
+def test_forward_first_queries_keep_more_digits_of_the_weights(ctx, Hq, H, T):
+    # The first 128 queries multiply the weights in two bf16 parts (relative error 2^-18 each), the others in one (2^-9).
+    # An output is a weighted mean of value rows, so its error stays below the weights' times the largest value, and what
+    # fp32 logits of up to 2^5 and exponentials add is 2^-19 of it each; twice to four times that are allowed.
+    q, k, v, m, _ = W.draw_training_attention(Hq, H, T, seed=8)
+    o_gpu, _ = run_forward(ctx, q, k, v, m)
+    qf, kf, vf = (O.bf16_bits_to_f64(x) for x in (q, k, v))
+    o_ref, _ = MA.forward(qf, kf, vf, m, SCALE)
+    err = np.abs(o_gpu - o_ref).max(axis=(0, 2)) / np.abs(vf).max()
+    assert err[:128].max() <= 2.0 ** -16, err[:128].max()
+    assert T <= 128 or err[128:].max() <= 2.0 ** -8, err[128:].max()
+
+
 def _log2_sum_against_first_keys(q, k, m):
     """Largest log2 over all queries of sum_j 2^(x_ij - ref_i) m_j, ref_i the largest x_ij among the first 32 keys."""
     G, most = q.shape[0] // k.shape[0], -np.inf
