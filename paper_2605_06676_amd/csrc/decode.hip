@@ -22,9 +22,9 @@
 // a chunk that crosses a segment boundary goes through it once per piece.  There the chunks start at the segments
 // instead: every wave loads the bounds of all segments at once, one per lane, and a prefix sum over the chunks of each
 // tells its block which segment and which rows are its own.  The grid is the most chunks that any split of the rows
-// over the segments can give.  (8 heads, 5 thousand rows, in a captured graph: 11.4 us with flat chunks, 8.6 us with
-// these; 40 thousand rows 18.1 and 13.6 us, 160 thousand 29.6 and 25.7 us; one head with nearly all of 5 thousand rows
-// 17.8 and 10.5 us.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
+// over the segments can give.  (8 heads, 5 thousand rows, in a captured graph: 11.4 us with flat chunks, 8.7 us with
+// these; 40 thousand rows 18.1 and 13.4 us, 160 thousand 29.6 and 25.8 us; one head with nearly all of 5 thousand rows
+// 17.8 and 10.6 us.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
 // one round of resident blocks however the rows are spread; with 256 segments of 5 thousand rows each the ends of the
 // segments would need a second round.
 //
@@ -46,6 +46,11 @@
 // gfx950 (row stride 288 B); both strides make the reads bank-conflict free.
 // The next 32 rows are prefetched into registers while the current 32 are
 // multiplied.  Softmax runs in fp32 in the log2 domain.
+//
+// P is rounded to bf16, exactly 1 at the largest logit a wave has met.  Chunks that start at the segments make fewer
+// pieces, hence fewer such exact weights, and the error of the output against 64 bits rose by 1 to 2 % with them; there
+// the matrix cores are idle next to the memory latencies, and what the rounding left is multiplied too: 1.17e-3 -> 1.8e-6
+// (8 heads, 5 thousand rows) for 0.1 to 0.3 us.  With flat chunks the error is 1.2e-3.
 #include <type_traits>
 
 #include "lkv_common.h"
@@ -270,9 +275,12 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
       for (int i = 0; i < 8; ++i) { sv[i] = fast_exp2(sv[i] - ref); psum += sv[i]; }
       l_run = l_run * alpha + psum;
       // A operand of the second product: P[head c][K-slots 8 r .. 8 r + 7] = this lane's own 8 values
-      bf16x8_t pfrag;
+      bf16x8_t pfrag, plow;   // rounded, and (chunks that start at the segments) what the rounding left
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pfrag[i] = (__bf16)sv[i];
+      for (int i = 0; i < 8; ++i) {
+        pfrag[i] = (__bf16)sv[i];
+        if (kAligned) plow[i] = (__bf16)(sv[i] - (float)pfrag[i]);
+      }
       // rescale the output rows (heads 4r+e) when any running max moved
       if (__ballot(alpha != 1.f) != 0ull) {
         float al[4];
@@ -284,13 +292,19 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
           for (int e = 0; e < 4; ++e) acc_o[ct][e] *= al[e];
       }
       // O += P V: B operand lane (channel c of tile ct, K-block r) holds V[tokens 4r..4r+3 and 16+4r..16+4r+3][ch]
+      s16x8_t vb[8];
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) {
         const unsigned char* base = v_lds + (4 * r + (c >> 2)) * kDecVStride + ct * 32 + (c & 3) * 8;
         const s16x4_t v0 = lds_read_tr16(base);
         const s16x4_t v1 = lds_read_tr16(base + 16 * kDecVStride);
-        const s16x8_t vb = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc_o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag, __builtin_bit_cast(bf16x8_t, vb), acc_o[ct], 0, 0, 0);
+        vb[ct] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+        acc_o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag, __builtin_bit_cast(bf16x8_t, vb[ct]), acc_o[ct], 0, 0, 0);
+      }
+      if (kAligned) {
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct)
+          acc_o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plow, __builtin_bit_cast(bf16x8_t, vb[ct]), acc_o[ct], 0, 0, 0);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();

@@ -161,6 +161,28 @@ def test_decode_chunks_that_start_at_the_segments_and_flat_ones(ctx, L, H, Hq, T
     _run_and_check(ctx, w, [T], seed=3, budgets=budgets, what=f"decode chunks {L}x{H}")
 
 
+@pytest.mark.parametrize("lengths,G_", [([1, 33, 64, 65, 700, 0, 2000, 5], 4), ([300] * 64, 1), ([9000], 16)])
+def test_decode_over_few_segments_keeps_more_digits_of_the_probabilities(ctx, lengths, G_):
+    """Up to 64 segments the probabilities are multiplied in two bf16 parts, relative error 2^-18 each.  An output is a
+    weighted mean of value rows, so its error stays below the probabilities' times the largest value; fp32 logits of up
+    to 2^4 and exponentials add about 2^-19.  Four times that is allowed (one part alone: 2^-9)."""
+    n, total = len(lengths), sum(lengths)
+    g = torch.Generator(device="cuda").manual_seed(total)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, k, v = normal(1, 1, n * G_, 128), normal(total, 128), normal(total, 128)
+    offsets = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+    assert lkv.lkv_plan_offsets(ctx, np.array(lengths, dtype=np.int32), offsets) == total
+    out = torch.empty(1, 1, n * G_, 128, device="cuda")
+    ws = torch.empty(lkv.lkv_decode_workspace_bytes(n, total, n * G_, n), dtype=torch.uint8, device="cuda")
+    lkv.lkv_decode_attn(ctx, 1, 1, n, n * G_, 128, q, k, v, offsets, total, 128 ** -0.5, out, None, ws)
+    qd, kd, vd, at = q.cpu().double().view(n, G_, 128), k.cpu().double(), v.cpu().double(), 0
+    for s, m in enumerate(lengths):
+        p = torch.softmax(qd[s] @ kd[at:at + m].T * 128 ** -0.5, dim=1)
+        err = (out[0, 0, s * G_:(s + 1) * G_].cpu().double() - p @ vd[at:at + m]).abs().max()
+        assert err <= 2.0 ** -16 * vd.abs().max(), (s, m, float(err))
+        at += m
+
+
 def test_group_size_limit(ctx):
     w = W.scaled(W.CONFIGS[0], L=1, H=1, Hq=17, T=64, b_min=4)
     K, V, Q, sc, B = _inputs(w, [64])
