@@ -419,8 +419,13 @@ lkv_status lkv_masked_attn_forward(lkv_ctx *ctx, int32_t n_q_heads, int32_t n_kv
  * dq  : DEVICE fp32 [n_q_heads, seq_len, d];  dk, dv : DEVICE fp32 [n_kv_heads, seq_len, d]
  * dm  : DEVICE fp32 [n_kv_heads, seq_len]
  * workspace : DEVICE, at least lkv_masked_attn_backward_workspace_bytes(n_q_heads, n_kv_heads, seq_len)
- *             bytes, 16-byte aligned (holds D and, where the query heads of a group are dealt to several
- *             blocks, their partial sums of dk, dv and dm, which a last pass adds up in a fixed order).
+ *             bytes, 16-byte aligned (holds D, 4 bytes per query row, and, where the query heads of a group are
+ *             dealt to several blocks, their partial sums of dk, dv and dm, 1032 bytes per key and part, which a
+ *             last pass adds up in a fixed order).  No group has more parts than query heads, so it is never much
+ *             more than twice the size of dq: 474 MB for 28 query heads over 4 KV heads and 16384 tokens, 136 MB
+ *             for 32 over 8 and 8192.  From n_kv_heads * ceil(seq_len / 128) = 512 on, a workspace that holds D
+ *             alone is accepted as well; the heads of a group then stay together (up to a sixth slower, and the
+ *             sums are rounded in another order).
  * Every output element is written exactly once (no atomics: results are reproducible bit for bit).
  * Outputs and workspace must not overlap the inputs or each other.
  * Errors as for the forward call, plus LKV_ERR_WORKSPACE. */

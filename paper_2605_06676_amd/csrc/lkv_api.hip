@@ -939,10 +939,10 @@ lkv_status lkv_masked_attn_backward(lkv_ctx* ctx, int32_t n_q_heads, int32_t n_k
     return fail(ctx, LKV_ERR_INVALID_ARG, "an input or output pointer is NULL");
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(d_o))
     return fail(ctx, LKV_ERR_INVALID_ARG, "q, k, v, o or d_o is not 16-byte aligned");
-  const size_t need = lkv::masked_attn_bwd_workspace_bytes(n_q_heads, n_kv_heads, seq_len);
+  const size_t need = lkv::masked_attn_bwd_least_workspace_bytes(n_q_heads, n_kv_heads, seq_len);
   if (lkv_status st = check_workspace(ctx, workspace, workspace_bytes, need, 16, "masked attention backward")) return st;
   lkv::launch_masked_attn_bwd(q, k, v, m, o, lse, d_o, n_q_heads, n_kv_heads, seq_len, scale, dq, dk, dv, dm,
-                              static_cast<float*>(workspace), as_stream(stream));
+                              static_cast<float*>(workspace), workspace_bytes, as_stream(stream));
   if (hipError_t e = hipGetLastError()) return hip_fail(ctx, e, "lkv_masked_attn_backward launch");
   return LKV_OK;
 }

@@ -755,40 +755,56 @@ hipError_t masked_attn_bwd_prepare() {
 // kernel where one block per query head gives it kMbFewBlocks blocks, and then the smallest divisor of G that does so;
 // each more costs the partial sums' way through memory.  The narrow one below that, one block per query head when a
 // group's would be fewer.  Wide against narrow, whole backward pass: 2345 tokens, 8 x 4 heads (320 wide blocks) 253
-// against 234 us; 12000, 8 x 1 (376) 1158 : 1150; 4096, 8 x 4 (512) 532 : 567; 5000, 4 x 7 (560) 703 : 743.
+// against 234 us; 12000, 8 x 1 (376) 1158 : 1150; 4096, 8 x 4 (512) 532 : 567; 5000, 4 x 7 (560) 703 : 743.  Split and
+// wide against the narrow kernel's whole groups: 8192, 8 x 4 (135 MB of partial sums) 1867 : 1976; 16384, 4 x 7 (470
+// MB) 6542 : 7111; 20000, 4 x 7 (580 MB) 9616 : 11371; 5000, 16 x 2 (164 MB) 810 : 814.  Parts of unlike size, two of 4
+// and 3 heads in place of seven, would take 136 MB and 7077 us at 16384, 4 x 7.
 struct DkvPlan {
   bool wide;
   int split;
 };
+// without the wide kernel's split: what a caller gets whose workspace does not hold the partial sums
+static DkvPlan dkv_narrow_plan(int n_kv_heads, int G, int T) {
+  const int64_t narrow = (int64_t)((T + kNarrowBlockK - 1) / kNarrowBlockK) * n_kv_heads;
+  return {false, narrow < kMbFewBlocks ? G : 1};
+}
 static DkvPlan dkv_plan(int n_kv_heads, int G, int T) {
   const int64_t wide = (int64_t)((T + kDkvBlockK - 1) / kDkvBlockK) * n_kv_heads;
   for (int s = 1; s <= G; ++s)
     if (G % s == 0 && wide * s >= kMbFewBlocks) return {true, s};
-  const int64_t narrow = (int64_t)((T + kNarrowBlockK - 1) / kNarrowBlockK) * n_kv_heads;
-  return {false, narrow < kMbFewBlocks ? G : 1};
+  return dkv_narrow_plan(n_kv_heads, G, T);
 }
 
 static size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // workspace: D (one float per query row), then, when the dK/dV kernel is split, the partial dK, dV
 // [n_kv_heads * split, T, 128] and dm [n_kv_heads * split, T]
-size_t masked_attn_bwd_workspace_bytes(int n_q_heads, int n_kv_heads, int T) {
+static size_t plan_bytes(int n_q_heads, int n_kv_heads, int T, const DkvPlan& plan) {
   size_t bytes = align256((size_t)n_q_heads * (size_t)T * sizeof(float));
-  if (n_kv_heads >= 1 && n_q_heads % n_kv_heads == 0) {
-    const size_t units = (size_t)n_kv_heads * dkv_plan(n_kv_heads, n_q_heads / n_kv_heads, T).split;
-    if (units > (size_t)n_kv_heads) bytes += 2 * align256(units * T * kHeadDim * sizeof(float)) + align256(units * T * sizeof(float));
-  }
+  const size_t units = (size_t)n_kv_heads * plan.split;
+  if (plan.split > 1) bytes += 2 * align256(units * T * kHeadDim * sizeof(float)) + align256(units * T * sizeof(float));
   return bytes;
+}
+size_t masked_attn_bwd_workspace_bytes(int n_q_heads, int n_kv_heads, int T) {
+  if (n_kv_heads < 1 || n_q_heads % n_kv_heads != 0) return align256((size_t)n_q_heads * (size_t)T * sizeof(float));
+  return plan_bytes(n_q_heads, n_kv_heads, T, dkv_plan(n_kv_heads, n_q_heads / n_kv_heads, T));
+}
+size_t masked_attn_bwd_least_workspace_bytes(int n_q_heads, int n_kv_heads, int T) {
+  const size_t narrow = plan_bytes(n_q_heads, n_kv_heads, T, dkv_narrow_plan(n_kv_heads, n_q_heads / n_kv_heads, T));
+  const size_t bytes = masked_attn_bwd_workspace_bytes(n_q_heads, n_kv_heads, T);
+  return narrow < bytes ? narrow : bytes;
 }
 
 void launch_masked_attn_bwd(const void* q, const void* k, const void* v, const float* m, const float* o,
                             const float* lse, const void* d_o, int n_q_heads, int n_kv_heads, int T, float scale,
-                            float* dq, float* dk, float* dv, float* dm, float* workspace, hipStream_t stream) {
+                            float* dq, float* dk, float* dv, float* dm, float* workspace, size_t workspace_bytes,
+                            hipStream_t stream) {
   const int G = n_q_heads / n_kv_heads;
   const int64_t n_rows = (int64_t)n_q_heads * T;
   hipLaunchKernelGGL(masked_attn_bwd_prep_kernel, dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, stream,
                      reinterpret_cast<const float4*>(o), static_cast<const uint4*>(d_o), n_rows, workspace);
-  const DkvPlan plan = dkv_plan(n_kv_heads, G, T);
+  DkvPlan plan = dkv_plan(n_kv_heads, G, T);
+  if (workspace_bytes < plan_bytes(n_q_heads, n_kv_heads, T, plan)) plan = dkv_narrow_plan(n_kv_heads, G, T);
   const int split = plan.split;
   const int n_units = n_kv_heads * split;
   unsigned char* ws = reinterpret_cast<unsigned char*>(workspace);

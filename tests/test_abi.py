@@ -2,6 +2,8 @@
 import os
 import re
 
+import numpy as np
+
 from paper_2605_06676_amd import lkv
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -19,6 +21,17 @@ def test_every_declared_symbol_is_exported():
     assert set(names) == set(lkv.EXPORTS)
     for n in names:
         assert getattr(lib, n) is not None
+
+
+def test_backward_workspace_is_bounded_by_the_gradient_of_q():
+    # no more parts than query heads: D (4 bytes per query row) and 1032 bytes per key and part, against 512 per row of dq
+    rng = np.random.default_rng(0)
+    for H, G, T in [(4, 7, 16384), (8, 4, 8192), (1, 1, 1)] + [
+            (int(rng.integers(1, 33)), int(rng.integers(1, 17)), int(rng.integers(1, 40000))) for _ in range(300)]:
+        n = lkv.lkv_masked_attn_backward_workspace_bytes(H * G, H, T)
+        assert n % 256 == 0 and H * G * T * 4 <= n <= H * G * T * (4 + 1032) + 1024, (H, G, T)
+    assert lkv.lkv_masked_attn_backward_workspace_bytes(28, 4, 16384) <= 476e6          # the sizes the header names
+    assert lkv.lkv_masked_attn_backward_workspace_bytes(32, 8, 8192) <= 137e6
 
 
 def test_calls_that_need_no_gpu():

@@ -332,6 +332,38 @@ def test_backward_of_many_heads(ctx, Hq, H, T):
         assert_rows_close(dm[h:h + 1], rm, tag + " dm")
 
 
+@pytest.mark.parametrize("Hq,H,T", [(128, 64, 1030), (96, 32, 2050)])
+def test_backward_with_a_workspace_for_whole_groups(ctx, Hq, H, T):
+    # enough narrow blocks without a split: D alone is a workspace, anything between it and the full size is used as D
+    # alone, and less is refused
+    q, k, v, m, d_o = W.draw_training_attention(Hq, H, T, seed=4)
+    tq, tk, tv, tg = (bits_to_bf16_gpu(x) for x in (q, k, v, d_o))
+    tm = torch.from_numpy(m).cuda()
+    f = dict(dtype=torch.float32, device="cuda")
+    o, lse = torch.empty(tq.shape, **f), torch.empty(tq.shape[:2], **f)
+    lkv.lkv_masked_attn_forward(ctx, tq, tk, tv, tm, SCALE, o, lse)
+    full = lkv.lkv_masked_attn_backward_workspace_bytes(Hq, H, T)
+    d_only = (Hq * T * 4 + 255) // 256 * 256
+    assert H * ((T + 127) // 128) >= 512 and full > d_only
+
+    def backward(n_bytes):
+        ws = torch.zeros(n_bytes + 4096, dtype=torch.uint8, device="cuda")
+        grads = [torch.full(s, float("nan"), **f) for s in (tq.shape, tk.shape, tk.shape, tm.shape)]
+        lkv.lkv_masked_attn_backward(ctx, tq, tk, tv, tm, o, lse, tg, SCALE, *grads, ws[:n_bytes])
+        torch.cuda.synchronize()
+        assert not ws[n_bytes:].any()                     # nothing behind the bytes it was given
+        return [x.cpu().numpy() for x in grads]
+
+    split, whole, between = backward(full), backward(d_only), backward(full - 256)
+    for a, b in zip(whole, between):
+        assert np.array_equal(a, b)
+    for a, b, what in zip(split, whole, ("dq", "dk", "dv", "dm")):
+        assert_rows_close(a, b, what)
+    with pytest.raises(lkv.LkvError) as e:
+        backward(d_only - 16)
+    assert e.value.status == 3
+
+
 def test_random_shapes(ctx):
     # seeded draws of head counts and lengths, forward and backward, every element against the oracle
     rng = np.random.default_rng(7)
