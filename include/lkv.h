@@ -199,8 +199,8 @@ lkv_status lkv_select(lkv_ctx *ctx, const lkv_cache *cache, const float *const *
 size_t lkv_counts_bytes(int64_t n_segments);
 /* The same plus room for two bitmaps of max_seq_len bits per segment behind the counters (no need to clear them).
  * Given a buffer of this size, lkv_evict_layer splits the top-k pass over the scores of every head over several
- * workgroups when a call covers few heads that are too long for the on-chip key cache (one layer of a
- * 65536-token or longer prompt: 8 heads would otherwise keep 8 compute units busy). */
+ * workgroups when a call covers few heads and all of them are too long for the top-k to hold on chip (more than 34816
+ * tokens, one layer at a time: 8 heads would otherwise keep 8 compute units busy). */
 size_t lkv_counts_bytes_split(int64_t n_segments, int32_t max_seq_len);
 lkv_status lkv_clear_counts(lkv_ctx *ctx, uint32_t *counts, int64_t n_segments, void *stream);
 lkv_status lkv_score_counted(lkv_ctx *ctx, const lkv_cache *cache, const lkv_scorer *scorer,

@@ -134,8 +134,6 @@ lkv_status check_attention_geometry(lkv_ctx* ctx, int32_t n_q_heads, int32_t n_k
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-// lkv_score, optionally counting the first-level top-k digits of every segment on the way (counts zero on entry).
-// The segment of (sequence s, view head j) is seg_base + s * seg_stride + j.
 // Rows per block of an MLP scoring launch over one sequence and few heads (one layer at a time).  Every wave starts by
 // loading the hidden layer's weights, so the launch takes as many blocks as the chip holds at once and not a second,
 // shorter round: 512 blocks of four waves (hidden widths up to 64), 1024 of two.  8 heads, hidden width 64: 131072
@@ -152,6 +150,8 @@ int score_mlp_rows_alone(int T, int heads, int hidden) {
   return even >= 256 && even <= (hidden > 64 ? 2048 : 4096) ? (int)even : rows;
 }
 
+// lkv_score, optionally counting the first-level top-k digits of every segment on the way (counts zero on entry).
+// The segment of (sequence s, view head j) is seg_base + s * seg_stride + j.
 lkv_status score_impl(lkv_ctx* ctx, const lkv_cache* cache, const lkv_scorer* scorer, float* const* scores,
                       uint32_t* counts, int seg_base, int seg_stride, void* stream) {
   if (ctx == nullptr) return LKV_ERR_INVALID_ARG;

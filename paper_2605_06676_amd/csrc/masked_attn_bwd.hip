@@ -301,10 +301,10 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
   __shared__ __align__(1024) unsigned char v_rows[kDkvBlockK * kDkvRow];   // the block's V rows, read as operands in every step
   __shared__ __align__(16) float aux_a[2 * kMbTile];   // lse (log2 domain) and D of the item's queries
   __shared__ __align__(16) float aux_b[2 * kMbTile];
-  // A block owns 128 keys of one KV head and the query heads g_lo .. g_lo + g_cnt - 1 of its group: all of them
-  // (split = 1, results go straight to dk, dv, dm) or one each (split = G: results are per-query-head partial sums,
-  // row `unit` of buffers the host passes in place of the outputs, added up by the reduce kernel).  Blocks in order
-  // of decreasing work: early keys have the most queries after them; key tile slow, unit fast.
+  // A block owns 256 keys of one KV head and the query heads g_lo .. g_lo + g_cnt - 1 of its group: all of them
+  // (split = 1, results go straight to dk, dv, dm) or an equal share (split divides G: results are partial sums, row
+  // `unit` of buffers the host passes in place of the outputs, added up by the reduce kernel).  Blocks in order of
+  // decreasing work: early keys have the most queries after them; key tile slow, unit fast.
   const int n_units = n_kv_heads * split;
   const int unit = (int)blockIdx.x % n_units;
   const int h = unit / split;

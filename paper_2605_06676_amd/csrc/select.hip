@@ -234,7 +234,7 @@ __device__ __forceinline__ uint32_t descend_counted_level(SelShared& sh, uint32_
   return enter_found_bin(sh, 0, prefix, prefix_mask, need);
 }
 
-// Ordered emission from a per-token key source `key_of(i)` (LDS key cache, or global scores).
+// Ordered emission from a per-token key source `key_of(i)`: heads too long for the bitmaps, which re-read their scores.
 template <typename KeyOf>
 __device__ __forceinline__ void emit_from_keys(SelShared& sh, int T, uint32_t thr, uint32_t need,
                                                int32_t* __restrict__ out, KeyOf key_of) {
@@ -894,7 +894,7 @@ void launch_select(const SeqTable& tab, const int32_t* host_offsets, int n_total
     for (int i = 0; i <= n_total_segments; ++i) inl.v[i] = host_offsets[i];
   const dim3 grid(segs), block(kSelThreads);
   // Few long heads (a layer at a time): split the pass over the scores of every head over several workgroups first.
-  // Needs the first-level counts, room for the two bitmaps, heads too long for the key cache and offsets on the device.
+  // Needs the first-level counts, room for the two bitmaps, heads too long for the registers and offsets on the device.
   bool split_heads = counts != nullptr && pre_maps != nullptr && host_offsets == nullptr && ragged_scores == nullptr &&
                      held_limit == 0 && bitmap_limit > 0 && segs <= kSelSplitMaxHeads;
   for (int i = 0; i < tab.n && split_heads; ++i)

@@ -203,7 +203,7 @@ def _layerwise_equals_whole(ctx, w, Ts, seed, split, Ks=None, Vs=None, sc=None, 
 
 @pytest.mark.parametrize("scorer,hidden,T", [("mlp", 64, 40000), ("linear", 0, 70001), ("mlp", 128, 34305), ("mlp", 32, 131072)])
 def test_long_heads_split_over_several_workgroups(ctx, scorer, hidden, T):
-    # one layer at a time over heads too long for the on-chip key cache, with room for the bitmaps behind the
+    # one layer at a time over heads too long for the top-k's registers, with room for the bitmaps behind the
     # counters: every head's pass over the scores is split over several workgroups; the result must not change
     L, H = (1, 2) if T > 100000 else (3, 2)
     w = W.scaled(W.CONFIGS[0], L=L, H=H, Hq=2 * H, scorer=scorer, hidden=hidden, act="gelu", per_head=hidden == 128, b_min=16, R=0.1)

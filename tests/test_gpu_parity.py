@@ -209,7 +209,7 @@ def test_all_scores_equal_keeps_the_first_tokens(ctx):
 @pytest.mark.parametrize("T", [12, 63, 4000, 4001, 16383, 16384, 32768, 34304, 34305, 40000, 40003, 131072, 327680, 327681])
 def test_select_on_crafted_scores(ctx, T):
     # NaN, infinities, signed zeros, duplicates, values one ulp apart; head lengths on both sides of
-    # every storage mode of the kernel (LDS key cache, LDS bitmaps, streaming) and off the 16-byte grid
+    # every storage mode of the kernels (registers, LDS bitmaps, streaming) and off the 16-byte grid
     rng = np.random.default_rng(T)
     H = 4
     k = torch.empty((1, H, T, 128), dtype=torch.bfloat16, device="cuda")   # contents unused by lkv_select
@@ -288,7 +288,7 @@ def test_select_on_distributions_the_bins_do_not_spread(ctx, lengths, budget_sha
 
 @pytest.mark.parametrize("n_top", [16383, 16384, 16385, 30000])
 def test_select_long_head_candidate_list_limit(ctx, n_top):
-    # a head too long for the key cache: after the first radix level the undecided bin holds n_top keys;
+    # a head too long for the registers: after the first radix level the undecided bin holds n_top keys;
     # up to 16384 of them are listed in LDS, more fall back to re-reading the scores
     rng = np.random.default_rng(n_top)
     T, H = 50000, 2
