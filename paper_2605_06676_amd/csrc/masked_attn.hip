@@ -21,14 +21,15 @@
 // The denominator that divides the output is one more output column of the second product (P times a column of
 // ones), see acc_l below.
 //
-// What bounds it: energy, then instruction issue.  At 16k tokens the chip holds 1.9 to 2.0 of its 2.4 GHz under this
-// kernel, and a variant that spends fewer cycles runs at a lower clock, so what pays is work not done: references
-// that stay put (no maximum, no rescaling: 8 %), rows that go from memory to LDS without passing registers (which
-// also frees the 32 registers that the pipeline needs), sums kept from being postponed into the next step (6 %).  The
-// steps are pipelined inside a wave (value products of step s - 1, weights of step s, logits of step s + 1 in one
-// scheduling region), which took the share of matrix time that vector work runs beside from 22 to 38 %.  32 query
-// heads, 8 KV heads: 2.44 -> 1.98 ms at 16384 tokens (1110 TFLOP/s; a library product of 8192 x 8192 x 8192 reaches
-// 1310 here), 649 -> 530 us at 8192, 182 -> 149 at 4096, 74 -> 61 at 2345.  Measured and dropped: 64 queries per wave
+// What bounds it: instruction issue, at the clock that the power allows.  At 16384 tokens the matrix pipe is busy for 56 %
+// of the cycles and the vector pipe for 58 %, 20 % of them together: 94 % in all, no LDS conflicts (counters), while the
+// chip holds 1.8 to 1.9 of its 2.4 GHz.  So what pays is work not done: references that stay put (no maximum, no
+// rescaling: 8 %), rows that go from memory to LDS without passing registers (which also frees the 32 registers that the
+// pipeline needs), sums kept from being postponed into the next step (6 %).  The steps are pipelined inside a wave (value
+// products of step s - 1, weights of step s, logits of step s + 1 in one scheduling region): vector work runs beside 36 %
+// of the matrix time, 17 % in the dq kernel, which has no such pipeline.  32 query heads, 8 KV heads, in turn with the
+// kernel of running maxima and staging through registers: 2.40 -> 2.02 ms at 16384 tokens (1090 TFLOP/s; a library product
+// of 8192 x 8192 x 8192 reaches 1310 here), 649 -> 530 us at 8192, 182 -> 147 at 4096, 74 -> 62 at 2345.  Measured and dropped: 64 queries per wave
 // at one wave per SIMD (half the LDS reads; 2.38 ms), a block of eight waves in two groups that split the keys (2.41
 // ms; 86 us at 2345 tokens), different wave priorities on a SIMD (no change).
 #include <type_traits>

@@ -284,9 +284,10 @@ constexpr int kDkvBlockK = kDkvThreads / 64 * kDkvWaveK;
 constexpr int kDkvRow = 256;                   // LDS bytes per staged row: rows lie as in memory, their 16-byte pieces permuted
 constexpr int kDkvTileLds = 2 * kMbTile * kDkvRow;   // Q rows, dO rows of one item
 
-// Bound by LDS reads and instruction issue: per 32 queries a wave reads 40 KB of operands for 64 matrix instructions
-// (1.25 times what the LDS delivers meanwhile to the four SIMDs; 64 KB with 16 keys per wave, where it was 78 % busy).  32 keys per
-// wave need 128 accumulator and 32 K operand registers; V operands come from LDS so that the rest fits 256.  32 query
+// Bound by instruction issue and by waiting for it: at 16384 tokens the matrix pipe is busy for 45 % of the cycles and
+// the vector pipe for 40 %, 7 % of them together, so a fifth of the cycles issue to neither; the LDS is busy 43 % (78 %
+// with 16 keys per wave and 64 KB of operands per 32 queries; a wave reads 40 KB here for 64 matrix instructions).  32
+// keys per wave need 128 accumulator and 32 K operand registers; V operands come from LDS so that the rest fits 256.  32 query
 // heads, 8 KV heads: 4.65 -> 4.33 ms at 16384 tokens; the whole backward pass 7.74 -> 7.30 ms, 1971 -> 1868 us at 8192,
 // 562 -> 524 us at 4096.  Measured and dropped: separate loops without the edge branch (the compiler then hoists
 // operand reads into spills: 7.72 ms).
