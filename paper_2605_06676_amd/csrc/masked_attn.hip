@@ -325,7 +325,7 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   // the block is the shortest of all.  It more than makes up for the references that stay put, which round the weight of
   // the largest logit too (exactly 1 against a running maximum).  Error of o against 64 bits at 1024, 2345 and 16384
   // tokens: 1.33e-3, 1.38e-3 and 1.44e-3 with running maxima, 1.35e-3, 1.41e-3 and 1.48e-3 with references that stay put
-  // alone, 1.04e-3, 1.16e-3 and 1.32e-3 with this; it takes 0.5 to 1 us per launch, 9.4 -> 10.7 us where T <= 128.
+  // alone, 1.04e-3, 1.16e-3 and 1.32e-3 with this; 128 tokens take 8.9 -> 9.8 us, 512 and more no longer.
   auto last_tile = [&](auto moving_tag, auto fine_tag, const unsigned char* tile, int t) __attribute__((always_inline)) {
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {   // wave-uniform branches
@@ -339,18 +339,16 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   // One barrier per tile: every wave waits for its transfers of the tile before it, so it makes the tile's rows visible,
   // and it means that every wave is done with the other array, which the next tile then fills.
   stage(tile_a, 0);
+  if (n_full == 0) stage_last(tile_b);   // all there is: one wait for both
   start();
   if (n_full == 0) {
 #pragma unroll
     for (int qb = 0; qb < kMaQB; ++qb)
 #pragma unroll
       for (int i = 0; i < 8; ++i) plow[qb][i] = (__bf16)0.f;
+    lds_fill_barrier();
 #pragma unroll 1
-    for (int t = 0; t < 2; ++t) {
-      lds_fill_barrier();
-      if (t == 0) stage_last(tile_b);
-      last_tile(std::false_type{}, std::true_type{}, t == 0 ? tile_a : tile_b, t);
-    }
+    for (int t = 0; t < 2; ++t) last_tile(std::false_type{}, std::true_type{}, t == 0 ? tile_a : tile_b, t);
   } else {
 #pragma unroll 1
     for (int t = 0; t < n_full; t += 2) {
