@@ -37,6 +37,7 @@
 #include "lkv_common.h"
 #include "lkv_kernels.h"
 #include "lkv_lds.h"
+#include "lkv_order.h"
 
 namespace lkv {
 
@@ -71,10 +72,9 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   __shared__ __align__(1024) unsigned char tile_a[kMaTileLds];
   __shared__ __align__(1024) unsigned char tile_b[kMaTileLds];
   const int n_qtiles = (T + kMaBlockQ - 1) / kMaBlockQ;
-  // blocks in order of decreasing work: the query tile is the slow index, the head the fast one,
-  // so that the longest rows of the causal triangle of every head start first
-  const int qtile = n_qtiles - 1 - (int)blockIdx.x / n_heads;
-  const int hq = (int)blockIdx.x % n_heads;
+  const CausalBlock mine = causal_block(blockIdx.x, n_qtiles, n_heads);
+  const int qtile = mine.tile;
+  const int hq = mine.head;
   const int h = hq / G;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
