@@ -215,6 +215,13 @@ def test_backward_small(ctx, Hq, H, T):
     check_backward(ctx, Hq, H, T)
 
 
+@pytest.mark.parametrize("T", [2, 32, 34, 95, 96, 97, 127, 160, 161, 255, 256, 385])
+def test_backward_around_the_steps_of_the_dq_pipeline(ctx, T):
+    # a wave's last step of 32 keys holds its diagonal; the four waves of a block end one step after the other, and the
+    # ring of key rows turns every four steps
+    check_backward(ctx, 2, 1, T, seed=11)
+
+
 def test_backward_mask_edge_cases(ctx):
     def zero_prefix(m):
         m = m.copy()

@@ -72,7 +72,8 @@ def test_the_check_itself():
 
 
 @pytest.mark.parametrize("source,kernel", [("masked_attn.hip", "masked_attn_fwd_kernel"),
-                                           ("masked_attn_bwd.hip", "masked_attn_bwd_dkv_kernel")])
+                                           ("masked_attn_bwd.hip", "masked_attn_bwd_dkv_kernel"),
+                                           ("masked_attn_bwd.hip", "masked_attn_bwd_dq_kernel")])
 def test_no_barrier_with_a_copy_in_flight(tmp_path, source, kernel):
     listing = tmp_path / "kernel.s"
     flags = [f for f in B.FLAGS if f != "-shared"]
