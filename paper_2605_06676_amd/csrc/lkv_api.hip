@@ -251,8 +251,7 @@ lkv_status lkv_create(lkv_ctx** out, int device) {
     }
   }
   if (lkv::select_prepare() != hipSuccess || lkv::decode_prepare(device) != hipSuccess ||
-      lkv::score_mlp_prepare() != hipSuccess ||
-      lkv::masked_attn_bwd_prepare() != hipSuccess) {
+      lkv::score_mlp_prepare() != hipSuccess) {
     lkv_destroy(ctx);
     return LKV_ERR_HIP;
   }

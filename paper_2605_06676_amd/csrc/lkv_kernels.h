@@ -75,7 +75,6 @@ void launch_masked_attn_fwd(const void* q, const void* k, const void* v, const f
                             int T, float scale, float* o, float* lse, hipStream_t stream);
 
 // masked_attn_bwd.hip
-hipError_t masked_attn_bwd_prepare();
 size_t masked_attn_bwd_workspace_bytes(int n_q_heads, int n_kv_heads, int T);
 size_t masked_attn_bwd_least_workspace_bytes(int n_q_heads, int n_kv_heads, int T);
 void launch_masked_attn_bwd(const void* q, const void* k, const void* v, const float* m, const float* o,

@@ -15,12 +15,11 @@
 // Two kernels (three for short sequences), no atomics, every output element written once:
 //   masked_attn_bwd_dq_kernel     one block per query head and 128 queries: Q and dO rows in registers,
 //                                 K and V rows of all earlier keys stream through LDS; yields dQ, and D_i for the next.
-//   masked_attn_bwd_dkv_kernel    one block (eight waves, 32 keys each) per KV head and 256 keys: the K rows of
-//                                 the block stay in registers as matrix operands, its V rows in LDS, the Q and dO rows of
+//   masked_attn_bwd_dkv_kernel    one block of eight waves per KV head and 256 (or 128) keys, 32 keys a wave: the K rows
+//                                 stay in registers as matrix operands, the V rows in LDS, the Q and dO rows of
 //                                 all later queries (and of every query head of the group) stream through LDS; yields
 //                                 dK, dV and dm of its keys.  When that gives too few blocks the query heads of a group
 //                                 are dealt to several and a reduce kernel adds the partial results in a fixed order.
-//   masked_attn_bwd_dkv_narrow_kernel   the same with 16 keys per wave, for short sequences.
 // Both recompute s and dP with the 16x16x32 bf16 matrix instruction.  As in the forward kernel the
 // products whose result feeds another product are computed transposed, so that the accumulator
 // layout of the first (lane (rb, col) holds rows 4 rb .. 4 rb + 3 of two 16-row halves) is the
@@ -41,13 +40,10 @@ namespace {
 constexpr int kMbThreads = 256;
 constexpr int kMbWaves = kMbThreads / 64;
 constexpr int kMbStep = 32;                    // streamed rows per K-step of the second products
-constexpr int kMbSteps = 2;                    // steps staged per barrier (64 rows)
-constexpr int kMbTile = kMbStep * kMbSteps;
-constexpr int kMbStride = 288;                 // LDS bytes per staged row: measured conflict free for the straight 16-byte
-                                               // reads and for the transposing reads (272 was not, for the straight ones)
+
 constexpr float kMbLog2e = 1.4426950408889634f;
 
-constexpr int kMbFewBlocks = 512;              // dkv grids below this leave compute units idle or wait for their longest block
+constexpr int kMbFewBlocks = 512;              // dK/dV grids below this leave compute units idle or wait for their longest block
 
 __device__ __forceinline__ float mb_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -55,24 +51,22 @@ __device__ __forceinline__ bf16x8_t mb_read_straight(const unsigned char* p) {
   return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(p));
 }
 
-// B operand of a product whose K dimension runs over the 32 staged rows of a step: lane (r, c) gets,
-// for output column c of column tile ct, rows 4r..4r+3 and 16+4r..16+4r+3 (the K-slot order in which
-// the first products leave their results)
-__device__ __forceinline__ bf16x8_t mb_read_transposed(const unsigned char* rows, int stride, int r, int c, int ct) {
-  const unsigned char* base = rows + (4 * r + (c >> 2)) * stride + ct * 32 + (c & 3) * 8;
-  const s16x4_t v0 =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(base));
-  const s16x4_t v1 =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(base + 16 * stride));
-  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 // Permutation of the 16-byte pieces of staged row `row`: piece p lies at slot p ^ row_turn(row).  With it neither the
 // straight reads (16 rows of one piece) nor the transposing ones (32 bytes of each of eight rows at a time) meet a bank
 // twice (measured; 2 (row % 8) + row / 8 and two others cost 18 to 29 % of the kernel's cycles in conflicts).
 __device__ __forceinline__ int row_turn(int row) { return 2 * row & 15; }
 
-// the same from rows whose 16-byte pieces are permuted: p is where the lane's rows 4r + c / 4 (and 16 further on) hold its channels
+// base ^ kBits, worked out where it is used: the compiler would keep every such address in a register of its own
+template <uint32_t kBits>
+__device__ __forceinline__ uint32_t address_xor(uint32_t base) {
+  uint32_t at;
+  asm volatile("v_xor_b32 %0, %2, %1" : "=v"(at) : "v"(base), "i"(kBits));
+  return at;
+}
+
+// B operand of a product whose K dimension runs over the 32 staged rows of a step: lane (r, c) gets, for output column c,
+// rows 4r..4r+3 and 16+4r..16+4r+3 (the K-slot order in which the first products leave their results); p is where the
+// lane's rows 4r + c / 4 (and 16 further on) hold its channels
 __device__ __forceinline__ bf16x8_t mb_read_turned(const unsigned char* p) {
   const s16x4_t v0 =
       __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p));
@@ -341,29 +335,38 @@ masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restric
 constexpr int kDkvThreads = 512;
 constexpr int kDkvKB = 2;                      // 16-key column blocks per wave
 constexpr int kDkvWaveK = 16 * kDkvKB;
-constexpr int kDkvBlockK = kDkvThreads / 64 * kDkvWaveK;
+constexpr int dkv_block_keys(int groups) { return kDkvThreads / 64 / groups * kDkvWaveK; }
 constexpr int kDkvRow = 256;                   // LDS bytes per staged row: rows lie as in memory, their 16-byte pieces permuted
-constexpr int kDkvTileLds = 2 * kMbTile * kDkvRow;   // Q rows, dO rows of one item
+constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one step of 32 queries
 
-// Bound by instruction issue and by waiting for it: at 16384 tokens the matrix pipe is busy for 45 % of the cycles and
-// the vector pipe for 40 %, 7 % of them together, so a fifth of the cycles issue to neither; the LDS is busy 43 % (78 %
-// with 16 keys per wave and 64 KB of operands per 32 queries; a wave reads 40 KB here for 64 matrix instructions).  32
-// keys per wave need 128 accumulator and 32 K operand registers; V operands come from LDS so that the rest fits 256.  32 query
-// heads, 8 KV heads: 4.65 -> 4.33 ms at 16384 tokens; the whole backward pass 7.74 -> 7.30 ms, 1971 -> 1868 us at 8192,
-// 562 -> 524 us at 4096.  Measured and dropped: separate loops without the edge branch (the compiler then hoists
-// operand reads into spills: 7.72 ms).
+// kGroups = 1: eight waves of 32 keys, each takes every step of 32 queries.  kGroups = 2: four times 32 keys, two waves
+// take the steps in turn and their sums are joined at the end, which halves the chain of steps per key (short sequences).
+//
+// Bound by instruction issue (see the counters below) and, for long sequences, by the power that the products draw.  A step
+// is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S and dP of
+// the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps exponentials
+// beside products.  32 keys per wave need 128 accumulator and 32 K operand registers; V operands come from LDS, 48 KB are
+// read per 64 matrix instructions.  256 registers are just enough, and only so: one loop with one way out (with breaks or a
+// second loop for the diagonal the compiler keeps several sets of sums, and spills), masks set in place in a branch
+// around nothing else, addresses worked out where they are used.  32 query heads, 8 KV heads, in turn with a kernel that did one
+// thing after the other: 4.59 -> 4.20 ms at 16384 tokens, 136 -> 130 us at 2345 (kGroups = 2); 8 and 8 heads of 4096 140 ->
+// 127.  Measured and dropped: 16 keys per wave with V in registers (64 KB of operands per 64 matrix instructions, LDS busy
+// 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the channels of dK and dV
+// and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at 16384), four waves and
+// 128 keys a block, two blocks per compute unit (143 us and 4.9 ms).
+template <int kGroups>
 __global__ void __launch_bounds__(kDkvThreads, 2)
 masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                            const float* __restrict__ m, const float* __restrict__ lse, const float* __restrict__ dvec,
                            const uint4* __restrict__ d_o, int T, int n_kv_heads, int G, int split, float scale,
                            float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dm) {
-  // Two arrays and not one: the compiler then knows that reads of one do not touch the rows on their way to the other.
-  __shared__ __align__(1024) unsigned char tile_a[kDkvTileLds];
-  __shared__ __align__(1024) unsigned char tile_b[kDkvTileLds];
-  __shared__ __align__(1024) unsigned char v_rows[kDkvBlockK * kDkvRow];   // the block's V rows, read as operands in every step
-  __shared__ __align__(16) float aux_a[2 * kMbTile];   // lse (log2 domain) and D of the item's queries
-  __shared__ __align__(16) float aux_b[2 * kMbTile];
-  // A block owns 256 keys of one KV head and the query heads g_lo .. g_lo + g_cnt - 1 of its group: all of them
+  constexpr int kBlockK = dkv_block_keys(kGroups);
+  constexpr int kItemQ = kGroups * kMbStep;      // queries of an item: a step for every group
+  // An array per slot: the compiler then knows that reads of one do not touch the rows on their way to another.
+  __shared__ __align__(1024) unsigned char slot_a[kGroups * kDkvStepLds], slot_b[kGroups * kDkvStepLds], slot_c[kGroups * kDkvStepLds];
+  __shared__ __align__(1024) unsigned char v_rows[kBlockK * kDkvRow];   // the block's V rows, read as operands in every step
+  __shared__ __align__(16) float aux_a[2 * kItemQ], aux_b[2 * kItemQ], aux_c[2 * kItemQ];   // per step: lse (log2 domain), -D
+  // A block owns kBlockK keys of one KV head and the query heads g_lo .. g_lo + g_cnt - 1 of its group: all of them
   // (split = 1, results go straight to dk, dv, dm) or an equal share (split divides G: results are partial sums, row
   // `unit` of buffers the host passes in place of the outputs, added up by the reduce kernel).  Blocks in order of
   // decreasing work: early keys have the most queries after them; key tile slow, unit fast.
@@ -372,52 +375,58 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
   const int h = unit / split;
   const int g_cnt = G / split;
   const int g_lo = (unit - h * split) * g_cnt;
-  const int k0 = (int)blockIdx.x / n_units * kDkvBlockK;
+  const int k0 = (int)blockIdx.x / n_units * kBlockK;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane >> 4;
   const int c = lane & 15;
-  const int kw0 = k0 + wave * kDkvWaveK;
+  const int key_wave = wave & (kDkvThreads / 64 / kGroups - 1);   // the wave's 32 keys
+  const int group = wave / (kDkvThreads / 64 / kGroups);          // and, of kGroups = 2, its 32 queries of an item
+  const int kw0 = k0 + key_wave * kDkvWaveK;
   const float qscale = scale * kMbLog2e;
 
-  // streamed items: for every query head of the group, the 64-query tiles from the one that holds query k0 on
-  const int n_items = g_cnt * ((T - k0 + kMbTile - 1) / kMbTile);
+  // Streamed items: for every query head of the group, tiles of queries from the last one down to the block's diagonal.
+  // Blocks of one KV head run on one XCD (where the units divide by 8) and meet the same rows at the same time, in its L2
+  // (4096 tokens, 8 x 4 heads: 295 -> 288 us against walking up from the diagonal; 16384: 4731 -> 4706).
+  const int n_items = g_cnt * ((T - k0 + kItemQ - 1) / kItemQ);
   // Staging, straight from memory into LDS: a wave instruction fills 1 KB, four rows; lane (row slot, piece slot) fetches
-  // piece `slot ^ f(row)` of its row (row_turn below), so that both the straight reads (eight rows of one piece at a time)
+  // piece `slot ^ f(row)` of its row (row_turn above), so that both the straight reads (eight rows of one piece at a time)
   // and the transposing reads (four rows of 32 bytes) find their banks apart.
   const int srow = tid >> 4;
   const uint32_t piece = (uint32_t)(((tid & 15) ^ row_turn(srow)) * 16);
-  float aux = 0.f;   // threads 0..63: lse of query tid; threads 64..127: D of query tid - 64
-  // From the last query down to the block's diagonal: blocks of one KV head run on one XCD (where the units divide by 8)
-  // and meet the same rows at the same time, in its L2 (4096 tokens, 8 x 4 heads: 295 -> 288 us; 16384: 4731 -> 4706).
-  const int q_last = k0 + (T - 1 - k0) / kMbTile * kMbTile;   // first query of the last tile
+  float aux = 0.f;   // wave w < kGroups: lse of query `lane` of step w, in its second half D of query lane - 32
+  const int q_last = k0 + (T - 1 - k0) / kItemQ * kItemQ;   // first query of the last item
   int next_head = 0, next_q0 = q_last;   // the item to be fetched next: query head of the group, first query
   auto fetch = [&](unsigned char* dst) __attribute__((always_inline)) {
     const size_t base = ((size_t)h * G + g_lo + next_head) * T;
     const unsigned char* qs = reinterpret_cast<const unsigned char*>(q + base * kChunksPerRow);
     const unsigned char* gs = reinterpret_cast<const unsigned char*>(d_o + base * kChunksPerRow);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t at = (uint32_t)min(next_q0 + srow + 32 * j, T - 1) * 256u + piece;   // past the end: the last row, masked later
-      lds_fill16(qs + at, dst + (32 * j + 4 * wave) * kDkvRow);
-      lds_fill16(gs + at, dst + (kMbTile + 32 * j + 4 * wave) * kDkvRow);
+    for (int j = 0; j < kGroups; ++j) {
+      const uint32_t at = (uint32_t)min(next_q0 + srow + kMbStep * j, T - 1) * 256u + piece;   // past the end: the last row, masked later
+      lds_fill16(qs + at, dst + j * kDkvStepLds + 4 * wave * kDkvRow);
+      lds_fill16(gs + at, dst + j * kDkvStepLds + (kMbStep + 4 * wave) * kDkvRow);
     }
-    const int query = min(next_q0 + lane, T - 1);
-    aux = (wave & 1) ? dvec[base + query] : lse[base + query];
-    next_q0 -= kMbTile;
-    if (next_q0 < k0) {
+    if (wave < kGroups) {
+      aux = (lane < kMbStep ? lse : dvec)[base + min(next_q0 + kMbStep * wave + (lane & 31), T - 1)];
+      if (lane < kMbStep && next_q0 + kMbStep * wave + lane >= T) aux = -INFINITY;
+    }
+    next_q0 -= kItemQ;
+    if (next_q0 < k0) {              // past the last item this wraps to rows nobody multiplies
       next_q0 = q_last;
       next_head = next_head + 1 < g_cnt ? next_head + 1 : 0;
     }
   };
   auto put_aux = [&](float* dst) __attribute__((always_inline)) {
-    // lse goes to the log2 domain; -inf (no weight in the prefix) becomes +inf so that every e_ij is 0
-    if (tid < 2 * kMbTile) dst[tid] = wave == 1 ? aux : (aux == -INFINITY ? INFINITY : aux * kMbLog2e);
+    // lse goes to the log2 domain; -inf (no weight in the prefix, or a query past the end) becomes +inf: every e_ij is 0
+    if (wave < kGroups) dst[tid] = lane >= kMbStep ? -aux : (aux == -INFINITY ? INFINITY : aux * kMbLog2e);
   };
-  fetch(tile_a);
+  fetch(slot_a);
+  put_aux(aux_a);
+  fetch(slot_b);
 #pragma unroll
-  for (int j = 0; j < kDkvBlockK / 32; ++j)
+  for (int j = 0; j < kBlockK / 32; ++j)
     lds_fill16(reinterpret_cast<const unsigned char*>(v) +
                    ((size_t)h * T + min(k0 + srow + 32 * j, T - 1)) * (kHeadDim * 2) + piece,
                v_rows + (32 * j + 4 * wave) * kDkvRow);
@@ -450,318 +459,187 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
   const int trow = 4 * r + (c >> 2);
   const uint32_t turned = trow * kDkvRow + ((((c >> 1) & 1) ^ row_turn(trow)) * 16) + (c & 1) * 8;
 
-  const unsigned char* v_mine = v_rows + wave * kDkvWaveK * kDkvRow;
+  const uint32_t v_straight = straight + key_wave * kDkvWaveK * kDkvRow;
 
-  // 32 queries (half a tile) against this wave's keys
-  auto step = [&](const unsigned char* tile, const float* aux_lds, int qs0) __attribute__((always_inline)) {
-    // wave-uniform: the plain path needs every query of the step at or after every key of the wave, and inside T
-    const bool edge = qs0 < kw0 + kDkvWaveK - 1 || qs0 + kMbStep > T;
-    const unsigned char* q_lds = tile;
-    const unsigned char* g_lds = tile + kMbTile * kDkvRow;
-    bf16x8_t pfrag[kDkvKB], dsfrag[kDkvKB];
-    // dP and S: lane (rb = r, key c) gets queries 16 tt + 4 r + e
-    f32x4_t pacc[2][kDkvKB];
+  // carried from step to step: S and dP - D of a step's first 16 queries: lane (rb = r, key c) has queries 4 r + e
+  f32x4_t sx[kDkvKB], px[kDkvKB];
+  uint32_t pw[kDkvKB][4], dw[kDkvKB][4];   // P and dS of a step, as operands
+  auto frag = [&](const uint32_t (&w)[4]) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+  };
+  // S and dP - D of 16 queries of a step
+  auto logits = [&](const unsigned char* rows, const float* aux_lds, int tt) __attribute__((always_inline)) {
+    const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(aux_lds + kMbStep + 16 * tt + 4 * r);
 #pragma unroll
-    for (int kb = 0; kb < kDkvKB; ++kb) pacc[0][kb] = pacc[1][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb < kDkvKB; ++kb) { sx[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f}; px[kb] = nd; }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      bf16x8_t vx[kDkvKB];
-#pragma unroll
-      for (int kb = 0; kb < kDkvKB; ++kb) vx[kb] = mb_read_straight(v_mine + kb * 16 * kDkvRow + (straight ^ (64 * ks)));
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        const bf16x8_t gx = mb_read_straight(g_lds + tt * 16 * kDkvRow + (straight ^ (64 * ks)));
-#pragma unroll
-        for (int kb = 0; kb < kDkvKB; ++kb)
-          pacc[tt][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx[kb], pacc[tt][kb], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      f32x4_t sacc[kDkvKB];
-#pragma unroll
-      for (int kb = 0; kb < kDkvKB; ++kb) sacc[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x8_t qx = mb_read_straight(q_lds + tt * 16 * kDkvRow + (straight ^ (64 * ks)));
-#pragma unroll
-        for (int kb = 0; kb < kDkvKB; ++kb)
-          sacc[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qx, kfrag[kb][ks], sacc[kb], 0, 0, 0);
-      }
-      const float4 l4 = *reinterpret_cast<const float4*>(aux_lds + 16 * tt + 4 * r);
-      const float4 d4 = *reinterpret_cast<const float4*>(aux_lds + kMbTile + 16 * tt + 4 * r);
-      const float lq[4] = {l4.x, l4.y, l4.z, l4.w};
-      const float dq_[4] = {d4.x, d4.y, d4.z, d4.w};
-      auto pointwise = [&](auto edge_tag) __attribute__((always_inline)) {
-        constexpr bool kEdge = decltype(edge_tag)::value;
-#pragma unroll
-        for (int kb = 0; kb < kDkvKB; ++kb) {
-          const int key = kw0 + 16 * kb + c;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int query = qs0 + 16 * tt + 4 * r + e;
-            float ev = mb_exp2(fmaf(sacc[kb][e], qscale, -lq[e]));
-            if (kEdge) ev = (key > query || query >= T) ? 0.f : ev;
-            const float diff = pacc[tt][kb][e] - dq_[e];
-            dm_acc[kb] = fmaf(ev, diff, dm_acc[kb]);
-            const float p = ev * mkey[kb];
-            pfrag[kb][tt * 4 + e] = (__bf16)p;
-            dsfrag[kb][tt * 4 + e] = (__bf16)(p * diff);
-          }
-          asm volatile("" : "+v"(dm_acc[kb]));   // due here: the compiler would keep the summands and add them up later
-        }
-      };
-      if (edge) pointwise(std::true_type{});
-      else pointwise(std::false_type{});
-    }
-    // dV += P^T dO and dK += dS^T Q: B operands from the dO and Q rows by the transposing read
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      const bf16x8_t gb = mb_read_turned(g_lds + (turned ^ (32 * ct)));
-      const bf16x8_t qb = mb_read_turned(q_lds + (turned ^ (32 * ct)));
+      const bf16x8_t gx = mb_read_straight(rows + (kMbStep + tt * 16) * kDkvRow + (straight ^ (64 * ks)));
+      const bf16x8_t qx = mb_read_straight(rows + tt * 16 * kDkvRow + (straight ^ (64 * ks)));
 #pragma unroll
       for (int kb = 0; kb < kDkvKB; ++kb) {
-        acc_v[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[kb], gb, acc_v[kb][ct], 0, 0, 0);
-        acc_k[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dsfrag[kb], qb, acc_k[kb][ct], 0, 0, 0);
+        const bf16x8_t vx = mb_read_straight(v_rows + kb * 16 * kDkvRow + (v_straight ^ (64 * ks)));
+        px[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx, px[kb], 0, 0, 0);
+        sx[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qx, kfrag[kb][ks], sx[kb], 0, 0, 0);
       }
+    }
+  };
+  // dV += P^T dO and dK += dS^T Q: B operands from the dO and Q rows by the transposing read
+  auto products = [&](const unsigned char* rows) __attribute__((always_inline)) {
+    bf16x8_t gb = mb_read_turned(rows + kMbStep * kDkvRow + turned), qb = mb_read_turned(rows + turned);
+    auto tile = [&](auto ct_tag) __attribute__((always_inline)) {
+      constexpr int ct = decltype(ct_tag)::value;
+      bf16x8_t g1, q1;
+      if constexpr (ct < 7) {
+        const uint32_t at = address_xor<32 * (ct + 1)>(turned);
+        g1 = mb_read_turned(rows + kMbStep * kDkvRow + at);
+        q1 = mb_read_turned(rows + at);
+      }
+#pragma unroll
+      for (int kb = 0; kb < kDkvKB; ++kb) {
+        acc_v[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(pw[kb]), gb, acc_v[kb][ct], 0, 0, 0);
+        acc_k[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(dw[kb]), qb, acc_k[kb][ct], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (ct < 7) { gb = g1; qb = q1; }
+    };
+    tile(std::integral_constant<int, 0>());
+    tile(std::integral_constant<int, 1>());
+    tile(std::integral_constant<int, 2>());
+    tile(std::integral_constant<int, 3>());
+    tile(std::integral_constant<int, 4>());
+    tile(std::integral_constant<int, 5>());
+    tile(std::integral_constant<int, 6>());
+    tile(std::integral_constant<int, 7>());
+  };
+  // P and dS of two queries: elements e, e + 1 of key block kb
+  auto pair = [&](const f32x4_t (&sv)[kDkvKB], const f32x4_t (&pv)[kDkvKB], const float (&lq)[4], int tt, int kb, int e)
+      __attribute__((always_inline)) {
+    bf16x2_t a, b;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float ev = mb_exp2(fmaf(sv[kb][e + j], qscale, -lq[e + j]));
+      dm_acc[kb] = fmaf(ev, pv[kb][e + j], dm_acc[kb]);
+      const float p = ev * mkey[kb];
+      a[j] = (__bf16)p;
+      b[j] = (__bf16)(p * pv[kb][e + j]);
+    }
+    uint32_t &pa = pw[kb][2 * tt + (e >> 1)], &da = dw[kb][2 * tt + (e >> 1)];
+    pa = __builtin_bit_cast(uint32_t, a);
+    da = __builtin_bit_cast(uint32_t, b);
+    asm volatile("" : "+v"(pa), "+v"(da), "+v"(dm_acc[kb]));   // due here, beside the products
+  };
+  // One step of the pipeline up to its products: P and dS of its first 16 queries beside S and dP of the others, theirs
+  // beside S and dP of the next step's first 16.  below: query less key of element 0 of key block 0 in this lane.
+  auto step = [&](const unsigned char* cur, const float* aux_cur, const unsigned char* next, const float* aux_next, bool diagonal, int below)
+      __attribute__((always_inline)) {
+    f32x4_t s1[kDkvKB], p1[kDkvKB];
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      // tt = 0: from sx, px of `cur` to s1, p1 of its second half; tt = 1: from those to sx, px of `next`
+      if (diagonal) {   // wave-uniform: some key of the wave comes after some query of the step
+#pragma unroll
+        for (int kb = 0; kb < kDkvKB; ++kb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (below < 16 * kb - (16 * tt + e)) (tt == 0 ? sx : s1)[kb][e] = -INFINITY;
+          }
+      }
+      const unsigned char* g_at = tt == 0 ? cur + (kMbStep + 16) * kDkvRow : next + kMbStep * kDkvRow;
+      const unsigned char* q_at = tt == 0 ? cur + 16 * kDkvRow : next;
+      f32x4_t(&so)[kDkvKB] = tt == 0 ? s1 : sx;
+      f32x4_t(&po)[kDkvKB] = tt == 0 ? p1 : px;
+      const float4 l4 = *reinterpret_cast<const float4*>(aux_cur + 16 * tt + 4 * r);
+      const float lq[4] = {l4.x, l4.y, l4.z, l4.w};
+      const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(tt == 0 ? aux_cur + kMbStep + 16 + 4 * r : aux_next + kMbStep + 4 * r);
+      bf16x8_t gx = mb_read_straight(g_at + straight), qx = mb_read_straight(q_at + straight);
+      bf16x8_t vx0 = mb_read_straight(v_rows + v_straight), vx1 = mb_read_straight(v_rows + v_straight + 16 * kDkvRow);
+      auto part = [&](auto ks_tag) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_tag)::value;
+        po[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx0, ks == 0 ? nd : po[0], 0, 0, 0);
+        po[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx1, ks == 0 ? nd : po[1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);   // the next operands after these products have taken theirs
+        uint32_t at = 0;
+        if constexpr (ks < 3) {
+          at = address_xor<64 * (ks + 1)>(straight);
+          const uint32_t v_at = address_xor<64 * (ks + 1)>(v_straight);
+          gx = mb_read_straight(g_at + at);
+          vx0 = mb_read_straight(v_rows + v_at);
+          vx1 = mb_read_straight(v_rows + v_at + 16 * kDkvRow);
+        }
+#pragma unroll
+        for (int kb = 0; kb < kDkvKB; ++kb)
+          so[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qx, kfrag[kb][ks], ks == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : so[kb], 0, 0, 0);
+        if (tt == 0) pair(sx, px, lq, 0, ks >> 1, 2 * (ks & 1));
+        else pair(s1, p1, lq, 1, ks >> 1, 2 * (ks & 1));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (ks < 3) qx = mb_read_straight(q_at + at);
+      };
+      part(std::integral_constant<int, 0>());
+      part(std::integral_constant<int, 1>());
+      part(std::integral_constant<int, 2>());
+      part(std::integral_constant<int, 3>());
     }
   };
   int q0 = q_last;   // first query of the current item
-  auto item = [&](const unsigned char* tile, const float* aux_lds) __attribute__((always_inline)) {
-#pragma unroll
-    for (int st = 0; st < kMbSteps; ++st) {
-      const int qs0 = q0 + st * kMbStep;
-      // wave-uniform: nothing to do when all 32 queries come before this wave's keys, or lie past the end
-      if (qs0 + kMbStep - 1 >= kw0 && qs0 < T && kw0 < T) step(tile + st * kMbStep * kDkvRow, aux_lds + st * kMbStep, qs0);
-    }
-    q0 = q0 > k0 ? q0 - kMbTile : q_last;
+  const int lane_below = group * kMbStep + 4 * r - kw0 - c;
+  // One barrier per item: every wave waits for its transfers of the item before it, so it makes the rows of the next
+  // item visible, and it means that every wave is done with the slot that is filled now.  What it takes of a next item
+  // that is not there is not used.
+  auto item = [&](const unsigned char* cur, const float* aux_cur, const unsigned char* next, const float* aux_next,
+                  unsigned char* fill, float* aux_fill) __attribute__((always_inline)) {
+    lds_fill_barrier();
+    fetch(fill);
+    const int at = group * kDkvStepLds, aux_at = group * 2 * kMbStep;
+    step(cur + at, aux_cur + aux_at, next + at, aux_next + aux_at, q0 + group * kMbStep < kw0 + kDkvWaveK, q0 + lane_below);
+    products(cur + at);
+    put_aux(aux_fill);
+    q0 = q0 > k0 ? q0 - kItemQ : q_last;
   };
-  // One barrier per item: every wave waits for its transfers of the item before it, so it makes the item's rows visible,
-  // and it means that every wave is done with the other array, which the next item then fills.
-  put_aux(aux_a);
+  put_aux(aux_b);
+  lds_fill_barrier();
+  logits(slot_a + group * kDkvStepLds, aux_a + group * 2 * kMbStep, 0);
 #pragma unroll 1
-  for (int it = 0; it < n_items; it += 2) {
-    lds_fill_barrier();
-    fetch(tile_b);
-    item(tile_a, aux_a);
-    put_aux(aux_b);
-    if (it + 1 >= n_items) break;
-    lds_fill_barrier();
-    fetch(tile_a);
-    item(tile_b, aux_b);
-    put_aux(aux_a);
+  for (int it = 0; it < n_items; it += 3) {
+    item(slot_a, aux_a, slot_b, aux_b, slot_c, aux_c);
+    if (it + 1 < n_items) item(slot_b, aux_b, slot_c, aux_c, slot_a, aux_a);
+    if (it + 2 < n_items) item(slot_c, aux_c, slot_a, aux_a, slot_b, aux_b);
   }
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): no copy may still be on its way to LDS that this block gives back
 
+  if constexpr (kGroups == 2) {
+    // the second group's sums join the first's: 16 KB per wave and matrix, lane by lane
+    f32x4_t* mine = reinterpret_cast<f32x4_t*>(key_wave & 2 ? slot_b : slot_a) + (key_wave & 1) * 1024 + lane;
+    auto join = [&](f32x4_t (&acc)[kDkvKB][8]) __attribute__((always_inline)) {
+      lds_fill_barrier();
+      if (group == 1) {
+#pragma unroll
+        for (int kb = 0; kb < kDkvKB; ++kb)
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct) mine[(kb * 8 + ct) * 64] = acc[kb][ct];
+      }
+      __syncthreads();
+      if (group == 0) {
+#pragma unroll
+        for (int kb = 0; kb < kDkvKB; ++kb)
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct) acc[kb][ct] += mine[(kb * 8 + ct) * 64];
+      }
+    };
+    join(acc_v);
+    join(acc_k);
+    float* dm_all = reinterpret_cast<float*>(v_rows);
+    __syncthreads();
+    if (group == 1)
+#pragma unroll
+      for (int kb = 0; kb < kDkvKB; ++kb) dm_all[(key_wave * kDkvKB + kb) * 64 + lane] = dm_acc[kb];
+    __syncthreads();
+    if (group == 1) return;
+#pragma unroll
+    for (int kb = 0; kb < kDkvKB; ++kb) dm_acc[kb] += dm_all[(key_wave * kDkvKB + kb) * 64 + lane];
+  }
 #pragma unroll
   for (int kb = 0; kb < kDkvKB; ++kb) {
-    float s = dm_acc[kb];
-    s = sum_over_row_blocks(s);
-    const int key = kw0 + 16 * kb + c;
-    if (r == 0 && key < T) dm[(size_t)unit * T + key] = s;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int krow = kw0 + 16 * kb + 4 * r + e;
-      if (krow < T) {
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-          dv[((size_t)unit * T + krow) * kHeadDim + 16 * ct + c] = acc_v[kb][ct][e];
-          dk[((size_t)unit * T + krow) * kHeadDim + 16 * ct + c] = acc_k[kb][ct][e] * scale;
-        }
-      }
-    }
-  }
-}
-
-// The same with 16 keys per wave and 128 per block, everything but the streamed rows in registers: twice the LDS reads
-// per product, but half as long a chain of items per key, which is what short sequences wait for.
-// per 32-query step buffer: Q rows, dO rows (both also read transposed), 32 x lse (log2 domain), 32 x D
-constexpr int kNarrowStepLds = kMbStep * 2 * kMbStride + 2 * kMbStep * 4;
-constexpr int kNarrowLds = 2 * kMbSteps * kNarrowStepLds;
-
-constexpr int kNarrowWaves = 8;                   // two per SIMD
-constexpr int kNarrowThreads = 64 * kNarrowWaves;
-constexpr int kNarrowBlockK = 16 * kNarrowWaves;
-
-__global__ void __launch_bounds__(kNarrowThreads, 2)
-masked_attn_bwd_dkv_narrow_kernel(const uint4* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                           const float* __restrict__ m, const float* __restrict__ lse, const float* __restrict__ dvec,
-                           const uint4* __restrict__ d_o, int T, int n_kv_heads, int G, int split, float scale,
-                           float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dm) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int kKB = 1;
-  constexpr int kWaveK = 16 * kKB;
-  constexpr int kBlockK = kNarrowBlockK;
-  constexpr int kTileLds = kMbSteps * kNarrowStepLds;
-  constexpr int kRowSlots = 4 * kNarrowWaves;               // staged rows covered by one pass of the block: 32, half a tile
-  // A block owns 128 keys of one KV head and the query heads g_lo .. g_lo + g_cnt - 1 of its group: all of them
-  // (split = 1, results go straight to dk, dv, dm) or one each (split = G: results are per-query-head partial sums,
-  // row `unit` of buffers the host passes in place of the outputs, added up by the reduce kernel).  Blocks in order
-  // of decreasing work: early keys have the most queries after them; key tile slow, unit fast.
-  const int n_units = n_kv_heads * split;
-  const int unit = (int)blockIdx.x % n_units;
-  const int h = unit / split;
-  const int g_cnt = G / split;
-  const int g_lo = (unit - h * split) * g_cnt;
-  const int k0 = (int)blockIdx.x / n_units * kBlockK;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int r = lane >> 4;
-  const int c = lane & 15;
-  const int kw0 = k0 + wave * kWaveK;
-  const float qscale = scale * kMbLog2e;
-
-  // B operands of the first products: lane (key c of block kb, K-block r) holds 8 channels of k and of v
-  bf16x8_t kfrag[kKB][4], vfrag[kKB][4];
-  float mkey[kKB], dm_acc[kKB];
-#pragma unroll
-  for (int kb = 0; kb < kKB; ++kb) {
-    const int key = min(kw0 + 16 * kb + c, T - 1);      // keys past the end repeat the last one; never stored
-    const size_t row = (size_t)h * T + key;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      kfrag[kb][ks] = __builtin_bit_cast(bf16x8_t, reinterpret_cast<const uint4*>(k + row * kHeadDim)[ks * 4 + r]);
-      vfrag[kb][ks] = __builtin_bit_cast(bf16x8_t, reinterpret_cast<const uint4*>(v + row * kHeadDim)[ks * 4 + r]);
-    }
-    mkey[kb] = m[row];
-    dm_acc[kb] = 0.f;
-  }
-  f32x4_t acc_v[kKB][8], acc_k[kKB][8];   // dV, dK[key 4 r + e of block kb][channel 16 ct + c]
-#pragma unroll
-  for (int kb = 0; kb < kKB; ++kb)
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      acc_v[kb][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      acc_k[kb][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-
-  // streamed items: for every query head of the group, the 64-query tiles from the one that holds query k0 on
-  const int q_first = k0 / kMbTile * kMbTile;
-  const int tiles_per_head = (T - q_first + kMbTile - 1) / kMbTile;
-  const int n_items = g_cnt * tiles_per_head;
-  const int srow = tid >> 4, spiece = tid & 15;
-  uint4 q_s0, q_s1, g_s0, g_s1;   // thread (row slot tid / 16 in 0..31, piece tid % 16) moves rows slot and slot + 32
-  float aux;   // threads 0..63: lse of query tid; threads 64..127: D of query tid - 64
-#define LKV_MB_LOAD_ROW(j_, qreg_, greg_, base_, q0_)                                                       \
-  {                                                                                                         \
-    const int query = min((q0_) + srow + kRowSlots * (j_), T - 1); /* past the end: the last row, masked later */ \
-    const uint32_t off = (uint32_t)query * 256u + (uint32_t)spiece * 16u; /* 32-bit offset, uniform base */ \
-    qreg_ = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(q + (base_) * kChunksPerRow) + off);   \
-    greg_ = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(d_o + (base_) * kChunksPerRow) + off); \
-  }
-#define LKV_MB_LOAD_ITEM(it_)                                                       \
-  {                                                                                 \
-    const int g_ = (it_) / tiles_per_head;                                          \
-    const int q0_ = q_first + ((it_) - g_ * tiles_per_head) * kMbTile;              \
-    const size_t base_ = ((size_t)h * G + g_lo + g_) * T;                           \
-    LKV_MB_LOAD_ROW(0, q_s0, g_s0, base_, q0_)                                      \
-    LKV_MB_LOAD_ROW(1, q_s1, g_s1, base_, q0_)                                      \
-    const int query_ = min(q0_ + (tid & (kMbTile - 1)), T - 1);                     \
-    aux = (tid & kMbTile) ? dvec[base_ + query_] : lse[base_ + query_];             \
-  }
-  /* staged row srow + kRowSlots * j of the 64-row tile: step (row / 32), row-in-step (row % 32) */
-#define LKV_MB_STORE_ROW(j_, qreg_, greg_)                                                                   \
-  {                                                                                                          \
-    const int trow = srow + kRowSlots * (j_);                                                                \
-    unsigned char* step_buf = buf + (trow >> 5) * kNarrowStepLds;                                               \
-    const int row = trow & 31;                                                                               \
-    *reinterpret_cast<uint4*>(step_buf + row * kMbStride + spiece * 16) = qreg_;                            \
-    *reinterpret_cast<uint4*>(step_buf + kMbStep * kMbStride + row * kMbStride + spiece * 16) = greg_;     \
-  }
-  LKV_MB_LOAD_ITEM(0)
-
-#pragma unroll 1
-  for (int it = 0; it < n_items; ++it) {
-    unsigned char* buf = smem + (it & 1) * kTileLds;
-    LKV_MB_STORE_ROW(0, q_s0, g_s0)
-    LKV_MB_STORE_ROW(1, q_s1, g_s1)
-    if (tid < 2 * kMbTile) {
-      // lse goes to the log2 domain; -inf (no weight in the prefix) becomes +inf so that every e_ij is 0
-      const float val = (tid & kMbTile) ? aux : (aux == -INFINITY ? INFINITY : aux * kMbLog2e);
-      float* aux_lds = reinterpret_cast<float*>(buf + ((tid >> 5) & 1) * kNarrowStepLds + 2 * kMbStep * kMbStride);
-      aux_lds[(tid & kMbTile ? kMbStep : 0) + (tid & 31)] = val;
-    }
-    const int g_cur = it / tiles_per_head;
-    const int qt0 = q_first + (it - g_cur * tiles_per_head) * kMbTile;   // first query of the staged tile
-    LKV_MB_LOAD_ITEM(min(it + 1, n_items - 1))   // the last iteration re-reads its own item: no branch around the loads
-    __syncthreads();                             // two buffers: one barrier per item is enough
-#pragma unroll
-    for (int st = 0; st < kMbSteps; ++st) {
-      const int qs0 = qt0 + st * kMbStep;
-      // wave-uniform: nothing to do when all 32 queries come before this wave's keys, or lie past the end
-      if (qs0 + kMbStep - 1 < kw0 || qs0 >= T || kw0 >= T) continue;
-      const unsigned char* q_lds = buf + st * kNarrowStepLds;
-      const unsigned char* g_lds = q_lds + kMbStep * kMbStride;
-      const float* aux_lds = reinterpret_cast<const float*>(g_lds + kMbStep * kMbStride);
-      // S and dP: lane (rb = r, key c) gets queries 16 tt + 4 r + e
-      f32x4_t sacc[kKB][2], pacc[kKB][2];
-#pragma unroll
-      for (int kb = 0; kb < kKB; ++kb)
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-          sacc[kb][tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-          pacc[kb][tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const bf16x8_t qx = mb_read_straight(q_lds + (tt * 16 + c) * kMbStride + ks * 64 + r * 16);
-          const bf16x8_t gx = mb_read_straight(g_lds + (tt * 16 + c) * kMbStride + ks * 64 + r * 16);
-#pragma unroll
-          for (int kb = 0; kb < kKB; ++kb) {
-            sacc[kb][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qx, kfrag[kb][ks], sacc[kb][tt], 0, 0, 0);
-            pacc[kb][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vfrag[kb][ks], pacc[kb][tt], 0, 0, 0);
-          }
-        }
-      bf16x8_t pfrag[kKB], dsfrag[kKB];
-      auto pointwise = [&](auto edge_tag) {
-        constexpr bool kEdge = decltype(edge_tag)::value;
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-          const float4 l4 = *reinterpret_cast<const float4*>(aux_lds + 16 * tt + 4 * r);
-          const float4 d4 = *reinterpret_cast<const float4*>(aux_lds + kMbStep + 16 * tt + 4 * r);
-          const float lq[4] = {l4.x, l4.y, l4.z, l4.w};
-          const float dq_[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-          for (int kb = 0; kb < kKB; ++kb) {
-            const int key = kw0 + 16 * kb + c;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int query = qs0 + 16 * tt + 4 * r + e;
-              float ev = mb_exp2(fmaf(sacc[kb][tt][e], qscale, -lq[e]));
-              if (kEdge) ev = (key > query || query >= T) ? 0.f : ev;
-              const float diff = pacc[kb][tt][e] - dq_[e];
-              dm_acc[kb] = fmaf(ev, diff, dm_acc[kb]);
-              const float p = ev * mkey[kb];
-              pfrag[kb][tt * 4 + e] = (__bf16)p;
-              dsfrag[kb][tt * 4 + e] = (__bf16)(p * diff);
-            }
-          }
-        }
-      };
-      // wave-uniform: the plain path needs every query of the step at or after every key of the wave, and inside T
-      if (qs0 < kw0 + kWaveK - 1 || qs0 + kMbStep > T) pointwise(std::true_type{});
-      else pointwise(std::false_type{});
-      // dV += P^T dO and dK += dS^T Q: B operands from the dO and Q rows by the transposing read
-#pragma unroll
-      for (int ct = 0; ct < 8; ++ct) {
-        const bf16x8_t gb = mb_read_transposed(g_lds, kMbStride, r, c, ct);
-        const bf16x8_t qb = mb_read_transposed(q_lds, kMbStride, r, c, ct);
-#pragma unroll
-        for (int kb = 0; kb < kKB; ++kb) {
-          acc_v[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[kb], gb, acc_v[kb][ct], 0, 0, 0);
-          acc_k[kb][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dsfrag[kb], qb, acc_k[kb][ct], 0, 0, 0);
-        }
-      }
-    }
-  }
-#undef LKV_MB_LOAD_ROW
-#undef LKV_MB_LOAD_ITEM
-#undef LKV_MB_STORE_ROW
-
-#pragma unroll
-  for (int kb = 0; kb < kKB; ++kb) {
     float s = dm_acc[kb];
     s = sum_over_row_blocks(s);
     const int key = kw0 + 16 * kb + c;
@@ -807,34 +685,29 @@ masked_attn_bwd_reduce_kernel(const float4* __restrict__ dk_part, const float4* 
   (blockIdx.z == 0 ? dk : dv)[(size_t)h * per_head + i] = acc;
 }
 
-hipError_t masked_attn_bwd_prepare() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(masked_attn_bwd_dkv_narrow_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kNarrowLds);
-}
-
-// Which dK/dV kernel, and into how many blocks the query heads of a group are dealt: the blocks of a KV head's whole
-// group are few and long for short sequences (the longest walks G * T / 64 staged tiles one after the other).  The wide
-// kernel where one block per query head gives it kMbFewBlocks blocks, and then the smallest divisor of G that does so;
-// each more costs the partial sums' way through memory.  The narrow one below that, one block per query head when a
-// group's would be fewer.  Wide against narrow, whole backward pass: 2345 tokens, 8 x 4 heads (320 wide blocks) 253
-// against 234 us; 12000, 8 x 1 (376) 1158 : 1150; 4096, 8 x 4 (512) 532 : 567; 5000, 4 x 7 (560) 703 : 743.  Split and
-// wide against the narrow kernel's whole groups: 8192, 8 x 4 (135 MB of partial sums) 1867 : 1976; 16384, 4 x 7 (470
-// MB) 6542 : 7111; 20000, 4 x 7 (580 MB) 9616 : 11371; 5000, 16 x 2 (164 MB) 810 : 814.  Parts of unlike size, two of 4
-// and 3 heads in place of seven, would take 136 MB and 7077 us at 16384, 4 x 7.
+// How many groups of waves, and into how many blocks the query heads of a group are dealt: the blocks of a KV head's whole
+// group are few and long for short sequences (the longest walks G * T / 32 steps one after the other).  256 keys a block
+// where one block per query head gives kMbFewBlocks blocks, and then the smallest divisor of G that does so; each more
+// costs the partial sums' way through memory.  Below that 128 keys and two groups, one block per query head when a group's
+// would be fewer.  Whole backward pass, this rule : kMbFewBlocks = 256 for 256 keys : 128 keys throughout.  8 x 4 heads: 2345
+// tokens 207 : 226 : 207, 4096 475 : 616 : 498, 8192 1687 : 2321 : 1745, 16384 6672 : 6629 : 6721; 4 x 7: 5000 625 : 633 : 647,
+// 16384 5935 : 8809 : 6089; 2 x 8: 5001 395 : 437 : 395, 16384 3209 : 4745 : 3365; 8 x 1: 9000 593 : 717 : 593.  Whole
+// groups cut into equal pieces that cross key tiles, 256 blocks of equal length, gained up to 7 % at some sizes between 3000
+// and 5000 tokens and lost 10 % at 1024 to its partial sums.
 struct DkvPlan {
-  bool wide;
+  int groups;
   int split;
 };
-// without the wide kernel's split: what a caller gets whose workspace does not hold the partial sums
-static DkvPlan dkv_narrow_plan(int n_kv_heads, int G, int T) {
-  const int64_t narrow = (int64_t)((T + kNarrowBlockK - 1) / kNarrowBlockK) * n_kv_heads;
-  return {false, narrow < kMbFewBlocks ? G : 1};
+// without a split of the 256-key blocks: what a caller gets whose workspace does not hold the partial sums
+static DkvPlan dkv_short_plan(int n_kv_heads, int G, int T) {
+  const int64_t blocks = (int64_t)((T + dkv_block_keys(2) - 1) / dkv_block_keys(2)) * n_kv_heads;
+  return {2, blocks < kMbFewBlocks ? G : 1};
 }
 static DkvPlan dkv_plan(int n_kv_heads, int G, int T) {
-  const int64_t wide = (int64_t)((T + kDkvBlockK - 1) / kDkvBlockK) * n_kv_heads;
+  const int64_t blocks = (int64_t)((T + dkv_block_keys(1) - 1) / dkv_block_keys(1)) * n_kv_heads;
   for (int s = 1; s <= G; ++s)
-    if (G % s == 0 && wide * s >= kMbFewBlocks) return {true, s};
-  return dkv_narrow_plan(n_kv_heads, G, T);
+    if (G % s == 0 && blocks * s >= kMbFewBlocks) return {1, s};
+  return dkv_short_plan(n_kv_heads, G, T);
 }
 
 static size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
@@ -852,9 +725,9 @@ size_t masked_attn_bwd_workspace_bytes(int n_q_heads, int n_kv_heads, int T) {
   return plan_bytes(n_q_heads, n_kv_heads, T, dkv_plan(n_kv_heads, n_q_heads / n_kv_heads, T));
 }
 size_t masked_attn_bwd_least_workspace_bytes(int n_q_heads, int n_kv_heads, int T) {
-  const size_t narrow = plan_bytes(n_q_heads, n_kv_heads, T, dkv_narrow_plan(n_kv_heads, n_q_heads / n_kv_heads, T));
+  const size_t shorter = plan_bytes(n_q_heads, n_kv_heads, T, dkv_short_plan(n_kv_heads, n_q_heads / n_kv_heads, T));
   const size_t bytes = masked_attn_bwd_workspace_bytes(n_q_heads, n_kv_heads, T);
-  return narrow < bytes ? narrow : bytes;
+  return shorter < bytes ? shorter : bytes;
 }
 
 void launch_masked_attn_bwd(const void* q, const void* k, const void* v, const float* m, const float* o,
@@ -867,17 +740,17 @@ void launch_masked_attn_bwd(const void* q, const void* k, const void* v, const f
                      stream, static_cast<const uint16_t*>(q), static_cast<const uint4*>(k), static_cast<const uint4*>(v), m,
                      lse, workspace, o, static_cast<const uint16_t*>(d_o), T, n_q_heads, G, scale, dq);
   DkvPlan plan = dkv_plan(n_kv_heads, G, T);
-  if (workspace_bytes < plan_bytes(n_q_heads, n_kv_heads, T, plan)) plan = dkv_narrow_plan(n_kv_heads, G, T);
+  if (workspace_bytes < plan_bytes(n_q_heads, n_kv_heads, T, plan)) plan = dkv_short_plan(n_kv_heads, G, T);
   const int split = plan.split;
   const int n_units = n_kv_heads * split;
   unsigned char* ws = reinterpret_cast<unsigned char*>(workspace);
   float* dk_part = reinterpret_cast<float*>(ws + align256((size_t)n_rows * sizeof(float)));
   float* dv_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(dk_part) + align256((size_t)n_units * T * kHeadDim * sizeof(float)));
   float* dm_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(dv_part) + align256((size_t)n_units * T * kHeadDim * sizeof(float)));
-  const int block_keys = plan.wide ? kDkvBlockK : kNarrowBlockK;
-  hipLaunchKernelGGL(plan.wide ? masked_attn_bwd_dkv_kernel : masked_attn_bwd_dkv_narrow_kernel,
-                     dim3((T + block_keys - 1) / block_keys * n_units), dim3(plan.wide ? kDkvThreads : kNarrowThreads),
-                     plan.wide ? 0 : kNarrowLds, stream, static_cast<const uint4*>(q), static_cast<const uint16_t*>(k),
+  const int block_keys = dkv_block_keys(plan.groups);
+  hipLaunchKernelGGL(plan.groups == 1 ? masked_attn_bwd_dkv_kernel<1> : masked_attn_bwd_dkv_kernel<2>,
+                     dim3((T + block_keys - 1) / block_keys * n_units), dim3(kDkvThreads),
+                     0, stream, static_cast<const uint4*>(q), static_cast<const uint16_t*>(k),
                      static_cast<const uint16_t*>(v), m, lse, workspace, static_cast<const uint4*>(d_o), T, n_kv_heads, G,
                      split, scale, split > 1 ? dk_part : dk, split > 1 ? dv_part : dv, split > 1 ? dm_part : dm);
   if (split > 1)
