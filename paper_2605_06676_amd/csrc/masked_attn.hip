@@ -29,7 +29,8 @@
 // products of step s - 1, weights of step s, logits of step s + 1 in one scheduling region): vector work runs beside 36 %
 // of the matrix time, 17 % in the dq kernel, which has no such pipeline.  32 query heads, 8 KV heads, in turn with the
 // kernel of running maxima and staging through registers: 2.40 -> 2.02 ms at 16384 tokens (1090 TFLOP/s; a library product
-// of 8192 x 8192 x 8192 reaches 1310 here), 649 -> 530 us at 8192, 182 -> 147 at 4096, 74 -> 62 at 2345.  Measured and dropped: 64 queries per wave
+// of 8192 x 8192 x 8192 reaches 1310 here), 649 -> 530 us at 8192, 182 -> 147 at 4096, 74 -> 62 at 2345; what the order of
+// the blocks and the pieces of plain_step took off since then stands there.  Measured and dropped: 64 queries per wave
 // at one wave per SIMD (half the LDS reads; 2.38 ms), a block of eight waves in two groups that split the keys (2.41
 // ms; 86 us at 2345 tokens), different wave priorities on a SIMD (no change).
 #include <type_traits>
@@ -43,6 +44,7 @@ namespace lkv {
 
 namespace {
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 constexpr int kMaThreads = 256;
 constexpr int kMaWaves = kMaThreads / 64;
 constexpr int kMaStep = 32;                   // keys per pipeline step: one K-step of the P.V product
@@ -268,6 +270,76 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) sacc[qb][sub] = next[qb][sub];
   };
+  // The same for the steps wholly below the diagonal, with references that stay put, in eight pieces that the compiler may
+  // not mix: the operands of the next products, four or six products, an eighth of the weights.  K operands are read two
+  // pieces ahead, V operands one (both one ahead: 2 to 3 % slower where a wave has a SIMD to itself, both two ahead or K three
+  // up to 1 % slower).  Against the compiler's own order: 2170 -> 2140 us at 16384 tokens, 32 heads, 562 -> 555 at 8192, 63.2 ->
+  // 62.5 at 2345; 8 heads of 4096 75.5 -> 73.3.
+  auto plain_step = [&](const unsigned char* tile, int half) __attribute__((always_inline)) {
+    const unsigned char* k_lds = tile + half * kMaStep * kMaRow;
+    const unsigned char* v_lds = k_lds + kMaTile * kMaRow;
+    const float* m_lds = reinterpret_cast<const float*>(tile + 2 * kMaTile * kMaRow) + half * kMaStep;
+    f32x4_t next[kMaQB][2];
+    uint32_t pw[kMaQB][4];
+    float psum[kMaQB], mw[4];
+    auto read_k = [&](int i) __attribute__((always_inline)) {
+      return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(k_lds + (i >> 2) * 16 * kMaRow + (k_at ^ (64 * (i & 3)))));
+    };
+    bf16x8_t kx = read_k(0), k1 = read_k(1);
+    auto read_v = [&](int ct) __attribute__((always_inline)) {
+      const s16x4_t v0 = ma_read_tr16(v_lds + (v_at ^ (32 * ct)));
+      const s16x4_t v1 = ma_read_tr16(v_lds + (v_at ^ (32 * ct)) + 16 * kMaRow);
+      return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    bf16x8_t vx = read_v(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int sub = i >> 2, ks = i & 3, qp = (i >> 1) & 1, e0 = 2 * (i & 1);
+      bf16x8_t kn, vn;
+      if (i < 6) kn = read_k(i + 2);
+      if (i < 7) vn = read_v(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks == 0) {
+        const float4 mw4 = *reinterpret_cast<const float4*>(m_lds + 16 * sub + 4 * r);
+        mw[0] = mw4.x; mw[1] = mw4.y; mw[2] = mw4.z; mw[3] = mw4.w;
+      }
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb) {
+        if (ks == 0) next[qb][sub] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        next[qb][sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kx, qfrag[qb][ks], next[qb][sub], 0, 0, 0);
+      }
+      float ev[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) ev[j] = ma_exp2(fmaf(sacc[qp][sub][e0 + j], qscale, -ref[qp]));
+#pragma unroll
+      for (int qb = 0; qb < kMaQB; ++qb) {
+        if (i == 0) acc_l[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb], ones, acc_l[qb], 0, 0, 0);
+        acc_o[qb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pfrag[qb], vx, acc_o[qb][i], 0, 0, 0);
+      }
+      bf16x2_t pair;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float p = ev[j] * mw[e0 + j];   // the mask multiplies the exponential (App. B.2)
+        psum[qp] = sub == 0 && e0 + j == 0 ? p : psum[qp] + p;
+        pair[j] = (__bf16)p;
+      }
+      uint32_t& word = pw[qp][2 * sub + (i & 1)];
+      word = __builtin_bit_cast(uint32_t, pair);
+      asm volatile("" : "+v"(word), "+v"(psum[qp]));   // due here, beside the products
+      __builtin_amdgcn_sched_barrier(0);
+      kx = k1;
+      k1 = kn;
+      vx = vn;
+    }
+#pragma unroll
+    for (int qb = 0; qb < kMaQB; ++qb) {
+      l_run[qb] += psum[qb];
+      asm volatile("" : "+v"(l_run[qb]));
+      pfrag[qb] = __builtin_bit_cast(bf16x8_t, make_uint4(pw[qb][0], pw[qb][1], pw[qb][2], pw[qb][3]));
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) sacc[qb][sub] = next[qb][sub];
+    }
+  };
   // References that stay put save the maximum, the branch on it and the rescaling it guards, 8 % of the time.  Any
   // reference gives the same weights to a rounding as long as no sum overflows (logits far below a reference vanish next
   // to the key that set it, as below a maximum), so a wave looks at its sums every 128 keys, and where one has passed
@@ -355,12 +427,12 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
       lds_fill_barrier();
       stage(tile_b, t + 1);
       if (__builtin_expect(__ballot(!(fmaxf(l_run[0], l_run[1]) < kMaMoveSum)) != 0ull, 0)) move_references();
-      step(std::false_type{}, std::false_type{}, std::false_type{}, tile_a, 2 * t, 0);
-      step(std::false_type{}, std::false_type{}, std::false_type{}, tile_a, 2 * t + 1, 1);
+      plain_step(tile_a, 0);
+      plain_step(tile_a, 1);
       lds_fill_barrier();
       stage(tile_a, t + 2);
-      step(std::false_type{}, std::false_type{}, std::false_type{}, tile_b, 2 * t + 2, 0);
-      step(std::false_type{}, std::false_type{}, std::false_type{}, tile_b, 2 * t + 3, 1);
+      plain_step(tile_b, 0);
+      plain_step(tile_b, 1);
     }
     lds_fill_barrier();
     stage_last(tile_b);

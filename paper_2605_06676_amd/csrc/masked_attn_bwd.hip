@@ -89,13 +89,15 @@ static_assert(kDqBlockQ == 4 * kMbStep, "the steps below the diagonal of a block
 // Bound by instruction issue and, for long sequences, by the power that the products draw.  Steps of 32 keys are pipelined
 // inside a wave, as in the forward kernel: products of step s - 1 with its key rows, dS of step s, S and dP of step s + 1.
 // Left to itself the compiler puts the exponentials of a step behind all of its products (9 % slower), so the step is cut
-// into eight pieces of six products, the operands of the next piece and an eighth of the dS, which it may not mix.  The
+// into eight pieces of six products, the operands of the next piece and an eighth of the dS, which it may not mix.  K rows
+// for the products are read a piece ahead, the others as soon as the products before have taken theirs (with all of them so
+// 85.6 instead of 82.3 us at 2345 tokens, 113 instead of 102 for 8 and 8 heads of 4096; all a piece ahead does not fit).  The
 // rows go from memory to LDS directly; a ring of four K slots holds what steps s - 1 to s + 2 need, two V slots s + 1 and
 // s + 2 (53 KB, two blocks per compute unit; tiles of 64 keys would need 80 KB).  D_i is summed here on the way in, from
 // rows that the block needs anyhow, and left for the dK/dV kernel: a launch of its own took 65 us at 16384 tokens, 9.4 at
 // 2345.  32 query heads, 8 KV heads, in turn with a kernel that did one thing after the other and staged through
-// registers: 2960 -> 2690 us at 16384 tokens (1225 TFLOP/s), 216 -> 193 at 4096, 97 -> 85 at 2345; 8 and 8 heads of 4096
-// 143 -> 108.
+// registers: 2960 -> 2680 us at 16384 tokens (1230 TFLOP/s), 216 -> 191 at 4096, 97 -> 82 at 2345; 8 and 8 heads of 4096
+// 143 -> 102.
 __global__ void __launch_bounds__(kMbThreads, 2)
 masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ k, const uint4* __restrict__ v,
                           const float* __restrict__ m, const float* __restrict__ lse, float* __restrict__ dvec,
@@ -232,9 +234,11 @@ masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restric
     bf16x8_t kx = mb_read_straight(k_next + straight), vx = mb_read_straight(v_next + straight), kb = mb_read_turned(k_prev + turned);
     uint32_t ds[kDqQB][4];
     float mw[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int tt = i >> 2, ks = i & 3, qp = (i >> 1) & 1, e0 = 2 * (i & 1);
+    auto piece_of_step = [&](auto i_tag) __attribute__((always_inline)) {
+      constexpr int i = decltype(i_tag)::value;
+      constexpr int tt = i >> 2, ks = i & 3, qp = (i >> 1) & 1, e0 = 2 * (i & 1);
+      bf16x8_t kbn;
+      if constexpr (i < 7) kbn = mb_read_turned(k_prev + address_xor<32 * (i + 1)>(turned));
       if (ks == 0) {
         const float4 mw4 = *reinterpret_cast<const float4*>(k_cur + kDqRows + (16 * tt + 4 * r) * 4);
         mw[0] = mw4.x; mw[1] = mw4.y; mw[2] = mw4.z; mw[3] = mw4.w;
@@ -253,7 +257,7 @@ masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restric
       for (int j = 0; j < 2; ++j) ev[j] = mb_exp2(fmaf(sacc[qp][tt][e0 + j], qscale, -lse2[qp]));
       __builtin_amdgcn_sched_barrier(0);   // the next operands after these products have taken theirs: 24 registers less
       if (i < 7) {
-        const uint32_t at = ((i + 1) >> 2) * 16 * kDqRow + (straight ^ (64 * ((i + 1) & 3)));
+        const uint32_t at = ((i + 1) >> 2) * 16 * kDqRow + (((i + 1) & 3) == 0 ? straight : address_xor<64 * ((i + 1) & 3)>(straight));
         kx = mb_read_straight(k_next + at);
         vx = mb_read_straight(v_next + at);
       }
@@ -266,8 +270,16 @@ masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restric
       word = __builtin_bit_cast(uint32_t, pair);
       asm volatile("" : "+v"(word));   // due here, beside the products
       __builtin_amdgcn_sched_barrier(0);
-      if (i < 7) kb = mb_read_turned(k_prev + (turned ^ (32 * (i + 1))));
-    }
+      kb = kbn;
+    };
+    piece_of_step(std::integral_constant<int, 0>());
+    piece_of_step(std::integral_constant<int, 1>());
+    piece_of_step(std::integral_constant<int, 2>());
+    piece_of_step(std::integral_constant<int, 3>());
+    piece_of_step(std::integral_constant<int, 4>());
+    piece_of_step(std::integral_constant<int, 5>());
+    piece_of_step(std::integral_constant<int, 6>());
+    piece_of_step(std::integral_constant<int, 7>());
 #pragma unroll
     for (int qb = 0; qb < kDqQB; ++qb) {
       dsfrag[qb] = __builtin_bit_cast(bf16x8_t, make_uint4(ds[qb][0], ds[qb][1], ds[qb][2], ds[qb][3]));
