@@ -23,15 +23,20 @@
 // (the prefill's attention kernel computes them for every query) passes them in: pass 1 and the
 // merge are skipped and the keys are read once.
 //
-// Pass 1 keeps a running reference per (row, lane) instead of a running maximum: the sum is
-// taken relative to a reference that is only moved when a logit exceeds it by more than 64
-// binary orders of magnitude, which costs one exponential per logit instead of two.  Any
-// reference within that distance of the true maximum gives the same sum to fp32 rounding.
+// Pass 1 takes its sums per (row, lane) relative to that lane's logit of the block's first 16 keys, and nothing looks at
+// a maximum: any reference gives the same sum to fp32 rounding as long as nothing overflows.  A sum that passes 2^100
+// is taken again with references that follow the largest logit.
 //
 // A block is a pair of waves that share the staged keys (two tiles of 16 between barriers); the
 // window rows are split between the two (at most 64 rows, 64 fragment registers, per wave).
-// Both passes are bound by instruction issue rather than by HBM: per key and row one exponential
-// (quarter rate) next to the matrix work, which the hardware overlaps only in part.
+// What bounds both passes: the keys' stream (341 us a pass of 2.1 GB at the 6.3 TB/s that a large read reaches here) and
+// the issue of one exponential, a multiplication and an addition per logit next to the matrix work, in one power budget.  So what pays
+// is work not done: references that stay put (no maximum and no vote on it), addresses from a scalar base, sums over
+// the row blocks of both tiles at once.  32 layers of 8 heads x 32768 keys, 128 window rows, in turn with a kernel that moved its
+// references: 908 -> 829 us on one machine, 852 -> 797 on another (given the normalisers 471 -> 439 and 434 -> 418); 4 x 7
+// heads, 20001 keys, 8 layers 105 -> 99; one layer of 4097 28.2 -> 27.8.  Measured and dropped: keys straight from memory to LDS (a ring of four steps, 37 KB
+// a block: too few bytes in flight, 433 -> 486 us a pass, 188 -> 216 with 8 window rows), temporal loads, and pass 2 from the
+// last block backwards so that it finds the end of the keys in the memory-side cache (0 to 7 % slower).
 #include "lkv_common.h"
 
 namespace lkv {
@@ -41,11 +46,12 @@ constexpr int kWinTokTile = 16;                  // keys per MFMA N tile
 constexpr int kWinRowStride = 256 + 32;          // bytes per staged key row in LDS
 constexpr int kWinTileLds = kWinTokTile * kWinRowStride;
 constexpr int kWinTilesPerStep = 2;     // tiles staged, multiplied and finished between two barriers
+constexpr int kWinStep = kWinTilesPerStep * kWinTokTile;
 constexpr int kWinStepLds = kWinTilesPerStep * kWinTileLds;
 constexpr int kWinMaxRowsPerBlock = 1024;
 constexpr int kWinMaxReach = 31;                // pooling widths up to 63
 constexpr int kWinVoteSlots = kWinMaxRowsPerBlock + 32 + kWinMaxReach + 17;   // pass 2: a block's keys, two tiles before, the reach after, rounded up to a tile
-constexpr float kWinRebase = 64.f;               // log2 distance at which pass 1 moves a reference
+constexpr float kWinMostSum = 1.2676506e30f;     // 2^100: sum beyond which pass 1 starts over with references that move
 constexpr float kWinNoRef = -1e30f;              // reference of a row that has seen no key yet
 
 __device__ __forceinline__ int win_seq_of_unit(const WinTable& tab, int unit) {
@@ -69,8 +75,10 @@ template <int MTW, int kPass>
 __global__ void __launch_bounds__(kWinThreads, 2)
 score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_per_block, float log2_scale,
                     int reach /* pass 2: pooling reach c, width 2 c + 1 */, int pool_kind, float inv_group) {
-  extern __shared__ __align__(16) unsigned char smem[];
   constexpr int RP = 32 * MTW;                      // padded rows of the block
+  __shared__ __align__(16) unsigned char x_lds[2 * kWinStepLds];   // the staged keys of two steps
+  // pass 2: the votes of the keys the block multiplies; both waves add the shares of their rows
+  __shared__ float v_lds[kPass == 2 ? kWinVoteSlots : 1];
 
   const int seq = win_seq_of_unit(tab, blockIdx.x);
   const int local = blockIdx.x - tab.first[seq];
@@ -98,14 +106,11 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   const int n_tiles = (block_rows + 15) >> 4;
 
   const int lane = threadIdx.x & 63;
-  const int half = threadIdx.x >> 6;
+  const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane >> 4;
   const int c = lane & 15;
-  unsigned char* x_lds = smem;   // the staged keys of two steps
-  // pass 2: the votes of the keys the block multiplies; both waves add the shares of their rows
-  float* v_lds = reinterpret_cast<float*>(smem + 2 * kWinStepLds);
   if (kPass == 2)
-    for (int i = threadIdx.x; i < kWinVoteSlots; i += kWinThreads) v_lds[i] = 0.f;   // ordered by the barrier below
+    for (int i = threadIdx.x; i < kWinVoteSlots; i += kWinThreads) v_lds[i] = 0.f;   // ordered by the barriers below
 
   // A fragments: window row 16 (half MTW + mw) + c, features 32 ks + 8 r .. +7
   bf16x8_t qfrag[MTW][4];
@@ -124,15 +129,11 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   }
 
   // per lane: rows 16 (half MTW + mw) + 4 r + e of token c of the current tile
-  float ref[MTW][4], sum[MTW][4];   // pass 1: running reference (log2 units) and sum; pass 2: ref = log-normaliser
+  float ref[MTW][4], sum[MTW][4];   // pass 1: reference (log2 units) and sum; pass 2: ref = log-normaliser
 #pragma unroll
   for (int mw = 0; mw < MTW; ++mw)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = 16 * (half * MTW + mw) + 4 * r + e;
-      ref[mw][e] = row < n_rows ? kWinNoRef : -kWinNoRef;   // a padding row never asks for a new reference
-      sum[mw][e] = 0.f;
-    }
+    for (int e = 0; e < 4; ++e) ref[mw][e] = sum[mw][e] = 0.f;
 
   const size_t part_row0 = ((size_t)lh * chunks) * RP;
   if (kPass == 2) {
@@ -159,100 +160,98 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
     }
   }
 
-  const uint4* Kh = reinterpret_cast<const uint4*>(tab.k[seq]) + (size_t)lh * (size_t)T * kChunksPerRow;
+  const unsigned char* Kh = reinterpret_cast<const unsigned char*>(tab.k[seq]) + ((size_t)lh * (size_t)T + block_row0) * 256;
 
   // Staging: thread (half, r, c) brings piece c of rows 16 nt + 8 half + r and 16 nt + 8 half + 4 + r of each step.
-  constexpr int NT = kWinTilesPerStep;
-  uint4 xa[2 * NT], xb[2 * NT];
   // No branch encloses a load between its issue and the staging that waits for it: the compiler counts the loads
   // still in flight at a wait from the path on which the fewest were issued, so a conditional load makes every wait
   // drain the whole queue.  Steps past the block's rows are clamped instead of skipped.
-  const int last_row = block_row0 + block_rows - 1;
-  auto load_step = [&](uint4 (&xx)[2 * NT], int i) {
+  const int n_steps = (block_rows + kWinStep - 1) / kWinStep;
+  uint4 xa[2 * kWinTilesPerStep], xb[2 * kWinTilesPerStep];
+  auto load_step = [&](uint4 (&xx)[2 * kWinTilesPerStep], int i) __attribute__((always_inline)) {
+    const int at = min(i * kWinStep, block_rows - 1);   // past the last step: the last row only
+    const unsigned char* src = Kh + (size_t)at * 256;
 #pragma unroll
-    for (int j = 0; j < 2 * NT; ++j) {
-      int row = block_row0 + 16 * NT * i + 16 * (j >> 1) + 8 * half + 4 * (j & 1) + r;
-      row = row < last_row ? row : last_row;   // past the block's rows: re-read its last row, masked below
-      xx[j] = load_stream16(Kh + (size_t)row * kChunksPerRow + c);
+    for (int j = 0; j < 2 * kWinTilesPerStep; ++j) {
+      // past the block's rows: its last row again, masked below
+      const uint32_t row = (uint32_t)min(16 * (j >> 1) + 8 * half + 4 * (j & 1) + r, block_rows - 1 - at);
+      xx[j] = load_stream16(reinterpret_cast<const uint4*>(src + (row * 256u + (uint32_t)c * 16u)));
     }
   };
-  auto stage_step = [&](const uint4 (&xx)[2 * NT], int buf) {
+  const uint32_t stage_at = (uint32_t)((8 * half + r) * kWinRowStride + c * 16);
+  auto stage_step = [&](const uint4 (&xx)[2 * kWinTilesPerStep], int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 2 * NT; ++j)
-      *reinterpret_cast<uint4*>(x_lds + buf * kWinStepLds + (16 * (j >> 1) + 8 * half + 4 * (j & 1) + r) * kWinRowStride + c * 16) = xx[j];
+    for (int j = 0; j < 2 * kWinTilesPerStep; ++j)
+      *reinterpret_cast<uint4*>(x_lds + buf * kWinStepLds + stage_at + (16 * (j >> 1) + 4 * (j & 1)) * kWinRowStride) = xx[j];
   };
-  auto products = [&](f32x4_t (&acc)[MTW], const unsigned char* xt) {
+  const uint32_t read_at = (uint32_t)(c * kWinRowStride + r * 16);
+  auto products = [&](f32x4_t (&acc)[MTW], const unsigned char* xt) __attribute__((always_inline)) {
 #pragma unroll
     for (int mw = 0; mw < MTW; ++mw) acc[mw] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const uint4 x = *reinterpret_cast<const uint4*>(xt + c * kWinRowStride + ks * 64 + r * 16);
-      const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, x);
+      const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(xt + read_at + ks * 64));
 #pragma unroll
       for (int mw = 0; mw < MTW; ++mw)
         acc[mw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfrag[mw][ks], xv, acc[mw], 0, 0, 0);
     }
   };
-  auto finish = [&](const f32x4_t (&acc)[MTW], int tile) {   // tile: 16-key tile of the block
-    const int row0 = block_row0 + 16 * tile;
+  // Whether window row `row` sees key j: rows past n_rows see none, row i of a head's window the keys up to its own.
+  auto sees = [&](int row, int j) __attribute__((always_inline)) {
+    int w = window;
+    asm volatile("" : "+s"(w));   // or the compiler keeps every row's place in the window in registers all the way
+    return row < n_rows && j <= prefix + row % w;
+  };
+  // One step: products and arithmetic of its two tiles, staging of step i + 1 (fetching step i + 3 behind it).  Barrier i
+  // makes the keys of step i visible and means both waves have finished reading those of step i - 1.
+  auto step = [&](uint4 (&x_next)[2 * kWinTilesPerStep], int i, int buf) __attribute__((always_inline)) {
+    const unsigned char* cur = x_lds + buf * kWinStepLds;
+    f32x4_t acc[2][MTW];
+    products(acc[0], cur);
+    products(acc[1], cur + kWinTileLds);
+    stage_step(x_next, buf ^ 1);               // past the last step: rows nobody reads
+    load_step(x_next, i + 3);
     if (kPass == 1) {
-      float x[MTW][4];
-      float top = -INFINITY;
+      // Sums against references that stay put: this lane's logits of the block's first tile.  Its later keys are seen by
+      // a row only where the first one is, so a reference is a logit of the sum, or the sum is empty.
+      if (i == 0) {   // uniform
 #pragma unroll
-      for (int mw = 0; mw < MTW; ++mw)
+        for (int mw = 0; mw < MTW; ++mw)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[mw][e] = fmaf(acc[mw][e], log2_scale, -ref[mw][e]);
-          top = fmaxf(top, x[mw][e]);
+          for (int e = 0; e < 4; ++e) ref[mw][e] = acc[0][mw][e] * log2_scale;
+      }
+      const bool causal = block_row0 + kWinStep * (i + 1) > prefix;   // uniform: the step touches the window or the ragged tail
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (causal) {
+          const int j = block_row0 + kWinStep * i + kWinTokTile * t + c;
+#pragma unroll
+          for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (!sees(16 * (half * MTW + mw) + 4 * r + e, j)) acc[t][mw][e] = -INFINITY;
         }
-      // tiles that touch the window (causal limits) or the ragged tail, and tiles in which some logit
-      // runs away from its reference, take the careful path
-      const bool careful = row0 + 16 > prefix || __ballot(top > kWinRebase) != 0;
-      if (!careful) {
 #pragma unroll
         for (int mw = 0; mw < MTW; ++mw)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sum[mw][e] += __builtin_amdgcn_exp2f(x[mw][e]);
-      } else {
-        const int j = row0 + c;
-#pragma unroll
-        for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int row = 16 * (half * MTW + mw) + 4 * r + e;
-            const int in_window = row % window;                       // this row's query stands at prefix + in_window
-            const bool seen = row < n_rows && j <= prefix + in_window;
-            const float s = acc[mw][e] * log2_scale;
-            const float moved = fmaxf(ref[mw][e], s);
-            const float kept = sum[mw][e] * __builtin_amdgcn_exp2f(ref[mw][e] - moved) + __builtin_amdgcn_exp2f(s - moved);
-            sum[mw][e] = seen ? kept : sum[mw][e];
-            ref[mw][e] = seen ? moved : ref[mw][e];
-          }
+          for (int e = 0; e < 4; ++e) sum[mw][e] += __builtin_amdgcn_exp2f(fmaf(acc[t][mw][e], log2_scale, -ref[mw][e]));
       }
     } else {
-      float part = 0.f;
+      float part[2] = {0.f, 0.f};
 #pragma unroll
-      for (int mw = 0; mw < MTW; ++mw)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) part += __builtin_amdgcn_exp2f(fmaf(acc[mw][e], log2_scale, -ref[mw][e]));
-      part = sum_over_row_blocks(part);
+        for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part[t] += __builtin_amdgcn_exp2f(fmaf(acc[t][mw][e], log2_scale, -ref[mw][e]));
+      // sums over the row blocks of both tiles at once: the first tile's in lanes r = 0, 1, the second's in r = 2, 3
+      const u32x2_swap_t a = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[0]), __float_as_uint(part[1]), false, false);
+      const float x = __uint_as_float(a.x) + __uint_as_float(a.y);
+      const u32x2_swap_t b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      const int key = kWinStep * i + kWinTokTile * (r >> 1) + c;
       // two additions to a zero: the same sum whichever wave comes first
-      if (r == 0 && row0 + c < block_end) atomicAdd(&v_lds[row0 + c - block_row0], part);
+      if ((r & 1) == 0 && key < block_rows) atomicAdd(&v_lds[key], __uint_as_float(b.x) + __uint_as_float(b.y));
     }
-  };
-
-  // Barrier i makes the keys of step i visible and means both waves have finished reading those of step i - 1.
-  const int n_steps = (n_tiles + NT - 1) / NT;
-  // One step: products and arithmetic of its NT tiles, staging of step i + 1 (fetching step i + 3 behind it).
-  f32x4_t acc[NT][MTW];
-  auto step = [&](uint4 (&x_next)[2 * NT], int i) {
-    const unsigned char* xt = x_lds + (i & 1) * kWinStepLds;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) products(acc[nt], xt + nt * kWinTileLds);
-    stage_step(x_next, (i + 1) & 1);               // past the last step: rows nobody reads
-    load_step(x_next, i + 3);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) finish(acc[nt], NT * i + nt);
     __syncthreads();
   };
   load_step(xa, 0);
@@ -260,18 +259,58 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   stage_step(xa, 0);
   load_step(xa, 2);
   __syncthreads();
-  int i = 0;
 #pragma unroll 1
-  for (; i + 1 < n_steps; i += 2) {
-    step(xb, i);                                   // stages the odd step i + 1
-    step(xa, i + 1);
+  for (int i = 0; i < n_steps; i += 2) {   // (no break: one way out of the loop keeps one set of sums)
+    step(xb, i, 0);                        // stages the odd step i + 1
+    if (i + 1 < n_steps) step(xa, i + 1, 1);
   }
-  if (i < n_steps) step(xb, i);
+  if (kPass == 1) {
+    // A sum that left the range (logits 100 binary orders above the reference, or a reference that is infinite) is taken
+    // again, with references that follow the largest logit and the keys straight from memory.
+    bool lost = false;
+#pragma unroll
+    for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lost |= !(sum[mw][e] < kWinMostSum);
+    if (__builtin_expect(__ballot(lost) != 0ull, 0)) {
+#pragma unroll
+      for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ref[mw][e] = kWinNoRef;
+          sum[mw][e] = 0.f;
+        }
+#pragma unroll 1
+      for (int row0 = 0; row0 < block_rows; row0 += kWinTokTile) {
+        f32x4_t acc[MTW];
+#pragma unroll
+        for (int mw = 0; mw < MTW; ++mw) acc[mw] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        const uint4* key = reinterpret_cast<const uint4*>(Kh + (size_t)min(row0 + c, block_rows - 1) * 256);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, key[ks * 4 + r]);
+#pragma unroll
+          for (int mw = 0; mw < MTW; ++mw)
+            acc[mw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfrag[mw][ks], xv, acc[mw], 0, 0, 0);
+        }
+#pragma unroll
+        for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool seen = sees(16 * (half * MTW + mw) + 4 * r + e, block_row0 + row0 + c);
+            const float s = acc[mw][e] * log2_scale;
+            const float moved = fmaxf(ref[mw][e], s);
+            const float kept = sum[mw][e] * __builtin_amdgcn_exp2f(ref[mw][e] - moved) + __builtin_amdgcn_exp2f(s - moved);
+            sum[mw][e] = seen ? kept : sum[mw][e];
+            ref[mw][e] = seen ? moved : ref[mw][e];
+          }
+      }
+    }
+  }
 
   if (kPass == 2) {
     // Scores of the block's own keys: centred pooling over the votes inside the prefix (votes are non-negative and
-    // the slots outside hold zeros, which change neither rule), group mean, +inf on window tokens.  The last
-    // barrier of the loop has made all votes visible.
+    // the slots outside hold zeros, which change neither rule), group mean, +inf on window tokens.  
     const float inv_width = 1.f / (float)(2 * reach + 1);
     for (int j = own_row0 + (int)threadIdx.x; j < own_end; j += kWinThreads) {
       float sc = INFINITY;
@@ -296,6 +335,13 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
     }
   }
   if (kPass == 1) {
+    if (block_row0 + kWinTokTile > prefix + 1) {   // uniform: some row does not see some lane's first key, so none of its keys
+#pragma unroll
+      for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!sees(16 * (half * MTW + mw) + 4 * r + e, block_row0 + c)) ref[mw][e] = kWinNoRef;
+    }
     // one (reference, sum) pair per row: merge the 16 token lanes
     float* part = tab.partial[seq] + (part_row0 + (size_t)chunk * RP) * 2;
 #pragma unroll
@@ -362,15 +408,13 @@ template <int MTW>
 static void launch_passes(const WinTable& tab, int heads, int window, int n_rows, int rows_per_block, float log2_scale,
                           int reach, int pool_kind, float inv_group, hipStream_t stream) {
   const int blocks = tab.first[tab.n];
-  const size_t lds1 = 2 * kWinStepLds;
-  const size_t lds2 = lds1 + kWinVoteSlots * sizeof(float);
   if (tab.lse[0] == nullptr) {   // all sequences of a call come with normalisers, or none does
-    hipLaunchKernelGGL((score_window_kernel<MTW, 1>), dim3(blocks), dim3(kWinThreads), lds1, stream, tab, heads, window,
+    hipLaunchKernelGGL((score_window_kernel<MTW, 1>), dim3(blocks), dim3(kWinThreads), 0, stream, tab, heads, window,
                        n_rows, rows_per_block, log2_scale, 0, 0, 0.f);
     hipLaunchKernelGGL(score_window_merge_kernel, dim3(tab.n * heads), dim3(128), 0, stream, tab, heads, n_rows,
                        rows_per_block, 32 * MTW);
   }
-  hipLaunchKernelGGL((score_window_kernel<MTW, 2>), dim3(blocks), dim3(kWinThreads), lds2, stream, tab, heads, window,
+  hipLaunchKernelGGL((score_window_kernel<MTW, 2>), dim3(blocks), dim3(kWinThreads), 0, stream, tab, heads, window,
                      n_rows, rows_per_block, log2_scale, reach, pool_kind, inv_group);
 }
 

@@ -378,3 +378,30 @@ def test_long_context_sampled_heads(ctx):
         Kb = G.bf16_gpu_to_bits(k[l, h])[None, None]
         Qb = G.bf16_gpu_to_bits(q[l, h * grp:(h + 1) * grp])[None]
         check_against_oracle(one[l, h][None, None].cpu().numpy(), Kb, Qb, window, 7, lkv.POOL_AVG, what=f"layer {l} head {h}, given normalisers")
+
+
+@pytest.mark.parametrize("prefix", [127, 128, 129, 142, 143, 144, 145, 159, 160, 161])
+@pytest.mark.parametrize("window", [3, 33])
+def test_blocks_that_begin_around_the_window(ctx, prefix, window):
+    # Blocks are 128 keys here, their references the logits of their first 16 keys, steps 32 keys: the prefix ends just
+    # before, inside and after the first tile and step of the second block, where some lanes see no key at all.
+    rng = np.random.default_rng(900 + prefix + window)
+    T = prefix + window
+    K = W.f32_to_bf16_bits(rng.standard_normal((1, 2, T, 128)).astype(np.float32))
+    Q = W.f32_to_bf16_bits(rng.standard_normal((1, 4, window, 128)).astype(np.float32))
+    _, s = run_gpu(ctx, [K], [Q], 4, window, 5, lkv.POOL_MAX)
+    check_against_oracle(s[0].cpu().numpy(), K, Q, window, 5, lkv.POOL_MAX, what=f"prefix {prefix} window {window}")
+
+
+@pytest.mark.parametrize("reach", [60, 99, 101, 126, 130, 400, -60, -101, -400])
+def test_either_side_of_the_limit_of_the_sums(ctx, reach):
+    # One key late in each block of 128 whose logit lies `reach` binary orders from the others' (about 0): sums against
+    # the first keys up to 2^100 stand, larger ones are taken again; far below, the key's weight vanishes.
+    rng = np.random.default_rng(77)
+    window, T = 8, 400
+    K = 0.02 * rng.standard_normal((1, 1, T, 128)).astype(np.float32)
+    Q = np.abs(rng.standard_normal((1, 2, window, 128)).astype(np.float32)) + 0.5
+    K[0, 0, 100::128] = reach / np.log2(np.e) / G.SCALE / Q.sum(axis=-1).mean()
+    K, Q = W.f32_to_bf16_bits(K), W.f32_to_bf16_bits(Q)
+    _, s = run_gpu(ctx, [K], [Q], 2, window, 1, lkv.POOL_MAX)
+    check_against_oracle(s[0].cpu().numpy(), K, Q, window, 1, lkv.POOL_MAX, what=f"reach {reach}")
