@@ -21,8 +21,10 @@
 // type's lowest: 88 us, 1.5 ms by halving the bracket that such values stretch.)
 // fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
 // Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
-// (they stay in L2).  256 vectors of 16384 fp32 values: 35 us (257 us for the LDS sort
-// and logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).
+// (they stay in L2).  256 vectors of 16384 fp32 values: 30.4 us (257 us for the LDS sort and logarithmic scans this
+// replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).  Of the 30: read and extremes 3.5,
+// histogram 3, two trials 4.5, fp64 pass 9.5, root 1.5, outputs the rest.  Row swaps and prefix sums on the vector ALU, fp32
+// where it only places the bracket, and a root without hypot: 32.6 -> 30.4 us; 4096 values 17.5 -> 15.7, 777 9.9 -> 8.8.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -46,6 +48,7 @@ constexpr int kStSearchSteps = 48;        // fp32 trials at most (bisection alon
 constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
 constexpr double kStCoarse = 1e15;         // |z| from which fp64 no longer resolves tenths of a unit
 constexpr double kStMost = 1e300;         // centre of the search at most: its multiples do not overflow
+constexpr double kStTinyProduct = 1e-250; // products of two sums below this have lost digits, or may have
 constexpr double kStTiny = 1e-280;        // sums below this have lost (or may have lost) terms to underflow
 
 // In a batched launch block b works on vector b: rows of x, y and info, and its own target sum, which the paper
@@ -70,6 +73,11 @@ struct StMin {
   __device__ __forceinline__ double operator()(double a, double b) const { return fmin(a, b); }
 };
 
+struct StMax {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+  __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+
 template <int kCtrl, typename V>
 __device__ __forceinline__ V st_dpp(V x) {
   if constexpr (sizeof(V) == 4) {
@@ -91,12 +99,42 @@ __device__ __forceinline__ V st_row16(V x, Op op) {
   return op(x, st_dpp<kDppRowMirror>(x));
 }
 
-// over the wave: the rows, then the four rows (operands in the same order in every lane)
+// x of this lane's row of 16 and of the row beside it (kRows = 16), or of both halves of the wave (32), in either order:
+// swaps on the vector ALU, where a shuffle waits for the LDS crossbar
+template <int kRows, typename V, typename Op>
+__device__ __forceinline__ V st_join(V x, Op op) {
+  auto swapped = [](unsigned u) {
+    if constexpr (kRows == 16) return __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    else return __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  };
+  if constexpr (sizeof(V) == 4) {
+    const u32x2_swap_t a = swapped(__builtin_bit_cast(unsigned, x));
+    return op(__builtin_bit_cast(V, (unsigned)a.x), __builtin_bit_cast(V, (unsigned)a.y));
+  } else {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const u32x2_swap_t lo = swapped((unsigned)u), hi = swapped((unsigned)(u >> 32));
+    return op(__builtin_bit_cast(V, ((unsigned long long)hi.x << 32) | lo.x),
+              __builtin_bit_cast(V, ((unsigned long long)hi.y << 32) | lo.y));
+  }
+}
+// over the wave: the rows, then the four rows
 template <typename V, typename Op>
 __device__ __forceinline__ V st_wave(V x, Op op) {
-  x = st_row16(x, op);
-  x = op(x, __shfl_xor(x, 16, 64));
-  return op(x, __shfl_xor(x, 32, 64));
+  return st_join<32>(st_join<16>(st_row16(x, op), op), op);
+}
+
+// inclusive prefix sum over the wave: four shifts within the rows of 16 lanes, then the last lane of a row joins those after
+template <int kCtrl, int kRows>
+__device__ __forceinline__ unsigned st_dpp_add(unsigned x) {
+  return x + (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xf, true);
+}
+__device__ __forceinline__ unsigned st_scan(unsigned x) {
+  x = st_dpp_add<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8 (zeros move in)
+  x = st_dpp_add<0x112, 0xf>(x);
+  x = st_dpp_add<0x114, 0xf>(x);
+  x = st_dpp_add<0x118, 0xf>(x);
+  x = st_dpp_add<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  return st_dpp_add<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
 }
 
 // Per-wave results of up to five values; two copies used in turn, so that one barrier per reduction is enough (a wave
@@ -164,6 +202,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
                  int32_t* __restrict__ budgets, double t, const double* __restrict__ k_vec) {
   constexpr bool kHeld = kE > 0;
   constexpr int kR = kHeld ? kE : 1;
+  constexpr bool kKeep = kHeld && kE * (int)sizeof(X) <= 32;   // the inputs stay in registers to the end (16 fp32 ones beside the exponentials: 0.4 us slower)
   constexpr double kLog2E = 1.44269504088896340736, kLn2 = 0.693147180559945309417;
   __shared__ StScratch sh;
   __shared__ StHist<kT> hist;
@@ -178,8 +217,8 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
 
   // ---- where to look: the value of rank k, by histograms of the inputs that narrow to one bin ----
   double lo, hi, zc;   // bracket of the threshold; centre of the search
+  X xr[kR];
   {
-    X xr[kR];
     if constexpr (kHeld) {
 #pragma unroll
       for (int e = 0; e < kR; ++e) xr[e] = x[min(tid + e * kT, n - 1)];   // padding repeats the last value
@@ -194,8 +233,8 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
 #pragma unroll 4
         for (int i = tid; i < n; i += kT) { small = x[i] < small ? x[i] : small; large = x[i] > large ? x[i] : large; }
       }
-      least = st_wave((double)small, StMin());
-      most = st_wave(-(double)large, StMin());
+      least = (double)st_wave(small, StMin());
+      most = -(double)st_wave(large, StMax());
     }
     auto& v = sh.v[turn];
     if (writer) { v[0][wave] = least; v[1][wave] = most; }
@@ -206,8 +245,10 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
     // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
     moderate = moderate && least > -INFINITY && most < INFINITY;
-    lo = st_uniform(least / tau - 1.0 - fmax(0.0, log((double)n / (2.0 * ((double)n - k)))));
-    hi = st_uniform(most / tau + 1.0 + fmax(0.0, log((double)n / (2.0 * k))));
+    // (logarithms in fp32, a thousandth to spare)
+    auto margin = [&](double part) { return 1.001 + (double)fmaxf(0.f, (float)kLn2 * __log2f((float)n / (2.f * (float)part))); };
+    lo = st_uniform(least / tau - margin((double)n - k));
+    hi = st_uniform(most / tau + margin(k));
     constexpr int kBins = StHist<kT>::kBins;
     double above = 0.0;   // values in higher bins
     auto for_each = [&](auto visit) {
@@ -230,16 +271,11 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       // from the top: thread t owns bins kBins - 1 - 2 t and kBins - 2 - 2 t
       const int top = kBins - 1 - 2 * tid;
       const unsigned c0 = hist.bin[top], c1 = hist.bin[top - 1];
-      unsigned incl = c0 + c1;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const unsigned below = __shfl_up(incl, d, 64);
-        if ((tid & 63) >= d) incl += below;
-      }
+      const unsigned incl = st_scan(c0 + c1);
       if ((tid & 63) == 63) hist.wave_total[wave] = incl;
       __syncthreads();
-      unsigned before = 0;
-      for (int w = 0; w < wave; ++w) before += hist.wave_total[w];
+      const int l = tid & 15;
+      const unsigned before = st_row16(l < wave && l < kT / 64 ? hist.wave_total[l] : 0u, StAdd());
       const double e0 = above + (double)(before + incl - c0 - c1);
       if (c0 != 0 && e0 < k && k <= e0 + c0) { hist.found = top; hist.above = e0; }
       if (c1 != 0 && e0 + c0 < k && k <= e0 + c0 + c1) { hist.found = top - 1; hist.above = e0 + c0; }
@@ -254,7 +290,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     for (int level = 0; level < kStLevels && looking; ++level) {
       clear();
       const double width = st_uniform(span * (kStWiden / (double)kBins));
-      const float to_bin = (float)(1.0 / width);
+      const float to_bin = 1.f / (float)width;
       for_each([&](X xv, bool in) {
         const float f = (float)(xv - (X)base) * to_bin;
         // the first level takes every value; the next ones the values of the bin found before
@@ -304,7 +340,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     if constexpr (kHeld) {
 #pragma unroll
       for (int e = 0; e < kR; ++e)   // the vector is in the caches by now; padding lies infinitely far down the tail
-        w[e] = tid + e * kT < n ? (float)fma((double)x[min(tid + e * kT, n - 1)], scale, shift) : -INFINITY;
+        w[e] = tid + e * kT < n ? (float)fma((double)(kKeep ? xr[e] : x[min(tid + e * kT, n - 1)]), scale, shift) : -INFINITY;
     }
     float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
     // nothing to search for at a centre that itself rounds to about a unit
@@ -385,7 +421,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
 #pragma unroll
       for (int e = 0; e < kR; ++e) {
         const int i = first + e * kT;
-        const double z = st_quotient(x[min(i, n - 1)], tau, rtau, moderate);
+        const double z = st_quotient(kKeep ? xr[e] : x[min(i, n - 1)], tau, rtau, moderate);
         ex[e] = visit(i < n ? z : -INFINITY);
         if (e & 1) __builtin_amdgcn_sched_barrier(0);   // two exponentials at a time fit the registers
       }
@@ -430,7 +466,8 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       factor = exp(delta);   // used for the outputs below only where the trial lies near the middle of the gap
     } else {
       // the root without a difference of close numbers; a = 0 (empty head) and b = 0 (empty tail) come out as they should
-      const double root = hypot(d, 2.0 * sqrt(a) * sqrt(b));
+      const double ab = a * b;
+      const double root = ab > kStTinyProduct ? sqrt(fma(d, d, 4.0 * ab)) : hypot(d, 2.0 * sqrt(a) * sqrt(b));
       factor = d >= 0.0 ? 2.0 * b / (d + root) : (root - d) / (2.0 * a);
       delta = log(factor);
     }
