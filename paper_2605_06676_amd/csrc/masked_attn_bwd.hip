@@ -354,18 +354,21 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // kGroups = 1: eight waves of 32 keys, each takes every step of 32 queries.  kGroups = 2: four times 32 keys, two waves
 // take the steps in turn and their sums are joined at the end, which halves the chain of steps per key (short sequences).
 //
-// Bound by instruction issue (see the counters below) and, for long sequences, by the power that the products draw.  A step
-// is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S and dP of
-// the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps exponentials
-// beside products.  32 keys per wave need 128 accumulator and 32 K operand registers; V operands come from LDS, 48 KB are
-// read per 64 matrix instructions.  256 registers are just enough, and only so: one loop with one way out (with breaks or a
-// second loop for the diagonal the compiler keeps several sets of sums, and spills), masks set in place in a branch
-// around nothing else, addresses worked out where they are used.  32 query heads, 8 KV heads, in turn with a kernel that did one
-// thing after the other: 4.59 -> 4.20 ms at 16384 tokens, 136 -> 130 us at 2345 (kGroups = 2); 8 and 8 heads of 4096 140 ->
-// 127.  Measured and dropped: 16 keys per wave with V in registers (64 KB of operands per 64 matrix instructions, LDS busy
+// Bound by instruction issue (see the counters below) and, for long sequences, by the power that the products draw.  A
+// step is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S
+// and dP of the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps
+// exponentials beside products.  Operands are read a piece ahead, also from one half to the next, into the products and on
+// to the next step (without that over these seams: 4.37 ms instead of 4.19 at 16384 tokens, 129 us instead of 126 at 2345,
+// 127 instead of 120 for 8 and 8 heads of 4096).  32 keys per wave need 128 accumulator and 32 K operand registers; V
+// operands come from LDS, 48 KB are read per 64 matrix instructions.  256 registers are just enough, and only so: one loop
+// with one way out (with breaks or a second loop for the diagonal the compiler keeps several sets of sums, and spills),
+// masks set in place in a branch around nothing else, addresses worked out where they are used.  32 query heads, 8 KV
+// heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at 2345
+// (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the products
+// (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix instructions, LDS busy
 // 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the channels of dK and dV
-// and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at 16384), four waves and
-// 128 keys a block, two blocks per compute unit (143 us and 4.9 ms).
+// and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at 16384), four waves and 128
+// keys a block, two blocks per compute unit (143 us and 4.9 ms).
 template <int kGroups>
 __global__ void __launch_bounds__(kDkvThreads, 2)
 masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -496,9 +499,16 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
       }
     }
   };
-  // dV += P^T dO and dK += dS^T Q: B operands from the dO and Q rows by the transposing read
-  auto products = [&](const unsigned char* rows) __attribute__((always_inline)) {
-    bf16x8_t gb = mb_read_turned(rows + kMbStep * kDkvRow + turned), qb = mb_read_turned(rows + turned);
+  bf16x8_t gx, qx, vx0, vx1;   // operands of the next products of S and dP, on their way
+  auto first_operands = [&](const unsigned char* rows) __attribute__((always_inline)) {   // those of a step's last 16 queries
+    gx = mb_read_straight(rows + (kMbStep + 16) * kDkvRow + straight);
+    qx = mb_read_straight(rows + 16 * kDkvRow + straight);
+    vx0 = mb_read_straight(v_rows + v_straight);
+    vx1 = mb_read_straight(v_rows + v_straight + 16 * kDkvRow);
+  };
+  // dV += P^T dO and dK += dS^T Q: B operands from the dO and Q rows by the transposing read, gb and qb the first of them;
+  // the first operands of the step that follows come after the last
+  auto products = [&](const unsigned char* rows, bf16x8_t gb, bf16x8_t qb, const unsigned char* next) __attribute__((always_inline)) {
     auto tile = [&](auto ct_tag) __attribute__((always_inline)) {
       constexpr int ct = decltype(ct_tag)::value;
       bf16x8_t g1, q1;
@@ -506,6 +516,8 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
         const uint32_t at = address_xor<32 * (ct + 1)>(turned);
         g1 = mb_read_turned(rows + kMbStep * kDkvRow + at);
         q1 = mb_read_turned(rows + at);
+      } else {
+        first_operands(next);
       }
 #pragma unroll
       for (int kb = 0; kb < kDkvKB; ++kb) {
@@ -541,14 +553,15 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     da = __builtin_bit_cast(uint32_t, b);
     asm volatile("" : "+v"(pa), "+v"(da), "+v"(dm_acc[kb]));   // due here, beside the products
   };
-  // One step of the pipeline up to its products: P and dS of its first 16 queries beside S and dP of the others, theirs
-  // beside S and dP of the next step's first 16.  below: query less key of element 0 of key block 0 in this lane.
+  // One step of the pipeline: P and dS of its first 16 queries beside S and dP of the others, theirs beside S and dP of the
+  // next step's first 16, then the products.  below: query less key of element 0 of key block 0 in this lane.
   auto step = [&](const unsigned char* cur, const float* aux_cur, const unsigned char* next, const float* aux_next, bool diagonal, int below)
       __attribute__((always_inline)) {
     f32x4_t s1[kDkvKB], p1[kDkvKB];
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
+    bf16x8_t gb, qb;
+    auto half = [&](auto tt_tag) __attribute__((always_inline)) {
       // tt = 0: from sx, px of `cur` to s1, p1 of its second half; tt = 1: from those to sx, px of `next`
+      constexpr int tt = decltype(tt_tag)::value;
       if (diagonal) {   // wave-uniform: some key of the wave comes after some query of the step
 #pragma unroll
         for (int kb = 0; kb < kDkvKB; ++kb)
@@ -564,34 +577,44 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
       const float4 l4 = *reinterpret_cast<const float4*>(aux_cur + 16 * tt + 4 * r);
       const float lq[4] = {l4.x, l4.y, l4.z, l4.w};
       const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(tt == 0 ? aux_cur + kMbStep + 16 + 4 * r : aux_next + kMbStep + 4 * r);
-      bf16x8_t gx = mb_read_straight(g_at + straight), qx = mb_read_straight(q_at + straight);
-      bf16x8_t vx0 = mb_read_straight(v_rows + v_straight), vx1 = mb_read_straight(v_rows + v_straight + 16 * kDkvRow);
       auto part = [&](auto ks_tag) __attribute__((always_inline)) {
         constexpr int ks = decltype(ks_tag)::value;
         po[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx0, ks == 0 ? nd : po[0], 0, 0, 0);
         po[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx1, ks == 0 ? nd : po[1], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);   // the next operands after these products have taken theirs
-        uint32_t at = 0;
+        uint32_t at = straight;
         if constexpr (ks < 3) {
           at = address_xor<64 * (ks + 1)>(straight);
           const uint32_t v_at = address_xor<64 * (ks + 1)>(v_straight);
           gx = mb_read_straight(g_at + at);
           vx0 = mb_read_straight(v_rows + v_at);
           vx1 = mb_read_straight(v_rows + v_at + 16 * kDkvRow);
+        } else if constexpr (tt == 0) {
+          gx = mb_read_straight(next + kMbStep * kDkvRow + straight);
+          vx0 = mb_read_straight(v_rows + v_straight);
+          vx1 = mb_read_straight(v_rows + v_straight + 16 * kDkvRow);
+        } else {
+          gb = mb_read_turned(cur + kMbStep * kDkvRow + turned);
         }
 #pragma unroll
         for (int kb = 0; kb < kDkvKB; ++kb)
           so[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qx, kfrag[kb][ks], ks == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : so[kb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (ks < 3) qx = mb_read_straight(q_at + at);
+        else if constexpr (tt == 0) qx = mb_read_straight(next + straight);
+        else qb = mb_read_turned(cur + turned);
         if (tt == 0) pair(sx, px, lq, 0, ks >> 1, 2 * (ks & 1));
         else pair(s1, p1, lq, 1, ks >> 1, 2 * (ks & 1));
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ks < 3) qx = mb_read_straight(q_at + at);
       };
       part(std::integral_constant<int, 0>());
       part(std::integral_constant<int, 1>());
       part(std::integral_constant<int, 2>());
       part(std::integral_constant<int, 3>());
-    }
+    };
+    half(std::integral_constant<int, 0>());
+    half(std::integral_constant<int, 1>());
+    products(cur, gb, qb, next);
   };
   int q0 = q_last;   // first query of the current item
   const int lane_below = group * kMbStep + 4 * r - kw0 - c;
@@ -604,13 +627,13 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     fetch(fill);
     const int at = group * kDkvStepLds, aux_at = group * 2 * kMbStep;
     step(cur + at, aux_cur + aux_at, next + at, aux_next + aux_at, q0 + group * kMbStep < kw0 + kDkvWaveK, q0 + lane_below);
-    products(cur + at);
     put_aux(aux_fill);
     q0 = q0 > k0 ? q0 - kItemQ : q_last;
   };
   put_aux(aux_b);
   lds_fill_barrier();
   logits(slot_a + group * kDkvStepLds, aux_a + group * 2 * kMbStep, 0);
+  first_operands(slot_a + group * kDkvStepLds);
 #pragma unroll 1
   for (int it = 0; it < n_items; it += 3) {
     item(slot_a, aux_a, slot_b, aux_b, slot_c, aux_c);
