@@ -334,7 +334,6 @@ lkv_status lkv_score_window(lkv_ctx* ctx, const lkv_cache* cache, const void* co
   if (!(scale > 0.f) || !std::isfinite(scale)) return fail(ctx, LKV_ERR_INVALID_ARG, "scale must be positive and finite");
   const int G = cache->n_q_heads / cache->n_kv_heads;
   const int64_t heads = (int64_t)cache->n_layers * cache->n_kv_heads;
-  int64_t cells = 0;
   for (int s = 0; s < cache->n_seq; ++s) {
     if (window > cache->seq_len[s])
       return fail(ctx, LKV_ERR_INVALID_ARG, "window = %d exceeds seq_len[%d] = %d", window, s, cache->seq_len[s]);
@@ -345,14 +344,13 @@ lkv_status lkv_score_window(lkv_ctx* ctx, const lkv_cache* cache, const void* co
     if (scores[s] == nullptr || !aligned16(scores[s]))
       return fail(ctx, LKV_ERR_INVALID_ARG, "scores[%d] is NULL or not 16-byte aligned", s);
     if (lse_win != nullptr && lse_win[s] == nullptr) return fail(ctx, LKV_ERR_INVALID_ARG, "lse_win[%d] is NULL", s);
-    cells += heads * cache->seq_len[s];
   }
   if ((int64_t)G * window > lkv::score_window_max_rows())
     return fail(ctx, LKV_ERR_UNSUPPORTED, "group %d x window %d exceeds %d query rows per KV head", G, window,
                 lkv::score_window_max_rows());
   const size_t need = lkv_score_window_workspace_bytes(cache);
   if (lkv_status st = check_workspace(ctx, workspace, workspace_bytes, need, 256, "window scoring")) return st;
-  const int rpb = lkv::score_window_rows_per_block(cells);
+  const int rpb = lkv::score_window_rows_per_block(cache->seq_len, cache->n_seq, heads, G * window);
   hipStream_t st = as_stream(stream);
 
   // every sequence's blocks must fit one grid before anything is launched

@@ -48,9 +48,10 @@ constexpr int kWinTileLds = kWinTokTile * kWinRowStride;
 constexpr int kWinTilesPerStep = 2;     // tiles staged, multiplied and finished between two barriers
 constexpr int kWinStep = kWinTilesPerStep * kWinTokTile;
 constexpr int kWinStepLds = kWinTilesPerStep * kWinTileLds;
-constexpr int kWinMaxRowsPerBlock = 1024;
+constexpr int kWinManyRounds = 1024;             // keys of a block where the blocks go round several times (see below)
 constexpr int kWinMaxReach = 31;                // pooling widths up to 63
-constexpr int kWinVoteSlots = kWinMaxRowsPerBlock + 32 + kWinMaxReach + 17;   // pass 2: a block's keys, two tiles before, the reach after, rounded up to a tile
+// pass 2: a block's keys, two tiles before, the reach after, rounded up to a tile
+constexpr int win_vote_slots(int keys) { return keys + 32 + kWinMaxReach + 17; }
 constexpr float kWinMostSum = 1.2676506e30f;     // 2^100: sum beyond which pass 1 starts over with references that move
 constexpr float kWinNoRef = -1e30f;              // reference of a row that has seen no key yet
 
@@ -77,8 +78,8 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
                     int reach /* pass 2: pooling reach c, width 2 c + 1 */, int pool_kind, float inv_group) {
   constexpr int RP = 32 * MTW;                      // padded rows of the block
   __shared__ __align__(16) unsigned char x_lds[2 * kWinStepLds];   // the staged keys of two steps
-  // pass 2: the votes of the keys the block multiplies; both waves add the shares of their rows
-  __shared__ float v_lds[kPass == 2 ? kWinVoteSlots : 1];
+  // pass 2: the votes of the keys the block multiplies (win_vote_slots of rows_per_block); both waves add the shares of their rows
+  extern __shared__ float v_lds[];
 
   const int seq = win_seq_of_unit(tab, blockIdx.x);
   const int local = blockIdx.x - tab.first[seq];
@@ -110,7 +111,7 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   const int r = lane >> 4;
   const int c = lane & 15;
   if (kPass == 2)
-    for (int i = threadIdx.x; i < kWinVoteSlots; i += kWinThreads) v_lds[i] = 0.f;   // ordered by the barriers below
+    for (int i = threadIdx.x; i < block_rows; i += kWinThreads) v_lds[i] = 0.f;   // ordered by the barriers below
 
   // A fragments: window row 16 (half MTW + mw) + c, features 32 ks + 8 r .. +7
   bf16x8_t qfrag[MTW][4];
@@ -390,11 +391,35 @@ score_window_merge_kernel(WinTable tab, int heads, int n_rows, int rows_per_bloc
 
 int score_window_max_rows() { return 128; }
 
-int score_window_rows_per_block(int64_t tokens_times_heads) {
-  // large blocks amortise the query fragments each wave loads; small problems take smaller blocks so
-  // that the grid still covers the chip
-  int rows = kWinMaxRowsPerBlock;
-  while (rows > 128 && tokens_times_heads / rows < 2048) rows >>= 1;
+// Keys of a block.  A block has a fixed price, its query fragments and the first loads (some 3 us before it streams), and a
+// second round that is a small part of the first leaves the chip idle.  So, where blocks of up to 4096 keys (2048 with
+// fewer than 97 window rows) get there: as few keys as leave one round of 1024 blocks, four on each of 256 compute units, or
+// 5/8 of one while they have under 256 keys.  More keys than that go round several times, 1024 at a time: the rounds mix, and
+// the votes of longer blocks take LDS that more of pass 2's would fit in (given the normalisers, 32 layers of 32768 keys:
+// 2048 keys a block 419 -> 453 us).
+// 8 heads, 128 window rows, both passes, against the power of two that gives 2048 blocks, 1024 keys at the most: 32768 keys of
+// one layer 74 -> 53 us, 131071 169 -> 123, of 8 layers 232 -> 202, of 16 440 -> 408; 12001 of one 39.9 -> 37.4, 16384 42.5 ->
+// 38.4, 9001 of 32 253 -> 222, 60001 of 8 405 -> 371.  With 64 window rows 32768 keys of 5 layers 125 -> 118; with 16, given
+// the normalisers, of 8 layers 97 -> 93.  5/8 and not less: 8193 keys of one layer take 32.6 with 520 blocks of 128 keys, 35.4
+// with 344 of 192.
+int score_window_rows_per_block(const int32_t* seq_len, int n_seq, int64_t heads, int n_rows) {
+  constexpr int64_t kRound = 1024;
+  constexpr int kUnit = 64;
+  const int mtw = (n_rows + 31) / 32;
+  const int most = mtw == 4 ? 4096 : 2048;
+  auto blocks = [&](int rows) {
+    int64_t n = 0;
+    for (int s = 0; s < n_seq; ++s) n += heads * (((int64_t)seq_len[s] + rows - 1) / rows);
+    return n;
+  };
+  if (blocks(most) > kRound) return kWinManyRounds;
+  int64_t keys = 0;
+  for (int s = 0; s < n_seq; ++s) keys += heads * seq_len[s];
+  int rows = 128;
+  while (rows < 256 && blocks(rows) > kRound * 5 / 8) rows += kUnit;
+  const int share = (int)(keys / kRound) / kUnit * kUnit;   // below this no split fits
+  if (rows < share) rows = share;
+  while (rows < most && blocks(rows) > kRound) rows += kUnit;
   return rows;
 }
 
@@ -414,8 +439,9 @@ static void launch_passes(const WinTable& tab, int heads, int window, int n_rows
     hipLaunchKernelGGL(score_window_merge_kernel, dim3(tab.n * heads), dim3(128), 0, stream, tab, heads, n_rows,
                        rows_per_block, 32 * MTW);
   }
-  hipLaunchKernelGGL((score_window_kernel<MTW, 2>), dim3(blocks), dim3(kWinThreads), 0, stream, tab, heads, window,
-                     n_rows, rows_per_block, log2_scale, reach, pool_kind, inv_group);
+  hipLaunchKernelGGL((score_window_kernel<MTW, 2>), dim3(blocks), dim3(kWinThreads),
+                     win_vote_slots(rows_per_block) * sizeof(float), stream, tab, heads, window, n_rows, rows_per_block,
+                     log2_scale, reach, pool_kind, inv_group);
 }
 
 // `tab.first` counts the blocks of the passes (the same grid for both).

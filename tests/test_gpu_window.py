@@ -405,3 +405,37 @@ def test_either_side_of_the_limit_of_the_sums(ctx, reach):
     K, Q = W.f32_to_bf16_bits(K), W.f32_to_bf16_bits(Q)
     _, s = run_gpu(ctx, [K], [Q], 2, window, 1, lkv.POOL_MAX)
     check_against_oracle(s[0].cpu().numpy(), K, Q, window, 1, lkv.POOL_MAX, what=f"reach {reach}")
+
+
+@pytest.mark.parametrize("L,H,grp,window,T", [
+    (1, 8, 4, 32, 12001),      # one round of short blocks: 192 keys
+    (1, 8, 4, 32, 30001),      # 256 and, as for all that follow, blocks that end inside the last tile
+    (4, 8, 4, 32, 40001),      # 1280: more than blocks that go round several times have
+    (16, 8, 4, 32, 32768),     # 4096 keys, the longest
+    (16, 8, 4, 32, 32769),     # one key more than a round of those: 1024
+    (8, 8, 1, 16, 16384),      # few window rows: 1024, and the longest of 2048
+    (8, 8, 1, 16, 32768),
+])
+def test_blocks_of_one_round_and_of_several(ctx, L, H, grp, window, T):
+    k = torch.randn((L, H, T, 128), dtype=torch.bfloat16, device="cuda")
+    q = torch.randn((L, H * grp, window, 128), dtype=torch.bfloat16, device="cuda")
+    cache = lkv.Cache([k], [k], H * grp)
+    s = torch.full((L, H, T), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(lkv.lkv_score_window_workspace_bytes(cache), dtype=torch.uint8, device="cuda")
+    lkv.lkv_score_window(ctx, cache, [q], window, 63, lkv.POOL_AVG, G.SCALE, [s], ws)
+    torch.cuda.synchronize()
+    assert torch.isinf(s[..., T - window:]).all() and torch.isfinite(s[..., :T - window]).all()
+    # the votes themselves, in every head
+    plain = torch.empty_like(s)
+    lkv.lkv_score_window(ctx, cache, [q], window, 1, lkv.POOL_AVG, G.SCALE, [plain], ws)
+    for l in range(L):
+        logits = torch.matmul(q[l].float().reshape(H, grp * window, 128), k[l].float().transpose(1, 2).contiguous()) * G.SCALE
+        row = torch.arange(window, device="cuda").repeat(grp)
+        logits.masked_fill_(torch.arange(T, device="cuda")[None, None] > (T - window + row)[None, :, None], float("-inf"))
+        vote = torch.softmax(logits, dim=-1).sum(dim=1)[:, :T - window] / grp
+        # fp32 logits of 128 products each (relative 2^-24 * 128 of terms of a few units) on both sides
+        torch.testing.assert_close(plain[l, :, :T - window], vote, rtol=1e-4, atol=1e-9)
+    for l, h in ((0, 0), (L - 1, H - 1)):
+        Kb = G.bf16_gpu_to_bits(k[l, h])[None, None]
+        Qb = G.bf16_gpu_to_bits(q[l, h * grp:(h + 1) * grp])[None]
+        check_against_oracle(s[l, h][None, None].cpu().numpy(), Kb, Qb, window, 63, lkv.POOL_AVG, what=f"layer {l} head {h}")
