@@ -134,22 +134,6 @@ lkv_status check_attention_geometry(lkv_ctx* ctx, int32_t n_q_heads, int32_t n_k
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-// Rows per block of an MLP scoring launch over one sequence and few heads (one layer at a time).  Every wave starts by
-// loading the hidden layer's weights, so the launch takes as many blocks as the chip holds at once and not a second,
-// shorter round: 512 blocks of four waves (hidden widths up to 64), 1024 of two.  8 heads, hidden width 64: 131072
-// tokens 81.9 us with tiles of a power of two for at least 1024 blocks, 77.6 us with this; 40000 tokens 41.9 and 29.5 us;
-// 32768 tokens 31.6 and 26.2 us; width 128, 100000 tokens 108.7 and 93.1 us.  Launches too large for one round of the
-// longest tiles keep the tiles they have (nothing in it: 32 heads of 200000 444 us both ways), as do heads so short that a
-// tile would fall under 256 rows.
-int score_mlp_rows_alone(int T, int heads, int hidden) {
-  const int rows = lkv::score_mlp_rows_per_block(T, heads, hidden);
-  const int resident = hidden > 64 ? 1024 : 512;
-  if (heads > resident) return rows;
-  const int tiles = resident / heads;
-  const int64_t even = (((int64_t)T + tiles - 1) / tiles + 63) / 64 * 64;
-  return even >= 256 && even <= (hidden > 64 ? 2048 : 4096) ? (int)even : rows;
-}
-
 // lkv_score, optionally counting the first-level top-k digits of every segment on the way (counts zero on entry).
 // The segment of (sequence s, view head j) is seg_base + s * seg_stride + j.
 lkv_status score_impl(lkv_ctx* ctx, const lkv_cache* cache, const lkv_scorer* scorer, float* const* scores,
@@ -166,29 +150,19 @@ lkv_status score_impl(lkv_ctx* ctx, const lkv_cache* cache, const lkv_scorer* sc
   const int heads_per_row = scorer->per_head ? 1 : cache->n_kv_heads;
   hipStream_t st = as_stream(stream);
 
-  // launches of up to kMaxSeqPerLaunch sequences; MLP launches also need one tile size per launch
+  // launches of up to kMaxSeqPerLaunch sequences; the MLP kernels take tiles of one size
+  const int rpb = scorer->kind == LKV_SCORER_MLP
+                      ? lkv::score_mlp_rows_per_block(cache->seq_len, cache->n_seq, heads, scorer->hidden) : 0;
   int s = 0;
   while (s < cache->n_seq) {
     lkv::SeqTable tab;
     memset(&tab, 0, sizeof(tab));
     int64_t blocks = 0;
     const int s_first = s;
-    const bool alone = cache->n_seq == 1;   // several sequences of unlike lengths share a launch only with the common tile sizes
-    auto rows_per_block = [&](int T) {
-      return alone ? score_mlp_rows_alone(T, (int)heads, scorer->hidden)
-                   : lkv::score_mlp_rows_per_block(T, (int)heads, scorer->hidden);
-    };
-    const int rpb0 = scorer->kind == LKV_SCORER_MLP ? rows_per_block(cache->seq_len[s]) : 0;
     int n = 0;
     while (s < cache->n_seq && n < lkv::kMaxSeqPerLaunch) {
       const int T = cache->seq_len[s];
-      int64_t per_head;
-      if (scorer->kind == LKV_SCORER_MLP) {
-        if (rows_per_block(T) != rpb0) break;
-        per_head = (T + rpb0 - 1) / rpb0;
-      } else {
-        per_head = lkv::score_linear_blocks_per_head(T);
-      }
+      const int64_t per_head = scorer->kind == LKV_SCORER_MLP ? ((int64_t)T + rpb - 1) / rpb : lkv::score_linear_blocks_per_head(T);
       if (blocks + per_head * heads >= ((int64_t)1 << 31) - 1) {
         if (n == 0) return fail(ctx, LKV_ERR_UNSUPPORTED, "sequence %d is too long for one launch", s);
         break;
@@ -220,7 +194,7 @@ lkv_status score_impl(lkv_ctx* ctx, const lkv_cache* cache, const lkv_scorer* sc
       }
     } else {
       lkv::launch_score_mlp(tab, static_cast<const uint16_t*>(scorer->w1), scorer->b1, scorer->w2, scorer->b2,
-                            scorer->hidden, scorer->act == LKV_ACT_SILU ? 0 : 1, heads_per_row, rpb0, st, counts,
+                            scorer->hidden, scorer->act == LKV_ACT_SILU ? 0 : 1, heads_per_row, rpb, st, counts,
                             launch_seg_base, seg_stride);
     }
     if (hipError_t e = hipGetLastError()) return hip_fail(ctx, e, "lkv_score launch");

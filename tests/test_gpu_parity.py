@@ -93,6 +93,17 @@ def test_mlp_tiles_that_fill_one_round_of_blocks(ctx, L, H, hidden, T):
     _run_and_check(ctx, w, [T], seed=9, what=f"one round {L}x{H} {hidden} {T}")
 
 
+@pytest.mark.parametrize("L,H,hidden,Ts", [(1, 8, 64, [9001, 3000, 17]),        # one tile size for all: 448 rows
+                                           (1, 8, 64, [40960]), (1, 8, 64, [40961]),   # the most of a block to itself, one more
+                                           (1, 8, 128, [12288]), (1, 8, 128, [12289]),
+                                           (1, 4, 128, [30001, 257]),             # the two-wave blocks, one round
+                                           (16, 32, 64, [1300, 700, 300])])       # several rounds
+def test_mlp_tiles_over_all_sequences(ctx, L, H, hidden, Ts):
+    w = W.scaled(W.CONFIGS[3], L=L, H=H, Hq=H, T=max(Ts), hidden=hidden, act="silu", per_head=False, b_min=1)
+    budgets = [[max(1, T // 40)] * (L * H) for T in Ts]
+    _run_and_check(ctx, w, Ts, seed=17, budgets=budgets, what=f"{L} x {H} heads of {Ts}, hidden width {hidden}")
+
+
 def test_mlp_without_output_bias_and_heavy_tails(ctx):
     w = W.scaled(W.CONFIGS[4], L=2, H=2, Hq=14, T=2500, n_seq=2, b_min=8)
     K, V, Q, sc, B = _inputs(w, [2500, 2500])
