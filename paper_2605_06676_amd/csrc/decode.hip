@@ -24,7 +24,7 @@
 // tells its block which segment and which rows are its own.  The grid is the most chunks that any split of the rows
 // over the segments can give.  (8 heads, 5 thousand rows, in a captured graph: 11.4 us with flat chunks, 8.7 us with
 // these; 40 thousand rows 18.1 and 13.4 us, 160 thousand 29.6 and 25.8 us; one head with nearly all of 5 thousand rows
-// 17.8 and 10.6 us.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
+// 17.8 and 10.6 us; since the merge shares a segment's pieces out among threads, 9.3, 10.8 and 18.8.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
 // one round of resident blocks however the rows are spread; with 256 segments of 5 thousand rows each the ends of the
 // segments would need a second round.
 //
@@ -386,14 +386,19 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
 // ceil(G * 128 / 256) blocks.  The kernel is a short chain of dependent memory latencies, so
 // the partials of up to eight pieces are loaded together and folded in with a running maximum:
 // the chain is the offsets load plus one round per eight pieces.
-template <bool kAligned>
-__global__ void __launch_bounds__(kDecThreads)
+// kParts > 1, for segments of many pieces: a block of kParts times 128 threads for every query head, the pieces of an
+// element shared out among kParts threads, whose sums meet in LDS: one round per 8 kParts pieces.
+constexpr int decode_merge_threads(int parts) { return parts == 1 ? kDecThreads : parts * kHeadDim; }
+template <bool kAligned, int kParts>
+__global__ void __launch_bounds__(decode_merge_threads(kParts))
 decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths, int n_segments, int G,
                     int blocks_per_segment, int chunk_rows,
                     const float* __restrict__ ws_acc, const float* __restrict__ ws_m,
                     const float* __restrict__ ws_l, float* __restrict__ out, float* __restrict__ lse) {
   const int s = blockIdx.x / blocks_per_segment;
-  const int o = (blockIdx.x - s * blocks_per_segment) * kDecThreads + threadIdx.x;
+  const int part = kParts == 1 ? 0 : threadIdx.x / kHeadDim;
+  const int o = kParts == 1 ? (blockIdx.x - s * blocks_per_segment) * kDecThreads + threadIdx.x
+                            : (blockIdx.x - s * blocks_per_segment) * kHeadDim + threadIdx.x % kHeadDim;
   AlignedChunk seg = {};
   if (kAligned) {
     int lo, hi, n, upto;   // by all lanes, before any leaves
@@ -417,7 +422,7 @@ decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restri
   if (c_first == c_last) return;   // a whole segment inside one chunk was finished by the first kernel
   constexpr int kU = 8;
   float mx = -INFINITY, num = 0.f, den = 0.f;
-  for (int c0 = c_first; c0 <= c_last; c0 += kU) {
+  for (int c0 = c_first + part * kU; c0 <= c_last; c0 += kParts * kU) {
     float mv[kU], lv[kU], av[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
@@ -440,6 +445,23 @@ decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restri
       const float wgt = c0 + u <= c_last ? fast_exp2(mv[u] - ref) : 0.f;
       num = fmaf(av[u], wgt, num);
       den = fmaf(lv[u], wgt, den);
+    }
+  }
+  if constexpr (kParts > 1) {
+    __shared__ float num_lds[kParts][kHeadDim], mx_lds[kParts], den_lds[kParts];
+    num_lds[part][ch] = num;
+    if (ch == 0) { mx_lds[part] = mx; den_lds[part] = den; }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int p = 1; p < kParts; ++p) mx = fmaxf(mx, mx_lds[p]);
+    const float ref = mx == -INFINITY ? 0.f : mx;
+    num = den = 0.f;
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+      const float wgt = fast_exp2(mx_lds[p] - ref);   // 0 for a part without pieces
+      num = fmaf(num_lds[p][ch], wgt, num);
+      den = fmaf(den_lds[p], wgt, den);
     }
   }
   out[row * kHeadDim + ch] = den > 0.f ? num / den : 0.f;
@@ -531,7 +553,6 @@ hipError_t launch_decode(int G, const void* q, const void* kp, const void* vp, c
   float* ws_acc = ws;
   float* ws_m = ws + slots * G * kHeadDim;
   float* ws_l = ws_m + slots * G;
-  const int blocks_per_segment = (G * kHeadDim + kDecThreads - 1) / kDecThreads;
   auto launch = [&](auto masked_tag, auto aligned_tag) {
     constexpr bool kMasked = decltype(masked_tag)::value, kAligned = decltype(aligned_tag)::value;
     const int chunk_rows = kAligned ? decode_aligned_chunk_rows(n_segments, total_kept) : decode_chunk_rows(total_kept);
@@ -542,8 +563,20 @@ hipError_t launch_decode(int G, const void* q, const void* kp, const void* vp, c
                          stream, reinterpret_cast<const uint16_t*>(q), reinterpret_cast<const uint4*>(kp),
                          reinterpret_cast<const uint4*>(vp), offsets, lengths, n_segments, total_kept, chunk_rows, G, scale,
                          out, lse, ws_acc, ws_m, ws_l, mask);
-    hipLaunchKernelGGL(decode_merge_kernel<kAligned>, dim3(n_segments * blocks_per_segment), dim3(kDecThreads), 0, stream,
-                       offsets, lengths, n_segments, G, blocks_per_segment, chunk_rows, ws_acc, ws_m, ws_l, out, lse);
+    auto merge = [&](auto parts_tag) {
+      constexpr int kParts = decltype(parts_tag)::value;
+      const int blocks_per_segment = kParts == 1 ? (G * kHeadDim + kDecThreads - 1) / kDecThreads : G;
+      hipLaunchKernelGGL((decode_merge_kernel<kAligned, kParts>), dim3(n_segments * blocks_per_segment),
+                         dim3(decode_merge_threads(kParts)), 0, stream, offsets, lengths, n_segments, G, blocks_per_segment,
+                         chunk_rows, ws_acc, ws_m, ws_l, out, lse);
+    };
+    if constexpr (kAligned) {
+      // From three chunks a segment on, which with flat chunks there never are.  8 heads in a captured graph, whole call:
+      // 24 chunks a call 9.0 us with one thread per element and 9.2 with eight, 38 9.6 and 9.3, 100 11.1 and 9.5, 375 18.3
+      // and 10.8, 491 of 320 rows 28.1 and 18.8; 64 heads of 7 chunks 17.4 and 16.4.
+      if (total_kept / chunk_rows >= 3 * (int64_t)n_segments) return merge(std::integral_constant<int, 8>{});
+    }
+    merge(std::integral_constant<int, 1>{});
   };
   if (n_segments <= kDecAlignedSegments) {
     if (mask != nullptr) launch(std::true_type{}, std::true_type{}); else launch(std::false_type{}, std::true_type{});

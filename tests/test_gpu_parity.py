@@ -194,6 +194,36 @@ def test_decode_over_few_segments_keeps_more_digits_of_the_probabilities(ctx, le
         at += m
 
 
+@pytest.mark.parametrize("lengths,G_", [([128 * 9, 0, 128 * 64 + 1, 1, 128 * 8, 700], 4),   # parts without a chunk; an empty segment
+                                        ([383] * 3, 16), ([384] * 3, 3),                     # either side of three chunks a segment
+                                        ([70000], 1), ([100] * 40 + [40000], 8)])            # longer chunks; one long among many short
+def test_decode_merges_of_many_chunks(ctx, lengths, G_):
+    """Segments of up to several hundred chunks, merged by eight threads per element.  Errors as in the test above; the log-sum-exp
+    is an fp32 sum of fp32 exponentials of logits below 2^4."""
+    n, total = len(lengths), sum(lengths)
+    g = torch.Generator(device="cuda").manual_seed(total)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, k, v = normal(1, 1, n * G_, 128), normal(total, 128), normal(total, 128)
+    k[total // 2:] *= 2    # the maxima of the parts differ
+    offsets = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+    assert lkv.lkv_plan_offsets(ctx, np.array(lengths, dtype=np.int32), offsets) == total
+    out = torch.full((1, 1, n * G_, 128), float("nan"), device="cuda")
+    lse = torch.full((1, 1, n * G_), float("nan"), device="cuda")
+    ws = torch.full((lkv.lkv_decode_workspace_bytes(n, total, n * G_, n),), 255, dtype=torch.uint8, device="cuda")
+    lkv.lkv_decode_attn(ctx, 1, 1, n, n * G_, 128, q, k, v, offsets, total, 128 ** -0.5, out, lse, ws)
+    qd, kd, vd, at = q.cpu().double().view(n, G_, 128), k.cpu().double(), v.cpu().double(), 0
+    for s, m in enumerate(lengths):
+        got, got_lse = out[0, 0, s * G_:(s + 1) * G_].cpu().double(), lse[0, 0, s * G_:(s + 1) * G_].cpu().double()
+        if m == 0:
+            assert (got == 0).all() and torch.isneginf(got_lse).all()
+            continue
+        x = qd[s] @ kd[at:at + m].T * 128 ** -0.5
+        err = (got - torch.softmax(x, dim=1) @ vd[at:at + m]).abs().max()
+        assert err <= 2.0 ** -16 * vd.abs().max(), (s, m, float(err))
+        assert (got_lse - torch.logsumexp(x, dim=1)).abs().max() <= 2.0 ** -16, (s, m)
+        at += m
+
+
 def test_group_size_limit(ctx):
     w = W.scaled(W.CONFIGS[0], L=1, H=1, Hq=17, T=64, b_min=4)
     K, V, Q, sc, B = _inputs(w, [64])
