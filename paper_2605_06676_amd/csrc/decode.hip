@@ -23,10 +23,10 @@
 // instead: every wave loads the bounds of all segments at once, one per lane, and a prefix sum over the chunks of each
 // tells its block which segment and which rows are its own.  The grid is the most chunks that any split of the rows
 // over the segments can give.  (8 heads, 5 thousand rows, in a captured graph: 11.4 us with flat chunks, 8.7 us with
-// these; 40 thousand rows 18.1 and 13.4 us, 160 thousand 29.6 and 25.8 us; one head with nearly all of 5 thousand rows
-// 17.8 and 10.6 us; since the merge shares a segment's pieces out among threads, 9.3, 10.8 and 18.8.)  Over many segments the flat chunks are the better ones: they are equally long, and their grid is
-// one round of resident blocks however the rows are spread; with 256 segments of 5 thousand rows each the ends of the
-// segments would need a second round.
+// these; 40 thousand rows 18.1 and 13.4 us, 160 thousand 29.6 and 25.8 us, and 18.8 us since the merge shares a segment's
+// pieces out among threads; one head with nearly all of 5 thousand rows 17.8 and 10.6 us.)  Over many segments the flat
+// chunks are the better ones: they are equally long, and their grid is one round of resident blocks however the rows are
+// spread; with 256 segments of 5 thousand rows each the ends of the segments would need a second round.
 //
 // (Merging inside the first kernel, by the block that delivers a segment's last piece, needs device-scope fences; with
 // one L2 per XCD those write back and invalidate L2 and were measured to cost more than the second launch.)

@@ -21,13 +21,13 @@
 // The denominator that divides the output is one more output column of the second product (P times a column of
 // ones), see acc_l below.
 //
-// What bounds it: instruction issue, at the clock that the power allows.  At 16384 tokens the matrix pipe is busy for 56 %
-// of the cycles and the vector pipe for 58 %, 20 % of them together: 94 % in all, no LDS conflicts (counters), while the
-// chip holds 1.8 to 1.9 of its 2.4 GHz.  So what pays is work not done: references that stay put (no maximum, no
+// What bounds it: instruction issue, at the clock that the power allows.  At 16384 tokens the matrix pipe is busy for 58 %
+// of the cycles and the vector pipe for 60 %, 21 % of them together: 97 % in all, no LDS conflicts (counters), while the
+// chip holds 1.7 to 1.9 of its 2.4 GHz.  So what pays is work not done: references that stay put (no maximum, no
 // rescaling: 8 %), rows that go from memory to LDS without passing registers (which also frees the 32 registers that the
 // pipeline needs), sums kept from being postponed into the next step (6 %).  The steps are pipelined inside a wave (value
-// products of step s - 1, weights of step s, logits of step s + 1 in one scheduling region): vector work runs beside 36 %
-// of the matrix time, 17 % in the dq kernel, which has no such pipeline.  32 query heads, 8 KV heads, in turn with the
+// products of step s - 1, weights of step s, logits of step s + 1, in fenced pieces): vector work runs beside 36 % of the
+// matrix time, and ran beside 15 to 17 % in kernels that did one thing after the other.  32 query heads, 8 KV heads, in turn with the
 // kernel of running maxima and staging through registers: 2.40 -> 2.02 ms at 16384 tokens (1090 TFLOP/s; a library product
 // of 8192 x 8192 x 8192 reaches 1310 here), 649 -> 530 us at 8192, 182 -> 147 at 4096, 74 -> 62 at 2345; what the order of
 // the blocks and the pieces of plain_step took off since then stands there.  Measured and dropped: 64 queries per wave

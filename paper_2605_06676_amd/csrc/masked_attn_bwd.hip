@@ -354,21 +354,22 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // kGroups = 1: eight waves of 32 keys, each takes every step of 32 queries.  kGroups = 2: four times 32 keys, two waves
 // take the steps in turn and their sums are joined at the end, which halves the chain of steps per key (short sequences).
 //
-// Bound by instruction issue (see the counters below) and, for long sequences, by the power that the products draw.  A
-// step is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S
-// and dP of the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps
-// exponentials beside products.  Operands are read a piece ahead, also from one half to the next, into the products and on
-// to the next step (without that over these seams: 4.37 ms instead of 4.19 at 16384 tokens, 129 us instead of 126 at 2345,
-// 127 instead of 120 for 8 and 8 heads of 4096).  32 keys per wave need 128 accumulator and 32 K operand registers; V
-// operands come from LDS, 48 KB are read per 64 matrix instructions.  256 registers are just enough, and only so: one loop
-// with one way out (with breaks or a second loop for the diagonal the compiler keeps several sets of sums, and spills),
-// masks set in place in a branch around nothing else, addresses worked out where they are used.  32 query heads, 8 KV
-// heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at 2345
-// (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the products
-// (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix instructions, LDS busy
-// 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the channels of dK and dV
-// and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at 16384), four waves and 128
-// keys a block, two blocks per compute unit (143 us and 4.9 ms).
+// Bound by instruction issue (16384 tokens: matrix pipe busy for 50 % of the cycles, vector pipe 43 %, 13 % together, LDS
+// 54 %, no conflicts) and by waiting for LDS operands, at 2.0 GHz where the dQ kernel, busy for 96 %, holds 1.8.  A step
+// is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S and dP
+// of the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps
+// exponentials beside products.  Operands are read a piece ahead, also from one half to the next, into the products and
+// on to the next step (without that over these seams: 4.37 ms instead of 4.19 at 16384 tokens, 129 us instead of 126 at
+// 2345, 127 instead of 120 for 8 and 8 heads of 4096).  32 keys per wave need 128 accumulator and 32 K operand registers;
+// V operands come from LDS, 48 KB are read per 64 matrix instructions.  256 registers are just enough, and only so: one
+// loop with one way out (with breaks or a second loop for the diagonal the compiler keeps several sets of sums, and
+// spills), masks set in place in a branch around nothing else, addresses worked out where they are used.  32 query heads,
+// 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at
+// 2345 (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the
+// products (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix
+// instructions, LDS busy 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the
+// channels of dK and dV and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at
+// 16384), four waves and 128 keys a block, two blocks per compute unit (143 us and 4.9 ms).
 template <int kGroups>
 __global__ void __launch_bounds__(kDkvThreads, 2)
 masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
