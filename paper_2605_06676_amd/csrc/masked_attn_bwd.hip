@@ -361,9 +361,12 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // exponentials beside products.  Operands are read a piece ahead, also from one half to the next, into the products and
 // on to the next step (without that over these seams: 4.37 ms instead of 4.19 at 16384 tokens, 129 us instead of 126 at
 // 2345, 127 instead of 120 for 8 and 8 heads of 4096).  32 keys per wave need 128 accumulator and 32 K operand registers;
-// V operands come from LDS, 48 KB are read per 64 matrix instructions.  256 registers are just enough, and only so: one
-// loop with one way out (with breaks or a second loop for the diagonal the compiler keeps several sets of sums, and
-// spills), masks set in place in a branch around nothing else, addresses worked out where they are used.  32 query heads,
+// V operands come from LDS, 48 KB are read per 64 matrix instructions.  256 registers are just enough, without a spill, and
+// only so: one loop with one way out (with breaks or a second loop for the diagonal the compiler keeps several sets of sums,
+// and spills), masks set in place in a branch around nothing else, addresses worked out where they are used.  A step wholly
+// above a wave's diagonal passes through the pipeline with S = -inf and dP - D = 0 and leaves the products out: its weights
+// are 0, but 0 times a row that is not finite is not (whole backward pass, in turn with multiplying it all the same: 79.0 ->
+// 77.1 us at 1024 tokens, 1674 -> 1648 at 8192; a branch around the whole step spills, 3 % slower).  32 query heads,
 // 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at
 // 2345 (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the
 // products (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix
@@ -411,9 +414,10 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
   // and the transposing reads (four rows of 32 bytes) find their banks apart.
   const int srow = tid >> 4;
   const uint32_t piece = (uint32_t)(((tid & 15) ^ row_turn(srow)) * 16);
-  float aux = 0.f;   // wave w < kGroups: lse of query `lane` of step w, in its second half D of query lane - 32
+  float aux = 0.f;   // wave w < kGroups: lse of query lane % 32 of step w; the next kGroups waves: its D
   const int q_last = k0 + (T - 1 - k0) / kItemQ * kItemQ;   // first query of the last item
   int next_head = 0, next_q0 = q_last;   // the item to be fetched next: query head of the group, first query
+  int aux_q0 = 0;                        // first query of this wave's aux
   auto fetch = [&](unsigned char* dst) __attribute__((always_inline)) {
     const size_t base = ((size_t)h * G + g_lo + next_head) * T;
     const unsigned char* qs = reinterpret_cast<const unsigned char*>(q + base * kChunksPerRow);
@@ -424,9 +428,10 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
       lds_fill16(qs + at, dst + j * kDkvStepLds + 4 * wave * kDkvRow);
       lds_fill16(gs + at, dst + j * kDkvStepLds + (kMbStep + 4 * wave) * kDkvRow);
     }
-    if (wave < kGroups) {
-      aux = (lane < kMbStep ? lse : dvec)[base + min(next_q0 + kMbStep * wave + (lane & 31), T - 1)];
-      if (lane < kMbStep && next_q0 + kMbStep * wave + lane >= T) aux = -INFINITY;
+    aux_q0 = next_q0 + kMbStep * (wave % kGroups);
+    if (wave < 2 * kGroups) {
+      const uint32_t at = (uint32_t)min(aux_q0 + (lane & 31), T - 1) * 4u;
+      aux = *reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>((wave < kGroups ? lse : dvec) + base) + at);
     }
     next_q0 -= kItemQ;
     if (next_q0 < k0) {              // past the last item this wraps to rows nobody multiplies
@@ -436,7 +441,13 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
   };
   auto put_aux = [&](float* dst) __attribute__((always_inline)) {
     // lse goes to the log2 domain; -inf (no weight in the prefix, or a query past the end) becomes +inf: every e_ij is 0
-    if (wave < kGroups) dst[tid] = lane >= kMbStep ? -aux : (aux == -INFINITY ? INFINITY : aux * kMbLog2e);
+    if (wave < 2 * kGroups) {
+      float val = -aux;
+      if (wave < kGroups) val = aux == -INFINITY || aux_q0 + (lane & 31) >= T ? INFINITY : aux * kMbLog2e;
+      int at = lane & 31;
+      asm volatile("" : "+v"(at));   // or the compiler keeps the address in each of the three arrays
+      dst[at + kMbStep * (2 * (wave % kGroups) + wave / kGroups)] = val;   // (lanes 32 apart write the same)
+    }
   };
   fetch(slot_a);
   put_aux(aux_a);
@@ -538,12 +549,12 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     tile(std::integral_constant<int, 7>());
   };
   // P and dS of two queries: elements e, e + 1 of key block kb
-  auto pair = [&](const f32x4_t (&sv)[kDkvKB], const f32x4_t (&pv)[kDkvKB], const float (&lq)[4], int tt, int kb, int e)
+  auto pair = [&](const f32x4_t (&sv)[kDkvKB], const f32x4_t (&pv)[kDkvKB], float to_log2, const float (&lq)[4], int tt, int kb, int e)
       __attribute__((always_inline)) {
     bf16x2_t a, b;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const float ev = mb_exp2(fmaf(sv[kb][e + j], qscale, -lq[e + j]));
+      const float ev = mb_exp2(fmaf(sv[kb][e + j], to_log2, -lq[e + j]));
       dm_acc[kb] = fmaf(ev, pv[kb][e + j], dm_acc[kb]);
       const float p = ev * mkey[kb];
       a[j] = (__bf16)p;
@@ -555,29 +566,38 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     asm volatile("" : "+v"(pa), "+v"(da), "+v"(dm_acc[kb]));   // due here, beside the products
   };
   // One step of the pipeline: P and dS of its first 16 queries beside S and dP of the others, theirs beside S and dP of the
-  // next step's first 16, then the products.  below: query less key of element 0 of key block 0 in this lane.
-  auto step = [&](const unsigned char* cur, const float* aux_cur, const unsigned char* next, const float* aux_next, bool diagonal, int below)
-      __attribute__((always_inline)) {
+  // next step's first 16, then the products.  below: query less key of element 0 of key block 0 in this lane; meets: some
+  // query of the step, inside the sequence, sees some key of the wave.
+  auto step = [&](const unsigned char* cur, const float* aux_cur, const unsigned char* next, const float* aux_next,
+                  bool diagonal, int below, bool meets) __attribute__((always_inline)) {
     f32x4_t s1[kDkvKB], p1[kDkvKB];
     bf16x8_t gb, qb;
     auto half = [&](auto tt_tag) __attribute__((always_inline)) {
       // tt = 0: from sx, px of `cur` to s1, p1 of its second half; tt = 1: from those to sx, px of `next`
       constexpr int tt = decltype(tt_tag)::value;
+      const float4 l4 = *reinterpret_cast<const float4*>(aux_cur + 16 * tt + 4 * r);
+      float lq[4] = {l4.x, l4.y, l4.z, l4.w};
+      const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(tt == 0 ? aux_cur + kMbStep + 16 + 4 * r : aux_next + kMbStep + 4 * r);
+      float to_log2 = qscale;
       if (diagonal) {   // wave-uniform: some key of the wave comes after some query of the step
+        // such a pair weighs 0 whatever the query's normaliser and D are, so the normaliser comes off here and not in pair()
 #pragma unroll
         for (int kb = 0; kb < kDkvKB; ++kb)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            if (below < 16 * kb - (16 * tt + e)) (tt == 0 ? sx : s1)[kb][e] = -INFINITY;
+            f32x4_t &s = (tt == 0 ? sx : s1)[kb], &p = (tt == 0 ? px : p1)[kb];
+            const bool unseen = below < 16 * kb - (16 * tt + e);
+            s[e] = unseen ? -INFINITY : fmaf(s[e], qscale, -lq[e]);
+            p[e] = unseen ? 0.f : p[e];
           }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lq[e] = 0.f;
+        to_log2 = 1.f;
       }
       const unsigned char* g_at = tt == 0 ? cur + (kMbStep + 16) * kDkvRow : next + kMbStep * kDkvRow;
       const unsigned char* q_at = tt == 0 ? cur + 16 * kDkvRow : next;
       f32x4_t(&so)[kDkvKB] = tt == 0 ? s1 : sx;
       f32x4_t(&po)[kDkvKB] = tt == 0 ? p1 : px;
-      const float4 l4 = *reinterpret_cast<const float4*>(aux_cur + 16 * tt + 4 * r);
-      const float lq[4] = {l4.x, l4.y, l4.z, l4.w};
-      const f32x4_t nd = *reinterpret_cast<const f32x4_t*>(tt == 0 ? aux_cur + kMbStep + 16 + 4 * r : aux_next + kMbStep + 4 * r);
       auto part = [&](auto ks_tag) __attribute__((always_inline)) {
         constexpr int ks = decltype(ks_tag)::value;
         po[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gx, vx0, ks == 0 ? nd : po[0], 0, 0, 0);
@@ -604,8 +624,8 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
         if constexpr (ks < 3) qx = mb_read_straight(q_at + at);
         else if constexpr (tt == 0) qx = mb_read_straight(next + straight);
         else qb = mb_read_turned(cur + turned);
-        if (tt == 0) pair(sx, px, lq, 0, ks >> 1, 2 * (ks & 1));
-        else pair(s1, p1, lq, 1, ks >> 1, 2 * (ks & 1));
+        if (tt == 0) pair(sx, px, to_log2, lq, 0, ks >> 1, 2 * (ks & 1));
+        else pair(s1, p1, to_log2, lq, 1, ks >> 1, 2 * (ks & 1));
         __builtin_amdgcn_sched_barrier(0);
       };
       part(std::integral_constant<int, 0>());
@@ -615,7 +635,8 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     };
     half(std::integral_constant<int, 0>());
     half(std::integral_constant<int, 1>());
-    products(cur, gb, qb, next);
+    if (meets) products(cur, gb, qb, next);   // wave-uniform
+    else first_operands(next);
   };
   int q0 = q_last;   // first query of the current item
   const int lane_below = group * kMbStep + 4 * r - kw0 - c;
@@ -627,7 +648,9 @@ masked_attn_bwd_dkv_kernel(const uint4* __restrict__ q, const uint16_t* __restri
     lds_fill_barrier();
     fetch(fill);
     const int at = group * kDkvStepLds, aux_at = group * 2 * kMbStep;
-    step(cur + at, aux_cur + aux_at, next + at, aux_next + aux_at, q0 + group * kMbStep < kw0 + kDkvWaveK, q0 + lane_below);
+    const int qs0 = q0 + group * kMbStep;
+    step(cur + at, aux_cur + aux_at, next + at, aux_next + aux_at, qs0 < kw0 + kDkvWaveK, q0 + lane_below,
+         qs0 + kMbStep > kw0 && (kGroups == 1 || qs0 < T));
     put_aux(aux_fill);
     q0 = q0 > k0 ? q0 - kItemQ : q_last;
   };

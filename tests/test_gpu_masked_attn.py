@@ -222,6 +222,47 @@ def test_backward_around_the_steps_of_the_dq_pipeline(ctx, T):
     check_backward(ctx, 2, 1, T, seed=11)
 
 
+@pytest.mark.parametrize("Hq,H,T,i", [(8, 2, 1000, 300),                       # 128 keys a block, a query head each
+                                      (2, 1, 385, 130), (2, 1, 385, 384),      # and the last query, alone in its item
+                                      (64, 64, 2049, 1000), (64, 64, 2049, 40)])   # 256 keys a block
+@pytest.mark.parametrize("bad", ["q", "d_o", "o", "lse"])
+def test_backward_reach_of_a_bad_query_row(ctx, Hq, H, T, i, bad):
+    """A query row that is not finite spoils the gradients of the keys it sees.  Later keys of its own step of 32 have it
+    multiplied with a weight of 0, which is finite in dV as long as dO is, and everywhere if only the normaliser is bad; keys of
+    later steps never meet it, and keep every bit."""
+    hq = Hq - 1
+    q, k, v, m, d_o = W.draw_training_attention(Hq, H, T, seed=21)
+    x = {"q": q, "k": k, "v": v, "d_o": d_o}
+    x = {name: bits_to_bf16_gpu(bits) for name, bits in x.items()}
+    x["m"] = torch.from_numpy(m).cuda()
+    f = dict(dtype=torch.float32, device="cuda")
+    x["o"], x["lse"] = torch.empty((Hq, T, 128), **f), torch.empty((Hq, T), **f)
+    lkv.lkv_masked_attn_forward(ctx, x["q"], x["k"], x["v"], x["m"], SCALE, x["o"], x["lse"])
+    ws = torch.empty(lkv.lkv_masked_attn_backward_workspace_bytes(Hq, H, T), dtype=torch.uint8, device="cuda")
+
+    def backward():
+        grads = [torch.full(s, 7.0, **f) for s in ((Hq, T, 128), (H, T, 128), (H, T, 128), (H, T))]
+        lkv.lkv_masked_attn_backward(ctx, x["q"], x["k"], x["v"], x["m"], x["o"], x["lse"], x["d_o"], SCALE, *grads, ws)
+        torch.cuda.synchronize()
+        return grads
+
+    clean = backward()
+    x[bad][hq, i] = float("nan")
+    got = backward()
+    for g, c, name in zip(got[1:], clean[1:], ("dK", "dV", "dm")):
+        if name == "dV" and bad == "o":
+            assert torch.equal(g, c)          # dV has no D in it
+            continue
+        first = i + 1 if bad == "lse" or (name == "dV" and bad == "q") else (i // 32 + 1) * 32
+        assert not torch.isfinite(g[H - 1, :i + 1]).any(), name
+        spoiled = (~torch.isfinite(g[H - 1])).nonzero()[:, 0].max().item()
+        assert spoiled < first, (name, spoiled)
+        assert torch.equal(g[H - 1, first:], c[H - 1, first:]) and torch.equal(g[:H - 1], c[:H - 1]), name
+    assert not torch.isfinite(got[0][hq, i]).any()
+    got[0][hq, i] = clean[0][hq, i]
+    assert torch.equal(got[0], clean[0])
+
+
 def test_backward_mask_edge_cases(ctx):
     def zero_prefix(m):
         m = m.copy()
