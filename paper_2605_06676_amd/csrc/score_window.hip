@@ -23,9 +23,14 @@
 // (the prefill's attention kernel computes them for every query) passes them in: pass 1 and the
 // merge are skipped and the keys are read once.
 //
-// Pass 1 takes its sums per (row, lane) relative to that lane's logit of the block's first 16 keys, and nothing looks at
-// a maximum: any reference gives the same sum to fp32 rounding as long as nothing overflows.  A sum that passes 2^100
-// is taken again with references that follow the largest logit.
+// Pass 1 takes its sums per (row, lane) relative to logits of the block's first 32 keys (that lane's own two, or the row's
+// largest where some are not modest): any reference gives the same sum to fp32 rounding as long as nothing overflows, so nothing
+// looks at a maximum.  A wave looks at its sums after 64 keys and then every 128; where some have grown their references
+// follow by whole binary orders, and where one overflowed (a logit more than 2^7 binary orders above its reference) the keys
+// since the last look are taken again with references that follow every key.  So the price of wide logits is bounded:
+// 32 layers of 8 heads x 32768 keys, 128 window rows, logits of a deviation of 1, 8, 16 and 32: 867, 868, 921 and 1092 us with
+// references that move tile by tile, 799, 818, 2045 and 2013 with whole blocks taken again beyond 2^100, 792, 804, 853 and
+// 902 with this.
 //
 // A block is a pair of waves that share the staged keys (two tiles of 16 between barriers); the
 // window rows are split between the two (at most 64 rows, 64 fragment registers, per wave).
@@ -52,7 +57,9 @@ constexpr int kWinManyRounds = 1024;             // keys of a block where the bl
 constexpr int kWinMaxReach = 31;                // pooling widths up to 63
 // pass 2: a block's keys, two tiles before, the reach after, rounded up to a tile
 constexpr int win_vote_slots(int keys) { return keys + 32 + kWinMaxReach + 17; }
-constexpr float kWinMostSum = 1.2676506e30f;     // 2^100: sum beyond which pass 1 starts over with references that move
+constexpr float kWinMoveSum = 4294967296.f;      // 2^32: sum over a lane's rows from which pass 1 moves its references
+constexpr float kWinModest = 24.f;               // first logits (log2 units) up to which a lane's own serve as its references
+constexpr int kWinMostOrders = 100;              // by which one goes at once (what is left of a sum stays far from underflow)
 constexpr float kWinNoRef = -1e30f;              // reference of a row that has seen no key yet
 
 // row / window, for the rows of a block, as row * win_turns(window) >> 16.  A step around the window asks for the place of every
@@ -226,14 +233,6 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
     stage_step(x_next, buf ^ 1);               // past the last step: rows nobody reads
     load_step(x_next, i + 3);
     if (kPass == 1) {
-      // Sums against references that stay put: this lane's logits of the block's first tile.  Its later keys are seen by
-      // a row only where the first one is, so a reference is a logit of the sum, or the sum is empty.
-      if (i == 0) {   // uniform
-#pragma unroll
-        for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ref[mw][e] = acc[0][mw][e] * log2_scale;
-      }
       const bool causal = block_row0 + kWinStep * (i + 1) > prefix;   // uniform: the step touches the window or the ragged tail
       if (causal) {
         const int j = block_row0 + kWinStep * i + c;
@@ -245,6 +244,22 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
             if (j > last) acc[0][mw][e] = -INFINITY;
             if (j + kWinTokTile > last) acc[1][mw][e] = -INFINITY;
           }
+      }
+      if (i == 0) {   // uniform: the first references
+        float most = 0.f;
+#pragma unroll
+        for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            ref[mw][e] = fmaxf(fmaxf(acc[0][mw][e], acc[1][mw][e]) * log2_scale, kWinNoRef);
+            most = fmaxf(most, fabsf(ref[mw][e]));
+          }
+        if (__ballot(most > kWinModest) != 0ull) {
+#pragma unroll
+          for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ref[mw][e] = row16_allreduce_max(ref[mw][e]);
+        }
       }
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -270,6 +285,77 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
     }
     __syncthreads();
   };
+  // Pass 1: a look at the sums, `upto` steps done.  Where some have grown, the references of their lanes follow by whole
+  // binary orders; where one overflowed, the keys since the last look are taken again, straight from memory and with
+  // references that follow every one of them.
+  float kept_sum[MTW][4];   // as the last look left them
+#pragma unroll
+  for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) kept_sum[mw][e] = 0.f;
+  int looked = 0;
+  auto look = [&](int upto) __attribute__((always_inline)) {
+    float total = 0.f;
+#pragma unroll
+    for (int mw = 0; mw < MTW; ++mw) total += (sum[mw][0] + sum[mw][1]) + (sum[mw][2] + sum[mw][3]);
+    if (__builtin_expect(__ballot(!(total < kWinMoveSum)) != 0ull, 0)) {
+      bool lost = false;
+#pragma unroll
+      for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lost |= !(sum[mw][e] < INFINITY);
+      if (__ballot(lost) != 0ull) {
+#pragma unroll
+        for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            sum[mw][e] = kept_sum[mw][e];
+            // the first references may be infinite (those of padding rows, which see no key, are not)
+            if (looked == 0 && 16 * (half * MTW + mw) + 4 * r + e < n_rows) ref[mw][e] = kWinNoRef;
+          }
+#pragma unroll 1
+        for (int row0 = looked * kWinStep; row0 < min(upto * kWinStep, block_rows); row0 += kWinTokTile) {
+          f32x4_t acc[MTW];
+#pragma unroll
+          for (int mw = 0; mw < MTW; ++mw) acc[mw] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          const uint4* key = reinterpret_cast<const uint4*>(Kh + (size_t)min(row0 + c, block_rows - 1) * 256);
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) {
+            const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, key[ks * 4 + r]);
+#pragma unroll
+            for (int mw = 0; mw < MTW; ++mw)
+              acc[mw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfrag[mw][ks], xv, acc[mw], 0, 0, 0);
+          }
+#pragma unroll
+          for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const bool seen = block_row0 + row0 + c <= last_seen(16 * (half * MTW + mw) + 4 * r + e);
+              const float s = acc[mw][e] * log2_scale;
+              const float moved = fmaxf(ref[mw][e], s);
+              const float kept = sum[mw][e] * __builtin_amdgcn_exp2f(ref[mw][e] - moved) + __builtin_amdgcn_exp2f(s - moved);
+              sum[mw][e] = seen ? kept : sum[mw][e];
+              ref[mw][e] = seen ? moved : ref[mw][e];
+            }
+        }
+      } else {
+#pragma unroll
+        for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int orders = sum[mw][e] >= 1.f ? min(__builtin_amdgcn_frexp_expf(sum[mw][e]), kWinMostOrders) : 0;
+            const float moved = ref[mw][e] + (float)orders;
+            sum[mw][e] *= __builtin_amdgcn_exp2f(ref[mw][e] - moved);
+            ref[mw][e] = moved;
+          }
+      }
+    }
+#pragma unroll
+    for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kept_sum[mw][e] = sum[mw][e];
+    looked = upto;
+  };
   load_step(xa, 0);
   load_step(xb, 1);
   stage_step(xa, 0);
@@ -279,49 +365,7 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   for (int i = 0; i < n_steps; i += 2) {   // (no break: one way out of the loop keeps one set of sums)
     step(xb, i, 0);                        // stages the odd step i + 1
     if (i + 1 < n_steps) step(xa, i + 1, 1);
-  }
-  if (kPass == 1) {
-    // A sum that left the range (logits 100 binary orders above the reference, or a reference that is infinite) is taken
-    // again, with references that follow the largest logit and the keys straight from memory.
-    bool lost = false;
-#pragma unroll
-    for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) lost |= !(sum[mw][e] < kWinMostSum);
-    if (__builtin_expect(__ballot(lost) != 0ull, 0)) {
-#pragma unroll
-      for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          ref[mw][e] = kWinNoRef;
-          sum[mw][e] = 0.f;
-        }
-#pragma unroll 1
-      for (int row0 = 0; row0 < block_rows; row0 += kWinTokTile) {
-        f32x4_t acc[MTW];
-#pragma unroll
-        for (int mw = 0; mw < MTW; ++mw) acc[mw] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        const uint4* key = reinterpret_cast<const uint4*>(Kh + (size_t)min(row0 + c, block_rows - 1) * 256);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const bf16x8_t xv = __builtin_bit_cast(bf16x8_t, key[ks * 4 + r]);
-#pragma unroll
-          for (int mw = 0; mw < MTW; ++mw)
-            acc[mw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qfrag[mw][ks], xv, acc[mw], 0, 0, 0);
-        }
-#pragma unroll
-        for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool seen = block_row0 + row0 + c <= last_seen(16 * (half * MTW + mw) + 4 * r + e);
-            const float s = acc[mw][e] * log2_scale;
-            const float moved = fmaxf(ref[mw][e], s);
-            const float kept = sum[mw][e] * __builtin_amdgcn_exp2f(ref[mw][e] - moved) + __builtin_amdgcn_exp2f(s - moved);
-            sum[mw][e] = seen ? kept : sum[mw][e];
-            ref[mw][e] = seen ? moved : ref[mw][e];
-          }
-      }
-    }
+    if (kPass == 1 && ((i & 2) == 0 || i + 2 >= n_steps)) look(min(i + 2, n_steps));
   }
 
   if (kPass == 2) {
@@ -351,13 +395,6 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
     }
   }
   if (kPass == 1) {
-    if (block_row0 + kWinTokTile > prefix + 1) {   // uniform: some row does not see some lane's first key, so none of its keys
-#pragma unroll
-      for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (block_row0 + c > last_seen(16 * (half * MTW + mw) + 4 * r + e)) ref[mw][e] = kWinNoRef;
-    }
     // one (reference, sum) pair per row: merge the 16 token lanes
     float* part = tab.partial[seq] + (part_row0 + (size_t)chunk * RP) * 2;
 #pragma unroll

@@ -439,3 +439,55 @@ def test_blocks_of_one_round_and_of_several(ctx, L, H, grp, window, T):
         Kb = G.bf16_gpu_to_bits(k[l, h])[None, None]
         Qb = G.bf16_gpu_to_bits(q[l, h * grp:(h + 1) * grp])[None]
         check_against_oracle(s[l, h][None, None].cpu().numpy(), Kb, Qb, window, 63, lkv.POOL_AVG, what=f"layer {l} head {h}")
+
+
+@pytest.mark.parametrize("grp,window", [(4, 32), (7, 16), (1, 5)])   # whole row tiles; padding rows; one wave without rows
+@pytest.mark.parametrize("shape", ["climb", "late jump", "early jump", "fall"])
+def test_references_that_follow_within_a_block(ctx, grp, window, shape):
+    """Blocks of more than 1024 keys whose logits leave the first keys behind: by 10 binary orders every 128 keys; by 200
+    after 300 keys, and by another 150 after 700; by 250 after 20 keys; and from 300 orders downwards."""
+    H, T = 8, 131072
+    j = torch.arange(T, device="cuda") % 1024
+    orders = {"climb": j * (10 / 128), "late jump": (j >= 300) * 200.0 + (j >= 700) * 150.0, "early jump": (j >= 20) * 250.0,
+              "fall": 300.0 - j * (10 / 128)}[shape].float()
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = (1 + 0.1 * torch.randn((1, H * grp, window, 128), device="cuda", generator=g)).bfloat16()
+    k = 0.2 * torch.randn((1, H, T, 128), device="cuda", generator=g)
+    k = (k + (orders / np.log2(np.e) / (128 * G.SCALE))[None, None, :, None]).bfloat16()
+    cache = lkv.Cache([k], [k], H * grp)
+    s = torch.full((1, H, T), float("nan"), device="cuda")
+    ws = torch.empty(lkv.lkv_score_window_workspace_bytes(cache), dtype=torch.uint8, device="cuda")
+    lkv.lkv_score_window(ctx, cache, [q], window, 1, lkv.POOL_AVG, G.SCALE, [s], ws)
+    row = torch.arange(window, device="cuda").repeat(grp)
+    unseen = torch.arange(T, device="cuda")[None] > (T - window + row)[:, None]
+    for h in range(H):
+        x = q[0, h * grp:(h + 1) * grp].double().reshape(grp * window, 128) @ k[0, h].double().T * G.SCALE
+        x.masked_fill_(unseen, float("-inf"))
+        vote = torch.softmax(x, dim=1).sum(dim=0)[:T - window] / grp
+        # logits of up to 2^8 are sums of 128 products in fp32, once in either pass: 2^-24 * 2^8 * 2 each, growing with
+        # the root of 128 at most where the roundings are not of one sign
+        torch.testing.assert_close(s[0, h, :T - window].double(), vote, rtol=2.0 ** -24 * 2 ** 8 * 2 * 12, atol=1e-12)
+
+
+def test_wide_logits_cost_little_more(ctx):
+    """Keys are taken again only since the last look at the sums: logits of a deviation of 16 (24 binary orders), a few of which
+    leave every reference behind, measured at 1.06 to 1.08 times the time of a deviation of 1 and at 2.5 times when a block was
+    taken again as a whole."""
+    L, H, grp, window, T = 4, 8, 4, 32, 32768
+    k = torch.randn((L, H, T, 128), dtype=torch.bfloat16, device="cuda")
+    q = torch.randn((L, H * grp, window, 128), device="cuda")
+    cache = lkv.Cache([k], [k], H * grp)
+    s = torch.empty((L, H, T), device="cuda")
+    ws = torch.empty(lkv.lkv_score_window_workspace_bytes(cache), dtype=torch.uint8, device="cuda")
+    times = {}
+    for rep in range(5):
+        for sigma in (1.0, 16.0):
+            qs = (q * sigma).bfloat16()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            for i in range(25):
+                if i == 5: a.record()
+                lkv.lkv_score_window(ctx, cache, [qs], window, 7, lkv.POOL_MAX, G.SCALE, [s], ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.setdefault(sigma, []).append(a.elapsed_time(b))
+    assert min(times[16.0]) <= 1.5 * min(times[1.0]), times
