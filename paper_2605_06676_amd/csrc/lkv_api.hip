@@ -3,6 +3,7 @@
 // Every check runs before anything is enqueued.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -12,6 +13,7 @@
 
 #include "../../include/lkv.h"
 #include "lkv_kernels.h"
+#include "lkv_tiles.h"
 
 namespace {
 
@@ -150,15 +152,16 @@ lkv_status score_impl(lkv_ctx* ctx, const lkv_cache* cache, const lkv_scorer* sc
   const int heads_per_row = scorer->per_head ? 1 : cache->n_kv_heads;
   hipStream_t st = as_stream(stream);
 
-  // launches of up to kMaxSeqPerLaunch sequences; the MLP kernels take tiles of one size
-  const int rpb = scorer->kind == LKV_SCORER_MLP
-                      ? lkv::score_mlp_rows_per_block(cache->seq_len, cache->n_seq, heads, scorer->hidden) : 0;
+  // launches of up to kMaxSeqPerLaunch sequences; the MLP kernels take tiles of one size in each
   int s = 0;
   while (s < cache->n_seq) {
     lkv::SeqTable tab;
     memset(&tab, 0, sizeof(tab));
     int64_t blocks = 0;
     const int s_first = s;
+    const int rpb = scorer->kind == LKV_SCORER_MLP
+                        ? lkv::score_mlp_rows_per_block(cache->seq_len + s, std::min(cache->n_seq - s, (int)lkv::kMaxSeqPerLaunch),
+                                                        heads, scorer->hidden) : 0;
     int n = 0;
     while (s < cache->n_seq && n < lkv::kMaxSeqPerLaunch) {
       const int T = cache->seq_len[s];

@@ -15,7 +15,6 @@ hipError_t score_mlp_prepare();
 void launch_score_mlp(const SeqTable& tab, const uint16_t* w1, const float* b1, const float* w2,
                       const float* b2, int hidden, int act, int heads_per_scorer_row, int rows_per_block,
                       hipStream_t stream, uint32_t* counts = nullptr, int seg_base = 0, int seg_stride = 0);
-int score_mlp_rows_per_block(const int32_t* seq_len, int n_seq, int64_t heads, int hidden);
 
 // score_window.hip
 int score_window_max_rows();

@@ -405,38 +405,6 @@ score_mlp_wide_kernel(SeqTable tab, const uint16_t* __restrict__ w1, const float
   }
 }
 
-// Rows per block of a launch over all sequences of a call.  Every wave starts by loading the hidden layer's weights, and a
-// last round that is a small part of one leaves the chip idle, so the rows go into as few blocks as fill whole rounds of what
-// the chip holds at once: 512 blocks of four waves (hidden widths up to 64), 1024 of two.  Few rows go one block to each of
-// the 256 compute units: a second block on some of them would take as long as one on all.
-// Against tiles of a power of two, chosen for each length and launched apart where they differ: hidden width 64, 8 heads,
-// sequences of 10001, 6214 and 2491 tokens 26.7 -> 18.9 us, of 40001, 24964 and 9991 77 -> 57, the first three with 64 heads
-// 134 -> 110, with 256 449 -> 410; width 128, 40001, 24964 and 9991 76 -> 62, 64 heads of the first three 152 -> 120.
-// One sequence, against one round with a tile of at least 256 rows or the power of two: 64 units, 8 heads of 12001 16.3 ->
-// 13.5, of 32768 27.6 -> 25.9, 64 heads of 60001 351 -> 338; 128 units, 256 heads of 20001 499 -> 474, of 9001 231 -> 219.
-// One block per compute unit only with up to 1280 rows each (64 units: 90001 tokens 64.0 us with a round of 1408 rows, 65.2
-// with 256 blocks of 2816), 384 of the two-wave blocks (16384 tokens 23.4 and 26.3).  Rows past 4096 gain nothing.
-int score_mlp_rows_per_block(const int32_t* seq_len, int n_seq, int64_t heads, int hidden) {
-  constexpr int kUnits = 256, kLeast = 256, kMost = 4096;
-  const int64_t round = hidden > 64 ? 1024 : 512;
-  const int most_alone = hidden > 64 ? 384 : 1280;   // rows of a block that has its compute unit to itself
-  int64_t keys = 0;
-  for (int s = 0; s < n_seq; ++s) keys += heads * seq_len[s];
-  auto blocks = [&](int rows) {
-    int64_t n = 0;
-    for (int s = 0; s < n_seq; ++s) n += heads * (((int64_t)seq_len[s] + rows - 1) / rows);
-    return n;
-  };
-  auto rows_for = [&](int64_t limit, int most) {   // the least of at most `most` that give up to `limit` blocks
-    const int64_t share = keys / limit / 64 * 64;   // below this nothing does
-    int rows = (int)(share < kLeast ? kLeast : share < most ? share : most);
-    while (rows < most && blocks(rows) > limit) rows += 64;
-    return rows;
-  };
-  if (blocks(most_alone) <= kUnits) return rows_for(kUnits, most_alone);
-  return rows_for((blocks(kMost) + round - 1) / round * round, kMost);
-}
-
 hipError_t score_mlp_prepare() { return hipSuccess; }
 
 template <int MT, bool kCount>

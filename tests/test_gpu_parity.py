@@ -104,6 +104,15 @@ def test_mlp_tiles_over_all_sequences(ctx, L, H, hidden, Ts):
     _run_and_check(ctx, w, Ts, seed=17, budgets=budgets, what=f"{L} x {H} heads of {Ts}, hidden width {hidden}")
 
 
+@pytest.mark.parametrize("L,H,hidden,Ts", [(24, 12, 64, [1100]), (24, 12, 128, [900, 900]),   # heads that do not divide a round
+                                           (16, 32, 96, [1300]), (16, 32, 32, [1300, 700]),      # narrow: at most 1024 rows
+                                           (1, 5, 64, [1500 - 40 * s for s in range(35)])])      # two launches, each its own tiles
+def test_mlp_tiles_of_several_rounds(ctx, L, H, hidden, Ts):
+    w = W.scaled(W.CONFIGS[3], L=L, H=H, Hq=H, T=max(Ts), hidden=hidden, act="gelu", per_head=False, b_min=1)
+    budgets = [[max(1, T // 40)] * (L * H) for T in Ts]
+    _run_and_check(ctx, w, Ts, seed=18, budgets=budgets, what=f"{L} x {H} heads of {Ts[:3]}, hidden width {hidden}")
+
+
 def test_mlp_without_output_bias_and_heavy_tails(ctx):
     w = W.scaled(W.CONFIGS[4], L=2, H=2, Hq=14, T=2500, n_seq=2, b_min=8)
     K, V, Q, sc, B = _inputs(w, [2500, 2500])
