@@ -40,17 +40,17 @@ ALSO_BY_DEFAULT = (1, 3, 4)
 # kernel's sources at the time of the measurement; when the sources have changed since, `traffic` is null.
 SCORE_KERNEL_SOURCES = {
     "score_linear_kernel": ("score_linear.hip", "lkv_common.h"),
-    "score_mlp_kernel": ("score_mlp.hip", "lkv_act.h", "lkv_common.h"),
-    "score_mlp_wide_kernel": ("score_mlp.hip", "lkv_act.h", "lkv_common.h"),
+    "score_mlp_kernel": ("score_mlp.hip", "lkv_tiles.h", "lkv_act.h", "lkv_common.h"),
+    "score_mlp_wide_kernel": ("score_mlp.hip", "lkv_tiles.h", "lkv_act.h", "lkv_common.h"),
 }
 MEASURED_SCORE_TRAFFIC = {
     # workload name: (bytes per launch, sha256[:16] of the kernel's sources, profile)
     "cfg1-L32-H8-T32768-linear": (4328897267, "8df6ec869a771fd8", "profiles/all_kernels__cfg1-L32-H8-T32768-linear.md"),
-    "cfg2-L32-H8-T131072-mlp64gelu": (17337178147, "cccc5a1a49061c04", "profiles/all_kernels__cfg2-L32-H8-T131072-mlp64gelu.md"),
+    "cfg2-L32-H8-T131072-mlp64gelu": (17337034758, "99c7421e7526e2dd", "profiles/all_kernels__cfg2-L32-H8-T131072-mlp64gelu.md"),
     "cfg3-16seq-T4096..16384-linear": (22846926438, "8df6ec869a771fd8", "profiles/all_kernels__cfg3-16seq-T4096-16384-linear.md"),
-    "cfg4-8seq-L28-H4-g7-T65536-mlp64gelu": (30385261136, "cccc5a1a49061c04", "profiles/all_kernels__cfg4-8seq-L28-H4-g7-T65536-mlp64gelu.md"),
-    "paper-L32-H8-T32768-mlp128silu-per-head": (4467541074, "cccc5a1a49061c04", "profiles/all_kernels__paper-L32-H8-T32768-mlp128silu-per-head.md"),
-    "paper-L36-H8-T32768-mlp128silu-per-head": (5026537330, "cccc5a1a49061c04", "profiles/all_kernels__paper-L36-H8-T32768-mlp128silu-per-head.md"),
+    "cfg4-8seq-L28-H4-g7-T65536-mlp64gelu": (30385678630, "99c7421e7526e2dd", "profiles/all_kernels__cfg4-8seq-L28-H4-g7-T65536-mlp64gelu.md"),
+    "paper-L32-H8-T32768-mlp128silu-per-head": (4467555675, "99c7421e7526e2dd", "profiles/all_kernels__paper-L32-H8-T32768-mlp128silu-per-head.md"),
+    "paper-L36-H8-T32768-mlp128silu-per-head": (5028562722, "99c7421e7526e2dd", "profiles/all_kernels__paper-L36-H8-T32768-mlp128silu-per-head.md"),
 }
 
 

@@ -227,8 +227,7 @@ lkv_status lkv_create(lkv_ctx** out, int device) {
       return LKV_ERR_HIP;
     }
   }
-  if (lkv::select_prepare() != hipSuccess || lkv::decode_prepare(device) != hipSuccess ||
-      lkv::score_mlp_prepare() != hipSuccess) {
+  if (lkv::select_prepare() != hipSuccess || lkv::decode_prepare(device) != hipSuccess) {
     lkv_destroy(ctx);
     return LKV_ERR_HIP;
   }

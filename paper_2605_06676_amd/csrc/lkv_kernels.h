@@ -11,7 +11,6 @@ void launch_score_linear(const SeqTable& tab, const uint16_t* w1, const float* b
 int score_linear_blocks_per_head(int T);
 
 // score_mlp.hip
-hipError_t score_mlp_prepare();
 void launch_score_mlp(const SeqTable& tab, const uint16_t* w1, const float* b1, const float* w2,
                       const float* b2, int hidden, int act, int heads_per_scorer_row, int rows_per_block,
                       hipStream_t stream, uint32_t* counts = nullptr, int seg_base = 0, int seg_stride = 0);

@@ -405,8 +405,6 @@ score_mlp_wide_kernel(SeqTable tab, const uint16_t* __restrict__ w1, const float
   }
 }
 
-hipError_t score_mlp_prepare() { return hipSuccess; }
-
 template <int MT, bool kCount>
 static void launch_mt(const SeqTable& tab, const uint16_t* w1, const float* b1, const float* w2,
                       const float* b2, int act, int heads_per_scorer_row, int rows_per_block,
