@@ -31,6 +31,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "lkv_bracket.h"
 #include "lkv_kernels.h"
 
 namespace lkv {
@@ -245,8 +246,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
     // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
     moderate = moderate && least > -INFINITY && most < INFINITY;
-    // (logarithms in fp32, a thousandth to spare)
-    auto margin = [&](double part) { return 1.001 + (double)fmaxf(0.f, (float)kLn2 * __log2f((float)n / (2.f * (float)part))); };
+    auto margin = [&](double part) { return bracket_margin(n, part, [](float x) { return __log2f(x); }); };
     lo = st_uniform(least / tau - margin((double)n - k));
     hi = st_uniform(most / tau + margin(k));
     constexpr int kBins = StHist<kT>::kBins;

@@ -543,3 +543,22 @@ def test_head_budgets_argument_errors(ctx):
             lkv.lkv_head_budgets(ctx, e, p, R, 100, r)
         assert err.value.status == 1
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n", [1, 5, 777, 4096, 40000])
+@pytest.mark.parametrize("k", [1e-7, 1e-30, 1e-39, 1e-40, 1e-300])
+def test_targets_far_below_one_value(ctx, n, k, f64):
+    """Every value lies far below the threshold, whose closed form is then log sum e^z - log 2 k."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, generator=g, device="cuda", dtype=torch.float64 if f64 else torch.float32)
+    y = torch.full((n,), 7.0, dtype=torch.float64, device="cuda")
+    info = torch.zeros(2, dtype=torch.float64, device="cuda")
+    lkv.lkv_soft_topk(ctx, x, k, 0.1, y, info)
+    torch.cuda.synchronize()
+    z = x.double() / 0.1
+    threshold = torch.logsumexp(z, 0).item() - math.log(2 * k)
+    assert abs(info[0].item() - threshold) <= 2.0 ** -50 * abs(threshold) + 2.0 ** -48
+    # a threshold of up to 2^10 is known to 2^-43, which is the relative error of e^(z - threshold); subnormal results to a
+    # spacing, 2^-1074, on either side
+    torch.testing.assert_close(y, 0.5 * torch.exp(z - threshold), rtol=2.0 ** -40, atol=2.0 ** -1073)
