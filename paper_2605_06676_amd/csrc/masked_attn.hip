@@ -202,10 +202,10 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
   };
   // One pipeline step: the value products of step s - 1, the weights of step s, the logits of step s + 1; nothing in
   // it waits for anything else in it, so matrix and vector instructions of one wave run side by side.
-  // kDiag: some key of the step may lie above some query's diagonal.  kMoving: the references follow the running maxima;
-  // else they stay and nothing looks at the maxima.
-  auto step = [&](auto diag_tag, auto moving_tag, auto fine_tag, const unsigned char* tile, int s, int half) __attribute__((always_inline)) {
-    constexpr bool kDiag = decltype(diag_tag)::value, kMoving = decltype(moving_tag)::value, kFine = decltype(fine_tag)::value;
+  // Some key of the step may lie above some query's diagonal.  kMoving: the references follow the running maxima; else they
+  // stay and nothing looks at the maxima.
+  auto step = [&](auto moving_tag, auto fine_tag, const unsigned char* tile, int s, int half) __attribute__((always_inline)) {
+    constexpr bool kMoving = decltype(moving_tag)::value, kFine = decltype(fine_tag)::value;
     const unsigned char* k_lds = tile + half * kMaStep * kMaRow;
     const float* m_lds = reinterpret_cast<const float*>(tile + 2 * kMaTile * kMaRow) + half * kMaStep;
     value_products(fine_tag, k_lds + kMaTile * kMaRow);
@@ -215,7 +215,7 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         float x = fmaf(sacc[qb][i >> 2][i & 3], qscale, -ref[qb]);
-        if (kDiag) x = s * kMaStep + 16 * (i >> 2) + 4 * r + (i & 3) > qw0 + 16 * qb + c ? -INFINITY : x;
+        x = s * kMaStep + 16 * (i >> 2) + 4 * r + (i & 3) > qw0 + 16 * qb + c ? -INFINITY : x;
         if (kMoving) top = fmaxf(top, x);
         sacc[qb][i >> 2][i & 3] = x;
       }
@@ -402,7 +402,7 @@ masked_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {   // wave-uniform branches
       const int s = 2 * t + half;
-      if (s < n_steps) step(std::true_type{}, moving_tag, fine_tag, tile, s, half);
+      if (s < n_steps) step(moving_tag, fine_tag, tile, s, half);
       else if (s == n_steps) value_products(fine_tag, tile + (kMaTile + half * kMaStep) * kMaRow);
     }
     if (t == n_full + 1 && n_steps == 2 * t + 2) value_products(fine_tag, tile + kMaStep * kMaRow);

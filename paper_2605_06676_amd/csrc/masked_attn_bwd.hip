@@ -237,7 +237,7 @@ masked_attn_bwd_dq_kernel(const uint16_t* __restrict__ q, const uint4* __restric
     auto piece_of_step = [&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value;
       constexpr int tt = i >> 2, ks = i & 3, qp = (i >> 1) & 1, e0 = 2 * (i & 1);
-      bf16x8_t kbn;
+      bf16x8_t kbn = kb;
       if constexpr (i < 7) kbn = mb_read_turned(k_prev + address_xor<32 * (i + 1)>(turned));
       if (ks == 0) {
         const float4 mw4 = *reinterpret_cast<const float4*>(k_cur + kDqRows + (16 * tt + 4 * r) * 4);

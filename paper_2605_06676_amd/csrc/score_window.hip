@@ -123,7 +123,6 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
   const int block_row0 = max(0, own_row0 - halo);
   const int block_end = kPass == 1 ? own_end : min(prefix, own_end + reach);
   const int block_rows = block_end - block_row0;
-  const int n_tiles = (block_rows + 15) >> 4;
 
   const int lane = threadIdx.x & 63;
   const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -370,7 +369,7 @@ score_window_kernel(WinTable tab, int heads, int window, int n_rows, int rows_pe
 
   if (kPass == 2) {
     // Scores of the block's own keys: centred pooling over the votes inside the prefix (votes are non-negative and
-    // the slots outside hold zeros, which change neither rule), group mean, +inf on window tokens.  
+    // the slots outside hold zeros, which change neither rule), group mean, +inf on window tokens.
     const float inv_width = 1.f / (float)(2 * reach + 1);
     for (int j = own_row0 + (int)threadIdx.x; j < own_end; j += kWinThreads) {
       float sc = INFINITY;
