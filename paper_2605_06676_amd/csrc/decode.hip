@@ -387,7 +387,8 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
 // the partials of up to eight pieces are loaded together and folded in with a running maximum:
 // the chain is the offsets load plus one round per eight pieces.
 // kParts > 1, for segments of many pieces: a block of kParts times 128 threads for every query head, the pieces of an
-// element shared out among kParts threads, whose sums meet in LDS: one round per 8 kParts pieces.
+// element shared out among kParts threads, whose sums meet in LDS: one round per 8 kParts pieces.  A segment of one round
+// is left to the first 128 threads alone.
 constexpr int decode_merge_threads(int parts) { return parts == 1 ? kDecThreads : parts * kHeadDim; }
 template <bool kAligned, int kParts>
 __global__ void __launch_bounds__(decode_merge_threads(kParts))
@@ -421,6 +422,8 @@ decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restri
   const size_t slot0 = kAligned ? 0 : (size_t)s;
   if (c_first == c_last) return;   // a whole segment inside one chunk was finished by the first kernel
   constexpr int kU = 8;
+  const bool shared_out = kParts > 1 && c_last - c_first >= kU;   // the same in the whole block
+  if (part > 0 && !shared_out) return;
   float mx = -INFINITY, num = 0.f, den = 0.f;
   for (int c0 = c_first + part * kU; c0 <= c_last; c0 += kParts * kU) {
     float mv[kU], lv[kU], av[kU];
@@ -447,7 +450,7 @@ decode_merge_kernel(const int32_t* __restrict__ offsets, const int32_t* __restri
       den = fmaf(lv[u], wgt, den);
     }
   }
-  if constexpr (kParts > 1) {
+  if (shared_out) {
     __shared__ float num_lds[kParts][kHeadDim], mx_lds[kParts], den_lds[kParts];
     num_lds[part][ch] = num;
     if (ch == 0) { mx_lds[part] = mx; den_lds[part] = den; }
@@ -571,10 +574,17 @@ hipError_t launch_decode(int G, const void* q, const void* kp, const void* vp, c
                          chunk_rows, ws_acc, ws_m, ws_l, out, lse);
     };
     if constexpr (kAligned) {
-      // From three chunks a segment on, which with flat chunks there never are.  8 heads in a captured graph, whole call:
-      // 24 chunks a call 9.0 us with one thread per element and 9.2 with eight, 38 9.6 and 9.3, 100 11.1 and 9.5, 375 18.3
-      // and 10.8, 491 of 320 rows 28.1 and 18.8; 64 heads of 7 chunks 17.4 and 16.4.
-      if (total_kept / chunk_rows >= 3 * (int64_t)n_segments) return merge(std::integral_constant<int, 8>{});
+      // Up to 64 segments: from three chunks a segment on, eight threads to an element where the launch has up to 256 blocks of
+      // them and four where it has more (each block then starts half the waves).  Flat chunks, of which 65 to 170 segments have
+      // three to eight each, keep one thread per element.  In a captured graph, whole call, one thread : eight : four (us):
+      // 8 heads of 4 queries, 24 chunks a call 9.0 : 9.2, 100 11.1 : 9.5, 375 18.3 : 10.8, 491 of 320 rows 28.1 : 18.8; 64 heads of 16
+      // queries, 5 chunks each 11.0 : 13.4 : 11.7, 10 each 14.5 : 16.8 : 14.9, one of them with nearly all of 300 and 600 29.8 : 15.9 :
+      // 17.0 and 39.2 : 20.7 : 22.3.
+      const int64_t heads = (int64_t)n_segments * G;
+      if (total_kept / chunk_rows >= 3 * (int64_t)n_segments) {
+        if (heads <= 256) return merge(std::integral_constant<int, 8>{});
+        return merge(std::integral_constant<int, 4>{});
+      }
     }
     merge(std::integral_constant<int, 1>{});
   };

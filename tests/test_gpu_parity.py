@@ -205,9 +205,11 @@ def test_decode_over_few_segments_keeps_more_digits_of_the_probabilities(ctx, le
 
 @pytest.mark.parametrize("lengths,G_", [([128 * 9, 0, 128 * 64 + 1, 1, 128 * 8, 700], 4),   # parts without a chunk; an empty segment
                                         ([383] * 3, 16), ([384] * 3, 3),                     # either side of three chunks a segment
-                                        ([70000], 1), ([100] * 40 + [40000], 8)])            # longer chunks; one long among many short
+                                        ([70000], 1), ([100] * 40 + [40000], 8),             # longer chunks; one long among many short
+                                        ([128 * 8, 128 * 8 + 1, 0, 128 * 40, 5] * 8, 7),     # more than 256 heads: four threads
+                                        ([128 * 8 + 1, 128 * 33] * 32, 16), ([1024, 128] * 16, 8)])
 def test_decode_merges_of_many_chunks(ctx, lengths, G_):
-    """Segments of up to several hundred chunks, merged by eight threads per element.  Errors as in the test above; the log-sum-exp
+    """Segments of up to several hundred chunks, merged by eight or four threads per element.  Errors as in the test above; the log-sum-exp
     is an fp32 sum of fp32 exponentials of logits below 2^4."""
     n, total = len(lengths), sum(lengths)
     g = torch.Generator(device="cuda").manual_seed(total)
