@@ -30,7 +30,8 @@
 // matrix time, and ran beside 15 to 17 % in kernels that did one thing after the other.  32 query heads, 8 KV heads, in turn with the
 // kernel of running maxima and staging through registers: 2.40 -> 2.02 ms at 16384 tokens (1090 TFLOP/s; a library product
 // of 8192 x 8192 x 8192 reaches 1310 here), 649 -> 530 us at 8192, 182 -> 147 at 4096, 74 -> 62 at 2345; what the order of
-// the blocks and the pieces of plain_step took off since then stands there.  Measured and dropped: 64 queries per wave
+// the blocks and the pieces of plain_step took off since then stands there.  18 registers are kept in scratch
+// memory around the loops, none inside them.  Measured and dropped: 64 queries per wave
 // at one wave per SIMD (half the LDS reads; 2.38 ms), a block of eight waves in two groups that split the keys (2.41
 // ms; 86 us at 2345 tokens), different wave priorities on a SIMD (no change).
 #include <type_traits>

@@ -354,8 +354,8 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // kGroups = 1: eight waves of 32 keys, each takes every step of 32 queries.  kGroups = 2: four times 32 keys, two waves
 // take the steps in turn and their sums are joined at the end, which halves the chain of steps per key (short sequences).
 //
-// Bound by instruction issue (16384 tokens: matrix pipe busy for 50 % of the cycles, vector pipe 43 %, 13 % together, LDS
-// 54 %, no conflicts) and by waiting for LDS operands, at 2.0 GHz where the dQ kernel, busy for 96 %, holds 1.8.  A step
+// Bound by instruction issue (16384 tokens: matrix pipe busy for 53 % of the cycles, vector pipe 47 %, 14 % together, LDS
+// 57 %, no conflicts) and by waiting for LDS operands, at 2.0 GHz where the dQ kernel, busy for 97 %, holds 1.9.  A step
 // is a pipeline inside the wave: P and dS of its first 16 queries beside S and dP of the other 16, theirs beside S and dP
 // of the next step's first 16, then the products with all 32; the pieces are fenced so that the compiler keeps
 // exponentials beside products.  Operands are read a piece ahead, also from one half to the next, into the products and
@@ -366,8 +366,8 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // and spills), masks set in place in a branch around nothing else, addresses worked out where they are used.  A step wholly
 // above a wave's diagonal passes through the pipeline with S = -inf and dP - D = 0 and leaves the products out: its weights
 // are 0, but 0 times a row that is not finite is not (whole backward pass, in turn with multiplying it all the same: 79.0 ->
-// 77.1 us at 1024 tokens, 1674 -> 1648 at 8192; a branch around the whole step spills, 3 % slower).  32 query heads,
-// 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at
+// 77.1 us at 1024 tokens, 1674 -> 1648 at 8192, 6549 -> 6422 at 16384; a branch around the whole step
+// spills, 3 % slower).  32 query heads, 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at
 // 2345 (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the
 // products (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix
 // instructions, LDS busy 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the

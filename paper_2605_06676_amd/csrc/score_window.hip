@@ -39,7 +39,7 @@
 // is work not done: references that stay put (no maximum and no vote on it), addresses from a scalar base, sums over
 // the row blocks of both tiles at once.  32 layers of 8 heads x 32768 keys, 128 window rows, in turn with a kernel that moved its
 // references: 908 -> 829 us on one machine, 852 -> 797 on another (given the normalisers 471 -> 439 and 434 -> 418); 4 x 7
-// heads, 20001 keys, 8 layers 105 -> 99; one layer of 4097 28.2 -> 27.8.  Measured and dropped: keys straight from memory to LDS (a ring of four steps, 37 KB
+// heads, 20001 keys, 8 layers 105 -> 99; one layer of 4097 28.2 -> 26.0.  Measured and dropped: keys straight from memory to LDS (a ring of four steps, 37 KB
 // a block: too few bytes in flight, 433 -> 486 us a pass, 188 -> 216 with 8 window rows), temporal loads, and pass 2 from the
 // last block backwards so that it finds the end of the keys in the memory-side cache (0 to 7 % slower).
 #include "lkv_common.h"

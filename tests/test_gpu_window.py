@@ -383,7 +383,7 @@ def test_long_context_sampled_heads(ctx):
 @pytest.mark.parametrize("prefix", [127, 128, 129, 142, 143, 144, 145, 159, 160, 161])
 @pytest.mark.parametrize("window", [3, 33])
 def test_blocks_that_begin_around_the_window(ctx, prefix, window):
-    # Blocks are 128 keys here, their references the logits of their first 16 keys, steps 32 keys: the prefix ends just
+    # Blocks are 128 keys here, steps 32 keys, their references logits of the first step: the prefix ends just
     # before, inside and after the first tile and step of the second block, where some lanes see no key at all.
     rng = np.random.default_rng(900 + prefix + window)
     T = prefix + window
@@ -396,7 +396,8 @@ def test_blocks_that_begin_around_the_window(ctx, prefix, window):
 @pytest.mark.parametrize("reach", [60, 99, 101, 126, 130, 400, -60, -101, -400])
 def test_either_side_of_the_limit_of_the_sums(ctx, reach):
     # One key late in each block of 128 whose logit lies `reach` binary orders from the others' (about 0): sums against
-    # the first keys up to 2^100 stand, larger ones are taken again; far below, the key's weight vanishes.
+    # the first keys move their references from 2^32 on, and from about 2^128 the keys are taken again; far below, the key's
+    # weight vanishes.
     rng = np.random.default_rng(77)
     window, T = 8, 400
     K = 0.02 * rng.standard_normal((1, 1, T, 128)).astype(np.float32)
