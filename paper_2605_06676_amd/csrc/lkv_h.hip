@@ -22,8 +22,8 @@
 // fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
 // Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
 // (they stay in L2).  256 vectors of 16384 fp32 values: 30.4 us, 32.6 under a tracer (257 us for the LDS sort and
-// logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).  Of the 30: read and extremes 3.5,
-// histogram 3, two trials 4.5, fp64 pass 9.5, root 1.5, outputs the rest.  Row swaps and prefix sums on the vector ALU, fp32
+// logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).  Of the 30: read
+// and extremes 3.5, histogram 3, two trials 4.5, fp64 pass 9.5, root 1.5, outputs the rest.  Row swaps and prefix sums on the vector ALU, fp32
 // where it only places the bracket, and a root without hypot: 32.6 -> 30.4 us; 4096 values 17.5 -> 15.7, 777 9.9 -> 8.8.
 #include <hip/hip_runtime.h>
 

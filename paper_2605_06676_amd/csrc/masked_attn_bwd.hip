@@ -367,8 +367,8 @@ constexpr int kDkvStepLds = 2 * kMbStep * kDkvRow;   // Q rows, dO rows of one s
 // above a wave's diagonal passes through the pipeline with S = -inf and dP - D = 0 and leaves the products out: its weights
 // are 0, but 0 times a row that is not finite is not (whole backward pass, in turn with multiplying it all the same: 79.0 ->
 // 77.1 us at 1024 tokens, 1674 -> 1648 at 8192, 6549 -> 6422 at 16384; a branch around the whole step
-// spills, 3 % slower).  32 query heads, 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms at 16384 tokens, 136 -> 126 us at
-// 2345 (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the
+// spills, 3 % slower).  32 query heads, 8 KV heads, in turn with a kernel that did one thing after the other: 4.59 -> 4.10 ms
+// at 16384 tokens, 136 -> 126 us at 2345 (kGroups = 2); 8 and 8 heads of 4096 140 -> 120.  Measured and dropped: P and dS of the first 16 beside the
 // products (spills; 3 to 20 % slower), 16 keys per wave with V in registers (64 KB of operands per 64 matrix
 // instructions, LDS busy 78 %; 136 us at 2345), pairs of waves that share 32 keys, halve the queries of S and dP and the
 // channels of dK and dV and swap P and dS through LDS (one barrier between any two uses; 133 us at 2345, 5.12 ms at
