@@ -59,7 +59,7 @@ struct InlineOffsets {
 };
 
 struct SelShared {
-  alignas(16) uint32_t hist[kSelBins];
+  alignas(16) uint32_t bins[4 + kSelBins];   // bin -1 takes what lies past the end of a head
   uint32_t wave_tot[kSelWaves];
   uint32_t wave_gt[kSelWaves];
   uint32_t wave_eq[kSelWaves];
@@ -68,6 +68,7 @@ struct SelShared {
   uint32_t found_above;
   uint32_t found_count;
   uint32_t cand_count;
+  __device__ __forceinline__ uint32_t* hist() { return bins + 4; }
 };
 
 // Inclusive prefix sum over the 64 lanes of a wave: four shifts within the rows of 16 lanes, then the last lane of a row
@@ -230,7 +231,7 @@ __device__ __forceinline__ uint32_t descend_level(SelShared& sh, uint32_t* copie
 }
 // The first level when sh.hist already holds its counts (and a barrier has passed).
 __device__ __forceinline__ uint32_t descend_counted_level(SelShared& sh, uint32_t& prefix, uint32_t& prefix_mask, uint32_t& need) {
-  find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist[bin]; });
+  find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist()[bin]; });
   return enter_found_bin(sh, 0, prefix, prefix_mask, need);
 }
 
@@ -389,7 +390,7 @@ __device__ __forceinline__ LinearBins linear_bins(SelShared& sh, float shift, fl
   sum = sum_over_row_blocks(row16_allreduce_sum(sum));
   sq = sum_over_row_blocks(row16_allreduce_sum(sq));
   if (lane == 0) { sh.stat[0][wave] = n; sh.stat[1][wave] = sum; sh.stat[2][wave] = sq; }
-  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = 0;
+  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist()[i] = 0;
   __syncthreads();
   n = fmaxf(row16_allreduce_sum(sh.stat[0][lane & 15]), 1.f);
   const float mean = row16_allreduce_sum(sh.stat[1][lane & 15]) / n;
@@ -399,26 +400,50 @@ __device__ __forceinline__ LinearBins linear_bins(SelShared& sh, float shift, fl
 
 __device__ __forceinline__ bool is_finite_score(float u) { return (__float_as_uint(u) & 0x7f800000u) != 0x7f800000u; }
 
+// The same from a few scores of every lane of a wave, without a barrier.
+template <int kN>
+__device__ __forceinline__ LinearBins run_bins(const float (&x)[kN], float shift) {
+  float n = 0.f, sum = 0.f, sq = 0.f;
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    const bool fin = is_finite_score(x[j]);
+    const float d = fin ? x[j] - shift : 0.f;
+    n += fin ? 1.f : 0.f;
+    sum += d;
+    sq = fmaf(d, d, sq);
+  }
+  n = fmaxf(sum_over_row_blocks(row16_allreduce_sum(n)), 1.f);
+  const float mean = sum_over_row_blocks(row16_allreduce_sum(sum)) / n;
+  const float dev = sqrtf(fmaxf(sum_over_row_blocks(row16_allreduce_sum(sq)) / n - mean * mean, 0.f));
+  return {shift + mean - kSelBinSpan * dev, (float)kSelBins / (2.f * kSelBinSpan * dev)};
+}
+
 // A listed token as one number, larger for what is kept first: the key, then the lower index.
-__device__ __forceinline__ uint64_t* ranking_list(SelShared& sh) { return reinterpret_cast<uint64_t*>(sh.hist); }
+__device__ __forceinline__ uint64_t* ranking_list(SelShared& sh) { return reinterpret_cast<uint64_t*>(sh.hist()); }
 __device__ __forceinline__ void list_for_ranking(SelShared& sh, uint32_t key, uint32_t token) {
   const uint32_t slot = atomicAdd(&sh.cand_count, 1u);
   if (slot < (uint32_t)kSelRankMax) ranking_list(sh)[slot] = ((uint64_t)key << 32) | (uint32_t)~token;
 }
 
-// The `need` best of the n <= kSelRankMax listed tokens join gt_map: those with fewer than `need` listed before them.
+// How many of the n <= kSelRankMax listed tokens come before token threadIdx.x / 4, which must be one of them: a quad per token,
+// a quarter of the list per thread.
+__device__ __forceinline__ uint32_t listed_rank(const uint64_t* list, uint32_t n) {
+  const uint64_t mine = list[threadIdx.x >> 2];
+  uint32_t rank = 0;
+#pragma unroll 4
+  for (uint32_t i = threadIdx.x & 3; i < n; i += 4) rank += list[i] > mine ? 1u : 0u;
+  rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0xb1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
+  rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0x4e, 0xf, 0xf, true);   // quad_perm [2, 3, 0, 1]
+  return rank;
+}
+
+// The `need` best of the listed tokens join gt_map: those with fewer than `need` listed before them.
 __device__ __forceinline__ void keep_best_listed(SelShared& sh, uint32_t n, uint32_t need, uint32_t* gt_map) {
   const uint64_t* list = ranking_list(sh);
-  const uint32_t j = threadIdx.x >> 2, part = threadIdx.x & 3;   // a quad per token, a quarter of the list per thread
+  const uint32_t j = threadIdx.x >> 2;
   if (j < n) {
-    const uint64_t mine = list[j];
-    uint32_t rank = 0;
-#pragma unroll 4
-    for (uint32_t i = part; i < n; i += 4) rank += list[i] > mine ? 1u : 0u;
-    rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0xb1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
-    rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0x4e, 0xf, 0xf, true);   // quad_perm [2, 3, 0, 1]
-    const uint32_t token = ~(uint32_t)mine;
-    if (part == 0 && rank < need) atomicOr(&gt_map[token >> 5], 1u << (token & 31));
+    const uint32_t token = ~(uint32_t)list[j];
+    if (listed_rank(list, n) < need && (threadIdx.x & 3) == 0) atomicOr(&gt_map[token >> 5], 1u << (token & 31));
   }
 }
 
@@ -427,9 +452,99 @@ __device__ __forceinline__ void keep_best_listed(SelShared& sh, uint32_t n, uint
 // steps are few: a histogram over linear bins, the tokens above the bin of the threshold kept, the few dozen inside it
 // ranked one by one.  Where a sample says that linear bins would not spread the scores (8 of a wave's 64 in one bin) or
 // more than kSelRankMax tokens share the bin, the radix descent over the held keys narrows them instead.  8 heads of
-// 32768 normal scores: 16.5 us, 256 heads 20 us, 8 heads of 4000: 7 us; of exp(3 x): 20 us; all equal: 29 us.  (With the
+// 32768 normal scores: 15 us, 256 heads 16 us, 8 heads of 4000: 7 us; of exp(3 x): 21 us; all equal: 29 us.  (With the
 // keys cached in LDS, three radix levels over them and prefix sums through the LDS crossbar: 24, 30, 11, 24 and 99 us.)
 // Emitting a run of 64 tokens at a time from a prefix count over runs instead of from the masks: 1.5 us more.
+// The bins come from a few scores that every wave reads for itself (no barrier, no LDS), and the tokens inside a bin are gathered as
+// bits of a round and listed afterwards, in place of a branch in each round: 16.4 -> 15.1 us for 8 heads of 32768, 18.0 -> 16.2 for 256.
+// The first part of the choice among a head of at most kE * 1024 tokens, by the whole workgroup; thread t has tokens
+// t, t + 1024, .. in rounds: v, their scores, and at_bin, whose values above `bin` are kept and below it not.  The n_left tokens
+// at `bin` are to be ranked, `need` of them kept; more than kSelRankMax: they share one key, and the first `need` are kept.
+// What lies past the end of the head is at bin -1.
+template <int kE>
+__device__ __forceinline__ uint32_t held_bins(SelShared& sh, const float* __restrict__ u, int T, int budget, uint32_t* stage,
+                                              float (&v)[kE], int (&at_bin)[kE], int& bin, uint32_t& need) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int rounds = (T + kSelThreads - 1) / kSelThreads;
+  // the bins come from eight runs of 64 scores, the same in every wave: any bins give the same selection, these a short list
+  // (158 of 256 from one to the next: unevenly spread, and not from the first tokens, whose scores can be unlike the others')
+  constexpr int kRuns = 8;
+  float x[kRuns];
+#pragma unroll
+  for (int j = 0; j < kRuns; ++j) x[j] = u[min((int)((int64_t)T * ((20 + 158 * j) & 255) >> 8) + lane, T - 1)];
+  // round k, token k * 1024 + tid: a wave's 64 tokens of a round are two words of the bitmaps
+#pragma unroll
+  for (int k = 0; k < kE; ++k) v[k] = u[min(k * kSelThreads + tid, T - 1)];
+  if (tid == 0) sh.cand_count = 0;
+  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist()[i] = 0;
+  need = (uint32_t)budget;   // rank of the threshold among the keys not yet decided (1-based)
+  uint32_t prefix = 0, prefix_mask = 0;
+  auto count = [&](auto fn) {
+#pragma unroll
+    for (int k = 0; k < kE; ++k)
+      if (k * kSelThreads + tid < T) fn(order_key(v[k]));
+  };
+  const float first = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x[0])));
+  const LinearBins bins = run_bins(x, is_finite_score(first) ? first : 0.f);
+  bool crowded = false;
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    at_bin[k] = bins.bin(v[k]);
+    if (k % 8 == 0 && (k == 0 || (k + 1) * kSelThreads <= T)) crowded |= lanes_crowd(at_bin[k]);
+    if (k * kSelThreads + tid >= T) at_bin[k] = -1;
+  }
+  uint32_t n_left = kSelRankMax + 1;
+  bin = 0;
+  if (!__syncthreads_or(crowded && wave * 64 + 64 <= T)) {
+#pragma unroll
+    for (int k = 0; k < kE; ++k)
+      if (k < rounds) atomicAdd(&sh.hist()[at_bin[k]], 1u);   // uniform
+    __syncthreads();
+    find_bin(sh, kSelBins, need, [&](int b) { return sh.hist()[b]; });
+    n_left = sh.found_count;
+    bin = (int)sh.found_bin;
+    if (n_left <= (uint32_t)kSelRankMax) need -= sh.found_above;
+    __syncthreads();   // the histogram and found_* are rewritten
+  }
+  if (n_left > (uint32_t)kSelRankMax) {
+#pragma unroll 1
+    for (int level = 0; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
+      n_left = descend_level(sh, stage, level, prefix, prefix_mask, need, count);
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      const uint32_t decided = order_key(v[k]) & prefix_mask;
+      at_bin[k] = k * kSelThreads + tid >= T ? -1 : decided > prefix ? 2 : decided == prefix ? 1 : 0;
+    }
+    bin = 1;
+  }
+  return n_left;
+}
+
+// One bit per round of a thread: bit k is test(k).  The bits are shifted in from the highest round down.
+template <int kE, typename Test>
+__device__ __forceinline__ uint64_t round_bits(Test test) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int k = kE - 1; k >= 32; --k) hi = hi + hi + (test(k) ? 1u : 0u);
+#pragma unroll
+  for (int k = (kE < 32 ? kE : 32) - 1; k >= 0; --k) lo = lo + lo + (test(k) ? 1u : 0u);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Lists the tokens of the rounds in `bits` for the ranking.  Their scores are read again: few threads have any, and a branch
+// around each of the rounds' registers costs more.
+__device__ __forceinline__ void list_rounds(SelShared& sh, const float* __restrict__ u, uint64_t bits) {
+  while (__ballot(bits != 0ull) != 0ull) {
+    if (bits) {
+      const uint32_t token = (uint32_t)(__builtin_ctzll(bits) * kSelThreads) + threadIdx.x;
+      list_for_ranking(sh, order_key(u[token]), token);
+      bits &= bits - 1;
+    }
+  }
+}
+
 template <bool kInline, int kE>
 __global__ void __launch_bounds__(kSelThreads)
 select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __restrict__ offsets, int32_t* __restrict__ idx,
@@ -466,76 +581,19 @@ select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* _
     return;
   }
 
-  // round k, token k * 1024 + tid: a wave's 64 tokens of a round are two words of the bitmaps
   float v[kE];
-#pragma unroll
-  for (int k = 0; k < kE; ++k) v[k] = u[min(k * kSelThreads + tid, T - 1)];
+  int at_bin[kE], bin;
+  uint32_t need;
+  const uint32_t n_left = held_bins<kE>(sh, u, T, budget, stage, v, at_bin, bin, need);
   const int rounds = (T + kSelThreads - 1) / kSelThreads;
-  auto for_each = [&](auto f) {
-#pragma unroll
-    for (int k = 0; k < kE; ++k)
-      if (k * kSelThreads + tid < T) f(v[k], k * kSelThreads + tid);
-  };
-  if (tid == 0) sh.cand_count = 0;
-  uint32_t need = (uint32_t)budget;   // rank of the threshold among the keys not yet decided (1-based)
-  uint32_t prefix = 0, prefix_mask = 0;
-  auto count = [&](auto fn) { for_each([&](float x, int) { fn(order_key(x)); }); };
-  int at_bin[kE];
-  // the bins come from some rounds' scores: any bins give the same selection, these a short list
-  constexpr int kSampleStep = kE < 16 ? 1 : 4;
-  const float first = u[0];
-  const float shift = is_finite_score(first) ? first : 0.f;
-  float n = 0.f, sum = 0.f, sq = 0.f;
-#pragma unroll
-  for (int k = 0; k < kE; k += kSampleStep) {
-    const bool fin = k * kSelThreads + tid < T && is_finite_score(v[k]);
-    const float d = fin ? v[k] - shift : 0.f;
-    n += fin ? 1.f : 0.f;
-    sum += d;
-    sq = fmaf(d, d, sq);
-  }
-  const LinearBins bins = linear_bins(sh, shift, n, sum, sq);
-  bool crowded = false;
-#pragma unroll
-  for (int k = 0; k < kE; ++k) {
-    at_bin[k] = bins.bin(v[k]);
-    if (k % 8 == 0 && (k == 0 || (k + 1) * kSelThreads <= T)) crowded |= lanes_crowd(at_bin[k]);
-  }
-  uint32_t n_left = kSelRankMax + 1;
-  int bin = 0;
-  if (!__syncthreads_or(crowded && wave * 64 + 64 <= T)) {
-#pragma unroll
-    for (int k = 0; k < kE; ++k)
-      if (k * kSelThreads + tid < T) atomicAdd(&sh.hist[at_bin[k]], 1u);
-    __syncthreads();
-    find_bin(sh, kSelBins, need, [&](int b) { return sh.hist[b]; });
-    n_left = sh.found_count;
-    bin = (int)sh.found_bin;
-    if (n_left <= (uint32_t)kSelRankMax) need -= sh.found_above;
-    __syncthreads();   // the histogram and found_* are rewritten
-  }
-  if (n_left > (uint32_t)kSelRankMax) {
-#pragma unroll 1
-    for (int level = 0; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
-      n_left = descend_level(sh, stage, level, prefix, prefix_mask, need, count);
-#pragma unroll
-    for (int k = 0; k < kE; ++k) {
-      const uint32_t decided = order_key(v[k]) & prefix_mask;
-      at_bin[k] = decided > prefix ? 2 : decided == prefix ? 1 : 0;
-    }
-    bin = 1;
-  }
   if (n_left <= (uint32_t)kSelRankMax) {
     // tokens above the undecided bin to the bitmap, those inside it to the list
+    list_rounds(sh, u, round_bits<kE>([&](int k) { return at_bin[k] == bin; }));
 #pragma unroll
     for (int k = 0; k < kE; ++k) {
       if (k < rounds) {   // uniform
-        const int i = k * kSelThreads + tid;
-        const bool above = i < T && at_bin[k] > bin;
-        const bool inside = i < T && at_bin[k] == bin;
-        const unsigned long long m = __ballot(above);
+        const unsigned long long m = __ballot(at_bin[k] > bin);
         if (lane == 0) reinterpret_cast<unsigned long long*>(gt_map)[k * kSelWaves + wave] = m;
-        if (inside) list_for_ranking(sh, order_key(v[k]), (uint32_t)i);
       }
     }
     __syncthreads();
@@ -565,9 +623,8 @@ select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* _
 #pragma unroll
   for (int k = 0; k < kE; ++k) {
     if (k < rounds) {   // uniform
-      const bool in = k * kSelThreads + tid < T;
-      const unsigned long long m_gt = __ballot(in && at_bin[k] > bin);
-      const unsigned long long m_eq = __ballot(in && at_bin[k] == bin);
+      const unsigned long long m_gt = __ballot(at_bin[k] > bin);
+      const unsigned long long m_eq = __ballot(at_bin[k] == bin);
       if (lane == 0) {
         reinterpret_cast<unsigned long long*>(gt_map)[k * kSelWaves + wave] = m_gt;
         reinterpret_cast<unsigned long long*>(eq_map)[k * kSelWaves + wave] = m_eq;
@@ -621,7 +678,7 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
   }
   if (kCounted) {
     for (int i = tid; i < kSelBins; i += kSelThreads) {
-      sh.hist[i] = my_counts[i];
+      sh.hist()[i] = my_counts[i];
       my_counts[i] = 0;
     }
     __syncthreads();
@@ -668,9 +725,9 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
     n_cand = descend_level(sh, copies, 0, prefix, prefix_mask, need, count);
     bin0 = prefix >> 21;
   } else {
-    for_each_global_score(u, T, [&](float s, int) { atomicAdd(&sh.hist[bins.bin(s)], 1u); });
+    for_each_global_score(u, T, [&](float s, int) { atomicAdd(&sh.hist()[bins.bin(s)], 1u); });
     __syncthreads();
-    find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist[bin]; });
+    find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist()[bin]; });
     n_cand = sh.found_count;
     bin0 = sh.found_bin;
     if (n_cand <= (uint32_t)kSelCandCap && T <= bitmap_limit) need -= sh.found_above;
@@ -810,7 +867,7 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
   const int budget = offsets[seg + 1] - offsets[seg];
   if (budget <= 0 || budget >= T) return;
   const uint32_t* my_counts = counts + (size_t)seg * kLevel0Bins;
-  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist[i] = my_counts[i];
+  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist()[i] = my_counts[i];
   __syncthreads();
   uint32_t prefix = 0, prefix_mask = 0, need = (uint32_t)budget;
   const uint32_t n_cand = descend_counted_level(sh, prefix, prefix_mask, need);
