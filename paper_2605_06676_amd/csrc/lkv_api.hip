@@ -679,7 +679,13 @@ lkv_status lkv_evict_layer(lkv_ctx* ctx, const lkv_cache* layer, int32_t layer_i
   }
   tab.first[layer->n_seq] = layer->n_seq * m * H;
   tab.n = layer->n_seq;
-  // select: segment of (sequence i, view head j) is i * n_layers * H + layer_index * H + j, offsets already on the device
+  // segment of (sequence i, view head j) is i * n_layers * H + layer_index * H + j, offsets already on the device
+  int blocks = 0;
+  if (const int rows = lkv::select_compact_rows(tab, budgets + layer_index * H, heads_all, layer_rows, &blocks)) {
+    lkv::launch_select_compact(tab, offsets, idx, layer_index * H, heads_all, rows, blocks, counts, kp, vp, st);
+    if (hipError_t e = hipGetLastError()) return hip_fail(ctx, e, "lkv_evict_layer launch");
+    return LKV_OK;
+  }
   lkv::launch_select(tab, nullptr, (int)n_seg, const_cast<int32_t*>(offsets), idx, layer_index * H, heads_all, st, nullptr,
                      nullptr, nullptr, counts, pre_maps, pre_words);
   if (hipError_t e = hipGetLastError()) return hip_fail(ctx, e, "lkv_evict_layer select launch");

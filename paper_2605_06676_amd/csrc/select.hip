@@ -52,6 +52,12 @@ constexpr int kSelBatch = 8;                                // loads in flight p
 constexpr int kSelInlineOffsets = 640;                      // offsets that fit the kernel arguments next to the launch table
 constexpr int kSelSplitMaxHeads = 64;                       // launches with at most this many (long) heads split each head's pass
 constexpr int kSelSplitTargetBlocks = 256;                  // over about this many workgroups in all,
+constexpr int kFuseMaxHeads = 64;                           // one lane each
+// Rows of a block of the one launch, at most: with more of them the copy decides, and sixteen waves a compute unit copy more slowly than
+// the compaction's blocks (against two launches, 34000 tokens: 32 heads, 214 rows a block 117 -> 114 us, 680 136 -> 137, 1850
+// 181 -> 190; 64 heads, 490 222 -> 215, 1460 259 -> 264).
+constexpr int kFuseMaxRows = 600;
+constexpr int kFuseBlocks = 256;                            // one round: a block to a compute unit
 constexpr int kSelSplitMax = 32;                            // at most this many per head
 
 struct InlineOffsets {
@@ -635,6 +641,156 @@ select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* _
   emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, stage);
 }
 
+// Top-k and compaction of few heads of at most kE * 1024 tokens in one launch (a layer evicted during prefill).  A head's
+// choice is a chain of short steps in one workgroup, which leaves the rest of the chip idle, so it is made again in every block that copies rows
+// of the head: blocks in proportion to the budgets, one to a compute unit, each with as many rows as the others.  What goes
+// away is the second launch, the emission of all but a block's own indices, their way through memory and the search for a row's segment.  8 heads of 32768, 39 thousand rows: 26.5 us in two launches,
+// 20.6 in one (the whole call with the linear scorer 51.2 -> 45.0, 49.3 of it with the two launches of today); of 4096 19.3 -> 16.6, 2 heads of 34000 30.4 -> 24.7.  Two rows' pieces
+// in flight per thread: four were 0.1 to 0.8 us slower up to 100 rows a block, eight up to 1.6.
+template <int kE>
+__global__ void __launch_bounds__(kSelThreads)
+select_compact_kernel(SeqTable tab, const int32_t* __restrict__ offsets, int32_t* __restrict__ idx, uint32_t* __restrict__ counts,
+                      int seg_base, int seg_stride, int map_words, int rows_per_block, uint4* __restrict__ kp, uint4* __restrict__ vp) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  SelShared& sh = *reinterpret_cast<SelShared*>(smem);
+  uint32_t* gt_map = reinterpret_cast<uint32_t*>(smem + sizeof(SelShared));
+  uint32_t* eq_map = gt_map + map_words;
+  uint32_t* stage = eq_map + map_words;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int n_segs = tab.first[tab.n];   // at most 64: a lane each
+
+  // the head and the packed rows of this block: every head has one block for each rows_per_block of its rows, and at least one
+  int my_off = 0, my_budget = 0;
+  if (lane < n_segs) {
+    int seq = 0;
+    while (seq + 1 < tab.n && lane >= tab.first[seq + 1]) ++seq;
+    const int seg = seg_base + seq * seg_stride + lane - tab.first[seq];
+    my_off = offsets[seg];
+    my_budget = offsets[seg + 1] - my_off;
+  }
+  const uint32_t my_blocks = lane < n_segs ? (uint32_t)max(1, (my_budget + rows_per_block - 1) / rows_per_block) : 0u;
+  const uint32_t last = wave_inclusive_scan(my_blocks);
+  const unsigned long long at = __ballot(last > blockIdx.x);
+  if (at == 0ull) return;
+  const int local_seg = __builtin_ctzll(at);
+  const int part = (int)blockIdx.x - (int)__builtin_amdgcn_readlane((int)(last - my_blocks), local_seg);
+  const int off = __builtin_amdgcn_readlane(my_off, local_seg);
+  const int budget = __builtin_amdgcn_readlane(my_budget, local_seg);
+  const int seq = seq_of_unit(tab, local_seg);
+  const int lh = local_seg - tab.first[seq];
+  const int T = tab.T[seq];
+  if (counts != nullptr && part == 0)   // not needed here, but left zero for the next scoring launch
+    for (int i = tid; i < kLevel0Bins; i += kSelThreads)
+      counts[(size_t)(seg_base + seq * seg_stride + lh) * kLevel0Bins + i] = 0;
+  const int p0 = part * rows_per_block, p1 = min(min(budget, T), p0 + rows_per_block);
+  if (p0 >= p1) return;
+  const int n_rows = p1 - p0;
+  uint32_t* tokens = stage;   // of the block's rows
+  if (budget >= T) {   // everything is kept
+    for (int i = tid; i < n_rows; i += kSelThreads) tokens[i] = (uint32_t)(p0 + i);
+  } else {
+    const float* u = tab.scores[seq] + (size_t)lh * (size_t)T;
+    const int rounds = (T + kSelThreads - 1) / kSelThreads;
+    const int groups = rounds * kSelWaves;   // of 64 tokens, at most 544: a thread each
+    unsigned long long* masks = reinterpret_cast<unsigned long long*>(gt_map);
+    float v[kE];
+    int at_bin[kE], bin;
+    uint32_t need;
+    const uint32_t n_left = held_bins<kE>(sh, u, T, budget, stage, v, at_bin, bin, need);
+    const bool ranked = n_left <= (uint32_t)kSelRankMax;
+    if (ranked) list_rounds(sh, u, round_bits<kE>([&](int k) { return at_bin[k] == bin; }));
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      if (k < rounds) {   // uniform
+        const unsigned long long m = __ballot(at_bin[k] > bin);
+        if (lane == 0) masks[k * kSelWaves + wave] = m;
+      }
+    }
+    if (!ranked) {
+#pragma unroll
+      for (int k = 0; k < kE; ++k) {
+        if (k < rounds) {   // uniform
+          const unsigned long long m = __ballot(at_bin[k] == bin);
+          if (lane == 0) reinterpret_cast<unsigned long long*>(eq_map)[k * kSelWaves + wave] = m;
+        }
+      }
+    }
+    __syncthreads();
+    if (ranked) {
+      keep_best_listed(sh, n_left, need, gt_map);
+      __syncthreads();
+    }
+    unsigned long long m = tid < groups ? masks[tid] : 0ull;
+    if (!ranked) {   // the first `need` copies of the threshold key join the tokens above it
+      const unsigned long long eq = tid < groups ? reinterpret_cast<const unsigned long long*>(eq_map)[tid] : 0ull;
+      const uint32_t n_eq = (uint32_t)__popcll(eq);
+      const uint32_t incl = wave_inclusive_scan(n_eq);
+      if (lane == 63) sh.wave_eq[wave] = incl;
+      __syncthreads();
+      const uint32_t before = waves_before(sh.wave_eq, wave, lane) + incl - n_eq;
+      const uint32_t take = before < need ? min(n_eq, need - before) : 0u;
+      const uint32_t n_low = (uint32_t)__popc((uint32_t)eq);
+      m |= lowest_set_bits((uint32_t)eq, min(take, n_low));
+      if (take > n_low) m |= (unsigned long long)lowest_set_bits((uint32_t)(eq >> 32), take - n_low) << 32;
+    }
+    // the tokens of the block's rows in order
+    const uint32_t cnt = (uint32_t)__popcll(m);
+    const uint32_t incl = wave_inclusive_scan(cnt);
+    if (lane == 63) sh.wave_tot[wave] = incl;
+    __syncthreads();
+    int at = (int)(waves_before(sh.wave_tot, wave, lane) + incl - cnt) - p0;   // place of the group's first among them
+    const unsigned long long some = __ballot(at < n_rows && at + (int)cnt > 0);   // groups with a row of the block
+    if (__popcll(some) <= 16) {   // few (a dense head): all lanes on one after the other
+      for (unsigned long long left = some; left != 0ull; left &= left - 1) {
+        const int g = __builtin_ctzll(left);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, g);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), g);
+        const int i = __builtin_amdgcn_readlane(at, g) + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        if ((((lane < 32 ? lo : hi) >> (lane & 31)) & 1u) && i >= 0 && i < n_rows) tokens[i] = (uint32_t)((wave * 64 + g) * 64 + lane);
+      }
+    } else {
+      unsigned long long bits = (some >> lane) & 1ull ? m : 0ull;
+      while (__ballot(bits != 0ull) != 0ull) {
+        if (bits) {
+          if (at >= 0 && at < n_rows) tokens[at] = (uint32_t)(tid * 64 + __builtin_ctzll(bits));
+          ++at;
+          bits &= bits - 1;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < n_rows; i += kSelThreads) idx[(size_t)off + p0 + i] = (int32_t)tokens[i];
+  // the rows: 16 lanes a row, 64 rows a round of the workgroup
+  constexpr int kRound = kSelThreads / 16;
+  constexpr int kU = 2;
+  const int c = tid & 15;
+  const uint4* kh = reinterpret_cast<const uint4*>(tab.k[seq]) + (size_t)lh * (size_t)T * kChunksPerRow + c;
+  const uint4* vh = reinterpret_cast<const uint4*>(tab.v[seq]) + (size_t)lh * (size_t)T * kChunksPerRow + c;
+  uint4* kd = kp + ((size_t)off + p0) * kChunksPerRow + c;
+  uint4* vd = vp + ((size_t)off + p0) * kChunksPerRow + c;
+#pragma unroll 1
+  for (int i0 = tid >> 4; i0 < n_rows; i0 += kRound * kU) {
+    uint4 kk[kU], vv[kU];
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const size_t row = tokens[min(i0 + j * kRound, n_rows - 1)];
+      kk[j] = load_stream16(kh + row * kChunksPerRow);
+      vv[j] = load_stream16(vh + row * kChunksPerRow);
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const int i = i0 + j * kRound;
+      if (i < n_rows) {
+        store_stream16(kd + (size_t)i * kChunksPerRow, kk[j]);
+        store_stream16(vd + (size_t)i * kChunksPerRow, vv[j]);
+      }
+    }
+  }
+}
+
 // kCounted: the first-level digits of every segment's scores have already been counted by the scoring launch
 // (`counts`: uint32 [segments][kLevel0Bins]); the block takes its histogram from there instead of from a pass over
 // the scores, and leaves the counters zero for the next scoring launch.
@@ -913,7 +1069,9 @@ hipError_t select_prepare() {
       reinterpret_cast<const void*>(select_kernel<false, true>),  reinterpret_cast<const void*>(select_kernel<true, true>),
 #define LKV_HELD_KERNELS(kE)                                                                                             \
   reinterpret_cast<const void*>(select_held_kernel<false, kE>), reinterpret_cast<const void*>(select_held_kernel<true, kE>)
-      LKV_HELD_KERNELS(8), LKV_HELD_KERNELS(16), LKV_HELD_KERNELS(kSelMaxHeld)};
+      LKV_HELD_KERNELS(8), LKV_HELD_KERNELS(16), LKV_HELD_KERNELS(kSelMaxHeld),
+      reinterpret_cast<const void*>(select_compact_kernel<8>), reinterpret_cast<const void*>(select_compact_kernel<16>),
+      reinterpret_cast<const void*>(select_compact_kernel<kSelMaxHeld>)};
 #undef LKV_HELD_KERNELS
   for (const void* k : kernels)
     if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
@@ -922,6 +1080,51 @@ hipError_t select_prepare() {
 
 int select_inline_capacity() { return kSelInlineOffsets; }
 int select_max_bitmap_tokens() { return kSelMaxBitmapT; }
+
+// Blocks of the one-launch top-k and compaction whose blocks take up to `rows` rows each.
+static int64_t select_compact_blocks(const int32_t* budgets, int n_seq, int seq_stride, int heads, int64_t rows) {
+  int64_t n = 0;
+  for (int i = 0; i < n_seq; ++i)
+    for (int j = 0; j < heads; ++j) {
+      const int64_t parts = (budgets[(size_t)i * seq_stride + j] + rows - 1) / rows;
+      n += parts > 1 ? parts : 1;
+    }
+  return n;
+}
+
+// Rows of a block of the one-launch top-k and compaction (and the blocks), 0 where the two launches are better.
+int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, int* blocks) {
+  const int segs = tab.first[tab.n];
+  if (segs > kFuseMaxHeads || total_rows <= 0) return 0;
+  for (int i = 0; i < tab.n; ++i)
+    if (tab.T[i] > kSelMaxHeldT) return 0;
+  auto count = [&](int64_t rows) { return select_compact_blocks(budgets, tab.n, seq_stride, segs / tab.n, rows); };
+  int64_t lo = total_rows / kFuseBlocks, hi = lo < 32 ? 64 : 2 * lo;   // hi fits one round, lo does not
+  if (lo < 63) lo = 63;
+  while (count(hi) > kFuseBlocks) hi *= 2;
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    (count(mid) > kFuseBlocks ? lo : hi) = mid;
+  }
+  if (hi > kFuseMaxRows) return 0;
+  *blocks = (int)count(hi);
+  return (int)hi;
+}
+
+void launch_select_compact(const SeqTable& tab, const int32_t* offsets, int32_t* idx, int seg_base, int seg_stride,
+                           int rows_per_block, int blocks, uint32_t* counts, void* kp, void* vp, hipStream_t stream) {
+  int most = 0;
+  for (int i = 0; i < tab.n; ++i) most = tab.T[i] > most ? tab.T[i] : most;
+  const int map_words = (most + kSelThreads - 1) / kSelThreads * 32;
+  const size_t lds = sizeof(SelShared) + 2 * (size_t)map_words * 4 + kSelStageBytes;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kSelThreads), lds, stream, tab, offsets, idx, counts, seg_base, seg_stride, map_words,
+                       rows_per_block, static_cast<uint4*>(kp), static_cast<uint4*>(vp));
+  };
+  if (most > 16 * kSelThreads) launch(select_compact_kernel<kSelMaxHeld>);
+  else if (most > 8 * kSelThreads) launch(select_compact_kernel<16>);
+  else launch(select_compact_kernel<8>);
+}
 
 // `host_offsets` non-null: all n_total_segments + 1 offsets are passed in the kernel arguments
 // (n_total_segments < kSelInlineOffsets) and the kernel writes the device array; null: the

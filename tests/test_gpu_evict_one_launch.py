@@ -1,0 +1,118 @@
+"""Top-k and compaction of a layer view in one launch (lkv_evict_layer, short heads and few of them) against the general
+path, lkv_select and lkv_compact over the same scores, bit for bit; and the indices against the oracle's top-k."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import lkv_oracle as O
+from paper_2605_06676_amd import lkv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = lkv.Context(0)
+    yield c
+    c.close()
+
+
+def draw_scores(kind, shape, rng):
+    u = rng.standard_normal(shape).astype(np.float32)
+    if kind == "ties":            # few values, each many times: more copies of the threshold than are ranked one by one
+        u = np.round(u * 2) / 2
+    elif kind == "equal":
+        u = np.full(shape, -0.5, np.float32)
+    elif kind == "special":
+        flat = u.reshape(-1)
+        for x in (np.nan, np.inf, -np.inf, 0.0, -0.0, 1e30, -1e30):
+            flat[rng.integers(0, flat.size, max(1, flat.size // 50))] = x
+    elif kind == "late":          # what is kept lies at the end of the head
+        u += np.linspace(0, 20, shape[-1], dtype=np.float32)
+    return u
+
+
+# sequence lengths, layers of the model and of the view, heads, and the kinds of scores
+CASES = [
+    ([1], 1, 1, 1, "normal"), ([63], 2, 1, 2, "normal"), ([64], 1, 1, 3, "special"), ([65, 1], 3, 2, 2, "normal"),
+    ([1023], 1, 1, 2, "ties"), ([1024], 1, 1, 2, "normal"), ([1025, 3000], 2, 1, 4, "special"),
+    ([8192], 1, 1, 8, "normal"), ([8193], 1, 1, 8, "late"), ([16384], 1, 1, 2, "equal"), ([16385, 700, 9001], 2, 2, 2, "ties"),
+    ([34816], 1, 1, 2, "normal"), ([34816, 17], 3, 2, 1, "special"), ([34000], 2, 2, 4, "late"), ([20001], 1, 1, 3, "ties"),
+    ([300], 8, 8, 8, "normal"),                       # 64 heads
+    ([300, 40], 11, 11, 3, "normal"),                 # 66: the general path
+    ([34817], 1, 1, 2, "normal"), ([34817, 900], 1, 1, 1, "ties"),   # too long for the registers
+]
+
+
+@pytest.mark.parametrize("counted", [False, True])
+@pytest.mark.parametrize("lens,n_layers,m,H,kind", CASES)
+def test_same_as_select_and_compact(ctx, lens, n_layers, m, H, kind, counted):
+    rng = np.random.default_rng(len(lens) * 1000 + lens[0] + H)
+    K = [torch.randint(-30000, 30000, (m, H, T, 128), dtype=torch.int16, device="cuda").view(torch.bfloat16) for T in lens]
+    V = [torch.randint(-30000, 30000, (m, H, T, 128), dtype=torch.int16, device="cuda").view(torch.bfloat16) for T in lens]
+    view = lkv.Cache(K, V, H)
+    u = [draw_scores(kind, (m, H, T), rng) for T in lens]
+    scores = [torch.from_numpy(x).cuda() for x in u]
+    budgets = np.zeros((len(lens), n_layers, H), np.int32)
+    layer = n_layers - m
+    for s, T in enumerate(lens):
+        b = rng.integers(0, T + 1, size=(n_layers, H))
+        b[:, 0] = rng.choice([0, 1, T - 1, T, T // 2], n_layers)
+        b[layer, -1] = max(1, T // 7)
+        budgets[s] = b
+    offsets = torch.empty(budgets.size + 1, dtype=torch.int32, device="cuda")
+    total = lkv.lkv_plan_offsets(ctx, budgets, offsets)
+    idx = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.zeros((total, 128), dtype=torch.int16, device="cuda").view(torch.bfloat16) for _ in range(2))
+    counts = None
+    if counted:   # with a NULL scorer nothing counts and the buffer stays as it is
+        counts = torch.zeros(lkv.lkv_counts_bytes(budgets.size), dtype=torch.uint8, device="cuda")
+    lkv.lkv_evict_layer(ctx, view, layer, n_layers, None, budgets, offsets, scores, idx, kp, vp, counts=counts)
+
+    mine = np.ascontiguousarray(budgets[:, layer:layer + m])
+    offsets2 = torch.empty(mine.size + 1, dtype=torch.int32, device="cuda")
+    n = lkv.lkv_plan_offsets(ctx, mine, offsets2)
+    idx2 = torch.empty(max(n, 1), dtype=torch.int32, device="cuda")
+    kp2, vp2 = (torch.empty((max(n, 1), 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    lkv.lkv_select(ctx, view, scores, None, idx2, offsets2)
+    lkv.lkv_compact(ctx, view, idx2, offsets2, n, kp2, vp2)
+    torch.cuda.synchronize()
+    off, off2 = offsets.cpu().numpy(), offsets2.cpu().numpy()
+    touched = np.zeros(total, bool)
+    for s, T in enumerate(lens):
+        for j in range(m * H):
+            a = (s * n_layers + layer) * H + j
+            lo, hi, l2, h2 = off[a], off[a + 1], off2[s * m * H + j], off2[s * m * H + j + 1]
+            assert hi - lo == h2 - l2
+            touched[lo:hi] = True
+            assert torch.equal(idx[lo:hi], idx2[l2:h2]), (s, j)
+            assert np.array_equal(idx[lo:hi].cpu().numpy(), O.select(u[s].reshape(m * H, T)[j], int(hi - lo))), (s, j)
+            assert torch.equal(kp[lo:hi].view(torch.int16), kp2[l2:h2].view(torch.int16))
+            assert torch.equal(vp[lo:hi].view(torch.int16), vp2[l2:h2].view(torch.int16))
+    # rows of other layers are not written
+    rest = torch.from_numpy(~touched).cuda()
+    assert (idx[rest] == -1).all() and (kp[rest].view(torch.int16) == 0).all() and (vp[rest].view(torch.int16) == 0).all()
+
+
+def test_counters_are_left_zero(ctx):
+    # the scoring launch counts, the one launch of short heads does not need the counts and clears them
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k, v = (torch.randn((2, 3, 5000, 128), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    view = lkv.Cache([k], [v], 3)
+    w1 = torch.randn((2, 32, 256), device="cuda", generator=g).mul(0.05).to(torch.bfloat16)
+    scorer = {"kind": "mlp", "act": "silu", "hidden": 32, "per_head": False, "w1": w1, "w2": torch.randn((2, 32), device="cuda", generator=g),
+              "b1": torch.zeros((2, 32), device="cuda"), "b2": None}
+    budgets = np.array([0, 700, 5000, 1, 4999, 333], np.int32)
+    offsets = torch.empty(7, dtype=torch.int32, device="cuda")
+    total = lkv.lkv_plan_offsets(ctx, budgets, offsets)
+    idx = torch.empty(total, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.empty((total, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    counts = torch.zeros(lkv.lkv_counts_bytes(6), dtype=torch.uint8, device="cuda")
+    u = torch.empty((2, 3, 5000), device="cuda")
+    for _ in range(3):
+        lkv.lkv_evict_layer(ctx, view, 0, 2, scorer, budgets, offsets, [u], idx, kp, vp, counts=counts)
+    torch.cuda.synchronize()
+    assert not counts.any()
+    uh, off = u.cpu().numpy().reshape(6, 5000), offsets.cpu().numpy()
+    for j in range(6):
+        assert np.array_equal(idx[off[j]:off[j + 1]].cpu().numpy(), O.select(uh[j], int(budgets[j])))
