@@ -11,20 +11,24 @@
 // form; otherwise it is the next trial (a Newton step that knows the curvature), kept inside a bracket.
 //
 // One workgroup per vector.  What bounds it: instruction issue, one exponential per element and trial, so the
-// trials are made where they are cheap: a histogram of the inputs finds the value of rank k to a bin's width, two to
-// four trials on fp32 differences to that centre (one hardware exponential per element) find the threshold to fp32
+// trials are made where they are cheap: a histogram of the inputs finds the value of rank k to a bin's width, one to
+// three trials on its bins (two exponentials per thread) come within a few hundredths of the threshold, one or two on fp32
+// differences to that centre (one hardware exponential per element) find it to fp32
 // accuracy, and only their end point is evaluated in fp64, where one pass both proves the split and yields the sums;
-// the exponentials of that pass also give the outputs (e^{v - z} y = e^{lambda - z}).
+// the exponentials of that pass also give the outputs (e^{v - z} y = e^{lambda - z}).  A trial leaves the cube of its step as error
+// (values crossed by the step count with the square of their distance), so a step under a hundredth is the last.
 // The trials never pass the threshold (beyond a crossed value the closed form takes more than f does) but cross few
 // values each where z is sparse, so they have to begin near rank k: where far values keep the histograms from getting
 // there, the value of rank k is found exactly, from the bits.  (256 vectors of 16384, half of them masked with the
 // type's lowest: 88 us, 1.5 ms by halving the bracket that such values stretch.)
 // fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
 // Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
-// (they stay in L2).  256 vectors of 16384 fp32 values: 30.4 us, 32.6 under a tracer (257 us for the LDS sort and
-// logarithmic scans this replaces), one vector of 131072: 0.15 ms (2.2 ms for halving a bracket in fp64).  Of the 30: read
-// and extremes 3.5, histogram 3, two trials 4.5, fp64 pass 9.5, root 1.5, outputs the rest.  Row swaps and prefix sums on the vector ALU, fp32
-// where it only places the bracket, and a root without hypot: 32.6 -> 30.4 us; 4096 values 17.5 -> 15.7, 777 9.9 -> 8.8.
+// (they stay in L2).  256 vectors of 16384 fp32 values: 25.3 us (257 us for the LDS sort and
+// logarithmic scans this replaces), one vector of 131072: 0.13 ms (2.2 ms for halving a bracket in fp64).  Of the 25: read
+// and extremes 4, histogram 2.5, trials 4, fp64 pass 7.5, root 0.7, outputs the rest.  Before that pass fetched its values ahead (7.5
+// us, 8.3 with two at a time) and before the trials on bins, values kept in registers up to the trials and the sums over the waves taken
+// side by side in the rows of 16 lanes: 30.4 us; 4096 values 15.7 -> 13.2, 8 vectors of 32768 42.6 -> 32.9, 777 values
+// 9.2 as before (the call's own price).
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -46,7 +50,11 @@ constexpr double kStWiden = 1.0 + 1e-6;   // bins this much wider than the span 
 constexpr double kStEnough = 0.5;         // bin width, in z, from which the fp32 trials converge in two to four steps
 constexpr double kStFar = 32.0;           // bin width, in z, up to which the trials still do without an exact start
 constexpr int kStSearchSteps = 48;        // fp32 trials at most (bisection alone would need about 30)
+constexpr int kStBinSteps = 6;            // trials on the bins at most
+constexpr float kStBinsDone = 0.05f;      // step of a trial on bins from which the trials go on with the values
+constexpr float kStDone = 0.01f;          // and the step that is the last
 constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
+constexpr double kStNoGap = 8.9e307;        // there is no value on that side
 constexpr double kStCoarse = 1e15;         // |z| from which fp64 no longer resolves tenths of a unit
 constexpr double kStMost = 1e300;         // centre of the search at most: its multiples do not overflow
 constexpr double kStTinyProduct = 1e-250; // products of two sums below this have lost digits, or may have
@@ -142,6 +150,7 @@ __device__ __forceinline__ unsigned st_scan(unsigned x) {
 // that writes a copy again has passed the barrier after every wave's reads of it).
 struct StScratch {
   double v[2][5][16];
+  float f[2][3][16];
 };
 
 // a value that is the same in every lane, moved to scalar registers (the vector ones are needed for the elements)
@@ -165,6 +174,26 @@ template <int kT, typename Op>
 __device__ __forceinline__ double st_collect(const double (&slot)[16], double identity, Op op) {
   const int l = threadIdx.x & 15;
   return st_uniform(st_row16(l < kT / 64 ? slot[l] : identity, op));
+}
+
+// The same for up to four sums (minima) at once, one to a row of 16 lanes: result i from lane 16 i.
+template <int kT, int kN, typename V, typename Op>
+__device__ __forceinline__ V st_collect_rows(const V (*slots)[16], V identity, Op op) {
+  const int l = threadIdx.x & 15, r = (threadIdx.x & 63) >> 4;
+  return st_row16(l < kT / 64 && r < kN ? slots[r][l] : identity, op);
+}
+__device__ __forceinline__ double st_lane(double x, int lane) {
+  const long long u = __builtin_bit_cast(long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ float st_lane(float x, int lane) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
+}
+
+__device__ __forceinline__ double st_high(unsigned high, unsigned low) {
+  return __builtin_bit_cast(double, (unsigned long long)high << 32 | low);
 }
 
 // keys whose unsigned order is the numeric order of the values
@@ -203,7 +232,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
                  int32_t* __restrict__ budgets, double t, const double* __restrict__ k_vec) {
   constexpr bool kHeld = kE > 0;
   constexpr int kR = kHeld ? kE : 1;
-  constexpr bool kKeep = kHeld && kE * (int)sizeof(X) <= 32;   // the inputs stay in registers to the end (16 fp32 ones beside the exponentials: 0.4 us slower)
+  constexpr bool kKeep = kHeld && kE * (int)sizeof(X) <= 32;   // the inputs stay in registers to the end (16 fp32 ones beside the exponentials: spills, 2.4 us slower)
   constexpr double kLog2E = 1.44269504088896340736, kLn2 = 0.693147180559945309417;
   __shared__ StScratch sh;
   __shared__ StHist<kT> hist;
@@ -218,12 +247,16 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
 
   // ---- where to look: the value of rank k, by histograms of the inputs that narrow to one bin ----
   double lo, hi, zc;   // bracket of the threshold; centre of the search
+  int found_bin;       // of the histogram over all values, zc its centre; -1: there is none
+  float bin_step = 0.f;   // its width in the units of the search
   X xr[kR];
   {
     if constexpr (kHeld) {
 #pragma unroll
       for (int e = 0; e < kR; ++e) xr[e] = x[min(tid + e * kT, n - 1)];   // padding repeats the last value
     }
+    for (int i = tid; i < StHist<kT>::kBins; i += kT) hist.bin[i] = 0;
+    if (tid == 0) hist.found = -1;
     double least = INFINITY, most = INFINITY;   // min x, min -x
     {
       X small = (X)INFINITY, large = (X)-INFINITY;
@@ -240,15 +273,17 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     auto& v = sh.v[turn];
     if (writer) { v[0][wave] = least; v[1][wave] = most; }
     __syncthreads();
-    least = st_collect<kT>(v[0], INFINITY, StMin());
-    most = -st_collect<kT>(v[1], INFINITY, StMin());
+    const double ends = st_collect_rows<kT, 2>(v, (double)INFINITY, StMin());
+    least = st_lane(ends, 0);
+    most = -st_lane(ends, 16);
     turn ^= 1;
     // g > 0 at lo: every f is at least 1 - e^{-L} / 2 with L >= 1 + log(n / (2 (n - k))), so the sum exceeds
     // n - (n - k) / e > k; g < 0 at hi: every f is at most e^{-U} / 2 with U >= 1 + log(n / (2 k)): sum <= k / e
+    // (both in one go: the first row of lanes has least and n - k, the second -most and k)
     moderate = moderate && least > -INFINITY && most < INFINITY;
-    auto margin = [&](double part) { return bracket_margin(n, part, [](float x) { return __log2f(x); }); };
-    lo = st_uniform(least / tau - margin((double)n - k));
-    hi = st_uniform(most / tau + margin(k));
+    const double bound = ends / tau - bracket_margin(n, (tid & 16) == 0 ? (double)n - k : k, [](float x) { return __log2f(x); });
+    lo = st_lane(bound, 0);
+    hi = -st_lane(bound, 16);
     constexpr int kBins = StHist<kT>::kBins;
     double above = 0.0;   // values in higher bins
     auto for_each = [&](auto visit) {
@@ -261,6 +296,7 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       }
     };
     auto clear = [&]() {
+      __syncthreads();
       for (int i = tid; i < kBins; i += kT) hist.bin[i] = 0;
       if (tid == 0) hist.found = -1;
       __syncthreads();
@@ -282,32 +318,43 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       __syncthreads();
       const int found = __builtin_amdgcn_readfirstlane(hist.found);
       if (found >= 0) above = st_uniform(hist.above);
-      __syncthreads();        // the next level clears what has just been read
       return found;
     };
     double base = least, span = most - least;
     bool looking = span > 0.0 && span < INFINITY;
+    found_bin = -1;
     for (int level = 0; level < kStLevels && looking; ++level) {
-      clear();
+      if (level > 0) {
+        clear();
+        found_bin = -1;
+      }
       const double width = st_uniform(span * (kStWiden / (double)kBins));
       const float to_bin = 1.f / (float)width;
-      for_each([&](X xv, bool in) {
-        const float f = (float)(xv - (X)base) * to_bin;
-        // the first level takes every value; the next ones the values of the bin found before
-        if (in && (level == 0 || (f >= 0.f && f < (float)kBins)))
-          atomicAdd(&hist.bin[(int)fminf(fmaxf(f, 0.f), (float)(kBins - 1))], 1u);
-      });
+      auto bin_of = [&](float f) { return (int)fminf(fmaxf(f, 0.f), (float)(kBins - 1)); };
+      if (level == 0) {   // every value
+        for_each([&](X xv, bool in) {
+          if (in) atomicAdd(&hist.bin[bin_of((float)(xv - (X)base) * to_bin)], 1u);
+        });
+      } else {            // the values of the bin found before
+        for_each([&](X xv, bool in) {
+          const float f = (float)(xv - (X)base) * to_bin;
+          if (in && f >= 0.f && f < (float)kBins) atomicAdd(&hist.bin[bin_of(f)], 1u);
+        });
+      }
       const int found = find_bin();
       if (found < 0) break;   // rounding moved a value across the bin's edge
+      if (level == 0) found_bin = found;
       span = width;
       base = st_uniform(base + found * span);
       looking = span > kStEnough * tau && base + span > base;
     }
     if (__builtin_expect(span <= kStFar * tau, 1)) {
       zc = st_uniform((base + 0.5 * span) / tau);
+      if (found_bin >= 0) bin_step = (float)st_uniform(span * rtau * kLog2E);
     } else {
       // Values so far apart (masked with the type's lowest, or infinite) that equal steps do not come down to the rest
       // of them: the value of rank k itself, digit by digit of its ordered bits.
+      found_bin = -1;
       using Key = decltype(st_key(X()));
       constexpr int kDigit = kT == 1024 ? 11 : 9;
       static_assert(1 << kDigit == kBins, "a digit per bin");
@@ -329,7 +376,10 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       zc = st_uniform((double)st_value(key) / tau);
     }
     zc = st_uniform(fmin(fmax(zc, -kStMost), kStMost));   // an infinite value of rank k: any threshold beyond the others
-    if (!(zc >= lo && zc <= hi)) zc = st_uniform(0.5 * (lo + hi));
+    if (!(zc >= lo && zc <= hi)) {
+      zc = st_uniform(0.5 * (lo + hi));
+      found_bin = -1;
+    }
   }
 
   // ---- search in fp32: w = (z - zc) log2 e ----
@@ -340,47 +390,76 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     if constexpr (kHeld) {
 #pragma unroll
       for (int e = 0; e < kR; ++e)   // the vector is in the caches by now; padding lies infinitely far down the tail
-        w[e] = tid + e * kT < n ? (float)fma((double)(kKeep ? xr[e] : x[min(tid + e * kT, n - 1)]), scale, shift) : -INFINITY;
+        w[e] = tid + e * kT < n ? (float)fma((double)xr[e], scale, shift) : -INFINITY;
     }
     float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
     // nothing to search for at a centre that itself rounds to about a unit
     const int n_search = fabs(zc) < kStCoarse ? kStSearchSteps : 0;
+    // trials on the bins first, each as many values in its middle, and split where the trial cuts it
+    float c0 = 0.f, c1 = 0.f, w0 = 0.f, w1 = 0.f, per_step = 0.f;
+    bool on_bins = found_bin >= 0 && bin_step > 0.f;
+    if (on_bins) {
+      c0 = (float)hist.bin[2 * tid];
+      c1 = (float)hist.bin[2 * tid + 1];
+      w0 = (float)(2 * tid - found_bin) * bin_step;
+      w1 = (float)(2 * tid + 1 - found_bin) * bin_step;
+      per_step = 1.f / bin_step;
+    }
 #pragma unroll 1
     for (int step = 0; step < n_search; ++step) {
-      float head = 0.f, all = 0.f;
-      int cnt = 0;
-      auto visit = [&](float wv) {
-        const float d = wv - fv;
-        const float e = __builtin_amdgcn_exp2f(-fabsf(d));
-        const bool up = d >= 0.f;
-        all += e;
-        head += up ? e : 0.f;
-        cnt += up ? 1 : 0;
-      };
-      if constexpr (kHeld) {
-#pragma unroll
-        for (int e = 0; e < kR; ++e) visit(w[e]);
+      float head = 0.f, all = 0.f, cnt = 0.f;
+      if (on_bins) {   // uniform
+        auto visit = [&](float wv, float c) {
+          const float d = wv - fv;
+          const float e = c * __builtin_amdgcn_exp2f(-fabsf(d));
+          const float up = fminf(fmaxf(fmaf(d, per_step, 0.5f), 0.f), 1.f);
+          all += e;
+          head = fmaf(up, e, head);
+          cnt = fmaf(up, c, cnt);
+        };
+        visit(w0, c0);
+        visit(w1, c1);
       } else {
+        int n_up = 0;
+        auto visit = [&](float wv) {
+          const float d = wv - fv;
+          const float e = __builtin_amdgcn_exp2f(-fabsf(d));
+          const bool up = d >= 0.f;
+          all += e;
+          head += up ? e : 0.f;
+          n_up += up ? 1 : 0;
+        };
+        if constexpr (kHeld) {
+#pragma unroll
+          for (int e = 0; e < kR; ++e) visit(w[e]);
+        } else {
 #pragma unroll 4
-        for (int i = tid; i < n; i += kT) visit((float)fma((double)x[i], scale, shift));
+          for (int i = tid; i < n; i += kT) visit((float)fma((double)x[i], scale, shift));
+        }
+        cnt = (float)n_up;
       }
       head = st_wave(head, StAdd());
       all = st_wave(all, StAdd());
-      cnt = st_wave(cnt, StAdd());
-      auto& sv = sh.v[turn];
+      cnt = st_wave(cnt, StAdd());   // exact: whole numbers up to 2^22
+      auto& sv = sh.f[turn];
       if (writer) { sv[0][wave] = head; sv[1][wave] = all; sv[2][wave] = cnt; }
       __syncthreads();
-      const double a2 = st_collect<kT>(sv[0], 0.0, StAdd());
-      const double b2 = st_collect<kT>(sv[1], 0.0, StAdd()) - a2;
-      const double m = st_collect<kT>(sv[2], 0.0, StAdd());
+      const float sums = st_collect_rows<kT, 3>(sv, 0.f, StAdd());
+      const float af = st_lane(sums, 0), bf = fmaxf(st_lane(sums, 16) - af, 0.f);   // A = af / 2, B = bf / 2
       turn ^= 1;
-      const double d = k - m;
-      if (0.5 * (b2 - a2) - d > 0.0) flo = fv; else fhi = fv;   // the threshold lies above, or below, this trial
-      const float df = (float)d, af = (float)a2, bf = (float)fmax(b2, 0.0);
-      const float root = sqrtf(fmaf(df, df, af * bf));   // A = a2 / 2, B = b2 / 2
-      const float ratio = df >= 0.f ? bf / (df + root) : (root - df) / af;
+      const double d = k - (double)st_lane(sums, 32);
+      const float df = (float)d;
+      const float root = __builtin_amdgcn_sqrtf(fmaf(df, df, af * bf));
+      const float ratio = df >= 0.f ? bf * __builtin_amdgcn_rcpf(df + root) : (root - df) * __builtin_amdgcn_rcpf(af);
       float next = fv + __log2f(ratio);
-      if (fabsf(next - fv) < 1e-3f) {   // an error of its square is left, below what fp32 resolves
+      if (on_bins) {
+        const bool usable = next > flo && next < fhi;
+        on_bins = usable && fabsf(next - fv) >= kStBinsDone && step < kStBinSteps;
+        if (usable) fv = next;
+        continue;
+      }
+      if (0.5f * (bf - af) - df > 0.f) flo = fv; else fhi = fv;   // the threshold lies above, or below, this trial
+      if (fabsf(next - fv) < kStDone) {   // an error of its cube is left, below what fp32 resolves
         fv = next;
         break;
       }
@@ -418,10 +497,16 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     if constexpr (kHeld) {
       int first = tid;
       asm volatile("" : "+v"(first));   // or the compiler keeps indices and quotients from step to step, in scratch memory
+      X ahead[kR];
+      if constexpr (!kKeep) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e) ahead[e] = x[min(first + e * kT, n - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int e = 0; e < kR; ++e) {
         const int i = first + e * kT;
-        const double z = st_quotient(kKeep ? xr[e] : x[min(i, n - 1)], tau, rtau, moderate);
+        const double z = st_quotient(kKeep ? xr[e] : ahead[e], tau, rtau, moderate);
         ex[e] = visit(i < n ? z : -INFINITY);
         if (e & 1) __builtin_amdgcn_sched_barrier(0);   // two exponentials at a time fit the registers
       }
@@ -435,13 +520,17 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     dn = st_wave(dn, StMin());
     cnt = st_wave(cnt, StAdd());
     auto& sv = sh.v[turn];
-    if (writer) { sv[0][wave] = a; sv[1][wave] = b; sv[2][wave] = up; sv[3][wave] = dn; sv[4][wave] = cnt; }
+    if (writer) { sv[0][wave] = a; sv[1][wave] = b; sv[2][wave] = cnt; sv[3][wave] = up; sv[4][wave] = dn; }
     __syncthreads();
-    a = 0.5 * st_collect<kT>(sv[0], 0.0, StAdd());
-    b = 0.5 * st_collect<kT>(sv[1], 0.0, StAdd());
-    up = st_collect<kT>(sv[2], INFINITY, StMin());
-    dn = st_collect<kT>(sv[3], INFINITY, StMin());
-    m = (int)st_collect<kT>(sv[4], 0.0, StAdd());
+    const double sums = st_collect_rows<kT, 3>(sv, 0.0, StAdd());
+    const double gaps = st_collect_rows<kT, 2>(sv + 3, (double)INFINITY, StMin());
+    a = 0.5 * st_lane(sums, 0);
+    b = 0.5 * st_lane(sums, 16);
+    m = (int)st_lane(sums, 32);
+    up = st_lane(gaps, 0);
+    dn = st_lane(gaps, 16);
+    if (up > kStNoGap) up = INFINITY;
+    if (dn > kStNoGap) dn = INFINITY;
     turn ^= 1;
     const double d = k - (double)m;
     double delta;

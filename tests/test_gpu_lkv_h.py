@@ -242,6 +242,27 @@ def test_soft_topk_whole_target_in_a_gap_with_one_value_far_away(ctx, n, dtype):
     assert np.array_equal(y0, y[0]) and lam == info[0, 0] and m == 2
 
 
+@pytest.mark.parametrize("n", [2, 257, 1024, 1025, 4096, 16384, 32768, 32769])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_soft_topk_where_the_histogram_says_little(ctx, n, dtype):
+    # The first trials stand on the histogram's bins as if each held its values evenly.  Here it does not: nearly all values
+    # in one bin, at its edges, all in two bins, ties, an end bin at the threshold; targets at both ends and in between.
+    rng = np.random.default_rng(n)
+    tau = 0.05
+    base = rng.uniform(0, 1, n)
+    shapes = [np.where(np.arange(n) == 0, 900 * tau, base * 0.4 * tau),              # one bin of a wide range
+              np.where(np.arange(n) == 0, 800 * tau, np.where(base < 0.5, 0.0, 0.39 * tau)),   # its two ends
+              np.where(base < 0.7, -3.0, 3.0) + 1e-4 * base, np.round(base * 4), -np.abs(rng.standard_normal(n)) ** 4, base * 1e-7]
+    rows, ks = [], []
+    for x in shapes:
+        for k in (1e-6, 0.01, 0.3 * n, 0.5 * n + 0.25, 0.7 * n, n - 0.01):
+            rows.append(x.astype(dtype))
+            ks.append(min(max(k, 1e-6), n - 1e-6))
+    y, info = _gpu_soft_topk_rows(ctx, np.stack(rows), ks, tau)
+    for i, x in enumerate(rows):
+        _check_at_returned_threshold(x, y[i], info[i, 0], int(info[i, 1]), ks[i], tau, (i, ks[i]))
+
+
 @pytest.mark.parametrize("n", [300, 1024, 1025, 16384, 32769])
 @pytest.mark.parametrize("dtype,far", [(np.float32, -1e20), (np.float32, 1e30), (np.float32, -np.finfo(np.float32).max),
                                        (np.float32, -np.inf), (np.float32, np.inf), (np.float64, -1e30),
