@@ -681,8 +681,8 @@ lkv_status lkv_evict_layer(lkv_ctx* ctx, const lkv_cache* layer, int32_t layer_i
   tab.n = layer->n_seq;
   // segment of (sequence i, view head j) is i * n_layers * H + layer_index * H + j, offsets already on the device
   int blocks = 0;
-  if (const int rows = lkv::select_compact_rows(tab, budgets + layer_index * H, heads_all, layer_rows, &blocks)) {
-    lkv::launch_select_compact(tab, offsets, idx, layer_index * H, heads_all, rows, blocks, counts, kp, vp, st);
+  if (const int rows = lkv::select_compact_rows(tab, budgets + layer_index * H, heads_all, layer_rows, counts, pre_words, &blocks)) {
+    lkv::launch_select_compact(tab, offsets, idx, layer_index * H, heads_all, rows, blocks, counts, pre_maps, pre_words, kp, vp, st);
     if (hipError_t e = hipGetLastError()) return hip_fail(ctx, e, "lkv_evict_layer launch");
     return LKV_OK;
   }

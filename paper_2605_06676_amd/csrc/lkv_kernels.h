@@ -31,9 +31,11 @@ void launch_select(const SeqTable& tab, const int32_t* host_offsets, int n_total
                    const int32_t* ragged_len = nullptr, uint32_t* counts = nullptr, uint32_t* pre_maps = nullptr,
                    int pre_words = 0);
 int select_max_bitmap_tokens();
-int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, int* blocks);
+int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, const uint32_t* counts,
+                        int pre_words, int* blocks);
 void launch_select_compact(const SeqTable& tab, const int32_t* offsets, int32_t* idx, int seg_base, int seg_stride,
-                           int rows_per_block, int blocks, uint32_t* counts, void* kp, void* vp, hipStream_t stream);
+                           int rows_per_block, int blocks, uint32_t* counts, uint32_t* pre_maps, int pre_words, void* kp, void* vp,
+                           hipStream_t stream);
 
 // counts.hip
 void launch_clear_counts(uint32_t* counts, int64_t n_segments, hipStream_t stream);

@@ -21,6 +21,8 @@
 //     classification re-read the scores instead.
 //   * T <= 327680 is the limit for the bitmaps; longer heads re-read the scores in order during
 //     emission, 64 tokens a step.
+// A layer's eviction (few heads) chooses in every block that copies rows and copies in the same launch: select_compact_kernel,
+// select_compact_long_kernel.
 // All global reads are issued many at a time per thread before any is used: the kernels are
 // latency-bound, not bandwidth-bound, so what counts is how few dependent round trips each pass
 // makes.  A launch can also rank ragged pieces of one flat score array (the re-eviction of a
@@ -57,6 +59,8 @@ constexpr int kFuseMaxHeads = 64;                           // one lane each
 // the compaction's blocks (against two launches, 34000 tokens: 32 heads, 214 rows a block 117 -> 114 us, 680 136 -> 137, 1850
 // 181 -> 190; 64 heads, 490 222 -> 215, 1460 259 -> 264).
 constexpr int kFuseMaxRows = 600;
+constexpr int kFuseMaxRowsFewHeads = 900;                   // up to 16 heads: 34000 tokens, 850 rows a block 102.7 -> 99.3 us
+constexpr int kFuseFewHeads = 16;
 constexpr int kFuseBlocks = 256;                            // one round: a block to a compute unit
 constexpr int kSelSplitMax = 32;                            // at most this many per head
 
@@ -74,6 +78,7 @@ struct SelShared {
   uint32_t found_above;
   uint32_t found_count;
   uint32_t cand_count;
+  uint32_t first_key;
   __device__ __forceinline__ uint32_t* hist() { return bins + 4; }
 };
 
@@ -641,6 +646,75 @@ select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* _
   emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, stage);
 }
 
+// The share of a block of the one launch: rows p0 .. p1 - 1 (none: p0 >= p1) of the kept tokens of a head.
+struct SelShare {
+  int seq, lh, seg, T, off, budget, p0, p1;
+};
+__device__ __forceinline__ SelShare block_share(const SeqTable& tab, const int32_t* __restrict__ offsets, uint32_t* __restrict__ counts,
+                                                int seg_base, int seg_stride, int rows_per_block) {
+  SelShare x;
+  const int lane = threadIdx.x & 63;
+  const int n_segs = tab.first[tab.n];   // at most 64: a lane each
+  // every head has one block for each rows_per_block of its rows, and at least one
+  int my_off = 0, my_budget = 0, my_seg = 0;
+  if (lane < n_segs) {
+    int seq = 0;
+    while (seq + 1 < tab.n && lane >= tab.first[seq + 1]) ++seq;
+    my_seg = seg_base + seq * seg_stride + lane - tab.first[seq];
+    my_off = offsets[my_seg];
+    my_budget = offsets[my_seg + 1] - my_off;
+  }
+  const uint32_t my_blocks = lane < n_segs ? (uint32_t)max(1, (my_budget + rows_per_block - 1) / rows_per_block) : 0u;
+  const uint32_t last = wave_inclusive_scan(my_blocks);
+  const unsigned long long at = __ballot(last > blockIdx.x);
+  const int local_seg = at == 0ull ? 0 : __builtin_ctzll(at);
+  const int part = (int)blockIdx.x - __builtin_amdgcn_readlane((int)(last - my_blocks), local_seg);
+  x.seg = __builtin_amdgcn_readlane(my_seg, local_seg);
+  x.off = __builtin_amdgcn_readlane(my_off, local_seg);
+  x.budget = __builtin_amdgcn_readlane(my_budget, local_seg);
+  x.seq = seq_of_unit(tab, local_seg);
+  x.lh = local_seg - tab.first[x.seq];
+  x.T = tab.T[x.seq];
+  x.p0 = part * rows_per_block;
+  x.p1 = at == 0ull ? 0 : min(min(x.budget, x.T), x.p0 + rows_per_block);
+  if (counts != nullptr && part == 0 && at != 0ull)   // no block reads them here: left zero for the next scoring launch
+    for (int i = threadIdx.x; i < kLevel0Bins; i += kSelThreads) counts[(size_t)x.seg * kLevel0Bins + i] = 0;
+  return x;
+}
+
+// The indices and the rows of a block's tokens (listed in LDS), 16 lanes a row, 64 rows a round of the workgroup.
+__device__ __forceinline__ void copy_share(const SeqTable& tab, const SelShare& x, const uint32_t* tokens, int32_t* __restrict__ idx,
+                                           uint4* __restrict__ kp, uint4* __restrict__ vp) {
+  const int tid = threadIdx.x;
+  const int n_rows = x.p1 - x.p0;
+  for (int i = tid; i < n_rows; i += kSelThreads) idx[(size_t)x.off + x.p0 + i] = (int32_t)tokens[i];
+  constexpr int kRound = kSelThreads / 16;
+  constexpr int kU = 2;
+  const int c = tid & 15;
+  const uint4* kh = reinterpret_cast<const uint4*>(tab.k[x.seq]) + (size_t)x.lh * (size_t)x.T * kChunksPerRow + c;
+  const uint4* vh = reinterpret_cast<const uint4*>(tab.v[x.seq]) + (size_t)x.lh * (size_t)x.T * kChunksPerRow + c;
+  uint4* kd = kp + ((size_t)x.off + x.p0) * kChunksPerRow + c;
+  uint4* vd = vp + ((size_t)x.off + x.p0) * kChunksPerRow + c;
+#pragma unroll 1
+  for (int i0 = tid >> 4; i0 < n_rows; i0 += kRound * kU) {
+    uint4 kk[kU], vv[kU];
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const size_t row = tokens[min(i0 + j * kRound, n_rows - 1)];
+      kk[j] = load_stream16(kh + row * kChunksPerRow);
+      vv[j] = load_stream16(vh + row * kChunksPerRow);
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const int i = i0 + j * kRound;
+      if (i < n_rows) {
+        store_stream16(kd + (size_t)i * kChunksPerRow, kk[j]);
+        store_stream16(vd + (size_t)i * kChunksPerRow, vv[j]);
+      }
+    }
+  }
+}
+
 // Top-k and compaction of few heads of at most kE * 1024 tokens in one launch (a layer evicted during prefill).  A head's
 // choice is a chain of short steps in one workgroup, which leaves the rest of the chip idle, so it is made again in every block that copies rows
 // of the head: blocks in proportion to the budgets, one to a compute unit, each with as many rows as the others.  What goes
@@ -659,39 +733,15 @@ select_compact_kernel(SeqTable tab, const int32_t* __restrict__ offsets, int32_t
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int n_segs = tab.first[tab.n];   // at most 64: a lane each
-
-  // the head and the packed rows of this block: every head has one block for each rows_per_block of its rows, and at least one
-  int my_off = 0, my_budget = 0;
-  if (lane < n_segs) {
-    int seq = 0;
-    while (seq + 1 < tab.n && lane >= tab.first[seq + 1]) ++seq;
-    const int seg = seg_base + seq * seg_stride + lane - tab.first[seq];
-    my_off = offsets[seg];
-    my_budget = offsets[seg + 1] - my_off;
-  }
-  const uint32_t my_blocks = lane < n_segs ? (uint32_t)max(1, (my_budget + rows_per_block - 1) / rows_per_block) : 0u;
-  const uint32_t last = wave_inclusive_scan(my_blocks);
-  const unsigned long long at = __ballot(last > blockIdx.x);
-  if (at == 0ull) return;
-  const int local_seg = __builtin_ctzll(at);
-  const int part = (int)blockIdx.x - (int)__builtin_amdgcn_readlane((int)(last - my_blocks), local_seg);
-  const int off = __builtin_amdgcn_readlane(my_off, local_seg);
-  const int budget = __builtin_amdgcn_readlane(my_budget, local_seg);
-  const int seq = seq_of_unit(tab, local_seg);
-  const int lh = local_seg - tab.first[seq];
-  const int T = tab.T[seq];
-  if (counts != nullptr && part == 0)   // not needed here, but left zero for the next scoring launch
-    for (int i = tid; i < kLevel0Bins; i += kSelThreads)
-      counts[(size_t)(seg_base + seq * seg_stride + lh) * kLevel0Bins + i] = 0;
-  const int p0 = part * rows_per_block, p1 = min(min(budget, T), p0 + rows_per_block);
-  if (p0 >= p1) return;
-  const int n_rows = p1 - p0;
+  const SelShare x = block_share(tab, offsets, counts, seg_base, seg_stride, rows_per_block);
+  if (x.p0 >= x.p1) return;
+  const int T = x.T, budget = x.budget, p0 = x.p0;
+  const int n_rows = x.p1 - p0;
   uint32_t* tokens = stage;   // of the block's rows
   if (budget >= T) {   // everything is kept
     for (int i = tid; i < n_rows; i += kSelThreads) tokens[i] = (uint32_t)(p0 + i);
   } else {
-    const float* u = tab.scores[seq] + (size_t)lh * (size_t)T;
+    const float* u = tab.scores[x.seq] + (size_t)x.lh * (size_t)T;
     const int rounds = (T + kSelThreads - 1) / kSelThreads;
     const int groups = rounds * kSelWaves;   // of 64 tokens, at most 544: a thread each
     unsigned long long* masks = reinterpret_cast<unsigned long long*>(gt_map);
@@ -762,33 +812,111 @@ select_compact_kernel(SeqTable tab, const int32_t* __restrict__ offsets, int32_t
     }
   }
   __syncthreads();
-  for (int i = tid; i < n_rows; i += kSelThreads) idx[(size_t)off + p0 + i] = (int32_t)tokens[i];
-  // the rows: 16 lanes a row, 64 rows a round of the workgroup
-  constexpr int kRound = kSelThreads / 16;
-  constexpr int kU = 2;
-  const int c = tid & 15;
-  const uint4* kh = reinterpret_cast<const uint4*>(tab.k[seq]) + (size_t)lh * (size_t)T * kChunksPerRow + c;
-  const uint4* vh = reinterpret_cast<const uint4*>(tab.v[seq]) + (size_t)lh * (size_t)T * kChunksPerRow + c;
-  uint4* kd = kp + ((size_t)off + p0) * kChunksPerRow + c;
-  uint4* vd = vp + ((size_t)off + p0) * kChunksPerRow + c;
-#pragma unroll 1
-  for (int i0 = tid >> 4; i0 < n_rows; i0 += kRound * kU) {
-    uint4 kk[kU], vv[kU];
+  copy_share(tab, x, tokens, idx, kp, vp);
+}
+
+// The words of a bitmap of up to kSelMaxBitmapT tokens, thread t's t, t + 1024, ..: all on their way at once.
+constexpr int kMapRounds = (kSelMaxBitmapT / 32 + kSelThreads - 1) / kSelThreads;
+__device__ __forceinline__ void load_map(const uint32_t* __restrict__ map, int n_words, uint32_t (&words)[kMapRounds]) {
 #pragma unroll
-    for (int j = 0; j < kU; ++j) {
-      const size_t row = tokens[min(i0 + j * kRound, n_rows - 1)];
-      kk[j] = load_stream16(kh + row * kChunksPerRow);
-      vv[j] = load_stream16(vh + row * kChunksPerRow);
-    }
+  for (int j = 0; j < kMapRounds; ++j) {
+    const int w = j * kSelThreads + threadIdx.x;
+    words[j] = 0;
+    if (j * kSelThreads < n_words) words[j] = w < n_words ? map[w] : 0u;   // the outer condition is uniform
+  }
+}
+
+// Lists their tokens (LDS list of up to kSelCandCap, sh.cand_count of them), in no particular order.  Starts from an empty list;
+// a barrier has to pass before the list is read.
+__device__ __forceinline__ void list_map(SelShared& sh, const uint32_t (&words)[kMapRounds], int n_words, uint32_t* cand) {
+  uint32_t n_bits = 0;
 #pragma unroll
-    for (int j = 0; j < kU; ++j) {
-      const int i = i0 + j * kRound;
-      if (i < n_rows) {
-        store_stream16(kd + (size_t)i * kChunksPerRow, kk[j]);
-        store_stream16(vd + (size_t)i * kChunksPerRow, vv[j]);
+  for (int j = 0; j < kMapRounds; ++j) n_bits += (uint32_t)__popc(words[j]);
+  // one place in the list per wave, shared out by a prefix count
+  const uint32_t incl = wave_inclusive_scan(n_bits);
+  uint32_t base = 0;
+  if ((threadIdx.x & 63) == 63) base = atomicAdd(&sh.cand_count, incl);
+  uint32_t slot = last_lane(base) + incl - n_bits;
+#pragma unroll
+  for (int j = 0; j < kMapRounds; ++j) {
+    if (j * kSelThreads < n_words) {   // uniform
+      uint32_t bits = words[j];
+      while (__ballot(bits != 0u) != 0ull) {
+        if (bits) {
+          if (slot < (uint32_t)kSelCandCap) cand[slot] = (uint32_t)(j * kSelThreads + threadIdx.x) * 32u + (uint32_t)__builtin_ctz(bits);
+          ++slot;
+          bits &= bits - 1;
+        }
       }
     }
   }
+}
+
+// Settles the n_cand listed tokens of an undecided bin: those that are kept join gt_map.  True: all of them.  False: more than
+// kSelRankMax share the threshold key; those above it joined, eq_map has its copies, and the first `need` of these are kept.
+// `level`: levels of the descent that the bin stands for: 0, or 1 when the keys in it agree in their first digit.  `space`: where the
+// list lies, used for histograms once the tokens are in registers.
+__device__ __forceinline__ bool settle_listed(SelShared& sh, const float* __restrict__ u, int T, int n_words, uint32_t n_cand, int level,
+                                              uint32_t& need, uint32_t* gt_map, uint32_t* eq_map, uint32_t* space) {
+  const int tid = threadIdx.x;
+  // the listed tokens and their keys, in registers: one round of gathers, all in flight
+  constexpr int kHeldCand = kSelCandCap / kSelThreads;
+  uint32_t token[kHeldCand], key[kHeldCand];
+#pragma unroll
+  for (int k = 0; k < kHeldCand; ++k) {
+    token[k] = 0;
+    if (k == 0 || (uint32_t)(k * kSelThreads) < n_cand)   // uniform
+      token[k] = min(space[min((uint32_t)(k * kSelThreads + tid), max(n_cand, 1u) - 1)], (uint32_t)T - 1);   // in range whatever the counts said
+  }
+#pragma unroll
+  for (int k = 0; k < kHeldCand; ++k) {
+    key[k] = 0;
+    if (k == 0 || (uint32_t)(k * kSelThreads) < n_cand) key[k] = order_key(u[token[k]]);
+  }
+  auto for_each_listed = [&](auto fn) {
+#pragma unroll
+    for (int k = 0; k < kHeldCand; ++k)
+      if ((uint32_t)(k * kSelThreads + tid) < n_cand) fn(key[k], token[k]);
+  };
+  if (tid == 0) { sh.cand_count = 0; sh.first_key = key[0]; }
+  // keys that agree in their first digit mostly differ in the next, and one copy of its histogram will do (2.9 -> 1.3 us)
+  const bool crowded = level == 0 || lanes_crowd((int)(key[0] >> 10 & 2047u));
+  for (int i = tid; i < kSelBins; i += kSelThreads) sh.hist()[i] = 0;
+  const bool copies = __syncthreads_or(crowded && (uint32_t)(tid | 63) < n_cand) != 0;
+  // the list is dead: its space becomes the staging buffer; the list for the ranking starts empty
+  uint32_t prefix_mask = level == 0 ? 0u : 0xffe00000u;
+  uint32_t prefix = sh.first_key & prefix_mask;   // bits of the threshold key decided so far
+  uint32_t n_left = n_cand;
+  if (!copies && n_left > (uint32_t)kSelRankMax) {
+    for_each_listed([&](uint32_t k, uint32_t) { atomicAdd(&sh.hist()[k >> 10 & 2047u], 1u); });
+    __syncthreads();
+    find_bin(sh, kSelBins, need, [&](int bin) { return sh.hist()[bin]; });
+    n_left = enter_found_bin(sh, 1, prefix, prefix_mask, need);
+    level = 2;
+  }
+#pragma unroll 1
+  for (; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
+    n_left = descend_level(sh, space, level, prefix, prefix_mask, need, [&](auto fn) { for_each_listed([&](uint32_t k, uint32_t) { fn(k); }); });
+  if (n_left <= (uint32_t)kSelRankMax) {
+    for_each_listed([&](uint32_t k, uint32_t t) {
+      const uint32_t decided = k & prefix_mask;
+      if (decided > prefix) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
+      else if (decided == prefix) list_for_ranking(sh, k, t);
+    });
+    __syncthreads();
+    keep_best_listed(sh, n_left, need, gt_map);
+    __syncthreads();
+    return true;
+  }
+  for (int i = tid; i < n_words; i += kSelThreads) eq_map[i] = 0;
+  __syncthreads();
+  const uint32_t thr_listed = prefix;
+  for_each_listed([&](uint32_t k, uint32_t t) {
+    if (k > thr_listed) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
+    else if (k == thr_listed) atomicOr(&eq_map[t >> 5], 1u << (t & 31));
+  });
+  __syncthreads();
+  return false;
 }
 
 // kCounted: the first-level digits of every segment's scores have already been counted by the scoring launch
@@ -898,27 +1026,15 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       // the pass over the scores has been done by the blocks of select_classify_kernel: take its two bitmaps
       // (above the undecided bin / inside it) and list the tokens inside
       const uint32_t* pre_gt = pre_maps + (size_t)seg * 2 * pre_words;
-      const uint32_t* pre_in = pre_gt + pre_words;
-      for (int i = tid; i < n_words; i += kSelThreads) gt_map[i] = pre_gt[i];
+      uint32_t above[kMapRounds], inside[kMapRounds];
+      load_map(pre_gt, n_words, above);
+      load_map(pre_gt + pre_words, n_words, inside);
       if (tid == 0) sh.cand_count = 0;
+#pragma unroll
+      for (int j = 0; j < kMapRounds; ++j)
+        if (j * kSelThreads + tid < n_words) gt_map[j * kSelThreads + tid] = above[j];
       __syncthreads();
-      for (int w0 = 0; w0 < n_words; w0 += kSelThreads) {   // uniform trip counts
-        const int w = w0 + tid;
-        uint32_t bits = w < n_words ? pre_in[w] : 0u;
-        // one place in the list per wave and round, shared out by a prefix count
-        const uint32_t n_bits = __popc(bits);
-        const uint32_t incl = wave_inclusive_scan(n_bits);
-        uint32_t base = 0;
-        if ((tid & 63) == 63) base = atomicAdd(&sh.cand_count, incl);
-        uint32_t slot = __shfl(base, 63, 64) + incl - n_bits;
-        while (__ballot(bits != 0u) != 0ull) {
-          if (bits) {
-            if (slot < (uint32_t)kSelCandCap) cand[slot] = ((uint32_t)w << 5) + (uint32_t)__builtin_ctz(bits);
-            ++slot;
-            bits &= bits - 1;
-          }
-        }
-      }
+      list_map(sh, inside, n_words, cand);
       __syncthreads();
     } else {
       for (int i = tid; i < n_words; i += kSelThreads) gt_map[i] = 0;
@@ -936,46 +1052,10 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       });
       __syncthreads();
     }
-    // the listed tokens and their keys, in registers: one round of gathers, all in flight
-    constexpr int kHeldCand = kSelCandCap / kSelThreads;
-    uint32_t token[kHeldCand], key[kHeldCand];
-#pragma unroll
-    for (int k = 0; k < kHeldCand; ++k)
-      token[k] = min(cand[min((uint32_t)(k * kSelThreads + tid), max(n_cand, 1u) - 1)], (uint32_t)T - 1);   // in range whatever the counts said
-#pragma unroll
-    for (int k = 0; k < kHeldCand; ++k) key[k] = order_key(u[token[k]]);
-    auto for_each_listed = [&](auto fn) {
-#pragma unroll
-      for (int k = 0; k < kHeldCand; ++k)
-        if ((uint32_t)(k * kSelThreads + tid) < n_cand) fn(key[k], token[k]);
-    };
-    if (tid == 0) sh.cand_count = 0;
-    __syncthreads();   // the list is dead: its space becomes the staging buffer; the list for the ranking starts empty
-    uint32_t n_left = n_cand;
-#pragma unroll 1
-    for (int level = keyed ? 1 : 0; level < 3 && n_left > (uint32_t)kSelRankMax; ++level)
-      n_left = descend_level(sh, copies, level, prefix, prefix_mask, need, [&](auto fn) { for_each_listed([&](uint32_t k, uint32_t) { fn(k); }); });
-    if (n_left <= (uint32_t)kSelRankMax) {
-      for_each_listed([&](uint32_t k, uint32_t t) {
-        const uint32_t decided = k & prefix_mask;
-        if (decided > prefix) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
-        else if (decided == prefix) list_for_ranking(sh, k, t);
-      });
-      __syncthreads();
-      keep_best_listed(sh, n_left, need, gt_map);
-      __syncthreads();
+    if (settle_listed(sh, u, T, n_words, n_cand, keyed ? 1 : 0, need, gt_map, eq_map, cand))
       emit_from_bitmaps<false>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
-      return;
-    }
-    for (int i = tid; i < n_words; i += kSelThreads) eq_map[i] = 0;
-    __syncthreads();
-    const uint32_t thr_listed = prefix;
-    for_each_listed([&](uint32_t k, uint32_t t) {
-      if (k > thr_listed) atomicOr(&gt_map[t >> 5], 1u << (t & 31));
-      else if (k == thr_listed) atomicOr(&eq_map[t >> 5], 1u << (t & 31));
-    });
-    __syncthreads();
-    emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+    else
+      emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
     return;
   }
 #pragma unroll 1
@@ -1007,6 +1087,7 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
 // candidates the remaining two levels choose from).  select_kernel then starts from the bitmaps instead of passing
 // over the scores.  The counters are left as they are (select_kernel reads them again and zeroes them).  A head
 // whose undecided bin holds more tokens than select_kernel can list is skipped here and takes the unsplit route there.
+template <bool kFinish>
 __global__ void __launch_bounds__(kSelThreads)
 select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const uint32_t* __restrict__ counts,
                        uint32_t* __restrict__ pre_maps, int pre_words, int seg_base, int seg_stride, int split) {
@@ -1027,7 +1108,46 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
   __syncthreads();
   uint32_t prefix = 0, prefix_mask = 0, need = (uint32_t)budget;
   const uint32_t n_cand = descend_counted_level(sh, prefix, prefix_mask, need);
-  if (n_cand > (uint32_t)kSelCandCap) return;
+  if (n_cand > (uint32_t)kSelCandCap) {
+    // too many to list: left to select_kernel, or (kFinish) all that is kept found here, by the head's first block, and nothing left inside
+    if constexpr (kFinish) {
+      if (part == 0) {
+        extern __shared__ __align__(16) uint32_t space[];
+        const int n_words = (T + 31) >> 5;
+        uint32_t* gt_map = space;
+        uint32_t* eq_map = space + n_words;
+        uint32_t* copies = space + ((2 * n_words + 3) & ~3);
+        auto count = [&](auto fn) { for_each_global_key(u, T, [&](uint32_t key, int) { fn(key); }); };
+#pragma unroll 1
+        for (int level = 1; level < 3; ++level) descend_level(sh, copies, level, prefix, prefix_mask, need, count);
+        const uint32_t thr = prefix;
+        for (int i = tid; i < 2 * n_words; i += kSelThreads) space[i] = 0;
+        __syncthreads();
+        for_each_global_key(u, T, [&](uint32_t key, int i) {
+          if (key > thr) atomicOr(&gt_map[i >> 5], 1u << (i & 31));
+          else if (key == thr) atomicOr(&eq_map[i >> 5], 1u << (i & 31));
+        });
+        __syncthreads();
+        uint32_t* out_gt = pre_maps + (size_t)seg * 2 * pre_words;
+        uint32_t seen = 0;   // copies of the threshold key in earlier words
+        for (int w0 = 0; w0 < n_words; w0 += kSelThreads) {   // uniform
+          const int w = w0 + tid;
+          const uint32_t eq = w < n_words ? eq_map[w] : 0u, n = (uint32_t)__popc(eq);
+          const uint32_t incl = wave_inclusive_scan(n);
+          if (lane == 63) sh.wave_eq[wave] = incl;
+          __syncthreads();
+          const uint32_t before = seen + waves_before(sh.wave_eq, wave, lane) + incl - n;
+          if (w < n_words) {
+            out_gt[w] = gt_map[w] | lowest_set_bits(eq, before < need ? min(n, need - before) : 0u);
+            out_gt[pre_words + w] = 0;
+          }
+          seen += wave_sum(lane < kSelWaves ? sh.wave_eq[lane] : 0u);
+          __syncthreads();
+        }
+      }
+    }
+    return;
+  }
   const uint32_t bin0 = prefix >> 21;
   uint32_t* out_gt = pre_maps + (size_t)seg * 2 * pre_words;
   uint32_t* out_in = out_gt + pre_words;
@@ -1062,6 +1182,121 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
   }
 }
 
+// The one launch for longer heads, after select_classify_kernel: every block that copies rows settles the listed tokens of its head for
+// itself.  What bounds it: the copy (14 of 30 us for 8 heads of 131072, 105 thousand rows), the way of the listed scores to each compute unit (4: one
+// line for every token or two), the list 2.4, the descent 1.4.  In turn with one block per head that emits and a compaction behind it, the whole call
+// with the 256-64-1 scorer: 8 heads of 131072 146 -> 137 us, 60001 82 -> 76, 200000 219 -> 204, 2 heads of 100001 75 -> 64.
+__global__ void __launch_bounds__(kSelThreads)
+select_compact_long_kernel(SeqTable tab, const int32_t* __restrict__ offsets, int32_t* __restrict__ idx, uint32_t* __restrict__ counts,
+                           const uint32_t* __restrict__ pre_maps, int pre_words, int seg_base, int seg_stride,
+                           int map_words, int rows_per_block, uint4* __restrict__ kp, uint4* __restrict__ vp) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  SelShared& sh = *reinterpret_cast<SelShared*>(smem);
+  uint32_t* gt_map = reinterpret_cast<uint32_t*>(smem + sizeof(SelShared));
+  uint32_t* eq_map = gt_map + map_words;
+  uint32_t* stage = eq_map + map_words;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const SelShare x = block_share(tab, offsets, counts, seg_base, seg_stride, rows_per_block);
+  if (x.p0 >= x.p1) return;
+  const int T = x.T, p0 = x.p0;
+  const int n_rows = x.p1 - p0;
+  uint32_t* tokens = stage;   // of the block's rows
+  if (x.budget >= T) {   // everything is kept
+    for (int i = tid; i < n_rows; i += kSelThreads) tokens[i] = (uint32_t)(p0 + i);
+  } else {
+    const int n_words = (T + 31) >> 5;
+    const uint32_t* pre_gt = pre_maps + (size_t)x.seg * 2 * pre_words;
+    uint32_t kept[kMapRounds], inside[kMapRounds];
+    load_map(pre_gt, n_words, kept);
+    load_map(pre_gt + pre_words, n_words, inside);
+    if (tid == 0) sh.cand_count = 0;
+    uint32_t above = 0;   // tokens kept for certain
+#pragma unroll
+    for (int j = 0; j < kMapRounds; ++j) {
+      if (j * kSelThreads + tid < n_words) gt_map[j * kSelThreads + tid] = kept[j];
+      above += (uint32_t)__popc(kept[j]);
+    }
+    above = wave_sum(above);
+    if (lane == 0) sh.wave_gt[wave] = above;
+    __syncthreads();
+    list_map(sh, inside, n_words, stage);
+    __syncthreads();
+    const uint32_t n_cand = min(sh.cand_count, (uint32_t)kSelCandCap);
+    uint32_t need = (uint32_t)x.budget - wave_sum(lane < kSelWaves ? sh.wave_gt[lane] : 0u);
+    __syncthreads();   // the list's counter is used again
+    bool ranked = true;
+    if (n_cand > 0)
+      ranked = settle_listed(sh, tab.scores[x.seq] + (size_t)x.lh * (size_t)T, T, n_words, n_cand, 1, need, gt_map, eq_map, stage);
+    // the words of the map, thread t's t, t + 1024, .., and what lies ahead of each: within its wave, then over waves and rounds
+    uint32_t* totals = sh.hist();   // of a round and wave
+    auto ahead = [&](uint32_t (&n)[kMapRounds]) {   // counts to the number ahead; a barrier on either side of the totals
+#pragma unroll
+      for (int j = 0; j < kMapRounds; ++j) {
+        if (j * kSelThreads < n_words) {   // uniform
+          const uint32_t incl = wave_inclusive_scan(n[j]);
+          if (lane == 63) totals[j * kSelWaves + wave] = incl;
+          n[j] = incl - n[j];
+        }
+      }
+      __syncthreads();
+      uint32_t carry = 0;
+#pragma unroll
+      for (int j = 0; j < kMapRounds; j += 4) {   // 64 totals a lane each
+        if (j * kSelThreads < n_words) {
+          const uint32_t mine = (j + (lane >> 4)) * kSelThreads < n_words ? totals[j * kSelWaves + lane] : 0u;
+          const uint32_t incl = wave_inclusive_scan(mine);
+#pragma unroll
+          for (int i = 0; i < 4 && j + i < kMapRounds; ++i)
+            n[j + i] += carry + (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), i * kSelWaves + wave);
+          carry += last_lane(incl);
+        }
+      }
+    };
+    uint32_t word[kMapRounds], before[kMapRounds];
+#pragma unroll
+    for (int j = 0; j < kMapRounds; ++j) {
+      const int w = j * kSelThreads + tid;
+      word[j] = j * kSelThreads < n_words && w < n_words ? gt_map[w] : 0u;
+    }
+    if (!ranked) {   // the first `need` copies of the threshold key join the tokens above it
+      uint32_t eq[kMapRounds];
+#pragma unroll
+      for (int j = 0; j < kMapRounds; ++j) {
+        const int w = j * kSelThreads + tid;
+        eq[j] = j * kSelThreads < n_words && w < n_words ? eq_map[w] : 0u;
+        before[j] = (uint32_t)__popc(eq[j]);
+      }
+      ahead(before);
+#pragma unroll
+      for (int j = 0; j < kMapRounds; ++j)
+        word[j] |= lowest_set_bits(eq[j], before[j] < need ? min((uint32_t)__popc(eq[j]), need - before[j]) : 0u);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < kMapRounds; ++j) before[j] = (uint32_t)__popc(word[j]);
+    ahead(before);
+#pragma unroll
+    for (int j = 0; j < kMapRounds; ++j) {
+      if (j * kSelThreads < n_words) {   // uniform
+        uint32_t bits = word[j];
+        int at = (int)before[j] - p0;   // place of the word's first among the block's rows
+        if (at >= n_rows || at + __popc(bits) <= 0) bits = 0;
+        if (at < 0) {   // the rows of the block before
+          bits ^= lowest_set_bits(bits, (uint32_t)-at);
+          at = 0;
+        }
+        if (at + __popc(bits) > n_rows) bits = lowest_set_bits(bits, (uint32_t)(n_rows - at));
+        const uint32_t first = (uint32_t)(j * kSelThreads + tid) * 32u;
+        for (; bits; bits &= bits - 1) tokens[at++] = first + (uint32_t)__builtin_ctz(bits);
+      }
+    }
+  }
+  __syncthreads();
+  copy_share(tab, x, tokens, idx, kp, vp);
+}
+
 hipError_t select_prepare() {
   const int lds = (int)(sizeof(SelShared) + (size_t)kSelRegionBytes);
   const void* kernels[] = {
@@ -1071,11 +1306,12 @@ hipError_t select_prepare() {
   reinterpret_cast<const void*>(select_held_kernel<false, kE>), reinterpret_cast<const void*>(select_held_kernel<true, kE>)
       LKV_HELD_KERNELS(8), LKV_HELD_KERNELS(16), LKV_HELD_KERNELS(kSelMaxHeld),
       reinterpret_cast<const void*>(select_compact_kernel<8>), reinterpret_cast<const void*>(select_compact_kernel<16>),
-      reinterpret_cast<const void*>(select_compact_kernel<kSelMaxHeld>)};
+      reinterpret_cast<const void*>(select_compact_kernel<kSelMaxHeld>), reinterpret_cast<const void*>(select_compact_long_kernel)};
 #undef LKV_HELD_KERNELS
   for (const void* k : kernels)
     if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds)) return e;
-  return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(select_classify_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kSelRegionBytes);   // its SelShared is static
 }
 
 int select_inline_capacity() { return kSelInlineOffsets; }
@@ -1092,12 +1328,21 @@ static int64_t select_compact_blocks(const int32_t* budgets, int n_seq, int seq_
   return n;
 }
 
-// Rows of a block of the one-launch top-k and compaction (and the blocks), 0 where the two launches are better.
-int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, int* blocks) {
+// Rows of a block of the one-launch top-k and compaction (and the blocks), 0 where the two launches are better.  Heads too long for
+// the registers need the scoring launch's counts and room for bitmaps of `pre_words` words; there up to kFuseFewHeads of them (32 heads of
+// 36000: 180 -> 177 us, but 185 -> 188 where one block a head has to finish the choice).
+int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, const uint32_t* counts,
+                        int pre_words, int* blocks) {
   const int segs = tab.first[tab.n];
   if (segs > kFuseMaxHeads || total_rows <= 0) return 0;
-  for (int i = 0; i < tab.n; ++i)
-    if (tab.T[i] > kSelMaxHeldT) return 0;
+  int least = tab.T[0], most = 0;
+  for (int i = 0; i < tab.n; ++i) {
+    least = tab.T[i] < least ? tab.T[i] : least;
+    most = tab.T[i] > most ? tab.T[i] : most;
+  }
+  if (most > kSelMaxHeldT && (segs > kFuseFewHeads || least <= kSelMaxHeldT || counts == nullptr || most > kSelMaxBitmapT ||
+                              (most + 31) / 32 > pre_words))
+    return 0;
   auto count = [&](int64_t rows) { return select_compact_blocks(budgets, tab.n, seq_stride, segs / tab.n, rows); };
   int64_t lo = total_rows / kFuseBlocks, hi = lo < 32 ? 64 : 2 * lo;   // hi fits one round, lo does not
   if (lo < 63) lo = 63;
@@ -1106,15 +1351,31 @@ int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_str
     const int64_t mid = (lo + hi) / 2;
     (count(mid) > kFuseBlocks ? lo : hi) = mid;
   }
-  if (hi > kFuseMaxRows) return 0;
+  if (hi > (segs <= kFuseFewHeads ? kFuseMaxRowsFewHeads : kFuseMaxRows)) return 0;
   *blocks = (int)count(hi);
   return (int)hi;
 }
 
+static int classify_split(int segs) {
+  const int split = kSelSplitTargetBlocks / segs;
+  return split > kSelSplitMax ? kSelSplitMax : split;
+}
+
 void launch_select_compact(const SeqTable& tab, const int32_t* offsets, int32_t* idx, int seg_base, int seg_stride,
-                           int rows_per_block, int blocks, uint32_t* counts, void* kp, void* vp, hipStream_t stream) {
+                           int rows_per_block, int blocks, uint32_t* counts, uint32_t* pre_maps, int pre_words, void* kp, void* vp,
+                           hipStream_t stream) {
   int most = 0;
   for (int i = 0; i < tab.n; ++i) most = tab.T[i] > most ? tab.T[i] : most;
+  if (most > kSelMaxHeldT) {
+    const int split = classify_split(tab.first[tab.n]), map_words = (most + 31) / 32;
+    const size_t maps = (2 * (size_t)map_words + 3) / 4 * 16;
+    hipLaunchKernelGGL(select_classify_kernel<true>, dim3(tab.first[tab.n] * split), dim3(kSelThreads), maps + kSelStageBytes, stream, tab,
+                       offsets, counts, pre_maps, pre_words, seg_base, seg_stride, split);
+    hipLaunchKernelGGL(select_compact_long_kernel, dim3(blocks), dim3(kSelThreads), sizeof(SelShared) + maps + kSelStageBytes, stream, tab,
+                       offsets, idx, counts, pre_maps, pre_words, seg_base, seg_stride, (int)(maps / 8), rows_per_block,
+                       static_cast<uint4*>(kp), static_cast<uint4*>(vp));
+    return;
+  }
   const int map_words = (most + kSelThreads - 1) / kSelThreads * 32;
   const size_t lds = sizeof(SelShared) + 2 * (size_t)map_words * 4 + kSelStageBytes;
   auto launch = [&](auto kernel) {
@@ -1160,9 +1421,8 @@ void launch_select(const SeqTable& tab, const int32_t* host_offsets, int n_total
   for (int i = 0; i < tab.n && split_heads; ++i)
     if (tab.T[i] > kSelMaxBitmapT || (tab.T[i] + 31) / 32 > pre_words) split_heads = false;
   if (split_heads) {
-    int split = kSelSplitTargetBlocks / segs;
-    split = split > kSelSplitMax ? kSelSplitMax : split;
-    hipLaunchKernelGGL(select_classify_kernel, dim3(segs * split), block, 0, stream, tab, offsets, counts, pre_maps,
+    const int split = classify_split(segs);
+    hipLaunchKernelGGL(select_classify_kernel<false>, dim3(segs * split), block, 0, stream, tab, offsets, counts, pre_maps,
                        pre_words, seg_base, seg_stride, split);
   } else {
     pre_maps = nullptr;

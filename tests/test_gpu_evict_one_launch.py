@@ -116,3 +116,60 @@ def test_counters_are_left_zero(ctx):
     uh, off = u.cpu().numpy().reshape(6, 5000), offsets.cpu().numpy()
     for j in range(6):
         assert np.array_equal(idx[off[j]:off[j + 1]].cpu().numpy(), O.select(uh[j], int(budgets[j])))
+
+
+# longer heads: classified by several blocks with the counts of the scoring launch, settled in every block that copies
+LONG = [([34817], 1, 1, 2), ([40000], 2, 1, 8), ([65537, 34900], 1, 1, 2), ([131077], 1, 1, 1), ([327680], 1, 1, 1),
+        ([36001], 4, 4, 4), ([36001], 5, 5, 4),         # 16 heads, 20 (two launches)
+        ([327681], 1, 1, 1), ([50000, 20000], 1, 1, 1)]  # too long for the bitmaps; one too short to be split
+
+
+@pytest.mark.parametrize("kind", ["plain", "narrow", "steps", "equal"])
+@pytest.mark.parametrize("lens,n_layers,m,H", LONG)
+def test_long_heads_same_as_select_and_compact(ctx, lens, n_layers, m, H, kind):
+    rng = np.random.default_rng(lens[0] + H)
+    g = torch.Generator(device="cuda").manual_seed(lens[0])
+    K, V = ([torch.empty((m, H, T, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for T in lens] for _ in range(2))
+    view = lkv.Cache(K, V, H)
+    w2 = torch.randn((n_layers, 16), device="cuda", generator=g)
+    scorer = {"kind": "mlp", "act": "silu", "hidden": 16, "per_head": False, "b1": torch.zeros((n_layers, 16), device="cuda"), "w2": w2, "b2": None,
+              "w1": torch.randn((n_layers, 16, 256), device="cuda", generator=g).mul(0.05).to(torch.bfloat16)}
+    if kind == "narrow":      # one first digit for all: more than can be listed
+        scorer["b2"] = torch.full((n_layers,), 1000.0, device="cuda")
+    elif kind == "steps":     # few values, many copies of the threshold
+        scorer["b2"] = torch.full((n_layers,), 3e5, device="cuda")
+    elif kind == "equal":
+        scorer["w2"] = w2 * 0
+    budgets = np.zeros((len(lens), n_layers, H), np.int32)
+    for s, T in enumerate(lens):
+        budgets[s] = rng.integers(1, T // 5, size=(n_layers, H))
+        if H > 1:
+            budgets[s, :, 0] = rng.choice([0, 1, 300, T // 2], n_layers)
+    if len(lens) == 1 and H == 1:
+        budgets[0, :, 0] = lens[0] // 3
+    offsets = torch.empty(budgets.size + 1, dtype=torch.int32, device="cuda")
+    total = lkv.lkv_plan_offsets(ctx, budgets, offsets)
+    idx = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.zeros((total, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    counts = torch.zeros(lkv.lkv_counts_bytes_split(budgets.size, max(lens)), dtype=torch.uint8, device="cuda")
+    scores = [torch.empty((m, H, T), device="cuda") for T in lens]
+    layer = n_layers - m
+    for _ in range(2):        # the second call finds the counters as the first one left them
+        lkv.lkv_evict_layer(ctx, view, layer, n_layers, scorer, budgets, offsets, scores, idx, kp, vp, counts=counts)
+    mine = np.ascontiguousarray(budgets[:, layer:layer + m])
+    offsets2 = torch.empty(mine.size + 1, dtype=torch.int32, device="cuda")
+    n = lkv.lkv_plan_offsets(ctx, mine, offsets2)
+    idx2 = torch.empty(max(n, 1), dtype=torch.int32, device="cuda")
+    kp2, vp2 = (torch.empty((max(n, 1), 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    lkv.lkv_select(ctx, view, scores, None, idx2, offsets2)
+    lkv.lkv_compact(ctx, view, idx2, offsets2, n, kp2, vp2)
+    torch.cuda.synchronize()
+    assert not counts[:lkv.lkv_counts_bytes(budgets.size)].any()
+    off, off2 = offsets.cpu().numpy(), offsets2.cpu().numpy()
+    for s, T in enumerate(lens):
+        for j in range(m * H):
+            a = (s * n_layers + layer) * H + j
+            lo, hi, l2, h2 = off[a], off[a + 1], off2[s * m * H + j], off2[s * m * H + j + 1]
+            assert torch.equal(idx[lo:hi], idx2[l2:h2]), (s, j)
+            assert torch.equal(kp[lo:hi].view(torch.int16), kp2[l2:h2].view(torch.int16))
+            assert torch.equal(vp[lo:hi].view(torch.int16), vp2[l2:h2].view(torch.int16))
