@@ -19,7 +19,10 @@ namespace lkv {
 constexpr int kScoreBlockThreads = 256;
 constexpr int kScoreRowsPerWave = 64;
 constexpr int kScoreRowsPerBlock = kScoreRowsPerWave * (kScoreBlockThreads / 64);   // 256
-constexpr int kScoreUnroll = 4;   // row groups whose loads are in flight together (8 loads per lane)
+// Row groups whose loads are in flight together: all of a wave's rows (32 loads a lane, three waves a SIMD).  Short calls are one
+// chain of latencies, long ones keep more of the memory's queues filled.  4 : 8 : 16 groups (us): 32 x 8 heads, four sequences of up
+// to 16384 852 : 847 : 834 (6.47 TB/s), 32 x 8 x 30001 632 : 627 : 620, 8 x 32768 22.7 : 22.0 : 21.8, 8 x 4096 7.1 : 6.2 : 6.1.
+constexpr int kScoreUnroll = 16;
 
 // Blocks are 64 KB windows of the key array's address space (256 rows).  A head's first row can lie anywhere inside
 // a window, so a head needs up to one block more than its rows fill; a block with no row of the head exits at once.
