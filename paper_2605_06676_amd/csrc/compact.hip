@@ -4,8 +4,8 @@
 // A pure gather: packed row p of segment s copies row idx[p] of that segment's
 // head, 256 bytes of K and 256 bytes of V, bit for bit.  The grid is flat over
 // packed rows, so skewed budgets do not unbalance it.  Sixteen lanes move one
-// row with one 16-byte load and store each; a block of 256 threads owns 64
-// consecutive packed rows.  The segment of the block's first row is found by a
+// row with one 16-byte load and store each; a block of 256 threads owns 32
+// (or 64) consecutive packed rows.  The segment of the block's first row is found by a
 // wave-uniform binary search over the offsets; later rows walk forward from it.
 #include <cstring>
 
@@ -14,9 +14,15 @@
 namespace lkv {
 
 constexpr int kCompactThreads = 256;
-constexpr int kCompactRowsPerBlock = 64;    // one pass: every thread moves 4 rows' pieces (8 loads in flight, then 8 stores).
-                                            // Blocks of 256 rows (four such passes in a loop) were 11 % slower.
-constexpr int kCompactUnroll = 4;
+// One pass over a block's rows: every thread moves the pieces of kUnroll rows (twice as many loads in flight, then the stores).
+// Fewer rows in a block let more blocks overlap one's loads with another's stores; below 32 the search for the segment weighs
+// in.  Blocks of 16 : 32 : 64 : 128 rows (us): 1.26 million rows of 32 x 8 heads 216.8 : 215.4 : 218.9 : 221.7 (5.98 TB/s in and
+// out), 105 thousand 20.3 : 20.9 : 21.8 : 23.4, 118 thousand of 32 x 8 heads 24.4 : 23.9 : 23.9 : 25.6, 3 thousand
+// 5.35 : 5.25 : 5.35 : 6.4.  A cache of more sequences than one launch takes gets several whose blocks mostly have nothing to do;
+// there twice the blocks cost more (100 sequences, 5.2 million rows: 1010 us with 32, 938 with 64).
+constexpr int kCompactRowsPerPass = kCompactThreads / 16;
+constexpr int kCompactUnroll = 2;
+constexpr int kCompactUnrollOwn = 4;   // launches that take the rows of their own sequences only
 
 __device__ __forceinline__ int len_or_one(const int32_t* len, int s) { return len != nullptr ? len[s] : 1; }
 
@@ -40,7 +46,7 @@ struct CompactGrow {
   const int32_t* len_old;  // [n_segments] rows in use of every old segment
 };
 
-template <int kMode>
+template <int kMode, int kUnroll>
 __global__ void __launch_bounds__(kCompactThreads)
 compact_kernel(SeqTable tab, const int32_t* __restrict__ idx, const int32_t* __restrict__ offsets,
                int n_segments, int heads_per_seq, int seq_lo, int head_lo, int n_heads_view, int64_t row_lo,
@@ -55,73 +61,75 @@ compact_kernel(SeqTable tab, const int32_t* __restrict__ idx, const int32_t* __r
     row_lo = offsets[min(seq_lo * heads_per_seq, n_segments)];
     row_hi = offsets[min((seq_lo + tab.n) * heads_per_seq, n_segments)];
   }
-  const int64_t p0 = row_lo + (int64_t)blockIdx.x * kCompactRowsPerBlock;
+  const int64_t p0 = row_lo + (int64_t)blockIdx.x * (kUnroll * kCompactRowsPerPass);
   if (p0 >= row_hi) return;
   // the segment that contains row p0: the last one with offsets[s] <= p0
   const int s0 = wave_upper_segment(offsets, n_segments, p0, threadIdx.x & 63);
 
-  const int rslot = threadIdx.x >> 4;   // 16 rows per pass over the block
+  const int rslot = threadIdx.x >> 4;
   const int c = threadIdx.x & 15;
-#pragma unroll 1
-  for (int it = 0; it < kCompactRowsPerBlock / 16; it += kCompactUnroll) {
-    // Loads are unconditional (a row past the end re-reads the last packed row) so that the
-    // staged rows stay in registers; only the stores are predicated.
-    uint4 kk[kCompactUnroll], vv[kCompactUnroll];
-    float uu[kCompactUnroll];
-    int64_t dst[kCompactUnroll];
-    bool live[kCompactUnroll];
+  // Loads are unconditional (a row past the end re-reads the last packed row) so that the
+  // staged rows stay in registers; only the stores are predicated.
+  uint4 kk[kUnroll], vv[kUnroll];
+  float uu[kUnroll];
+  int64_t dst[kUnroll];
+  bool live[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kCompactUnroll; ++u) {
-      int64_t p = p0 + (it + u) * 16 + rslot;
-      live[u] = p < row_hi;
-      p = live[u] ? p : row_hi - 1;
-      int s = s0;
-      // skips empty segments too; p < offsets[n_segments] when total_kept matches the table, and the
-      // walk stops at the last segment when it does not
-      while (s + 1 < n_segments && (int64_t)offsets[s + 1] <= p) ++s;
-      dst[u] = kMode == kCompactPlain ? p : p + (int64_t)grow.slack * s;
-      if (kMode == kCompactGrowPacked) {
-        // a row index outside the old segment cannot come from the selection; clamped, never followed
-        const int len = max(len_or_one(grow.len_old, s), 1);
-        const int tok = min(max(idx[p], 0), len - 1);
-        const size_t row = (size_t)grow.cap_old[s] + (size_t)tok;
-        kk[u] = load_stream16(grow.kp_old + row * kChunksPerRow + c);
-        vv[u] = load_stream16(grow.vp_old + row * kChunksPerRow + c);
-        uu[u] = grow.up_old[row];
-      } else {
-        const int seq = s / heads_per_seq;
-        int lh = s - seq * heads_per_seq - head_lo;
-        int sl = seq - seq_lo;                        // this launch describes sequences seq_lo .. seq_lo + tab.n - 1
-        live[u] = live[u] && sl >= 0 && sl < tab.n && lh >= 0 && lh < n_heads_view;
-        sl = min(max(sl, 0), tab.n - 1);
-        lh = min(max(lh, 0), n_heads_view - 1);       // rows of other heads are not this launch's: never followed
-        // a token index outside [0, T) cannot come from lkv_select; it is clamped, never followed
-        const int T = tab.T[sl];
-        const int tok = min(max(idx[p], 0), T - 1);
-        const size_t src = ((size_t)lh * (size_t)T + (size_t)tok) * kChunksPerRow + c;
-        kk[u] = load_stream16(reinterpret_cast<const uint4*>(tab.k[sl]) + src);
-        vv[u] = load_stream16(reinterpret_cast<const uint4*>(tab.v[sl]) + src);
-        if (kMode == kCompactGrowCache) uu[u] = tab.scores[sl][(size_t)lh * (size_t)T + (size_t)tok];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kCompactUnroll; ++u) {
-      if (live[u]) {
-        store_stream16(kp + dst[u] * kChunksPerRow + c, kk[u]);
-        store_stream16(vp + dst[u] * kChunksPerRow + c, vv[u]);
-        if (kMode != kCompactPlain && c == 0) grow.up[dst[u]] = uu[u];
-      }
+  for (int u = 0; u < kUnroll; ++u) {
+    int64_t p = p0 + u * kCompactRowsPerPass + rslot;
+    live[u] = p < row_hi;
+    p = live[u] ? p : row_hi - 1;
+    int s = s0;
+    // skips empty segments too; p < offsets[n_segments] when total_kept matches the table, and the
+    // walk stops at the last segment when it does not
+    while (s + 1 < n_segments && (int64_t)offsets[s + 1] <= p) ++s;
+    dst[u] = kMode == kCompactPlain ? p : p + (int64_t)grow.slack * s;
+    if (kMode == kCompactGrowPacked) {
+      // a row index outside the old segment cannot come from the selection; clamped, never followed
+      const int len = max(len_or_one(grow.len_old, s), 1);
+      const int tok = min(max(idx[p], 0), len - 1);
+      const size_t row = (size_t)grow.cap_old[s] + (size_t)tok;
+      kk[u] = load_stream16(grow.kp_old + row * kChunksPerRow + c);
+      vv[u] = load_stream16(grow.vp_old + row * kChunksPerRow + c);
+      uu[u] = grow.up_old[row];
+    } else {
+      const int seq = s / heads_per_seq;
+      int lh = s - seq * heads_per_seq - head_lo;
+      int sl = seq - seq_lo;                        // this launch describes sequences seq_lo .. seq_lo + tab.n - 1
+      live[u] = live[u] && sl >= 0 && sl < tab.n && lh >= 0 && lh < n_heads_view;
+      sl = min(max(sl, 0), tab.n - 1);
+      lh = min(max(lh, 0), n_heads_view - 1);       // rows of other heads are not this launch's: never followed
+      // a token index outside [0, T) cannot come from lkv_select; it is clamped, never followed
+      const int T = tab.T[sl];
+      const int tok = min(max(idx[p], 0), T - 1);
+      const size_t src = ((size_t)lh * (size_t)T + (size_t)tok) * kChunksPerRow + c;
+      kk[u] = load_stream16(reinterpret_cast<const uint4*>(tab.k[sl]) + src);
+      vv[u] = load_stream16(reinterpret_cast<const uint4*>(tab.v[sl]) + src);
+      if (kMode == kCompactGrowCache) uu[u] = tab.scores[sl][(size_t)lh * (size_t)T + (size_t)tok];
     }
   }
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    if (live[u]) {
+      store_stream16(kp + dst[u] * kChunksPerRow + c, kk[u]);
+      store_stream16(vp + dst[u] * kChunksPerRow + c, vv[u]);
+      if (kMode != kCompactPlain && c == 0) grow.up[dst[u]] = uu[u];
+    }
+  }
+}
+
+static int compact_blocks(int64_t rows, bool rows_of_own_sequences) {
+  const int per_block = kCompactRowsPerPass * (rows_of_own_sequences ? kCompactUnrollOwn : kCompactUnroll);
+  return (int)((rows + per_block - 1) / per_block);
 }
 
 void launch_compact(const SeqTable& tab, const int32_t* idx, const int32_t* offsets, int n_segments,
                     int heads_per_seq, int seq_lo, int head_lo, int n_heads_view, int64_t row_lo, int64_t row_hi,
                     void* kp, void* vp, hipStream_t stream, bool rows_of_own_sequences) {
   if (row_hi <= row_lo) return;
-  const int blocks = (int)((row_hi - row_lo + kCompactRowsPerBlock - 1) / kCompactRowsPerBlock);
   CompactGrow none = {};
-  hipLaunchKernelGGL(compact_kernel<kCompactPlain>, dim3(blocks), dim3(kCompactThreads), 0, stream, tab, idx,
+  const auto kernel = rows_of_own_sequences ? compact_kernel<kCompactPlain, kCompactUnrollOwn> : compact_kernel<kCompactPlain, kCompactUnroll>;
+  hipLaunchKernelGGL(kernel, dim3(compact_blocks(row_hi - row_lo, rows_of_own_sequences)), dim3(kCompactThreads), 0, stream, tab, idx,
                      offsets, n_segments, heads_per_seq, seq_lo, head_lo, n_heads_view, row_lo, row_hi,
                      rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), none);
 }
@@ -132,11 +140,11 @@ void launch_compact_grow(const SeqTable& tab, const int32_t* idx, const int32_t*
                          int heads_per_seq, int seq_lo, int64_t total_kept, int slack, void* kp, void* vp, float* up,
                          hipStream_t stream, bool rows_of_own_sequences) {
   if (total_kept <= 0) return;
-  const int blocks = (int)((total_kept + kCompactRowsPerBlock - 1) / kCompactRowsPerBlock);
   CompactGrow g = {};
   g.slack = slack;
   g.up = up;
-  hipLaunchKernelGGL(compact_kernel<kCompactGrowCache>, dim3(blocks), dim3(kCompactThreads), 0, stream, tab, idx,
+  const auto kernel = rows_of_own_sequences ? compact_kernel<kCompactGrowCache, kCompactUnrollOwn> : compact_kernel<kCompactGrowCache, kCompactUnroll>;
+  hipLaunchKernelGGL(kernel, dim3(compact_blocks(total_kept, rows_of_own_sequences)), dim3(kCompactThreads), 0, stream, tab, idx,
                      offsets, n_segments, heads_per_seq, seq_lo, 0, heads_per_seq, (int64_t)0, total_kept,
                      rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), g);
 }
@@ -146,12 +154,11 @@ void launch_compact_regrow(const int32_t* idx, const int32_t* offsets, int n_seg
                            const void* kp_old, const void* vp_old, const float* up_old, const int32_t* cap_old,
                            const int32_t* len_old, void* kp, void* vp, float* up, hipStream_t stream) {
   if (total_kept <= 0) return;
-  const int blocks = (int)((total_kept + kCompactRowsPerBlock - 1) / kCompactRowsPerBlock);
   SeqTable tab;
   memset(&tab, 0, sizeof(tab));
   CompactGrow g = {slack, up, reinterpret_cast<const uint4*>(kp_old), reinterpret_cast<const uint4*>(vp_old), up_old,
                    cap_old, len_old};
-  hipLaunchKernelGGL(compact_kernel<kCompactGrowPacked>, dim3(blocks), dim3(kCompactThreads), 0, stream, tab, idx,
+  hipLaunchKernelGGL((compact_kernel<kCompactGrowPacked, kCompactUnroll>), dim3(compact_blocks(total_kept, false)), dim3(kCompactThreads), 0, stream, tab, idx,
                      offsets, n_segments, 1, 0, 0, 1, (int64_t)0, total_kept, 0, reinterpret_cast<uint4*>(kp),
                      reinterpret_cast<uint4*>(vp), g);
 }
