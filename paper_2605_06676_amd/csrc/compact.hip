@@ -8,6 +8,7 @@
 // (or 64) consecutive packed rows.  The segment of the block's first row is found by a
 // wave-uniform binary search over the offsets; later rows walk forward from it.
 #include <cstring>
+#include <type_traits>
 
 #include "lkv_common.h"
 
@@ -16,13 +17,15 @@ namespace lkv {
 constexpr int kCompactThreads = 256;
 // One pass over a block's rows: every thread moves the pieces of kUnroll rows (twice as many loads in flight, then the stores).
 // Fewer rows in a block let more blocks overlap one's loads with another's stores; below 32 the search for the segment weighs
-// in.  Blocks of 16 : 32 : 64 : 128 rows (us): 1.26 million rows of 32 x 8 heads 216.8 : 215.4 : 218.9 : 221.7 (5.98 TB/s in and
-// out), 105 thousand 20.3 : 20.9 : 21.8 : 23.4, 118 thousand of 32 x 8 heads 24.4 : 23.9 : 23.9 : 25.6, 3 thousand
-// 5.35 : 5.25 : 5.35 : 6.4.  A cache of more sequences than one launch takes gets several whose blocks mostly have nothing to do;
-// there twice the blocks cost more (100 sequences, 5.2 million rows: 1010 us with 32, 938 with 64).
+// in, and past two million rows so does starting twice the blocks.  Blocks of 16 : 32 : 64 : 128 rows (us): 1.26 million rows of 32 x 8 heads
+// 216.8 : 215.4 : 218.9 : 221.7 (5.98 TB/s in and out), 105 thousand 20.3 : 20.9 : 21.8 : 23.4, 118 thousand of 32 x 8 heads
+// 24.4 : 23.9 : 23.9 : 25.6, 3 thousand 5.35 : 5.25 : 5.35 : 6.4; 32 : 64: 1.66 million 292.8 : 294.8, 2.9 million 531 : 525, 3.4 million
+// 592 : 590, 4.2 million 745 : 734.  A cache of more sequences than one launch takes gets several whose blocks mostly have nothing
+// to do; there twice the blocks cost more (100 sequences, 5.2 million rows: 1010 with 32, 938 with 64).
 constexpr int kCompactRowsPerPass = kCompactThreads / 16;
-constexpr int kCompactUnroll = 2;
-constexpr int kCompactUnrollOwn = 4;   // launches that take the rows of their own sequences only
+constexpr int kCompactUnroll = 4;
+constexpr int kCompactUnrollShort = 2;            // launches over at most this many rows, all of them its own:
+constexpr int64_t kCompactShortRows = 2 << 20;
 
 __device__ __forceinline__ int len_or_one(const int32_t* len, int s) { return len != nullptr ? len[s] : 1; }
 
@@ -118,9 +121,15 @@ compact_kernel(SeqTable tab, const int32_t* __restrict__ idx, const int32_t* __r
   }
 }
 
-static int compact_blocks(int64_t rows, bool rows_of_own_sequences) {
-  const int per_block = kCompactRowsPerPass * (rows_of_own_sequences ? kCompactUnrollOwn : kCompactUnroll);
-  return (int)((rows + per_block - 1) / per_block);
+// Calls launch(rows a thread moves, blocks) for a launch whose grid covers `rows`.
+template <typename Launch>
+static void compact_shape(int64_t rows, bool rows_of_own_sequences, Launch launch) {
+  auto shape = [&](auto unroll) {
+    constexpr int kPerBlock = decltype(unroll)::value * kCompactRowsPerPass;
+    launch(unroll, dim3((unsigned)((rows + kPerBlock - 1) / kPerBlock)));
+  };
+  if (!rows_of_own_sequences && rows <= kCompactShortRows) shape(std::integral_constant<int, kCompactUnrollShort>{});
+  else shape(std::integral_constant<int, kCompactUnroll>{});
 }
 
 void launch_compact(const SeqTable& tab, const int32_t* idx, const int32_t* offsets, int n_segments,
@@ -128,10 +137,11 @@ void launch_compact(const SeqTable& tab, const int32_t* idx, const int32_t* offs
                     void* kp, void* vp, hipStream_t stream, bool rows_of_own_sequences) {
   if (row_hi <= row_lo) return;
   CompactGrow none = {};
-  const auto kernel = rows_of_own_sequences ? compact_kernel<kCompactPlain, kCompactUnrollOwn> : compact_kernel<kCompactPlain, kCompactUnroll>;
-  hipLaunchKernelGGL(kernel, dim3(compact_blocks(row_hi - row_lo, rows_of_own_sequences)), dim3(kCompactThreads), 0, stream, tab, idx,
-                     offsets, n_segments, heads_per_seq, seq_lo, head_lo, n_heads_view, row_lo, row_hi,
-                     rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), none);
+  compact_shape(row_hi - row_lo, rows_of_own_sequences, [&](auto unroll, dim3 blocks) {
+    hipLaunchKernelGGL((compact_kernel<kCompactPlain, decltype(unroll)::value>), blocks, dim3(kCompactThreads), 0, stream, tab, idx,
+                       offsets, n_segments, heads_per_seq, seq_lo, head_lo, n_heads_view, row_lo, row_hi,
+                       rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), none);
+  });
 }
 
 // Compaction into a cache with `slack` spare rows behind every segment, from the prefilled cache
@@ -143,10 +153,11 @@ void launch_compact_grow(const SeqTable& tab, const int32_t* idx, const int32_t*
   CompactGrow g = {};
   g.slack = slack;
   g.up = up;
-  const auto kernel = rows_of_own_sequences ? compact_kernel<kCompactGrowCache, kCompactUnrollOwn> : compact_kernel<kCompactGrowCache, kCompactUnroll>;
-  hipLaunchKernelGGL(kernel, dim3(compact_blocks(total_kept, rows_of_own_sequences)), dim3(kCompactThreads), 0, stream, tab, idx,
-                     offsets, n_segments, heads_per_seq, seq_lo, 0, heads_per_seq, (int64_t)0, total_kept,
-                     rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), g);
+  compact_shape(total_kept, rows_of_own_sequences, [&](auto unroll, dim3 blocks) {
+    hipLaunchKernelGGL((compact_kernel<kCompactGrowCache, decltype(unroll)::value>), blocks, dim3(kCompactThreads), 0, stream, tab, idx,
+                       offsets, n_segments, heads_per_seq, seq_lo, 0, heads_per_seq, (int64_t)0, total_kept,
+                       rows_of_own_sequences ? 1 : 0, reinterpret_cast<uint4*>(kp), reinterpret_cast<uint4*>(vp), g);
+  });
 }
 
 // The same from an older packed cache with slack: idx[p] is a row position inside the old segment.
@@ -158,9 +169,11 @@ void launch_compact_regrow(const int32_t* idx, const int32_t* offsets, int n_seg
   memset(&tab, 0, sizeof(tab));
   CompactGrow g = {slack, up, reinterpret_cast<const uint4*>(kp_old), reinterpret_cast<const uint4*>(vp_old), up_old,
                    cap_old, len_old};
-  hipLaunchKernelGGL((compact_kernel<kCompactGrowPacked, kCompactUnroll>), dim3(compact_blocks(total_kept, false)), dim3(kCompactThreads), 0, stream, tab, idx,
-                     offsets, n_segments, 1, 0, 0, 1, (int64_t)0, total_kept, 0, reinterpret_cast<uint4*>(kp),
-                     reinterpret_cast<uint4*>(vp), g);
+  compact_shape(total_kept, false, [&](auto unroll, dim3 blocks) {
+    hipLaunchKernelGGL((compact_kernel<kCompactGrowPacked, decltype(unroll)::value>), blocks, dim3(kCompactThreads), 0, stream, tab, idx,
+                       offsets, n_segments, 1, 0, 0, 1, (int64_t)0, total_kept, 0, reinterpret_cast<uint4*>(kp),
+                       reinterpret_cast<uint4*>(vp), g);
+  });
 }
 
 // cap[s] = offsets[s] + slack * s (s = 0..n_segments), len[s] = offsets[s + 1] - offsets[s]
