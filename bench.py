@@ -45,9 +45,9 @@ SCORE_KERNEL_SOURCES = {
 }
 MEASURED_SCORE_TRAFFIC = {
     # workload name: (bytes per launch, sha256[:16] of the kernel's sources, profile)
-    "cfg1-L32-H8-T32768-linear": (4328897267, "8df6ec869a771fd8", "profiles/all_kernels__cfg1-L32-H8-T32768-linear.md"),
+    "cfg1-L32-H8-T32768-linear": (4328892531, "724d5a236938c1b1", "profiles/all_kernels__cfg1-L32-H8-T32768-linear.md"),
     "cfg2-L32-H8-T131072-mlp64gelu": (17337034758, "99c7421e7526e2dd", "profiles/all_kernels__cfg2-L32-H8-T131072-mlp64gelu.md"),
-    "cfg3-16seq-T4096..16384-linear": (22846926438, "8df6ec869a771fd8", "profiles/all_kernels__cfg3-16seq-T4096-16384-linear.md"),
+    "cfg3-16seq-T4096..16384-linear": (22840916840, "724d5a236938c1b1", "profiles/all_kernels__cfg3-16seq-T4096-16384-linear.md"),
     "cfg4-8seq-L28-H4-g7-T65536-mlp64gelu": (30385678630, "99c7421e7526e2dd", "profiles/all_kernels__cfg4-8seq-L28-H4-g7-T65536-mlp64gelu.md"),
     "paper-L32-H8-T32768-mlp128silu-per-head": (4467555675, "99c7421e7526e2dd", "profiles/all_kernels__paper-L32-H8-T32768-mlp128silu-per-head.md"),
     "paper-L36-H8-T32768-mlp128silu-per-head": (5028562722, "99c7421e7526e2dd", "profiles/all_kernels__paper-L36-H8-T32768-mlp128silu-per-head.md"),
