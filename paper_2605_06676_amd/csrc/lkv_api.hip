@@ -647,6 +647,9 @@ lkv_status lkv_evict_layer(lkv_ctx* ctx, const lkv_cache* layer, int32_t layer_i
       sl.w2 = scorer->w2 + rows * scorer->hidden;
       sl.b2 = scorer->b2 != nullptr ? scorer->b2 + rows : nullptr;
     }
+    // before the scoring launch: it adds to the counters of this view's segments
+    if (counts != nullptr && counts_bytes < lkv_counts_bytes(n_seg))
+      return fail(ctx, LKV_ERR_WORKSPACE, "counts: need %zu bytes, got %zu", lkv_counts_bytes(n_seg), counts_bytes);
     if (lkv_status st = score_impl(ctx, layer, &sl, scores, counts, layer_index * H, heads_all, stream)) return st;
   } else {
     counts = nullptr;   // the scores came from elsewhere: nothing has counted them
@@ -656,8 +659,6 @@ lkv_status lkv_evict_layer(lkv_ctx* ctx, const lkv_cache* layer, int32_t layer_i
   uint32_t* pre_maps = nullptr;
   int pre_words = 0;
   if (counts != nullptr) {
-    if (counts_bytes < lkv_counts_bytes(n_seg))
-      return fail(ctx, LKV_ERR_WORKSPACE, "counts: need %zu bytes, got %zu", lkv_counts_bytes(n_seg), counts_bytes);
     const size_t words = (counts_bytes - lkv_counts_bytes(n_seg)) / ((size_t)n_seg * 2 * sizeof(uint32_t));
     int max_T = 0;
     for (int s = 0; s < layer->n_seq; ++s) max_T = layer->seq_len[s] > max_T ? layer->seq_len[s] : max_T;

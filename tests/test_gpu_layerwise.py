@@ -109,3 +109,25 @@ def test_layerwise_argument_errors(ctx):
         lkv.lkv_plan_offsets(ctx, np.array([3, -1], dtype=np.int32), run.offsets)
     assert e.value.status == 1
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("scorer,hidden", [("linear", 0), ("mlp", 64), ("mlp", 128)])
+@pytest.mark.parametrize("short_of", ["one segment", "all but the view's"])
+def test_counters_too_few_for_the_call_are_refused_before_anything_is_launched(ctx, scorer, hidden, short_of):
+    w = W.scaled(W.CONFIGS[0], L=3, H=2, Hq=4, scorer=scorer, hidden=hidden, b_min=4)
+    K, V, Q, sc, B = _inputs(w, [700])
+    run = G.LayerwiseRun(ctx, K, V, Q, sc, B, w.Hq)
+    lkv.lkv_plan_offsets(ctx, run.budgets, run.offsets)
+    n_seg = w.L * w.H
+    buffer = torch.zeros((n_seg + 1, 2048), dtype=torch.int32, device="cuda")
+    counts = buffer[:n_seg - 1 if short_of == "one segment" else w.H]      # the rows behind are there to be looked at
+    layer = w.L - 1                                                       # its counters lie behind the buffer's end
+    view = lkv.Cache([run.k[0][layer:layer + 1]], [run.v[0][layer:layer + 1]], w.Hq)
+    scratch = torch.full((w.H, 700), -7.0, dtype=torch.float32, device="cuda")
+    run.idx.fill_(-1)
+    with pytest.raises(lkv.LkvError) as e:
+        lkv.lkv_evict_layer(ctx, view, layer, w.L, run.scorer, run.budgets, run.offsets, [scratch], run.idx, run.kp, run.vp,
+                            counts=counts)
+    assert e.value.status == 3
+    torch.cuda.synchronize()
+    assert not buffer.any() and (scratch == -7.0).all() and (run.idx == -1).all()
