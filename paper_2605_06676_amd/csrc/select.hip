@@ -682,12 +682,14 @@ __device__ __forceinline__ SelShare block_share(const SeqTable& tab, const int32
   return x;
 }
 
-// The indices and the rows of a block's tokens (listed in LDS), 16 lanes a row, 64 rows a round of the workgroup.
+// The indices and the rows of a block's tokens (listed in LDS), 16 lanes a row, 64 rows a round of the workgroup.  Where the
+// counters did not count these scores the list has gaps, and what lies there is clamped, never followed.
 __device__ __forceinline__ void copy_share(const SeqTable& tab, const SelShare& x, const uint32_t* tokens, int32_t* __restrict__ idx,
                                            uint4* __restrict__ kp, uint4* __restrict__ vp) {
   const int tid = threadIdx.x;
   const int n_rows = x.p1 - x.p0;
-  for (int i = tid; i < n_rows; i += kSelThreads) idx[(size_t)x.off + x.p0 + i] = (int32_t)tokens[i];
+  const uint32_t last = (uint32_t)x.T - 1u;
+  for (int i = tid; i < n_rows; i += kSelThreads) idx[(size_t)x.off + x.p0 + i] = (int32_t)min(tokens[i], last);
   constexpr int kRound = kSelThreads / 16;
   constexpr int kU = 2;
   const int c = tid & 15;
@@ -700,7 +702,7 @@ __device__ __forceinline__ void copy_share(const SeqTable& tab, const SelShare& 
     uint4 kk[kU], vv[kU];
 #pragma unroll
     for (int j = 0; j < kU; ++j) {
-      const size_t row = tokens[min(i0 + j * kRound, n_rows - 1)];
+      const size_t row = min(tokens[min(i0 + j * kRound, n_rows - 1)], last);
       kk[j] = load_stream16(kh + row * kChunksPerRow);
       vv[j] = load_stream16(vh + row * kChunksPerRow);
     }
@@ -904,7 +906,7 @@ __device__ __forceinline__ bool settle_listed(SelShared& sh, const float* __rest
       else if (decided == prefix) list_for_ranking(sh, k, t);
     });
     __syncthreads();
-    keep_best_listed(sh, n_left, need, gt_map);
+    keep_best_listed(sh, min(n_left, sh.cand_count), need, gt_map);   // no more than were listed, whatever the counts said
     __syncthreads();
     return true;
   }
@@ -1224,7 +1226,7 @@ select_compact_long_kernel(SeqTable tab, const int32_t* __restrict__ offsets, in
     list_map(sh, inside, n_words, stage);
     __syncthreads();
     const uint32_t n_cand = min(sh.cand_count, (uint32_t)kSelCandCap);
-    uint32_t need = (uint32_t)x.budget - wave_sum(lane < kSelWaves ? sh.wave_gt[lane] : 0u);
+    uint32_t need = (uint32_t)max(x.budget - (int)wave_sum(lane < kSelWaves ? sh.wave_gt[lane] : 0u), 0);
     __syncthreads();   // the list's counter is used again
     bool ranked = true;
     if (n_cand > 0)

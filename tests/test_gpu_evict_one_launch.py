@@ -173,3 +173,49 @@ def test_long_heads_same_as_select_and_compact(ctx, lens, n_layers, m, H, kind):
             assert torch.equal(idx[lo:hi], idx2[l2:h2]), (s, j)
             assert torch.equal(kp[lo:hi].view(torch.int16), kp2[l2:h2].view(torch.int16))
             assert torch.equal(vp[lo:hi].view(torch.int16), vp2[l2:h2].view(torch.int16))
+
+
+@pytest.mark.parametrize("dirt", ["ones", "many", "negative", "low", "random"])
+@pytest.mark.parametrize("T,H", [(34817, 2), (40000, 8), (131077, 1)])
+def test_counters_that_are_not_zero_on_entry_lead_out_of_no_head(ctx, T, H, dirt):
+    # a caller's error: which rows are kept means nothing then, but they are rows of the head, copied as the index says, the
+    # rows of other layers stay as they are, and the counters are zero again for the next call
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.empty((1, H, T, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(2))
+    view = lkv.Cache([K], [V], H)
+    scorer = {"kind": "mlp", "act": "silu", "hidden": 16, "per_head": False, "b1": torch.zeros((2, 16), device="cuda"), "b2": None,
+              "w1": torch.randn((2, 16, 256), device="cuda", generator=g).mul(0.05).to(torch.bfloat16),
+              "w2": torch.randn((2, 16), device="cuda", generator=g)}
+    budgets = np.full((2, H), T // 11, np.int32)
+    n_seg = 2 * H
+    offsets = torch.empty(n_seg + 1, dtype=torch.int32, device="cuda")
+    total = lkv.lkv_plan_offsets(ctx, budgets, offsets)
+    idx = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    kp, vp = (torch.zeros((total, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    counts = torch.zeros(lkv.lkv_counts_bytes_split(n_seg, T) // 4, dtype=torch.int32, device="cuda")
+    mine = counts[:n_seg * 2048].view(n_seg, 2048)[:H]        # of layer 0
+    if dirt == "ones":
+        mine += 1
+    elif dirt == "many":
+        mine[:, 1100:] = T
+    elif dirt == "negative":                                   # the bin found lies too low: too many tokens above it
+        mine[:, 1024:] = -40
+    elif dirt == "low":
+        mine[:, :300] = 1 << 30
+    else:
+        mine.random_(-2 ** 31, 2 ** 31 - 1, generator=g)
+    scores = torch.empty((1, H, T), device="cuda")
+    lkv.lkv_evict_layer(ctx, view, 0, 2, scorer, budgets, offsets, [scores], idx, kp, vp, counts=counts)
+    torch.cuda.synchronize()
+    assert not counts[:n_seg * 2048].any()
+    b, half = T // 11, total // 2
+    got = idx[:half].view(H, b).long()
+    assert (got >= 0).all() and (got < T).all()
+    for h in range(H):
+        assert torch.equal(kp[h * b:(h + 1) * b].view(torch.int16), K[0, h][got[h]].view(torch.int16))
+        assert torch.equal(vp[h * b:(h + 1) * b].view(torch.int16), V[0, h][got[h]].view(torch.int16))
+    assert (idx[half:] == -1).all() and (kp[half:].view(torch.int16) == 0).all() and (vp[half:].view(torch.int16) == 0).all()
+    lkv.lkv_evict_layer(ctx, view, 0, 2, scorer, budgets, offsets, [scores], idx, kp, vp, counts=counts)
+    u = scores.cpu().numpy()[0]
+    for h in range(H):
+        assert np.array_equal(idx[h * b:(h + 1) * b].cpu().numpy(), O.select(u[h], b))
