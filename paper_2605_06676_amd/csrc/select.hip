@@ -247,8 +247,10 @@ __device__ __forceinline__ uint32_t descend_counted_level(SelShared& sh, uint32_
 }
 
 // Ordered emission from a per-token key source `key_of(i)`: heads too long for the bitmaps, which re-read their scores.
+// Nothing is written past the `budget` indices of the segment, also where the counters of another call's scores led to a
+// threshold that more tokens pass.
 template <typename KeyOf>
-__device__ __forceinline__ void emit_from_keys(SelShared& sh, int T, uint32_t thr, uint32_t need,
+__device__ __forceinline__ void emit_from_keys(SelShared& sh, int T, uint32_t thr, uint32_t need, uint32_t budget,
                                                int32_t* __restrict__ out, KeyOf key_of) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -280,7 +282,8 @@ __device__ __forceinline__ void emit_from_keys(SelShared& sh, int T, uint32_t th
     const uint32_t eq_rank = eq_seen + __popcll(eq_mask & below);
     const bool keep = in && (key > thr || (is_eq && eq_rank < need));
     const unsigned long long keep_mask = __ballot(keep);
-    if (keep) out[pos + __popcll(keep_mask & below)] = i;
+    const uint32_t at = pos + __popcll(keep_mask & below);
+    if (keep && at < budget) out[at] = i;
     pos += __popcll(keep_mask);
     eq_seen += __popcll(eq_mask);
   }
@@ -311,9 +314,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 // one 16-bit half word per lane.  Loops whose trip count could differ between lanes are avoided
 // (the expansion loop runs a fixed 16 times), and every cross-lane exchange of a step comes
 // before the staging traffic.
-// kEq = false: there is no map of equal keys, every kept token is in gt_map.
+// kEq = false: there is no map of equal keys, every kept token is in gt_map.  As above, `budget` indices at most.
 template <bool kEq>
-__device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t need, int32_t* __restrict__ out,
+__device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t need, uint32_t budget, int32_t* __restrict__ out,
                                                   const uint32_t* gt_map, const uint32_t* eq_map, uint32_t* stage_all) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -363,7 +366,7 @@ __device__ __forceinline__ void emit_from_bitmaps(SelShared& sh, int T, uint32_t
     wave_lds_sync();
     for (uint32_t j0 = 0; j0 < total; j0 += 64) {   // uniform trip count
       const uint32_t j = j0 + lane;
-      if (j < total) out[pos + j] = stage[j];
+      if (j < total && pos + j < budget) out[pos + j] = stage[j];
     }
     pos += total;
     wave_lds_sync();   // the staging buffer is rewritten by the next step
@@ -643,7 +646,7 @@ select_held_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* _
     }
   }
   __syncthreads();
-  emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, stage);
+  emit_from_bitmaps<true>(sh, T, need, (uint32_t)budget, out, gt_map, eq_map, stage);
 }
 
 // The share of a block of the one launch: rows p0 .. p1 - 1 (none: p0 >= p1) of the kept tokens of a head.
@@ -1055,9 +1058,9 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       __syncthreads();
     }
     if (settle_listed(sh, u, T, n_words, n_cand, keyed ? 1 : 0, need, gt_map, eq_map, cand))
-      emit_from_bitmaps<false>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+      emit_from_bitmaps<false>(sh, T, need, (uint32_t)budget, out, gt_map, eq_map, region + bitmap_stage_off);
     else
-      emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+      emit_from_bitmaps<true>(sh, T, need, (uint32_t)budget, out, gt_map, eq_map, region + bitmap_stage_off);
     return;
   }
 #pragma unroll 1
@@ -1075,9 +1078,9 @@ select_kernel(SeqTable tab, InlineOffsets inl, SelRagged ragged, int32_t* __rest
       else if (key == thr) atomicOr(&eq_map[i >> 5], 1u << (i & 31));
     });
     __syncthreads();
-    emit_from_bitmaps<true>(sh, T, need, out, gt_map, eq_map, region + bitmap_stage_off);
+    emit_from_bitmaps<true>(sh, T, need, (uint32_t)budget, out, gt_map, eq_map, region + bitmap_stage_off);
   } else {
-    emit_from_keys(sh, T, thr, need, out, [&](int i) { return order_key(u[i]); });
+    emit_from_keys(sh, T, thr, need, (uint32_t)budget, out, [&](int i) { return order_key(u[i]); });
   }
 }
 

@@ -249,3 +249,30 @@ def test_counts_buffer_too_small_is_an_error(ctx):
     assert e.value.status == 3
     assert lkv.lkv_counts_bytes_split(4, 100) == 4 * 2048 * 4 + 4 * 2 * 4 * 4
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("T", [34817, 40000, 327680, 327681])
+def test_counts_of_other_scores_write_no_index_past_a_segment(ctx, T):
+    # a caller's error: the counters counted scores below zero, the scores selected from are above it, so every token lies
+    # above the bin found; what is kept means nothing then, but each segment gets as many indices as its budget
+    K = torch.zeros((1, 2, T, 128), dtype=torch.bfloat16, device="cuda")
+    cache = lkv.Cache([K], [K], 2)
+    scorer = {"kind": "linear", "act": "silu", "hidden": 0, "per_head": False, "w2": None, "b2": None,
+              "w1": torch.zeros((1, 256), dtype=torch.bfloat16, device="cuda"), "b1": torch.full((1,), -3.0, device="cuda")}
+    counts = torch.zeros((2, 2048), dtype=torch.int32, device="cuda")
+    scores = torch.empty((1, 2, T), device="cuda")
+    lkv.lkv_score_counted(ctx, cache, scorer, [scores], counts)
+    scores.uniform_(1.0, 9.0)
+    b = 500
+    buffer = torch.full((2 * b + T,), -1, dtype=torch.int32, device="cuda")
+    offsets = torch.empty(3, dtype=torch.int32, device="cuda")
+    lkv.lkv_select_counted(ctx, cache, [scores], np.full(2, b, np.int32), counts, buffer[:2 * b], offsets)
+    torch.cuda.synchronize()
+    assert offsets.tolist() == [0, b, 2 * b]
+    assert (buffer[2 * b:] == -1).all()
+    assert (buffer[:2 * b] >= -1).all() and (buffer[:2 * b] < T).all()
+    assert not counts.any()
+    lkv.lkv_select(ctx, cache, [scores], np.full(2, b, np.int32), buffer[:2 * b], offsets)     # and the call itself is sound
+    u = scores.cpu().numpy()[0]
+    for h in range(2):
+        assert np.array_equal(buffer[h * b:(h + 1) * b].cpu().numpy(), O.select(u[h], b))
