@@ -54,7 +54,6 @@ constexpr int kStBinSteps = 6;            // trials on the bins at most
 constexpr float kStBinsDone = 0.05f;      // step of a trial on bins from which the trials go on with the values
 constexpr float kStDone = 0.01f;          // and the step that is the last
 constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
-constexpr double kStNoGap = 8.9e307;        // there is no value on that side
 constexpr double kStCoarse = 1e15;         // |z| from which fp64 no longer resolves tenths of a unit
 constexpr double kStMost = 1e300;         // centre of the search at most: its multiples do not overflow
 constexpr double kStTinyProduct = 1e-250; // products of two sums below this have lost digits, or may have
@@ -190,10 +189,6 @@ __device__ __forceinline__ double st_lane(double x, int lane) {
 }
 __device__ __forceinline__ float st_lane(float x, int lane) {
   return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
-}
-
-__device__ __forceinline__ double st_high(unsigned high, unsigned low) {
-  return __builtin_bit_cast(double, (unsigned long long)high << 32 | low);
 }
 
 // keys whose unsigned order is the numeric order of the values
@@ -529,8 +524,6 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     m = (int)st_lane(sums, 32);
     up = st_lane(gaps, 0);
     dn = st_lane(gaps, 16);
-    if (up > kStNoGap) up = INFINITY;
-    if (dn > kStNoGap) dn = INFINITY;
     turn ^= 1;
     const double d = k - (double)m;
     double delta;

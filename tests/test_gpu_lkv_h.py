@@ -297,6 +297,25 @@ def test_soft_topk_of_masked_values(ctx, n, dtype, far):
         assert np.abs(y[0] - (x > far if far < 0 else x >= far)).max() <= 1e-300 and np.isfinite(info[0, 0]), tau
 
 
+@pytest.mark.parametrize("n", [300, 5000, 16384, 40000])
+@pytest.mark.parametrize("far", [-np.finfo(np.float64).max, np.finfo(np.float64).max])
+@pytest.mark.parametrize("tau", [1.0, 1.25, 1.999, 3.0])
+def test_soft_topk_whole_target_in_the_widest_gap(ctx, n, far, tau):
+    # the head or the tail is masked with the type's largest magnitude and the target is the size of the head: the threshold is the
+    # one of App. A.1 in that split, (min head + max tail + log(sum_tail e^{z - max tail}) - log(sum_head e^{min head - z})) / 2
+    x = np.random.default_rng(n).standard_normal(n)
+    masked = np.arange(n) % 2 == 1 if far < 0 else np.arange(n) < 3
+    x[masked] = far
+    head = ~masked if far < 0 else masked
+    z = x / tau
+    h, t = z[head].min(), z[~head].max()
+    expected = 0.5 * h + 0.5 * t + 0.5 * (np.log(np.exp(z[~head] - t).sum()) - np.log(np.exp(h - z[head]).sum()))
+    y, info = _gpu_soft_topk_rows(ctx, x[None], [float(head.sum())], tau)
+    assert info[0, 1] == head.sum()
+    assert abs(info[0, 0] / expected - 1) <= 1e-15      # some roundings of numbers near 9e307
+    assert np.array_equal(y[0], head.astype(np.float64))
+
+
 def test_soft_topk_argument_errors(ctx):
     x = torch.zeros(10, dtype=torch.float64, device="cuda")
     y = torch.empty_like(x)
