@@ -21,13 +21,15 @@
 // values each where z is sparse, so they have to begin near rank k: where far values keep the histograms from getting
 // there, the value of rank k is found exactly, from the bits.  (256 vectors of 16384, half of them masked with the
 // type's lowest: 88 us, 1.5 ms by halving the bracket that such values stretch.)
-// fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.
+// fp32 only chooses where fp64 looks: a poor choice costs further fp64 passes, never digits.  The trials on values are summed over
+// the waves and told above from below in fp64 all the same (0.25 us): their bracket must not lose the threshold to rounding where
+// a vector is long.
 // Up to 32768 values the operands stay in registers between passes; longer vectors are read again in every pass
-// (they stay in L2).  256 vectors of 16384 fp32 values: 25.3 us (257 us for the LDS sort and
+// (they stay in L2).  256 vectors of 16384 fp32 values: 25.5 us (257 us for the LDS sort and
 // logarithmic scans this replaces), one vector of 131072: 0.13 ms (2.2 ms for halving a bracket in fp64).  Of the 25: read
 // and extremes 4, histogram 2.5, trials 4, fp64 pass 7.5, root 0.7, outputs the rest.  Before that pass fetched its values ahead (7.5
 // us, 8.3 with two at a time) and before the trials on bins, values kept in registers up to the trials and the sums over the waves taken
-// side by side in the rows of 16 lanes: 30.4 us; 4096 values 15.7 -> 13.2, 8 vectors of 32768 42.6 -> 32.9, 777 values
+// side by side in the rows of 16 lanes: 30.4 us; 4096 values 15.7 -> 13.7, 8 vectors of 32768 42.6 -> 32.9, 777 values
 // 9.2 as before (the call's own price).
 #include <hip/hip_runtime.h>
 
@@ -52,7 +54,7 @@ constexpr double kStFar = 32.0;           // bin width, in z, up to which the tr
 constexpr int kStSearchSteps = 48;        // fp32 trials at most (bisection alone would need about 30)
 constexpr int kStBinSteps = 6;            // trials on the bins at most
 constexpr float kStBinsDone = 0.05f;      // step of a trial on bins from which the trials go on with the values
-constexpr float kStDone = 0.01f;          // and the step that is the last
+constexpr float kStDone = 0.01f;          // and the step that is the last: it ends within 1e-6 (777 to 131072 values, temperatures of .02 to 1)
 constexpr int kStExactSteps = 200;        // fp64 trials at most (bisection alone would need about 60)
 constexpr double kStCoarse = 1e15;         // |z| from which fp64 no longer resolves tenths of a unit
 constexpr double kStMost = 1e300;         // centre of the search at most: its multiples do not overflow
@@ -390,7 +392,13 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
     // nothing to search for at a centre that itself rounds to about a unit
     const int n_search = fabs(zc) < kStCoarse ? kStSearchSteps : 0;
-    // trials on the bins first, each as many values in its middle, and split where the trial cuts it
+    // the threshold that a trial's split would have: d = k - m, af = 2 A, bf = 2 B
+    auto step_to = [&](float df, float af, float bf) {
+      const float root = __builtin_amdgcn_sqrtf(fmaf(df, df, af * bf));
+      return fv + __log2f(df >= 0.f ? bf * __builtin_amdgcn_rcpf(df + root) : (root - df) * __builtin_amdgcn_rcpf(af));
+    };
+    // trials on the bins first, each as many values in its middle, and split where the trial cuts it: in fp32, since the bins
+    // are no better
     float c0 = 0.f, c1 = 0.f, w0 = 0.f, w1 = 0.f, per_step = 0.f;
     bool on_bins = found_bin >= 0 && bin_step > 0.f;
     if (on_bins) {
@@ -436,24 +444,29 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
       head = st_wave(head, StAdd());
       all = st_wave(all, StAdd());
       cnt = st_wave(cnt, StAdd());   // exact: whole numbers up to 2^22
-      auto& sv = sh.f[turn];
-      if (writer) { sv[0][wave] = head; sv[1][wave] = all; sv[2][wave] = cnt; }
-      __syncthreads();
-      const float sums = st_collect_rows<kT, 3>(sv, 0.f, StAdd());
-      const float af = st_lane(sums, 0), bf = fmaxf(st_lane(sums, 16) - af, 0.f);   // A = af / 2, B = bf / 2
-      turn ^= 1;
-      const double d = k - (double)st_lane(sums, 32);
-      const float df = (float)d;
-      const float root = __builtin_amdgcn_sqrtf(fmaf(df, df, af * bf));
-      const float ratio = df >= 0.f ? bf * __builtin_amdgcn_rcpf(df + root) : (root - df) * __builtin_amdgcn_rcpf(af);
-      float next = fv + __log2f(ratio);
       if (on_bins) {
+        auto& sf = sh.f[turn];
+        if (writer) { sf[0][wave] = head; sf[1][wave] = all; sf[2][wave] = cnt; }
+        __syncthreads();
+        const float sums = st_collect_rows<kT, 3>(sf, 0.f, StAdd());
+        const float af = st_lane(sums, 0);
+        turn ^= 1;
+        const float next = step_to((float)(k - (double)st_lane(sums, 32)), af, fmaxf(st_lane(sums, 16) - af, 0.f));
         const bool usable = next > flo && next < fhi;
         on_bins = usable && fabsf(next - fv) >= kStBinsDone && step < kStBinSteps;
         if (usable) fv = next;
         continue;
       }
-      if (0.5f * (bf - af) - df > 0.f) flo = fv; else fhi = fv;   // the threshold lies above, or below, this trial
+      // the sums over the waves and the side of the trial in fp64
+      auto& sv = sh.v[turn];
+      if (writer) { sv[0][wave] = head; sv[1][wave] = all; sv[2][wave] = cnt; }
+      __syncthreads();
+      const double sums = st_collect_rows<kT, 3>(sv, 0.0, StAdd());
+      const double a2 = st_lane(sums, 0), b2 = st_lane(sums, 16) - a2;   // 2 A, 2 B
+      turn ^= 1;
+      const double d = k - st_lane(sums, 32);
+      float next = step_to((float)d, (float)a2, (float)fmax(b2, 0.0));
+      if (0.5 * (b2 - a2) - d > 0.0) flo = fv; else fhi = fv;   // the threshold lies above, or below, this trial
       if (fabsf(next - fv) < kStDone) {   // an error of its cube is left, below what fp32 resolves
         fv = next;
         break;

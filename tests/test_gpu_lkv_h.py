@@ -263,6 +263,20 @@ def test_soft_topk_where_the_histogram_says_little(ctx, n, dtype):
         _check_at_returned_threshold(x, y[i], info[i, 0], int(info[i, 1]), ks[i], tau, (i, ks[i]))
 
 
+@pytest.mark.parametrize("n", [(1 << 20) + 1, 1 << 22])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_soft_topk_of_the_longest_vectors(ctx, n, dtype):
+    # sums of a million and more exponentials, read again in every pass
+    rng = np.random.default_rng(n)
+    tau = 0.05
+    base = rng.uniform(0, 1, n)
+    for x in (rng.standard_normal(n), np.where(np.arange(n) == 0, 900 * tau, base * 0.4 * tau), base * 1e-7, np.round(base * 4)):
+        for k in (0.01, 0.3 * n, 0.5 * n + 0.25, n - 0.01):
+            y, info = _gpu_soft_topk_rows(ctx, x[None].astype(dtype), [k], tau)
+            # added up in 64 bits of mantissa: 22 levels of pairwise fp64 sums of four million values may be 22 * 2^-53 * n = 1e-8 off
+            _check_at_returned_threshold(x.astype(dtype), y[0].astype(np.longdouble), info[0, 0], int(info[0, 1]), k, tau, k)
+
+
 @pytest.mark.parametrize("n", [300, 1024, 1025, 16384, 32769])
 @pytest.mark.parametrize("dtype,far", [(np.float32, -1e20), (np.float32, 1e30), (np.float32, -np.finfo(np.float32).max),
                                        (np.float32, -np.inf), (np.float32, np.inf), (np.float64, -1e30),
