@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "lkv_common.h"
+#include "lkv_shares.h"
 
 namespace lkv {
 
@@ -55,13 +56,7 @@ constexpr int kSelInlineOffsets = 640;                      // offsets that fit 
 constexpr int kSelSplitMaxHeads = 64;                       // launches with at most this many (long) heads split each head's pass
 constexpr int kSelSplitTargetBlocks = 256;                  // over about this many workgroups in all,
 constexpr int kFuseMaxHeads = 64;                           // one lane each
-// Rows of a block of the one launch, at most: with more of them the copy decides, and sixteen waves a compute unit copy more slowly than
-// the compaction's blocks (against two launches, 34000 tokens: 32 heads, 214 rows a block 117 -> 114 us, 680 136 -> 137, 1850
-// 181 -> 190; 64 heads, 490 222 -> 215, 1460 259 -> 264).
-constexpr int kFuseMaxRows = 600;
-constexpr int kFuseMaxRowsFewHeads = 900;                   // up to 16 heads: 34000 tokens, 850 rows a block 102.7 -> 99.3 us
-constexpr int kFuseFewHeads = 16;
-constexpr int kFuseBlocks = 256;                            // one round: a block to a compute unit
+constexpr int kFuseLongHeads = 16;                          // heads too long for the registers, in one launch at most
 constexpr int kSelSplitMax = 32;                            // at most this many per head
 
 struct InlineOffsets {
@@ -722,9 +717,10 @@ __device__ __forceinline__ void copy_share(const SeqTable& tab, const SelShare& 
 
 // Top-k and compaction of few heads of at most kE * 1024 tokens in one launch (a layer evicted during prefill).  A head's
 // choice is a chain of short steps in one workgroup, which leaves the rest of the chip idle, so it is made again in every block that copies rows
-// of the head: blocks in proportion to the budgets, one to a compute unit, each with as many rows as the others.  What goes
-// away is the second launch, the emission of all but a block's own indices, their way through memory and the search for a row's segment.  8 heads of 32768, 39 thousand rows: 26.5 us in two launches,
-// 20.6 in one (the whole call with the linear scorer 51.2 -> 45.0, 49.3 of it with the two launches of today); of 4096 19.3 -> 16.6, 2 heads of 34000 30.4 -> 24.7.  Two rows' pieces
+// of the head: blocks in proportion to the budgets, each with as many rows as the others (how many: lkv_shares.h).  What goes
+// away is the second launch, the emission of all but a block's own indices, their way through memory and the search for a row's segment.  8 heads of 32768, 39 thousand rows: 26.8 us in two launches,
+// 22.1 in one (the whole call with the linear scorer 51.4 -> 45.2, 46.9 with the two launches of today); of 4096 18.5 -> 14.7, 2 heads of
+// 34000 30.3 -> 25.0.  Two rows' pieces
 // in flight per thread: four were 0.1 to 0.8 us slower up to 100 rows a block, eight up to 1.6.
 template <int kE>
 __global__ void __launch_bounds__(kSelThreads)
@@ -1188,9 +1184,9 @@ select_classify_kernel(SeqTable tab, const int32_t* __restrict__ offsets, const 
 }
 
 // The one launch for longer heads, after select_classify_kernel: every block that copies rows settles the listed tokens of its head for
-// itself.  What bounds it: the copy (14 of 30 us for 8 heads of 131072, 105 thousand rows), the way of the listed scores to each compute unit (4: one
+// itself.  What bounds it: the copy (14 of 30 us for 8 heads of 131072, 105 thousand rows, 256 blocks), the way of the listed scores to each compute unit (4: one
 // line for every token or two), the list 2.4, the descent 1.4.  In turn with one block per head that emits and a compaction behind it, the whole call
-// with the 256-64-1 scorer: 8 heads of 131072 146 -> 137 us, 60001 82 -> 76, 200000 219 -> 204, 2 heads of 100001 75 -> 64.
+// with the 256-64-1 scorer: 8 heads of 131072 143.9 -> 138.6 us, 60001 80.7 -> 76.9, 2 heads of 100001 58.5 -> 49.9.
 __global__ void __launch_bounds__(kSelThreads)
 select_compact_long_kernel(SeqTable tab, const int32_t* __restrict__ offsets, int32_t* __restrict__ idx, uint32_t* __restrict__ counts,
                            const uint32_t* __restrict__ pre_maps, int pre_words, int seg_base, int seg_stride,
@@ -1322,19 +1318,8 @@ hipError_t select_prepare() {
 int select_inline_capacity() { return kSelInlineOffsets; }
 int select_max_bitmap_tokens() { return kSelMaxBitmapT; }
 
-// Blocks of the one-launch top-k and compaction whose blocks take up to `rows` rows each.
-static int64_t select_compact_blocks(const int32_t* budgets, int n_seq, int seq_stride, int heads, int64_t rows) {
-  int64_t n = 0;
-  for (int i = 0; i < n_seq; ++i)
-    for (int j = 0; j < heads; ++j) {
-      const int64_t parts = (budgets[(size_t)i * seq_stride + j] + rows - 1) / rows;
-      n += parts > 1 ? parts : 1;
-    }
-  return n;
-}
-
 // Rows of a block of the one-launch top-k and compaction (and the blocks), 0 where the two launches are better.  Heads too long for
-// the registers need the scoring launch's counts and room for bitmaps of `pre_words` words; there up to kFuseFewHeads of them (32 heads of
+// the registers need the scoring launch's counts and room for bitmaps of `pre_words` words; there up to kFuseLongHeads of them (32 heads of
 // 36000: 180 -> 177 us, but 185 -> 188 where one block a head has to finish the choice).
 int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_stride, int64_t total_rows, const uint32_t* counts,
                         int pre_words, int* blocks) {
@@ -1345,20 +1330,10 @@ int select_compact_rows(const SeqTable& tab, const int32_t* budgets, int seq_str
     least = tab.T[i] < least ? tab.T[i] : least;
     most = tab.T[i] > most ? tab.T[i] : most;
   }
-  if (most > kSelMaxHeldT && (segs > kFuseFewHeads || least <= kSelMaxHeldT || counts == nullptr || most > kSelMaxBitmapT ||
+  if (most > kSelMaxHeldT && (segs > kFuseLongHeads || least <= kSelMaxHeldT || counts == nullptr || most > kSelMaxBitmapT ||
                               (most + 31) / 32 > pre_words))
     return 0;
-  auto count = [&](int64_t rows) { return select_compact_blocks(budgets, tab.n, seq_stride, segs / tab.n, rows); };
-  int64_t lo = total_rows / kFuseBlocks, hi = lo < 32 ? 64 : 2 * lo;   // hi fits one round, lo does not
-  if (lo < 63) lo = 63;
-  while (count(hi) > kFuseBlocks) hi *= 2;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) / 2;
-    (count(mid) > kFuseBlocks ? lo : hi) = mid;
-  }
-  if (hi > (segs <= kFuseFewHeads ? kFuseMaxRowsFewHeads : kFuseMaxRows)) return 0;
-  *blocks = (int)count(hi);
-  return (int)hi;
+  return share_rows(budgets, tab.n, seq_stride, segs / tab.n, total_rows, most > kSelMaxHeldT, blocks);
 }
 
 static int classify_split(int segs) {
