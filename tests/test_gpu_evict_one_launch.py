@@ -219,3 +219,51 @@ def test_counters_that_are_not_zero_on_entry_lead_out_of_no_head(ctx, T, H, dirt
     u = scores.cpu().numpy()[0]
     for h in range(H):
         assert np.array_equal(idx[h * b:(h + 1) * b].cpu().numpy(), O.select(u[h], b))
+
+
+@pytest.mark.parametrize("n_streams", [2, 4])
+@pytest.mark.parametrize("T,H,counted", [(5000, 8, False), (20001, 4, True), (34816, 2, False), (40000, 4, True), (65537, 2, True)])
+def test_layers_evicted_on_several_streams_at_once(ctx, T, H, counted, n_streams):
+    # eight layers, enqueued in turn on the streams without a wait between them, into one packed cache, with one counter buffer:
+    # the same as one layer after the other, in every round
+    L = 8
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = ([torch.empty((1, H, T, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(L)] for _ in range(2))
+    views = [lkv.Cache([K[l]], [V[l]], H) for l in range(L)]
+    scorer = {"kind": "mlp", "act": "silu", "hidden": 16, "per_head": False, "b1": torch.zeros((L, 16), device="cuda"), "b2": None,
+              "w1": torch.randn((L, 16, 256), device="cuda", generator=g).mul(0.05).to(torch.bfloat16),
+              "w2": torch.randn((L, 16), device="cuda", generator=g)}
+    rng = np.random.default_rng(T)
+    budgets = rng.integers(0, T // 6, size=(L, H)).astype(np.int32)
+    budgets[1, 0], budgets[2, -1] = 0, T // 3
+    offsets = torch.empty(L * H + 1, dtype=torch.int32, device="cuda")
+    total = lkv.lkv_plan_offsets(ctx, budgets, offsets)
+    counts = torch.zeros(lkv.lkv_counts_bytes_split(L * H, T) // 4, dtype=torch.int32, device="cuda") if counted else None
+    streams = [torch.cuda.Stream() for _ in range(n_streams)]
+    scratch = [torch.empty((1, H, T), device="cuda") for _ in range(n_streams)]
+
+    def evict(on):
+        idx = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+        kp, vp = (torch.zeros((total, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        for l in range(L):
+            j = l % n_streams
+            lkv.lkv_evict_layer(ctx, views[l], l, L, scorer, budgets, offsets, [scratch[j]], idx, kp, vp,
+                                stream=streams[j] if on else None, counts=counts)
+        torch.cuda.synchronize()
+        assert counts is None or not counts[:L * H * 2048].any()
+        return idx, kp.view(torch.int16), vp.view(torch.int16)
+
+    one_by_one = evict(False)
+    off = offsets.cpu().numpy()
+    for l in range(0, L, 3):      # and these are the oracle's, on the scores of the general path
+        u = torch.empty((1, H, T), device="cuda")
+        sl = dict(scorer, w1=scorer["w1"][l:l + 1], b1=scorer["b1"][l:l + 1], w2=scorer["w2"][l:l + 1])
+        lkv.lkv_score(ctx, views[l], sl, [u])
+        uh = u.cpu().numpy()[0]
+        for h in range(H):
+            a, b = off[l * H + h], off[l * H + h + 1]
+            assert np.array_equal(one_by_one[0][a:b].cpu().numpy(), O.select(uh[h], int(b - a)))
+    for _ in range(4):
+        for got, want in zip(evict(True), one_by_one):
+            assert torch.equal(got, want)
