@@ -356,6 +356,14 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
 
 #pragma unroll 1
     for (int t = t_first; t < n_tiles; t += t_step) {
+      // The weights of the tile's rows: asked for ahead of the rows to come, which would have to arrive first (loads are waited for
+      // in order).  After them: 200 heads of 2000 rows 46.9 us, 41.0 so; 512 of 500 36.5 and 32.6; 288 of 60 16.6 and 15.3.
+      float weight[8];
+      if constexpr (kMasked) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) weight[i] = mask[(int64_t)a + min(t * kDecTile + (i >> 2) * 16 + 4 * r + (i & 3), n_rows - 1)];
+        asm volatile("" ::: "memory");
+      }
       // stage 32 rows: row 4j + r, piece c
       if ((t + 1) * kDecTile <= n_rows) {   // wave-uniform: a full tile
 #pragma unroll
@@ -402,7 +410,7 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
           const int tok = tok0 + tt * 16 + 4 * r + e;
           const bool ok = tok < n_rows;
           float sc = sacc[tt][e] * qscale;
-          if (kMasked) sc += __log2f(mask[(int64_t)a + (ok ? tok : 0)]);   // log2(0) = -inf drops the row
+          if constexpr (kMasked) sc += __log2f(weight[tt * 4 + e]);   // log2(0) = -inf drops the row
           sv[tt * 4 + e] = ok ? sc : -INFINITY;
           mx = fmaxf(mx, sv[tt * 4 + e]);
         }
