@@ -256,6 +256,8 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
     list_pieces(wave_upper_segment(offsets, n_segments, p0, lane));
     const int t = lane_rows > 0 ? (lane_rows + kDecTile - 1) / kDecTile : 0;
     int best = 0x7fffffff;
+    alone_tiles = 2;
+    if (__ballot(t > 2) != 0)   // else all go to single waves
 #pragma unroll
     for (int tiles = 2; tiles <= 32; tiles *= 2) {
       // in quarters of a tile: what the waves do alone (the longest of it last) and what they share
@@ -342,10 +344,10 @@ decode_partial_kernel(const uint16_t* __restrict__ q, const uint4* __restrict__ 
     const bool small = now.owner >= 0, whole = now.whole;
     const int t_first = small ? 0 : wave, t_step = small ? 1 : kDecWaves;
     if (!kAligned) {
-      // waited for here: inside the loop the wait would reach the rows on their way as well
+      next = next_piece();   // while the rows are on their way (behind the wait: 288 heads of 60 rows 12.4 us, 12.0 so)
+      // waited for here: inside the loop the wait would reach the rows to come as well
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(qfrag[ks]));
-      next = next_piece();
       if (next.s >= 0 && t_first >= n_tiles) load_first(next);
     }
     float m_run = -INFINITY;   // running max of head c (log2 domain), identical in the four lanes of a head
