@@ -297,7 +297,7 @@ lkv_status lkv_plan_offsets(lkv_ctx *ctx, int64_t n_segments, const int32_t *bud
  *               counters, so they can share the buffer.
  * counts_bytes: size of that buffer: lkv_counts_bytes(n_segments), or lkv_counts_bytes_split(n_segments,
  *               longest sequence) to let the call split long heads over several workgroups; smaller:
- *               LKV_ERR_WORKSPACE */
+ *               LKV_ERR_WORKSPACE before anything is enqueued */
 lkv_status lkv_evict_layer(lkv_ctx *ctx, const lkv_cache *layer, int32_t layer_index, int32_t n_layers,
                            const lkv_scorer *scorer, const int32_t *budgets, const int32_t *offsets,
                            float *const *scores, int32_t *idx, void *kp, void *vp, uint32_t *counts,
