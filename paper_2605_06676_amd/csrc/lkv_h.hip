@@ -392,7 +392,8 @@ soft_topk_kernel(const X* x, int n, double k, double tau, double* y /* may alias
     float flo = (float)((lo - zc) * kLog2E), fhi = (float)((hi - zc) * kLog2E), fv = 0.f;
     // nothing to search for at a centre that itself rounds to about a unit
     const int n_search = fabs(zc) < kStCoarse ? kStSearchSteps : 0;
-    // the threshold that a trial's split would have: d = k - m, af = 2 A, bf = 2 B
+    // the threshold that a trial's split would have: d = k - m, af = 2 A, bf = 2 B.  Only a place for the next trial: the hardware's
+    // root and reciprocal will do (IEEE ones: 0.5 us)
     auto step_to = [&](float df, float af, float bf) {
       const float root = __builtin_amdgcn_sqrtf(fmaf(df, df, af * bf));
       return fv + __log2f(df >= 0.f ? bf * __builtin_amdgcn_rcpf(df + root) : (root - df) * __builtin_amdgcn_rcpf(af));
